@@ -5,83 +5,10 @@
 //   down:     y_slot[r,h] = <act[r], W_down[e][h]>
 // for the rows r of expert e in expert-sorted order.  Both operands have the reduction dimension
 // contiguous, so every MFMA fragment is one 16-byte LDS read.  The tile kernel is in zeda_ffn_tile.h;
-// this file picks the tile shapes and holds the plain fp32 path.
+// this file picks the tile shapes.  fp32 layers: zeda_ffn_f32.hip.
 #include "zeda_ffn_tile.h"
 
 namespace zeda {
-
-// ---------------------------------------------------------------------------------------------
-// fp32 path (plain FMA, for the fp32 configuration): one workgroup per sorted row.
-// ---------------------------------------------------------------------------------------------
-constexpr int kF32Threads = 256;
-
-__device__ __forceinline__ int expert_of_row(const int32_t *__restrict__ offsets, int N, int r)
-{
-    int lo = 0, hi = N;  // largest e with offsets[e] <= r (empty experts share an offset with the next one)
-    while (hi - lo > 1) {
-        int mid = (lo + hi) >> 1;
-        if (offsets[mid] <= r) lo = mid; else hi = mid;
-    }
-    return lo;
-}
-
-__device__ __forceinline__ float wave_sum_f(float v)
-{
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-    return v;
-}
-
-__global__ __launch_bounds__(kF32Threads) void ffn_f32_gateup_kernel(const float *__restrict__ x,
-                                                                     const float *__restrict__ wg,
-                                                                     const float *__restrict__ wu,
-                                                                     const int32_t *__restrict__ offsets,
-                                                                     const int32_t *__restrict__ sorted_slot,
-                                                                     float *__restrict__ act, int N, int K, int H, int I, int T)
-{
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    float *xs = reinterpret_cast<float *>(lds);
-    const int r = blockIdx.x;
-    if (r >= offsets[N]) return;
-    const int e = expert_of_row(offsets, N, r);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const float *xr = x + (size_t)min(max(sorted_slot[r] / K, 0), T - 1) * H;
-    for (int h = tid; h < H; h += kF32Threads) xs[h] = xr[h];
-    __syncthreads();
-    for (int i = wave; i < I; i += kF32Threads / 64) {
-        const float *g = wg + ((size_t)e * I + i) * H, *u = wu + ((size_t)e * I + i) * H;
-        float sg = 0.f, su = 0.f;
-        for (int h = lane; h < H; h += 64) {
-            sg = fmaf(g[h], xs[h], sg);
-            su = fmaf(u[h], xs[h], su);
-        }
-        sg = wave_sum_f(sg);
-        su = wave_sum_f(su);
-        if (lane == 0) act[(size_t)r * I + i] = sg / (1.f + expf(-sg)) * su;
-    }
-}
-
-__global__ __launch_bounds__(kF32Threads) void ffn_f32_down_kernel(const float *__restrict__ act,
-                                                                   const float *__restrict__ wd,
-                                                                   const int32_t *__restrict__ offsets,
-                                                                   float *__restrict__ y, int N, int H, int I)
-{
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    float *as = reinterpret_cast<float *>(lds);
-    const int r = blockIdx.x;
-    if (r >= offsets[N]) return;
-    const int e = expert_of_row(offsets, N, r);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int i = tid; i < I; i += kF32Threads) as[i] = act[(size_t)r * I + i];
-    __syncthreads();
-    for (int h = wave; h < H; h += kF32Threads / 64) {
-        const float *w = wd + ((size_t)e * H + h) * I;
-        float s = 0.f;
-        for (int i = lane; i < I; i += 64) s = fmaf(w[i], as[i], s);
-        s = wave_sum_f(s);
-        if (lane == 0) y[(size_t)r * H + h] = s;
-    }
-}
 
 // ---------------------------------------------------------------------------------------------
 // launchers
@@ -214,21 +141,14 @@ int launch_gateup(const zeda_layer_desc *d, const void *x, const void *wg, const
                   const int32_t *sorted_slot, void *act, hipStream_t s)
 {
     if (d->dtype == ZEDA_BF16) return launch_bf16<true>(d, x, wg, wu, offsets, sorted_slot, act, s);
-    const int S = d->T * d->K;
-    ffn_f32_gateup_kernel<<<S, kF32Threads, (size_t)d->H * sizeof(float), s>>>(
-        (const float *)x, (const float *)wg, (const float *)wu, offsets, sorted_slot, (float *)act, d->N, d->K, d->H, d->I,
-        d->T);
-    return last_launch_status();
+    return launch_gateup_f32(d, x, wg, wu, offsets, sorted_slot, act, s);
 }
 
 int launch_down(const zeda_layer_desc *d, const void *act, const void *wd, const int32_t *offsets, void *y_slot,
                 hipStream_t s)
 {
     if (d->dtype == ZEDA_BF16) return launch_bf16<false>(d, act, wd, nullptr, offsets, nullptr, y_slot, s);
-    const int S = d->T * d->K;
-    ffn_f32_down_kernel<<<S, kF32Threads, (size_t)d->I * sizeof(float), s>>>((const float *)act, (const float *)wd, offsets,
-                                                                              (float *)y_slot, d->N, d->H, d->I);
-    return last_launch_status();
+    return launch_down_f32(d, act, wd, offsets, y_slot, s);
 }
 
 }  // namespace zeda

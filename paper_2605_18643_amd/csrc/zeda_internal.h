@@ -64,6 +64,11 @@ int launch_gateup(const zeda_layer_desc *d, const void *x, const void *wg, const
                   const int32_t *sorted_slot, void *act, hipStream_t s);
 int launch_down(const zeda_layer_desc *d, const void *act, const void *wd, const int32_t *offsets, void *y_slot,
                 hipStream_t s);
+// the same for fp32 layers (launch_gateup and launch_down call them)
+int launch_gateup_f32(const zeda_layer_desc *d, const void *x, const void *wg, const void *wu, const int32_t *offsets,
+                      const int32_t *sorted_slot, void *act, hipStream_t s);
+int launch_down_f32(const zeda_layer_desc *d, const void *act, const void *wd, const int32_t *offsets, void *y_slot,
+                    hipStream_t s);
 // row-major -> tiled copy of one expert weight tensor (down: [N,H,I], else [N,I,H])
 int launch_pack_weights(const zeda_layer_desc *d, const void *w, void *out, bool down, hipStream_t s);
 int launch_combine(const zeda_layer_desc *d, const void *y_slot, const int32_t *ids, const float *gates,

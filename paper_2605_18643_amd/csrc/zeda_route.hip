@@ -3,7 +3,7 @@
 // the normalisation choices).  One fused kernel: projection -> LDS -> wave-level selection.
 #include <limits.h>
 
-#include "zeda_internal.h"
+#include "zeda_f32_tile.h"
 
 namespace zeda {
 
@@ -372,57 +372,64 @@ __global__ __launch_bounds__(kRouteThreads) void route_select_kernel(const float
     }
 }
 
-// fp32 router (plain FMA): a workgroup owns 8 tokens staged in LDS chunk by chunk; a wave walks the
-// experts, its lanes stride over the hidden dimension, partial sums meet in a fixed butterfly.
-constexpr int kRouteF32Tokens = 8;
-constexpr int kRouteF32Chunk = 1024;
+// fp32 router.  A workgroup owns 16 tokens and all experts; its 16 waves split the hidden dimension and, above 32
+// experts, the experts: each multiplies NA blocks of 16 router rows with the token block (zeda_f32_tile.h), the slices'
+// sums meet in LDS and are added in slice order, and four waves select.  NC: candidates per lane of the selection, the
+// expert count in blocks of 16 rounded up to a power of two.  Loads in flight are what counts here (513 tokens of
+// H = 1024, 40 experts: 33 workgroups); one wave walking expert after expert with a sum over its lanes took 70 us.
+constexpr int kRouteF32Tokens = 16;
+constexpr int kRouteF32Threads = 1024;
 
-__global__ __launch_bounds__(kRouteThreads) void route_f32_kernel(const float *__restrict__ x,
-                                                                  const float *__restrict__ wr,
-                                                                  const float *__restrict__ bias, int T, int H, int N,
-                                                                  int NE, int K, int gate_norm,
-                                                                  int32_t *__restrict__ ids, float *__restrict__ gates,
-                                                                  float *__restrict__ logits_out, int LDg)
+template <int NC>
+__global__ __launch_bounds__(kRouteF32Threads) void route_f32_kernel(const float *__restrict__ x, const float *__restrict__ wr,
+                                                                     const float *__restrict__ bias, int T, int H, int N,
+                                                                     int NE, int K, int gate_norm, int32_t *__restrict__ ids,
+                                                                     float *__restrict__ gates, float *__restrict__ logits_out,
+                                                                     int LDg)
 {
-    __shared__ float xs[kRouteF32Tokens * kRouteF32Chunk];
-    __shared__ float lg[kRouteF32Tokens * (kMaxExperts + 1)];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int t0 = blockIdx.x * kRouteF32Tokens;
-    constexpr int LD = kMaxExperts + 1;
-    for (int i = tid; i < kRouteF32Tokens * NE; i += kRouteThreads) lg[(i / NE) * LD + (i % NE)] = 0.f;
-    for (int h0 = 0; h0 < H; h0 += kRouteF32Chunk) {
-        const int hc = min(kRouteF32Chunk, H - h0);
-        __syncthreads();
-        for (int i = tid; i < kRouteF32Tokens * hc; i += kRouteThreads) {
-            int tk = i / hc, h = i - tk * hc;
-            int t = min(t0 + tk, T - 1);
-            xs[tk * kRouteF32Chunk + h] = x[(size_t)t * H + h0 + h];
-        }
-        __syncthreads();
-        for (int e = wave; e < NE; e += 4) {
-            float part[kRouteF32Tokens];
+    constexpr int NA = NC < 2 ? NC : 2, GROUPS = NC / NA, SLICES = kRouteF32Threads / 64 / GROUPS, LD = NC * 16;
+    static_assert(SLICES * kRouteF32Tokens * LD * 4 <= 64 * 1024, "the slices' logit tables fit in the default LDS size");
+    __shared__ __attribute__((aligned(16))) float lg[SLICES * kRouteF32Tokens * LD];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15;
+    const int group = wave % GROUPS, slice = wave / GROUPS, t0 = blockIdx.x * kRouteF32Tokens;
+    const float *pa[NA], *pb[1] = {x + (size_t)min(t0 + l16, T - 1) * H};
 #pragma unroll
-            for (int tk = 0; tk < kRouteF32Tokens; ++tk) part[tk] = 0.f;
-            const float *w = wr + (size_t)e * H + h0;
-            for (int h = lane; h < hc; h += 64) {
-                float wv = w[h];
+    for (int a = 0; a < NA; ++a) pa[a] = wr + (size_t)min((group * NA + a) * 16 + l16, NE - 1) * H;
+    {
+        F32Tile<NA, 1> t;
+        t.run(pa, pb, slice, SLICES, (int)blockIdx.x, H);
 #pragma unroll
-                for (int tk = 0; tk < kRouteF32Tokens; ++tk) part[tk] = fmaf(wv, xs[tk * kRouteF32Chunk + h], part[tk]);
-            }
+        for (int a = 0; a < NA; ++a)  // lane l: experts 4 (l / 16) .. + 3 of the block, token l % 16
+            *reinterpret_cast<f32x4 *>(lg + (slice * kRouteF32Tokens + l16) * LD + (group * NA + a) * 16 + 4 * (lane >> 4)) = t.total(a, 0);
+    }
+    __syncthreads();
+    for (int i = tid; i < kRouteF32Tokens * LD; i += kRouteF32Threads) {
+        float v = lg[i];
 #pragma unroll
-            for (int tk = 0; tk < kRouteF32Tokens; ++tk) {
-                float s = wave_sum(part[tk]);
-                if (lane == 0) lg[tk * LD + e] += s;
-            }
-        }
+        for (int q = 1; q < SLICES; ++q) v += lg[q * kRouteF32Tokens * LD + i];
+        lg[i] = v;
     }
     __syncthreads();
     if (logits_out) {  // statistics run: hand the logits (without the bias) to route_stats_kernel
-        for (int i = tid; i < kRouteF32Tokens * NE; i += kRouteThreads)
+        for (int i = tid; i < kRouteF32Tokens * NE; i += kRouteF32Threads)
             logits_out[(size_t)(t0 + i / NE) * LDg + (i % NE)] = lg[(i / NE) * LD + (i % NE)];
         return;
     }
-    select_block<kMaxExperts / 16, 1, 4>(lg, LD, 0, 1, bias, kRouteF32Tokens, t0, T, NE, N, K, gate_norm, ids, gates);
+    select_block<NC, 1, kRouteF32Threads / 64>(lg, LD, 0, 1, bias, kRouteF32Tokens, t0, T, NE, N, K, gate_norm, ids, gates);
+}
+
+static int launch_route_f32(const zeda_layer_desc *d, const void *x, const void *wr, const float *bias, int32_t *ids,
+                            float *gates, float *logits_out, int LDg, hipStream_t s)
+{
+    const int NE = d->N + d->Z, grid = ceil_div(d->T, kRouteF32Tokens);
+#define ZEDA_ROUTE_F32(NC) route_f32_kernel<NC><<<grid, kRouteF32Threads, 0, s>>>((const float *)x, (const float *)wr, bias, d->T, d->H, d->N, NE, d->K, d->gate_norm, ids, gates, logits_out, LDg)
+    if (NE <= 16) ZEDA_ROUTE_F32(1);
+    else if (NE <= 32) ZEDA_ROUTE_F32(2);
+    else if (NE <= 64) ZEDA_ROUTE_F32(4);
+    else if (NE <= 128) ZEDA_ROUTE_F32(8);
+    else ZEDA_ROUTE_F32(16);
+#undef ZEDA_ROUTE_F32
+    return last_launch_status();
 }
 
 // How many workgroups share a token block (bf16 with scratch): as many as still run in one round of workgroups
@@ -701,9 +708,7 @@ int launch_routing_stats(const zeda_layer_desc *d, const void *x, const void *wr
     float *logits = (float *)ws;
     float *p_part = (float *)((char *)ws + stats_logits_bytes(d));
     int32_t *f_part = (int32_t *)((char *)p_part + align_up((size_t)nblk * NE * 4, 256));
-    route_f32_kernel<<<ceil_div(d->T, kRouteF32Tokens), kRouteThreads, 0, s>>>(
-        (const float *)x, (const float *)wr, bias, d->T, d->H, d->N, NE, d->K, d->gate_norm, nullptr, nullptr, logits, LDg);
-    if (hipGetLastError() != hipSuccess) return ZEDA_EHIP;
+    if (launch_route_f32(d, x, wr, bias, nullptr, nullptr, logits, LDg, s) != ZEDA_OK) return ZEDA_EHIP;
 #define ZEDA_STATS(NC) route_stats_kernel<NC><<<nblk, kRouteThreads, 0, s>>>(logits, 1, Tpad, LDg, bias, d->T, NE, d->K, p_part, f_part)
     switch (ceil_div(NE, 16)) {
         case 1: ZEDA_STATS(1); break;   case 2: ZEDA_STATS(2); break;   case 3: ZEDA_STATS(3); break;
@@ -723,15 +728,11 @@ int launch_routing_stats(const zeda_layer_desc *d, const void *x, const void *wr
 int launch_route(const zeda_layer_desc *d, const void *x, const void *wr, const float *bias, int32_t *ids,
                  float *gates, float *partial, uint8_t *cnt8, hipStream_t s)
 {
-    const int NE = d->N + d->Z;
     if (d->dtype == ZEDA_BF16) {
         const RouteExtras ex = {cnt8, cnt8 ? route_counts_ld(d) : 0, nullptr};
         return launch_route_bf16_any(d, x, wr, bias, ids, gates, partial, ex, s);
     }
-    dim3 grid(ceil_div(d->T, kRouteF32Tokens));
-    route_f32_kernel<<<grid, kRouteThreads, 0, s>>>((const float *)x, (const float *)wr, bias, d->T, d->H, d->N, NE, d->K,
-                                                    d->gate_norm, ids, gates, nullptr, 0);
-    return last_launch_status();
+    return launch_route_f32(d, x, wr, bias, ids, gates, nullptr, 0, s);
 }
 
 }  // namespace zeda
