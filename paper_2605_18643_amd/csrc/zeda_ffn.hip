@@ -16,7 +16,6 @@ namespace zeda {
 //              G FB WF NSW NST KC   (NSW, NST: depth of the weight and of the token ring)
 typedef TileCfg<4, 2, 4, 2, 2, 64> CfgPrefill;  // 256 tokens x 256 weight rows, 8 waves, one workgroup per CU
 typedef TileCfg<4, 2, 2, 2, 2, 64> CfgNarrow;   // 256 tokens x 128 weight rows, 4 waves: any H % 128 == 0, I % 64 == 0
-typedef TileCfg<1, 2, 2, 4, 4, 32> CfgDecode;   // 64 tokens x 128 weight rows, 4 waves, two workgroups per CU
 // tiled weights come in 32-wide k blocks: 32-wide chunks, four deep
 typedef TileCfg<4, 2, 4, 4, 4, 32> CfgPrefillT;
 typedef TileCfg<4, 2, 2, 4, 4, 32> CfgNarrowT;
@@ -112,10 +111,7 @@ template <bool GATEUP>
 static int launch_bf16(const zeda_layer_desc *d, const void *tok, const void *w0, const void *w1, const int32_t *offsets,
                        const int32_t *sorted_slot, void *out, hipStream_t s)
 {
-    // an expert never has more rows than there are tokens: small batches take the short token tile
-    const bool decode = d->T <= CfgDecode::BT && cfg_fits<CfgDecode>(d);
     if (d->weight_layout == ZEDA_WEIGHTS_TILED) {
-        if (decode) return launch_tile_kernel<CfgDecode, GATEUP, true>(d, tok, w0, w1, offsets, sorted_slot, out, s);
         if (cfg_fits<CfgPrefillT>(d)) {
             if (rows_may_straddle_tile(d))
                 return launch_adaptive_kernel<CfgPrefillT, CfgPrefillT5, GATEUP, true>(d, tok, w0, w1, offsets, sorted_slot, out, s);
@@ -123,7 +119,6 @@ static int launch_bf16(const zeda_layer_desc *d, const void *tok, const void *w0
         }
         return launch_tile_kernel<CfgNarrowT, GATEUP, true>(d, tok, w0, w1, offsets, sorted_slot, out, s);
     }
-    if (decode) return launch_tile_kernel<CfgDecode, GATEUP, false>(d, tok, w0, w1, offsets, sorted_slot, out, s);
     if (cfg_fits<CfgPrefill>(d))
         return launch_tile_kernel<CfgPrefill, GATEUP, false>(d, tok, w0, w1, offsets, sorted_slot, out, s);
     return launch_tile_kernel<CfgNarrow, GATEUP, false>(d, tok, w0, w1, offsets, sorted_slot, out, s);
@@ -140,6 +135,7 @@ int launch_pack_weights(const zeda_layer_desc *d, const void *w, void *out, bool
 int launch_gateup(const zeda_layer_desc *d, const void *x, const void *wg, const void *wu, const int32_t *offsets,
                   const int32_t *sorted_slot, void *act, hipStream_t s)
 {
+    if (d->dtype == ZEDA_BF16 && ffn_few_supported(d)) return launch_gateup_few(d, x, wg, wu, offsets, sorted_slot, act, s);
     if (d->dtype == ZEDA_BF16) return launch_bf16<true>(d, x, wg, wu, offsets, sorted_slot, act, s);
     return launch_gateup_f32(d, x, wg, wu, offsets, sorted_slot, act, s);
 }
@@ -147,6 +143,7 @@ int launch_gateup(const zeda_layer_desc *d, const void *x, const void *wg, const
 int launch_down(const zeda_layer_desc *d, const void *act, const void *wd, const int32_t *offsets, void *y_slot,
                 hipStream_t s)
 {
+    if (d->dtype == ZEDA_BF16 && ffn_few_supported(d)) return launch_down_few(d, act, wd, offsets, y_slot, s);
     if (d->dtype == ZEDA_BF16) return launch_bf16<false>(d, act, wd, nullptr, offsets, nullptr, y_slot, s);
     return launch_down_f32(d, act, wd, offsets, y_slot, s);
 }
