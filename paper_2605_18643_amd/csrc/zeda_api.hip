@@ -1,6 +1,6 @@
 // C ABI of libzeda: argument validation, workspace carving and the order of the launches.
 // The layer is Eq. 1 of Section 2.1; see include/zeda.h for the meaning of every argument.
-#include "zeda_internal.h"
+#include "zeda_place.h"
 
 namespace zeda {
 
@@ -109,13 +109,17 @@ static int forward_impl(const zeda_layer_desc *desc, const void *x, const void *
         for (int i = 1; i <= ZEDA_NUM_STAGES; ++i) mark(i);
         return rc;
     }
-    if (fused_counts(desc)) {
+    if (route_places(desc)) {
+        const PlaceOut place = {offsets, sorted_slot, slot_to_row, num_real, num_real_out};
+        if ((rc = launch_route(desc, x, w_router, router_bias, ids, gates, route_ws, nullptr, &place, s)) != ZEDA_OK) return rc;
+        mark(1 + ZEDA_STAGE_ROUTE);
+    } else if (fused_counts(desc)) {
         uint8_t *cnt8 = (uint8_t *)(w + L.dispatch_ws);
-        if ((rc = launch_route(desc, x, w_router, router_bias, ids, gates, route_ws, cnt8, s)) != ZEDA_OK) return rc;
+        if ((rc = launch_route(desc, x, w_router, router_bias, ids, gates, route_ws, cnt8, nullptr, s)) != ZEDA_OK) return rc;
         mark(1 + ZEDA_STAGE_ROUTE);
         if ((rc = launch_dispatch_counts(desc, ids, cnt8, offsets, sorted_slot, slot_to_row, num_real, num_real_out, s)) != ZEDA_OK) return rc;
     } else {
-        if ((rc = launch_route(desc, x, w_router, router_bias, ids, gates, route_ws, nullptr, s)) != ZEDA_OK) return rc;
+        if ((rc = launch_route(desc, x, w_router, router_bias, ids, gates, route_ws, nullptr, nullptr, s)) != ZEDA_OK) return rc;
         mark(1 + ZEDA_STAGE_ROUTE);
         if ((rc = launch_dispatch(desc, ids, offsets, sorted_slot, slot_to_row, num_real, num_real_out, w + L.dispatch_ws, s)) != ZEDA_OK) return rc;
     }
@@ -352,7 +356,7 @@ int zeda_route(const zeda_layer_desc *desc, const void *x, const void *w_router,
     if (ws && ws_bytes < route_ws_bytes(desc)) return ZEDA_EWORKSPACE;
     if (desc->T == 0) return ZEDA_OK;
     float *partial = (ws && route_ws_bytes(desc)) ? (float *)ws : nullptr;
-    return launch_route(desc, x, w_router, router_bias, topk_ids, topk_gates, partial, nullptr, (hipStream_t)stream);
+    return launch_route(desc, x, w_router, router_bias, topk_ids, topk_gates, partial, nullptr, nullptr, (hipStream_t)stream);
 }
 
 int zeda_dispatch(const zeda_layer_desc *desc, const int32_t *topk_ids, int32_t *expert_offsets, int32_t *sorted_slot,

@@ -15,7 +15,7 @@
 // eight ballots over the bits of the id (no loop over experts), its rank among them is a bit count, and the
 // running row of an expert lives in LDS per wave.  Still no atomics: in a group only the first lane of each expert
 // updates that expert's counter, and waves own disjoint counters, so the order is again ascending slot index.
-#include "zeda_internal.h"
+#include "zeda_place.h"
 
 namespace zeda {
 
@@ -136,18 +136,6 @@ constexpr int kSegGroups = 4;                                  // 64-slot groups
 constexpr int kSegSlots = kSegWaves * kSegGroups * 64;         // 2048
 constexpr int kSegMax = 256;                                   // segments at most (the place kernel walks them all)
 constexpr int kSegMinSlots = 32769;  // up to 32768 slots the one-kernel form is faster (8 us against 10.6; above, 13 us)
-
-// lanes of the wave whose slot is on the same normal expert as this lane's (0 for a lane that is on none)
-__device__ __forceinline__ unsigned long long same_expert_lanes(int id, bool real)
-{
-    unsigned long long m = __ballot(real);
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-        const unsigned long long bb = __ballot((id >> b) & 1);
-        m &= ((id >> b) & 1) ? bb : ~bb;
-    }
-    return real ? m : 0ull;
-}
 
 // s_cnt[wave][e] += number of this wave's slots on expert e, for its kSegGroups groups of 64 slots
 __device__ __forceinline__ void count_wave(const int32_t *__restrict__ ids, int S, int N, int first_slot, int *cnt_w)

@@ -33,10 +33,13 @@ inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 
 inline size_t elt_size(const zeda_layer_desc *d) { return d->dtype == ZEDA_BF16 ? 2 : 4; }
 
 // stage launchers: arguments are already validated; each returns ZEDA_OK or ZEDA_EHIP
-// partial: scratch of route_ws_bytes(d) for the split-k launch, or NULL (one kernel, no scratch)
+// partial: scratch of route_ws_bytes(d) for a split of the hidden dimension, or NULL (one kernel, no scratch)
 // cnt8: route_counts_bytes(d) of scratch that receives the per-block expert counts, or NULL (bf16 only)
-int launch_route(const zeda_layer_desc *d, const void *x, const void *wr, const float *bias, int32_t *ids,
-                 float *gates, float *partial, uint8_t *cnt8, hipStream_t s);
+// place: where the expert-sorted placement goes (only where route_places(d)), or NULL
+struct PlaceOut;
+int launch_route(const zeda_layer_desc *d, const void *x, const void *wr, const float *bias, int32_t *ids, float *gates,
+                 float *partial, uint8_t *cnt8, const PlaceOut *place, hipStream_t s);
+bool route_places(const zeda_layer_desc *d);  // given scratch, the router can place the whole batch itself
 size_t route_ws_bytes(const zeda_layer_desc *d);
 // Per-block expert counts of the bf16 router: cnt8 [N+Z][route_counts_ld(d)] bytes receive, per block of 16 tokens,
 // the number of slots on every expert - what launch_dispatch_counts starts from.

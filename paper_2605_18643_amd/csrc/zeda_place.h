@@ -1,0 +1,86 @@
+// Expert-sorted placement of a short slot list by one workgroup (Section 2.1: slots on zero experts are dropped).
+#pragma once
+#include "zeda_internal.h"
+
+namespace zeda {
+
+// lanes of the wave whose slot is on the same normal expert as this lane's (0 for a lane that is on none)
+__device__ __forceinline__ unsigned long long same_expert_lanes(int id, bool real)
+{
+    unsigned long long m = __ballot(real);
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        const unsigned long long bb = __ballot((id >> b) & 1);
+        m &= ((id >> b) & 1) ? bb : ~bb;
+    }
+    return real ? m : 0ull;
+}
+
+// Where a placement goes (see zeda_dispatch for the meaning of the tables).
+struct PlaceOut {
+    int32_t *offsets, *sorted_slot, *slot_to_row, *num_real, *num_real_copy;
+};
+
+// LDS of place_list
+struct PlaceLds {
+    int cnt[kMaxK][kMaxExperts];  // slots of wave w's group on every expert, then the running rows
+    int first[kMaxExperts];
+    int wsum[kMaxExperts / 64];
+};
+
+// The S <= 64 * kMaxK slots of s_ids (LDS), one group of 64 per wave, by a workgroup of THREADS >= 64 * kMaxK threads that
+// has met since s_ids was written.  Stable: ascending slot index inside an expert.
+template <int THREADS>
+__device__ __forceinline__ void place_list(const int *s_ids, int S, int N, PlaceLds &s, const PlaceOut &o)
+{
+    static_assert(THREADS / 64 >= kMaxK && THREADS >= kMaxExperts, "one wave per group, one thread per expert");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, groups = (S + 63) / 64;
+    for (int i = tid; i < groups * kMaxExperts; i += THREADS) (&s.cnt[0][0])[i] = 0;
+    __syncthreads();
+    const int slot = tid;
+    const bool in = slot < S;
+    const int id = in ? s_ids[slot] : -1;
+    const bool real = (unsigned)id < (unsigned)N;
+    const unsigned long long m = same_expert_lanes(id, real);
+    const int rank = __popcll(m & ((1ull << lane) - 1ull));
+    if (real && rank == 0) s.cnt[wave][id] = __popcll(m);
+    __syncthreads();
+    int total = 0;
+    if (tid < kMaxExperts) {
+        for (int w = 0; w < groups; ++w) total += s.cnt[w][tid];
+        int incl = total;
+#pragma unroll
+        for (int sh = 1; sh < 64; sh <<= 1) {
+            const int v = __shfl_up(incl, sh);
+            if (lane >= sh) incl += v;
+        }
+        if (lane == 63) s.wsum[wave] = incl;
+        s.first[tid] = incl - total;
+    }
+    __syncthreads();
+    if (tid < kMaxExperts) {
+        int row = s.first[tid];
+        for (int w = 0; w < wave; ++w) row += s.wsum[w];
+        if (tid < N) o.offsets[tid] = row;
+        if (tid == N - 1) {
+            o.offsets[N] = row + total;
+            o.num_real[0] = row + total;
+            if (o.num_real_copy) o.num_real_copy[0] = row + total;
+        }
+        for (int w = 0; w < groups; ++w) {
+            const int c = s.cnt[w][tid];
+            s.cnt[w][tid] = row;
+            row += c;
+        }
+    }
+    __syncthreads();
+    if (real) {
+        const int r = s.cnt[wave][id] + rank;
+        o.sorted_slot[r] = slot;
+        o.slot_to_row[slot] = r;
+    } else if (in) {
+        o.slot_to_row[slot] = -1;
+    }
+}
+
+}  // namespace zeda

@@ -4,11 +4,11 @@
 #include <limits.h>
 
 #include "zeda_f32_tile.h"
+#include "zeda_lds.h"
+#include "zeda_place.h"
 
 namespace zeda {
 
-constexpr int kRouteTokens = 32;  // tokens per workgroup of the bf16 kernel (one MFMA column block)
-constexpr int kRouteThreads = 256;
 
 // Selection runs four tokens per wave, one per row of 16 lanes (the unit of the VALU's data-parallel-primitive
 // cross-lane path), so all reductions stay inside a row and need no LDS traffic and no scalar round trips.
@@ -17,7 +17,15 @@ constexpr int kRouteThreads = 256;
 template <int N>
 __device__ __forceinline__ int dpp_row_ror(int v)
 {
-    return __builtin_amdgcn_update_dpp(v, v, 0x120 + N, 0xf, 0xf, false);
+    return __builtin_amdgcn_mov_dpp(v, 0x120 + N, 0xf, 0xf, true);
+}
+__device__ __forceinline__ int row_max(int v)
+{
+    v = max(v, dpp_row_ror<8>(v));
+    v = max(v, dpp_row_ror<4>(v));
+    v = max(v, dpp_row_ror<2>(v));
+    v = max(v, dpp_row_ror<1>(v));
+    return v;
 }
 __device__ __forceinline__ float row_max(float v)
 {
@@ -35,6 +43,15 @@ __device__ __forceinline__ int row_min(int v)
     v = min(v, dpp_row_ror<1>(v));
     return v;
 }
+// Integers in the order of the floats (both zeros alike; no-numbers come last, as kNoKey): one max instruction takes the
+// lane permutation along, where a float max first quiets its operands.
+constexpr int kNoKey = INT_MIN;
+__device__ __forceinline__ int logit_key(float v)
+{
+    const int b = __float_as_int(v + 0.0f);  // -0 -> +0
+    return v == v ? b ^ ((b >> 31) & 0x7fffffff) : kNoKey;
+}
+__device__ __forceinline__ float key_logit(int k) { return __int_as_float(k ^ ((k >> 31) & 0x7fffffff)); }
 // Sum over the row in one fixed order (an inclusive scan with row_shr 1, 2, 4, 8 leaves the total in the row's
 // last lane), handed to every lane of the row, so that all lanes divide by the same number.
 __device__ __forceinline__ float row_sum(float v)
@@ -71,43 +88,44 @@ __device__ __forceinline__ float wave_sum(float v)
 // candidates equal to it (ties go to the lower index), which its owner then removes.  Lane j of the row keeps
 // slot j, so lanes 0..K-1 end up with the slots in descending-logit order (K <= 16).
 // Returns the expert of the slot this lane keeps (lane j < K of a row: slot j of the row's token), or -1.
+// bias: this lane's candidates' biases.
 // probs (may be NULL): an LDS table [token][LDP] that receives, for every token of the wave, the routing
 // probability of every expert (softmax over all NE logits).
 template <int NC, int NP>
-__device__ __forceinline__ int select_rows(const float *lg, int LD, int pstride, int np_rt, const float *__restrict__ bias, int tk0,
+__device__ __forceinline__ int select_rows(const float *lg, int LD, int pstride, const float (&bias)[NC], int tk0,
                                            int ntok, int t0, int T, int NE, int N, int K, int gate_norm,
                                            int32_t *__restrict__ ids, float *__restrict__ gates, float *probs = nullptr,
                                            int LDP = 0)
 {
     const int lane = threadIdx.x & 63, l16 = lane & 15, tk = tk0 + (lane >> 4);
     const bool ok = tk < ntok && t0 + tk < T;
-    float cand[NC];
+    int cand[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
         const int e = l16 + 16 * c;
-        float v = -INFINITY;
-        if (ok && e < NE) {
-            // the NP partial sums over slices of the hidden dimension, added in a fixed order, then the bias
-            v = lg[tk * LD + e];
+        // the NP partial sums over slices of the hidden dimension, added in a fixed order, then the bias (columns past
+        // NE of the tables are readable and left out)
+        float v = lg[tk * LD + e];
 #pragma unroll
-            for (int q = 1; q < NP; ++q) v += lg[(size_t)q * pstride + tk * LD + e];
-            if (bias) v += bias[e];
-        }
-        cand[c] = v;
+        for (int q = 1; q < NP; ++q) v += lg[q * pstride + tk * LD + e];
+        int key = logit_key(v + bias[c]);
+        asm volatile("" : "+v"(key));  // (no branch around every candidate)
+        cand[c] = ok && e < NE ? key : kNoKey;
     }
     auto local_max = [&]() {
-        float m = cand[0];
+        int m = cand[0];
 #pragma unroll
-        for (int c = 1; c < NC; ++c) m = fmaxf(m, cand[c]);
+        for (int c = 1; c < NC; ++c) m = max(m, cand[c]);
         return m;
     };
-    const float all_max = row_max(local_max());
+    int m = row_max(local_max());
+    const float all_max = key_logit(m);
     float all_sum = 0.f;
     if (gate_norm == ZEDA_GATE_SOFTMAX || probs) {
         float ex[NC], sacc = 0.f;
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            ex[c] = (ok && l16 + 16 * c < NE) ? expf(cand[c] - all_max) : 0.f;
+            ex[c] = (ok && l16 + 16 * c < NE) ? expf(key_logit(cand[c]) - all_max) : 0.f;
             sacc += ex[c];
         }
         all_sum = row_sum(sacc);
@@ -120,16 +138,17 @@ __device__ __forceinline__ int select_rows(const float *lg, int LD, int pstride,
     int my_id = 0;
     float my_logit = -INFINITY;
     for (int j = 0; j < K; ++j) {
-        const float m = row_max(local_max());
+        if (j > 0) m = row_max(local_max());
         int mine = INT_MAX;
 #pragma unroll
         for (int c = NC - 1; c >= 0; --c)
             if (cand[c] == m) mine = l16 + 16 * c;  // descending c: the lowest index survives
-        const int win = row_min(mine);
+        int win = row_min(mine);
 #pragma unroll
         for (int c = 0; c < NC; ++c)
-            if (win == l16 + 16 * c) cand[c] = -INFINITY;
-        if (l16 == j) { my_id = win; my_logit = m; }
+            if (win == l16 + 16 * c) cand[c] = kNoKey;
+        if (m == kNoKey) win = INT_MAX;  // nothing but no-numbers left: no expert
+        if (l16 == j) { my_id = win; my_logit = key_logit(m); }
     }
     const bool slot = l16 < K;
     const float ex = slot ? expf(my_logit - all_max) : 0.f;
@@ -145,26 +164,112 @@ __device__ __forceinline__ int select_rows(const float *lg, int LD, int pstride,
     return (slot && ok) ? my_id : -1;
 }
 
+// The same for one token by a whole wave: lane l holds the candidates l, l + 64, ...; a round's winner is found from
+// ballots, lowest candidate group and lane first, i.e. the lowest index.  Shorter rounds than the above (few
+// candidates per lane): for workgroups with a wave for every token.  lg: the token's logits, biases included.
+template <int NC>
+__device__ __forceinline__ int select_wave(const float *lg, bool ok, size_t t, int NE, int N, int K, int gate_norm,
+                                           int32_t *__restrict__ ids, float *__restrict__ gates, float *probs = nullptr)
+{
+    const int lane = threadIdx.x & 63;
+    int cand[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        const int e = lane + 64 * c;
+        int key = logit_key(lg[e]);
+        asm volatile("" : "+v"(key));
+        cand[c] = ok && e < NE ? key : kNoKey;
+    }
+    auto wave_max = [&]() {
+        int m = cand[0];
+#pragma unroll
+        for (int c = 1; c < NC; ++c) m = max(m, cand[c]);
+        m = row_max(m);
+        return max(max(__builtin_amdgcn_readlane(m, 0), __builtin_amdgcn_readlane(m, 16)),
+                   max(__builtin_amdgcn_readlane(m, 32), __builtin_amdgcn_readlane(m, 48)));
+    };
+    int m = wave_max();
+    const float all_max = key_logit(m);
+    float all_sum = 0.f;
+    if (gate_norm == ZEDA_GATE_SOFTMAX || probs) {
+        float ex[NC], sacc = 0.f;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            ex[c] = (ok && lane + 64 * c < NE) ? expf(key_logit(cand[c]) - all_max) : 0.f;
+            sacc += ex[c];
+        }
+        all_sum = wave_sum(sacc);
+        if (probs && ok) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+                if (lane + 64 * c < NE) probs[lane + 64 * c] = ex[c] / all_sum;
+        }
+    }
+    int my_id = 0;
+    float my_logit = -INFINITY;
+    for (int j = 0; j < K; ++j) {
+        if (j > 0) m = wave_max();
+        int win = INT_MAX;
+#pragma unroll
+        for (int c = NC - 1; c >= 0; --c) {
+            const unsigned long long eq = __ballot(cand[c] == m);
+            if (eq) win = 64 * c + __ffsll((long long)eq) - 1;
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+            if (win == lane + 64 * c) cand[c] = kNoKey;
+        if (m == kNoKey) win = INT_MAX;  // nothing but no-numbers left: no expert
+        if (lane == j) { my_id = win; my_logit = key_logit(m); }
+    }
+    const bool slot = lane < K;
+    const float ex = slot ? expf(my_logit - all_max) : 0.f;
+    float dn;
+    if (gate_norm == ZEDA_GATE_SOFTMAX) dn = all_sum;
+    else if (gate_norm == ZEDA_GATE_TOPK_NORM) dn = row_sum(ex);
+    else dn = row_sum((slot && my_id < N) ? ex : 0.f);
+    if (slot && ok && ids) {
+        ids[t * K + lane] = my_id;
+        gates[t * K + lane] = dn > 0.f ? ex / dn : 0.f;
+    }
+    return (slot && ok) ? my_id : -1;
+}
+
+// this lane's NC candidates' router biases (past NE: any)
+template <int NC>
+__device__ __forceinline__ void load_bias(float (&b)[NC], const float *__restrict__ bias, int NE)
+{
+    const int l16 = threadIdx.x & 15;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) b[c] = 0.f;
+    if (bias) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) b[c] = bias[min(l16 + 16 * c, NE - 1)];
+    }
+}
+
 // All ntok tokens of a workgroup of NWAVES waves, four per wave at a time.  lg holds NP partial logit tables
 // pstride floats apart.
 // s_cnt (LDS, may be NULL): [ntok / 16][kMaxExperts] counters, zeroed by the caller; every selected slot adds one to
 // the counter of its expert in its block of 16 tokens (the counts do not depend on the order of the additions).
 // probs (LDS, may be NULL): [ntok][LDP] table that receives every token's routing probabilities.
 template <int NC, int NP, int NWAVES>
-__device__ __forceinline__ void select_block(const float *lg, int LD, int pstride, int np_rt, const float *__restrict__ bias, int ntok,
+__device__ __forceinline__ void select_block(const float *lg, int LD, int pstride, const float (&bias)[NC], int ntok,
                                              int t0, int T, int NE, int N, int K, int gate_norm, int32_t *__restrict__ ids,
                                              float *__restrict__ gates, int *s_cnt = nullptr, float *probs = nullptr,
                                              int LDP = 0)
 {
     const int wave = threadIdx.x >> 6;
     for (int tk0 = 4 * wave; tk0 < ntok; tk0 += 4 * NWAVES) {
-        const int id = select_rows<NC, NP>(lg, LD, pstride, np_rt, bias, tk0, ntok, t0, T, NE, N, K, gate_norm, ids, gates, probs, LDP);
-        if (s_cnt && id >= 0) atomicAdd(&s_cnt[(tk0 >> 4) * kMaxExperts + id], 1);
+        const int id = select_rows<NC, NP>(lg, LD, pstride, bias, tk0, ntok, t0, T, NE, N, K, gate_norm, ids, gates, probs, LDP);
+        if (s_cnt && (unsigned)id < (unsigned)kMaxExperts) atomicAdd(&s_cnt[(tk0 >> 4) * kMaxExperts + id], 1);
     }
 }
 
+// floats from one block's row of the statistics tables to the next: rows start at 16 bytes
+__host__ __device__ constexpr int stats_ld(int NE) { return (NE + 3) & ~3; }
+
 // After select_block (and a barrier): what the workgroup's blocks of 16 tokens hand to the expert-sorted placement
-// and to the routing statistics.  cnt8[e][cnt_ld] bytes: slots of every block on expert e; p_part[block][NE]: the
+// and to the routing statistics.  cnt8[e][cnt_ld] bytes: slots of every block on expert e; p_part[block][stats_ld(NE)]: the
 // block's sum of every expert's routing probability, added in token order.
 template <int THREADS>
 __device__ __forceinline__ void publish_blocks(const int *s_cnt, const float *probs, int LDP, int ntok, int t0, int T, int NE,
@@ -179,29 +284,43 @@ __device__ __forceinline__ void publish_blocks(const int *s_cnt, const float *pr
             float ps = 0.f;
             const int nt = min(16, min(ntok, T - t0) - u * 16);
             for (int t = 0; t < nt; ++t) ps += probs[(u * 16 + t) * LDP + e];
-            p_part[(size_t)blk * NE + e] = ps;
+            p_part[(size_t)blk * stats_ld(NE) + e] = ps;
         }
     }
 }
 
-// bf16 router.  A workgroup owns kRouteTokens tokens and all NE experts (NB MFMA row blocks of 32; tokens
-// are the MFMA columns).  x rows and router rows stream through an LDS ring (up to six slots) in 64-wide
-// k chunks with global->LDS loads, 128-byte rows whose 16-byte pieces are XOR-permuted by the row index
-// (applied on the global address) so that fragment reads spread over the banks; a counted s_waitcnt and
-// one s_barrier per chunk order the ring.  The four waves split the four 16-wide MFMA steps of every
-// chunk, so each holds a partial sum over a quarter of the hidden dimension; each stores it in an LDS table
-// of its own and the selection adds the four tables in wave order (a fixed order: the logits are
-// reproducible); each wave selects for 8 tokens, four at a time (one per row of 16 lanes).
-// With many tokens the router rows, which every workgroup reads in full, are most of the traffic (640 KiB per
-// workgroup from L2 against 128 KiB of token rows): TB = 2 gives a workgroup two token blocks (64 tokens), which
-// halves that traffic per token; it is used once there are enough token blocks to fill the device without it.
-// ring depth: as many slots as fit in LDS, at most six
-constexpr int route_stages(int nb, int tb = 1)
-{
-    return 160 * 1024 / ((32 * tb + 32 * nb) * 128) < 6 ? 160 * 1024 / ((32 * tb + 32 * nb) * 128) : 6;
-}
+// bf16 router.  A workgroup of 16 waves owns 16 TB tokens, all NE experts (experts are MFMA rows, tokens MFMA columns,
+// 16x16x32) and a slice of the hidden dimension, which may be all of it.  x rows and router rows stream through an LDS ring
+// in KC-wide k chunks with global->LDS loads whose 16-byte pieces are XOR-permuted by the row (on the global address) so
+// that fragment reads spread over the banks.  The waves split a chunk's k steps and the expert blocks; the k steps' sums
+// meet in LDS tables.  Without a split the workgroup selects for its tokens, four per wave, adding the tables in order;
+// with one it leaves its logits to route_select_kernel.  All orders are fixed: the logits are reproducible.
+//
+// What bounds it is what a CU pulls from L2: every router row of its slice (8-row pieces of 128 bytes and more arrive at up
+// to 129 GB/s per CU, 64-byte pieces at half of that), then launch and selection (route_plan weighs them).
+constexpr int kRouteThreads = 1024;
+constexpr int kRouteWaves = kRouteThreads / 64;
+constexpr int kRouteLds = 160 * 1024;
 
-__device__ __forceinline__ int route_swz(int row, int piece) { return piece ^ ((row >> 1) & 7); }
+template <int NB, int TB>
+struct RouteCfg {
+    static constexpr int TOK = 16 * TB;              // tokens of the workgroup
+    static constexpr int KC = TB == 1 ? 128 : 64;    // k chunk
+    static constexpr int KS = KC / 32;               // MFMA k steps per chunk
+    static constexpr int GROUPS = kRouteWaves / KS;  // expert groups: group g owns the 16-expert blocks g, g + GROUPS, ...
+    static constexpr int EB = 2 * NB, BPW = (EB + GROUPS - 1) / GROUPS;
+    static constexpr int ROWB = 2 * KC, PPR = ROWB / 16, RPI = 64 / PPR;  // bytes, 16-byte pieces per row; rows per load instruction
+    static constexpr int ROWS = TOK + 32 * NB, STAGE = ROWS * ROWB;
+    static constexpr int NI = ROWS / RPI;            // load instructions per chunk, dealt out to the waves
+    static constexpr int STAGES = kRouteLds / STAGE < 8 ? kRouteLds / STAGE : 8;
+    static constexpr int LD = NB * 32 + 1;
+    static constexpr int TABLES = KS * TOK * LD * 4;  // bytes of the logit tables, which reuse the ring, as do the counters
+    static constexpr int CNT_OFF = (TABLES + 15) / 16 * 16, END = CNT_OFF + TB * kMaxExperts * 4;
+    static constexpr int LDS_BYTES = STAGES * STAGE > END ? STAGES * STAGE : END;
+    static_assert(ROWS % RPI == 0 && STAGES >= 2 && LDS_BYTES <= kRouteLds, "");
+    static_assert((STAGES - 1) * ((NI + kRouteWaves - 1) / kRouteWaves) <= 63, "vmcnt is a 6-bit counter");
+    static __device__ __forceinline__ int swz(int row, int piece) { return KC == 128 ? piece ^ (row & 15) : piece ^ ((row >> 1) & 7); }
+};
 
 template <int N>
 __device__ __forceinline__ void route_wait_vmcnt()
@@ -209,167 +328,181 @@ __device__ __forceinline__ void route_wait_vmcnt()
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// partial (may be NULL): receives the logits of the workgroup's slice of the hidden dimension instead of a selection.
+// cnt8, p_part (either may be NULL): see publish_blocks.
 template <int NB, int TB>
-__global__ __launch_bounds__(kRouteThreads) void route_bf16_kernel(const bf16_t *__restrict__ x,
-                                                                   const bf16_t *__restrict__ wr,
-                                                                   const float *__restrict__ bias, int T, int H, int N,
-                                                                   int NE, int K, int gate_norm,
-                                                                   int32_t *__restrict__ ids, float *__restrict__ gates,
-                                                                   float *__restrict__ partial, int Tpad,
+__global__ __launch_bounds__(kRouteThreads) void route_bf16_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ wr,
+                                                                   const float *__restrict__ bias, int T, int H, int N, int NE,
+                                                                   int K, int gate_norm, int32_t *__restrict__ ids,
+                                                                   float *__restrict__ gates, float *__restrict__ partial,
                                                                    uint8_t *__restrict__ cnt8, int cnt_ld,
                                                                    float *__restrict__ p_part)
 {
-    constexpr int TOK = 32 * TB;                  // tokens of the workgroup
-    constexpr int LD = NB * 32 + 1;
-    constexpr int ROWS = TOK + 32 * NB;           // rows of one ring slot: tokens first, then router rows
-    constexpr int STAGE = ROWS * 128;
-    constexpr int NL = TB + NB;                   // wave load instructions (8 rows each) per chunk and wave
-    constexpr int kRouteStages = route_stages(NB, TB);
-    constexpr int NT = 4 / TB;                    // partial logit tables in LDS (the four waves' sums meet in them)
-    static_assert(kRouteThreads == kMaxExperts, "");
-    static_assert(kRouteTokens == 32 && kRouteThreads == 256 && (TB == 1 || TB == 2), "token blocks of 32, four waves");
-    static_assert(NT * TOK * LD * 4 + (TOK / 16) * kMaxExperts * 4 <= kRouteStages * STAGE,
-                  "the partial logit tables and the per-block expert counters reuse the ring");
+    typedef RouteCfg<NB, TB> C;
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
-    float *lg = reinterpret_cast<float *>(lds);
-
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int t0 = blockIdx.x * TOK;
-    const int col = lane & 31, half = lane >> 5;
+    const int t0 = blockIdx.x * C::TOK, l16 = lane & 15, kq = lane >> 4;
+    const int ks = wave % C::KS, grp = wave / C::KS;
 
-    const bf16_t *src[NL];
+    float bias_c[2 * NB];
+    load_bias<2 * NB>(bias_c, bias, NE);
+
+    constexpr int NLHI = (C::NI + kRouteWaves - 1) / kRouteWaves, NLLO = C::NI / kRouteWaves;
+    const bool hi = wave < C::NI % kRouteWaves || NLHI == NLLO;  // this wave issues NLHI loads per chunk, else NLLO
+    const bf16_t *src[NLHI];
 #pragma unroll
-    for (int i = 0; i < NL; ++i) {
-        const int row = (wave + 4 * i) * 8 + (lane >> 3), piece = lane & 7;
-        const bf16_t *base = row < TOK ? x + (size_t)min(t0 + row, T - 1) * H : wr + (size_t)min(row - TOK, NE - 1) * H;
-        src[i] = base + route_swz(row, piece) * 8;
+    for (int i = 0; i < NLHI; ++i) {
+        const int row = min((wave + kRouteWaves * i) * C::RPI + lane / C::PPR, C::ROWS - 1), piece = lane % C::PPR;
+        const bf16_t *base = row < C::TOK ? x + (size_t)min(t0 + row, T - 1) * H : wr + (size_t)min(row - C::TOK, NE - 1) * H;
+        src[i] = base + (size_t)blockIdx.y * (H / gridDim.y) + C::swz(row, piece) * 8;
     }
-    // All workgroups read the same router rows, and rows are a power-of-two number of bytes apart, so one
-    // k chunk of every row sits on a single L2 channel: workgroups walking the chunks in the same order
-    // would queue on that channel.  Each starts at a different chunk instead (the sum over k does not
-    // depend on the order; the order is fixed per workgroup, so results stay reproducible).
-    // gridDim.y workgroups share a token block: each takes a contiguous slice of the hidden dimension
-    const int nk = H / 64 / gridDim.y, k0 = blockIdx.y * nk;
+    // All workgroups read the same router rows, and rows are a power-of-two number of bytes apart, so one k chunk of every
+    // row sits on a few L2 channels: each workgroup starts at a chunk of its own (a fixed order, so results are
+    // reproducible).
+    const int nk = H / C::KC / gridDim.y;  // gridDim.y workgroups share a token block: each takes a slice of the hidden dimension
     const int rot = (int)((blockIdx.x * 5u) % (unsigned)nk);
-    auto issue = [&](int chunk) {
-        unsigned char *slot = lds + (chunk % kRouteStages) * STAGE;
-        int kc = chunk + rot;
-        if (kc >= nk) kc -= nk;
+    int kc = rot;  // the next chunk to fetch
+    auto issue = [&](int s) {
+        unsigned char *slot = lds + s * C::STAGE;
 #pragma unroll
-        for (int i = 0; i < NL; ++i)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src[i] + (size_t)(k0 + kc) * 64),
-                                             (__attribute__((address_space(3))) void *)(slot + (wave + 4 * i) * 1024), 16, 0, 0);
+        for (int i = 0; i < NLHI; ++i)
+            if (i < NLLO || hi)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src[i] + (size_t)kc * C::KC),
+                                                 (__attribute__((address_space(3))) void *)(slot + (wave + kRouteWaves * i) * 1024), 16, 0, 0);
+        kc = kc + 1 == nk ? 0 : kc + 1;
     };
 
-    f32x16 acc[NB][TB];
+    f32x4 acc[C::BPW][TB];
 #pragma unroll
-    for (int b = 0; b < NB; ++b)
+    for (int b = 0; b < C::BPW; ++b)
+#pragma unroll
+        for (int u = 0; u < TB; ++u) acc[b][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+#pragma unroll
+    for (int c = 0; c < C::STAGES - 1; ++c) issue(c);  // (with fewer chunks than slots some are fetched again and not used)
+#pragma unroll
+    for (int c = 0; c < 2 * NB; ++c) asm volatile("" : "+v"(bias_c[c]));  // (fetched up here, not where the selection uses it)
+    // (blocks start at multiples of 16 rows, so the piece permutation depends on l16 only)
+    const uint32_t ring = lds_addr(lds), pos = C::swz(l16, 4 * ks + kq) * 16;
+    int cslot = 0, fslot = C::STAGES - 1;  // slots of the chunk being multiplied and of the next one to fetch
+    for (int it = 0; it < nk; ++it) {
+        if (it + C::STAGES - 2 < nk) {
+            if (hi) route_wait_vmcnt<(C::STAGES - 2) * NLHI>();
+            else route_wait_vmcnt<(C::STAGES - 2) * NLLO>();
+        } else {
+            route_wait_vmcnt<0>();
+        }
+        __builtin_amdgcn_s_barrier();
+        if (it + C::STAGES - 1 < nk) issue(fslot);
+        const uint32_t cur = ring + cslot * C::STAGE;
+        cslot = cslot + 1 == C::STAGES ? 0 : cslot + 1;
+        fslot = fslot + 1 == C::STAGES ? 0 : fslot + 1;
+        // this wave's 32-wide step of the chunk: pieces 4 ks .. 4 ks + 3 of every row (groups with fewer blocks than BPW
+        // read their last block again and leave it out)
+        u32x4 tb[TB], fa[C::BPW];
+#pragma unroll
+        for (int u = 0; u < TB; ++u) tb[u] = lds_read_b128(cur + (u * 16 + l16) * C::ROWB + pos);
+#pragma unroll
+        for (int b = 0; b < C::BPW; ++b)
+            fa[b] = lds_read_b128(cur + (C::TOK + min(grp + C::GROUPS * b, C::EB - 1) * 16 + l16) * C::ROWB + pos);
+#pragma unroll
+        for (int u = 0; u < TB; ++u) lds_wait(tb[u]);
+#pragma unroll
+        for (int b = 0; b < C::BPW; ++b) lds_wait(fa[b]);
+#pragma unroll
+        for (int b = 0; b < C::BPW; ++b) {
+            if (C::EB % C::GROUPS && b == C::BPW - 1 && grp + C::GROUPS * b >= C::EB) break;
+#pragma unroll
+            for (int u = 0; u < TB; ++u)
+                acc[b][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fa[b]), __builtin_bit_cast(bf16x8, tb[u]),
+                                                                    acc[b][u], 0, 0, 0);
+        }
+    }
+    __syncthreads();  // everyone is done with the ring: its memory now holds the logits and what the selection leaves
+
+    // acc[b][u][v]: expert 16 (grp + GROUPS b) + 4 kq + v, token 16 u + l16; one table per k step of the chunk
+    float *lg = reinterpret_cast<float *>(lds);
+    int *s_cnt = reinterpret_cast<int *>(lds + C::CNT_OFF);
+#pragma unroll
+    for (int b = 0; b < C::BPW; ++b) {
+        if (grp + C::GROUPS * b >= C::EB) break;
 #pragma unroll
         for (int u = 0; u < TB; ++u)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[b][u][v] = 0.f;
-
-#pragma unroll
-    for (int c = 0; c < kRouteStages - 1; ++c)
-        if (c < nk) issue(c);
-    for (int it = 0; it < nk; ++it) {
-        if (it + kRouteStages - 2 < nk) route_wait_vmcnt<(kRouteStages - 2) * NL>();
-        else route_wait_vmcnt<0>();
-        __builtin_amdgcn_s_barrier();
-        if (it + kRouteStages - 1 < nk) issue(it + kRouteStages - 1);
-        const unsigned char *cur = lds + (it % kRouteStages) * STAGE;
-        // this wave's 16-wide step of the chunk: pieces 2*wave and 2*wave+1 of every row
-        bf16x8 tb[TB];
-#pragma unroll
-        for (int u = 0; u < TB; ++u) {
-            const int trow = u * 32 + col;
-            tb[u] = *reinterpret_cast<const bf16x8 *>(cur + trow * 128 + route_swz(trow, 2 * wave + half) * 16);
-        }
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const int row = TOK + b * 32 + col;
-            const bf16x8 fa = *reinterpret_cast<const bf16x8 *>(cur + row * 128 + route_swz(row, 2 * wave + half) * 16);
-#pragma unroll
-            for (int u = 0; u < TB; ++u) acc[b][u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, tb[u], acc[b][u], 0, 0, 0);
-        }
+            for (int v = 0; v < 4; ++v)
+                lg[(ks * C::TOK + u * 16 + l16) * C::LD + (grp + C::GROUPS * b) * 16 + 4 * kq + v] = acc[b][u][v];
     }
-    __syncthreads();  // everyone is done with the ring: its memory now holds the logits
-
-    // acc[b][u][v]: expert 32b + 8(v/4) + 4*half + v%4, token 32u + col.  The waves' partial sums (each over a
-    // quarter of the hidden dimension) meet in NT tables: wave w uses table w % NT, the waves of a table take turns
-    // in wave order, the first one storing and the later ones adding; the selection adds the tables in order.
-    // Every order is fixed, so the logits are reproducible.
-    float *mine = lg + (wave % NT) * (TOK * LD);
-#pragma unroll
-    for (int turn = 0; turn < 4 / NT; ++turn) {
-        if (wave / NT == turn) {
-#pragma unroll
-            for (int b = 0; b < NB; ++b)
-#pragma unroll
-                for (int u = 0; u < TB; ++u)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        float *p = mine + (u * 32 + col) * LD + b * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
-                        *p = turn == 0 ? acc[b][u][v] : *p + acc[b][u][v];
-                    }
-        }
+    if (partial) {
+        // this slice's sums (the tables added in order) go to partial[slice][token][expert]: route_select_kernel adds the
+        // slices in order and selects
         __syncthreads();
-    }
-    if (partial == nullptr) {
-        // cnt8, p_part (either may be NULL): per block of 16 tokens, the slots on every expert (for the expert-sorted
-        // placement) and the sums of the routing probabilities (routing statistics), see publish_blocks.  The
-        // probabilities of a token overwrite its row of the first logit table once the token's logits are in registers.
-        int *s_cnt = reinterpret_cast<int *>(lg + NT * TOK * LD);
-        if (cnt8) {
-            for (int i = tid; i < (TOK / 16) * kMaxExperts; i += kRouteThreads) s_cnt[i] = 0;
-            __syncthreads();
-        }
-        select_block<2 * NB, NT, 4>(lg, LD, TOK * LD, NT, bias, TOK, t0, T, NE, N, K, gate_norm, ids, gates,
-                                    cnt8 ? s_cnt : nullptr, p_part ? lg : nullptr, LD);
-        if (cnt8 || p_part) {
-            __syncthreads();
-            publish_blocks<kRouteThreads>(s_cnt, lg, LD, TOK, t0, T, NE, cnt8, cnt_ld, p_part);
-        }
-    } else {
-        // split-k launch: this workgroup's sums over its slice (the tables added in order) go to
-        // partial[blockIdx.y][token][expert]; route_select_kernel adds the slices in order and selects
-        float *dst = partial + ((size_t)blockIdx.y * Tpad + t0) * (NB * 32);
-        for (int i = tid; i < TOK * NB * 32; i += kRouteThreads) {
-            const int tk = i / (NB * 32), e = i - tk * (NB * 32);
-            float v = lg[tk * LD + e];
+        f32x4 *dst = reinterpret_cast<f32x4 *>(partial + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * (C::TOK * NB * 32));
+        for (int i = tid; i < C::TOK * NB * 8; i += kRouteThreads) {
+            const float *p = lg + (i / (NB * 8)) * C::LD + (i % (NB * 8)) * 4;
+            f32x4 v;
 #pragma unroll
-            for (int q = 1; q < NT; ++q) v += lg[q * TOK * LD + tk * LD + e];
+            for (int k = 0; k < 4; ++k) {
+                v[k] = p[k];
+#pragma unroll
+                for (int q = 1; q < C::KS; ++q) v[k] += p[q * C::TOK * C::LD + k];
+            }
             dst[i] = v;
         }
+        return;
+    }
+    if (cnt8)
+        for (int i = tid; i < TB * kMaxExperts; i += kRouteThreads) s_cnt[i] = 0;
+    __syncthreads();
+    // The probabilities of a token overwrite its row of the first logit table once the token's logits are in registers.
+    select_block<2 * NB, C::KS, kRouteWaves>(lg, C::LD, C::TOK * C::LD, bias_c, C::TOK, t0, T, NE, N, K, gate_norm, ids, gates,
+                                             cnt8 ? s_cnt : nullptr, p_part ? lg : nullptr, C::LD);
+    if (cnt8 || p_part) {
+        __syncthreads();
+        publish_blocks<kRouteThreads>(s_cnt, lg, C::LD, C::TOK, t0, T, NE, cnt8, cnt_ld, p_part);
     }
 }
 
-// Second step of a split-k launch: 16 tokens per workgroup, four per wave, logits read from the partial tables.
+// Second kernel where the hidden dimension was split: 16 tokens per workgroup, a wave each.  All threads add up the slices'
+// tables (16-byte loads, all slices' in flight), then every wave selects for its token.
+// cnt8, p_part (either may be NULL): see publish_blocks.  place.offsets (may be NULL): one workgroup, which then places.
 constexpr int kSelectTokens = 16;
-template <int NB, int NSPLIT>
+template <int NB, int NP>
 __global__ __launch_bounds__(kRouteThreads) void route_select_kernel(const float *__restrict__ partial, int Tpad,
                                                                      const float *__restrict__ bias, int T, int N, int NE,
                                                                      int K, int gate_norm, int32_t *__restrict__ ids,
                                                                      float *__restrict__ gates, uint8_t *__restrict__ cnt8,
-                                                                     int cnt_ld, float *__restrict__ p_part)
+                                                                     int cnt_ld, float *__restrict__ p_part, PlaceOut place)
 {
-    static_assert(kSelectTokens == 16, "one block of the per-block tables per workgroup");
-    constexpr int LDP = NB * 32 + 1;
-    __shared__ int s_cnt[kMaxExperts];
-    __shared__ float s_probs[kSelectTokens * LDP];  // (used by the statistics run only)
-    const int t0 = blockIdx.x * kSelectTokens;
-    if (cnt8) {
-        s_cnt[threadIdx.x] = 0;  // (kRouteThreads == kMaxExperts)
-        __syncthreads();
+    static_assert(kSelectTokens == 16 && kRouteWaves == 16, "one block of the per-block tables, a wave per token");
+    constexpr int E = NB * 32, NC = (E + 63) / 64, LD = NC * 64;
+    __shared__ __attribute__((aligned(16))) float lg[kSelectTokens * LD];
+    __shared__ int s_cnt[kMaxExperts], s_ids[kSelectTokens * kMaxK];
+    __shared__ PlaceLds s_place;
+    const int t0 = blockIdx.x * kSelectTokens, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (int i = threadIdx.x; i < kSelectTokens * E / 4; i += kRouteThreads) {
+        const int tk = i / (E / 4), e = (i - tk * (E / 4)) * 4;
+        f32x4 b = {0.f, 0.f, 0.f, 0.f};
+        if (bias) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) b[k] = bias[min(e + k, NE - 1)];
+        }
+        f32x4 v[NP];
+#pragma unroll
+        for (int q = 0; q < NP; ++q) v[q] = *reinterpret_cast<const f32x4 *>(partial + ((size_t)q * Tpad + t0 + tk) * E + e);
+#pragma unroll
+        for (int q = 1; q < NP; ++q) v[0] += v[q];
+        *reinterpret_cast<f32x4 *>(lg + tk * LD + e) = v[0] + b;
     }
-    // (the number of slices is a template parameter so that all loads of a lane's candidates are issued together)
-    select_block<2 * NB, NSPLIT, 4>(partial + (size_t)t0 * (NB * 32), NB * 32, Tpad * NB * 32, NSPLIT, bias, kSelectTokens,
-                                    t0, T, NE, N, K, gate_norm, ids, gates, cnt8 ? s_cnt : nullptr,
-                                    p_part ? s_probs : nullptr, LDP);
-    if (cnt8 || p_part) {
-        __syncthreads();
-        publish_blocks<kRouteThreads>(s_cnt, s_probs, LDP, kSelectTokens, t0, T, NE, cnt8, cnt_ld, p_part);
-    }
+    if (threadIdx.x < kMaxExperts) s_cnt[threadIdx.x] = 0;
+    __syncthreads();
+    // (a token's probabilities overwrite its logits, which are in its wave's registers by then)
+    const int id = select_wave<NC>(lg + wave * LD, t0 + wave < T, (size_t)t0 + wave, NE, N, K, gate_norm, ids, gates,
+                                   p_part ? lg + wave * LD : nullptr);
+    if ((unsigned)id < (unsigned)kMaxExperts) atomicAdd(&s_cnt[id], 1);
+    if (lane < K) s_ids[wave * K + lane] = id;
+    __syncthreads();
+    if (cnt8 || p_part) publish_blocks<kRouteThreads>(s_cnt, lg, LD, kSelectTokens, t0, T, NE, cnt8, cnt_ld, p_part);
+    if (place.offsets) place_list<kRouteThreads>(s_ids, T * K, N, s_place, place);
 }
 
 // fp32 router.  A workgroup owns 16 tokens and all experts; its 16 waves split the hidden dimension and, above 32
@@ -415,7 +548,9 @@ __global__ __launch_bounds__(kRouteF32Threads) void route_f32_kernel(const float
             logits_out[(size_t)(t0 + i / NE) * LDg + (i % NE)] = lg[(i / NE) * LD + (i % NE)];
         return;
     }
-    select_block<NC, 1, kRouteF32Threads / 64>(lg, LD, 0, 1, bias, kRouteF32Tokens, t0, T, NE, N, K, gate_norm, ids, gates);
+    float bias_c[NC];
+    load_bias<NC>(bias_c, bias, NE);
+    select_block<NC, 1, kRouteF32Threads / 64>(lg, LD, 0, bias_c, kRouteF32Tokens, t0, T, NE, N, K, gate_norm, ids, gates);
 }
 
 static int launch_route_f32(const zeda_layer_desc *d, const void *x, const void *wr, const float *bias, int32_t *ids,
@@ -432,106 +567,111 @@ static int launch_route_f32(const zeda_layer_desc *d, const void *x, const void 
     return last_launch_status();
 }
 
-// How many workgroups share a token block (bf16 with scratch): as many as still run in one round of workgroups
-// (one per CU; a round and a half costs as much as two), never more than eight, and the hidden dimension must split
-// into whole 64-wide chunks.
-int route_ksplit(const zeda_layer_desc *d)
+// How a bf16 router launch is split: 16 tb tokens per workgroup and `slices` workgroups per token block.
+struct RoutePlan {
+    int tb, slices;
+};
+
+// One round of workgroups at most (one per CU).  Among those the split for which a CU moves the least: the rows that a
+// projecting workgroup reads, the logits it writes, the slices' logits a selecting workgroup reads; the second kernel
+// counts as 450 KB.  160 experts, H = 2048, split against one kernel: 13 against 16 us for one token, 14.8 against 15.9
+// at 997, 20.4 against 18.4 at 4096 (four slices of 64-token blocks), 25.3 against 22.6 at 6000.)
+static RoutePlan route_plan(const zeda_layer_desc *d, bool scratch)
 {
-    if (d->dtype != ZEDA_BF16) return 1;
-    const int blocks = ceil_div(d->T, kRouteTokens), chunks = d->H / 64;
-    int c = 1;
-    while (c < 8 && blocks * 2 * c <= 256 && chunks % (2 * c) == 0) c *= 2;
-    return c;
+    const int64_t NE = d->N + d->Z;
+    RoutePlan best = {4, 1};
+    int64_t least = INT64_MAX;
+    for (int tb = 1; tb <= 4; tb *= 2) {
+        const int64_t tok = 16 * tb, blocks = (d->T + tok - 1) / tok, chunks = d->H / (tb == 1 ? 128 : 64);
+        for (int c = 1; c <= 16; c *= 2) {
+            if (c > 1 && (!scratch || chunks % c != 0)) break;
+            if (blocks * c > 256 && !(c == 1 && tb == 4)) break;
+            const int64_t cost = (NE + tok) * d->H * 2 / c + (c > 1 ? NE * 4 * tok + c * NE * 4 * 16 + 450000 : 0);
+            if (cost < least) { least = cost; best = {tb, c}; }
+        }
+    }
+    return best;
 }
 
+// Scratch: the slices' logits.  (Never less than the tables of an earlier split, whose size callers may rely on being
+// asked for: 32-token blocks, up to eight slices while blocks times slices stay within 256.)
 size_t route_ws_bytes(const zeda_layer_desc *d)
 {
-    const int c = route_ksplit(d);
-    if (c == 1) return 0;
-    const size_t Tpad = (size_t)ceil_div(d->T, kRouteTokens) * kRouteTokens;
-    return (size_t)c * Tpad * ceil_div(d->N + d->Z, 32) * 32 * sizeof(float);
+    if (d->dtype != ZEDA_BF16) return 0;
+    const size_t row = (size_t)ceil_div(d->N + d->Z, 32) * 32 * sizeof(float);
+    const int blocks = ceil_div(d->T, 32);
+    size_t c = 1;
+    while (c < 8 && blocks * 2 * c <= 256 && d->H / 64 % (2 * c) == 0) c *= 2;
+    const size_t floor_bytes = c == 1 ? 0 : c * blocks * 32 * row;
+    const RoutePlan p = route_plan(d, true);
+    const size_t need = p.slices == 1 ? 0 : (size_t)p.slices * ceil_div(d->T, 16 * p.tb) * (16 * p.tb) * row;
+    return need > floor_bytes ? need : floor_bytes;
 }
 
-// One kernel, no scratch, 64 tokens per workgroup: for token counts that fill the device with such blocks.
-// The router kernels use more LDS than a launch gets by default: opt in once per kernel and device.
-template <int NB, int TB>
-static bool route_lds_opt_in(int lds_bytes)
-{
-    static bool done[kMaxDevices] = {};  // per instantiation and device; idempotent, so a race between host threads is harmless
-    const int dev = current_device();
-    if (dev < 0) return false;
-    if (!done[dev]) {
-        if (hipFuncSetAttribute((const void *)route_bf16_kernel<NB, TB>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                lds_bytes) != hipSuccess)
-            return false;
-        done[dev] = true;
-    }
-    return true;
-}
-
-// Optional per-block outputs of a router launch (see publish_blocks); all NULL / 0 when not wanted.
+// Optional outputs of a router launch (see publish_blocks, place_list); all NULL / 0 when not wanted.
 struct RouteExtras {
     uint8_t *cnt8;
     int cnt_ld;
     float *p_part;
+    PlaceOut place;
 };
 
-template <int NB>
-static int launch_route_bf16_wide(const zeda_layer_desc *d, const void *x, const void *wr, const float *bias,
-                                  int32_t *ids, float *gates, const RouteExtras &ex, hipStream_t s)
+template <int NB, int TB>
+static int launch_route_bf16(const zeda_layer_desc *d, const void *x, const void *wr, const float *bias, int32_t *ids,
+                             float *gates, float *partial, int slices, const RouteExtras &ex, hipStream_t s)
 {
-    const int blocks = ceil_div(d->T, 64);
-    constexpr int lds_bytes = route_stages(NB, 2) * (64 + 32 * NB) * 128;
-    if (!route_lds_opt_in<NB, 2>(lds_bytes)) return ZEDA_EHIP;
-    route_bf16_kernel<NB, 2><<<dim3(blocks, 1), kRouteThreads, lds_bytes, s>>>(
-        (const bf16_t *)x, (const bf16_t *)wr, bias, d->T, d->H, d->N, d->N + d->Z, d->K, d->gate_norm, ids, gates, nullptr,
-        blocks * 64, ex.cnt8, ex.cnt_ld, ex.p_part);
+    typedef RouteCfg<NB, TB> C;
+    // the kernel uses more LDS than a launch gets by default: opt in once per kernel and device
+    static bool done[kMaxDevices] = {};  // idempotent, so a race between host threads is harmless
+    const int dev = current_device();
+    if (dev < 0) return ZEDA_EHIP;
+    if (!done[dev]) {
+        if (hipFuncSetAttribute((const void *)route_bf16_kernel<NB, TB>, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES) != hipSuccess)
+            return ZEDA_EHIP;
+        done[dev] = true;
+    }
+    const int blocks = ceil_div(d->T, C::TOK), Tpad = blocks * C::TOK, NE = d->N + d->Z;
+    route_bf16_kernel<NB, TB><<<dim3(blocks, slices), kRouteThreads, C::LDS_BYTES, s>>>(
+        (const bf16_t *)x, (const bf16_t *)wr, bias, d->T, d->H, d->N, NE, d->K, d->gate_norm, ids, gates, slices > 1 ? partial : nullptr,
+        ex.cnt8, ex.cnt_ld, ex.p_part);
+    const dim3 sgrid(ceil_div(d->T, kSelectTokens));
+#define ZEDA_SELECT(NP) route_select_kernel<NB, NP><<<sgrid, kRouteThreads, 0, s>>>(partial, Tpad, bias, d->T, d->N, NE, d->K, d->gate_norm, ids, gates, ex.cnt8, ex.cnt_ld, ex.p_part, ex.place)
+    if (slices == 2) ZEDA_SELECT(2);
+    else if (slices == 4) ZEDA_SELECT(4);
+    else if (slices == 8) ZEDA_SELECT(8);
+    else if (slices == 16) ZEDA_SELECT(16);
+#undef ZEDA_SELECT
     return last_launch_status();
 }
 
-// More than 256 blocks of 32 tokens: a second round of 32-token workgroups would start behind the first (8500 tokens:
-// 38 us); 64-token blocks run in one round and read the router rows half as often (33 us from 8193 to 16384 tokens).
-constexpr int kRouteWideTokens = 8193;
-
 template <int NB>
-static int launch_route_bf16(const zeda_layer_desc *d, const void *x, const void *wr, const float *bias, int32_t *ids,
-                             float *gates, float *partial, const RouteExtras &ex, hipStream_t s)
+static int launch_route_bf16_tok(const zeda_layer_desc *d, const void *x, const void *wr, const float *bias, int32_t *ids,
+                                 float *gates, float *partial, const RouteExtras &ex, hipStream_t s)
 {
-    if constexpr (NB <= 6) {
-        if (d->T >= kRouteWideTokens) return launch_route_bf16_wide<NB>(d, x, wr, bias, ids, gates, ex, s);
-    }
-    const int blocks = ceil_div(d->T, kRouteTokens), Tpad = blocks * kRouteTokens;
-    const int c = partial ? route_ksplit(d) : 1;
-    constexpr int lds_bytes = route_stages(NB) * (kRouteTokens + 32 * NB) * 128;
-    if (!route_lds_opt_in<NB, 1>(lds_bytes)) return ZEDA_EHIP;
-    route_bf16_kernel<NB, 1><<<dim3(blocks, c), kRouteThreads, lds_bytes, s>>>(
-        (const bf16_t *)x, (const bf16_t *)wr, bias, d->T, d->H, d->N, d->N + d->Z, d->K, d->gate_norm, ids, gates,
-        c > 1 ? partial : nullptr, Tpad, ex.cnt8, ex.cnt_ld, ex.p_part);
-    if (c == 1) return last_launch_status();
-    const dim3 sgrid(ceil_div(d->T, kSelectTokens));
-    const int NE = d->N + d->Z;
-    if (c == 2)
-        route_select_kernel<NB, 2><<<sgrid, kRouteThreads, 0, s>>>(partial, Tpad, bias, d->T, d->N, NE, d->K, d->gate_norm, ids, gates, ex.cnt8, ex.cnt_ld, ex.p_part);
-    else if (c == 4)
-        route_select_kernel<NB, 4><<<sgrid, kRouteThreads, 0, s>>>(partial, Tpad, bias, d->T, d->N, NE, d->K, d->gate_norm, ids, gates, ex.cnt8, ex.cnt_ld, ex.p_part);
-    else
-        route_select_kernel<NB, 8><<<sgrid, kRouteThreads, 0, s>>>(partial, Tpad, bias, d->T, d->N, NE, d->K, d->gate_norm, ids, gates, ex.cnt8, ex.cnt_ld, ex.p_part);
-    return last_launch_status();
+    const RoutePlan p = route_plan(d, partial != nullptr);
+    if (p.tb == 1) return launch_route_bf16<NB, 1>(d, x, wr, bias, ids, gates, partial, p.slices, ex, s);
+    if (p.tb == 2) return launch_route_bf16<NB, 2>(d, x, wr, bias, ids, gates, partial, p.slices, ex, s);
+    return launch_route_bf16<NB, 4>(d, x, wr, bias, ids, gates, partial, p.slices, ex, s);
 }
 
 static int launch_route_bf16_any(const zeda_layer_desc *d, const void *x, const void *wr, const float *bias, int32_t *ids,
                                  float *gates, float *partial, const RouteExtras &ex, hipStream_t s)
 {
     switch (ceil_div(d->N + d->Z, 32)) {
-        case 1: return launch_route_bf16<1>(d, x, wr, bias, ids, gates, partial, ex, s);
-        case 2: return launch_route_bf16<2>(d, x, wr, bias, ids, gates, partial, ex, s);
-        case 3: return launch_route_bf16<3>(d, x, wr, bias, ids, gates, partial, ex, s);
-        case 4: return launch_route_bf16<4>(d, x, wr, bias, ids, gates, partial, ex, s);
-        case 5: return launch_route_bf16<5>(d, x, wr, bias, ids, gates, partial, ex, s);
-        case 6: return launch_route_bf16<6>(d, x, wr, bias, ids, gates, partial, ex, s);
-        case 7: return launch_route_bf16<7>(d, x, wr, bias, ids, gates, partial, ex, s);
-        default: return launch_route_bf16<8>(d, x, wr, bias, ids, gates, partial, ex, s);
+        case 1: return launch_route_bf16_tok<1>(d, x, wr, bias, ids, gates, partial, ex, s);
+        case 2: return launch_route_bf16_tok<2>(d, x, wr, bias, ids, gates, partial, ex, s);
+        case 3: return launch_route_bf16_tok<3>(d, x, wr, bias, ids, gates, partial, ex, s);
+        case 4: return launch_route_bf16_tok<4>(d, x, wr, bias, ids, gates, partial, ex, s);
+        case 5: return launch_route_bf16_tok<5>(d, x, wr, bias, ids, gates, partial, ex, s);
+        case 6: return launch_route_bf16_tok<6>(d, x, wr, bias, ids, gates, partial, ex, s);
+        case 7: return launch_route_bf16_tok<7>(d, x, wr, bias, ids, gates, partial, ex, s);
+        default: return launch_route_bf16_tok<8>(d, x, wr, bias, ids, gates, partial, ex, s);
     }
+}
+
+bool route_places(const zeda_layer_desc *d)
+{
+    return d->dtype == ZEDA_BF16 && d->T <= kSelectTokens && route_plan(d, true).slices > 1;
 }
 
 int route_counts_ld(const zeda_layer_desc *d) { return (int)align_up((size_t)ceil_div(d->T, 16), 16); }
@@ -546,10 +686,11 @@ bool route_counts_supported(const zeda_layer_desc *d) { return d->dtype == ZEDA_
 // (route_stats_final_kernel).  fp32: logits to scratch (route_f32_kernel), per-block sums (route_stats_kernel), the
 // same final workgroup.  Every floating-point sum runs in a fixed order.
 // ---------------------------------------------------------------------------------------------
+constexpr int kStatsThreads = 256;
 constexpr int kStatsTokens = 64;  // tokens per workgroup of route_stats_kernel: four batches of four per wave
 
 template <int NC>
-__global__ __launch_bounds__(kRouteThreads) void route_stats_kernel(const float *__restrict__ logits, int nsplit, int Tpad,
+__global__ __launch_bounds__(kStatsThreads) void route_stats_kernel(const float *__restrict__ logits, int nsplit, int Tpad,
                                                                     int LDg, const float *__restrict__ bias, int T, int NE,
                                                                     int K, float *__restrict__ p_part,
                                                                     int32_t *__restrict__ f_part)
@@ -630,58 +771,108 @@ __global__ __launch_bounds__(kRouteThreads) void route_stats_kernel(const float 
         int fs = 0;
 #pragma unroll
         for (int r = 0; r < 16; ++r) { ps += s_p[r][tid]; fs += s_f[r][tid]; }
-        p_part[(size_t)blockIdx.x * NE + tid] = ps;
-        f_part[(size_t)blockIdx.x * NE + tid] = fs;
+        p_part[(size_t)blockIdx.x * stats_ld(NE) + tid] = ps;
+        f_part[(size_t)blockIdx.x * stats_ld(NE) + tid] = fs;
     }
 }
 
-// f_part: [nblocks][NE] int32 counts, or NULL: then cnt8[e][cnt_ld] holds them as bytes
-__global__ __launch_bounds__(kRouteThreads) void route_stats_final_kernel(const float *__restrict__ p_part,
-                                                                          const int32_t *__restrict__ f_part,
-                                                                          const uint8_t *__restrict__ cnt8, int cnt_ld, int nblocks,
-                                                                          int T, int N, int NE, int K, float alpha, float w,
-                                                                          float *__restrict__ f, float *__restrict__ P,
-                                                                          float *__restrict__ summary)
+// Final workgroup: adds the blocks up.  p_part [nblocks][ld] (ld a multiple of 4: a thread takes four experts with one
+// 16-byte load) and either f_part, int32 counts laid out alike, or cnt8[e][cnt_ld], the counts as bytes.  The threads of
+// an expert quad take every PARTS-th block, eight loads in flight, and their sums are added in a fixed order; the byte
+// counts are added as integers, so their order does not matter.  (One thread per expert walking all blocks spent 142 us
+// of latency on the 512 blocks of 8192 tokens.)
+constexpr int kStatsFinalThreads = 1024;
+
+__global__ __launch_bounds__(kStatsFinalThreads) void route_stats_final_kernel(const float *__restrict__ p_part,
+                                                                               const int32_t *__restrict__ f_part, int ld,
+                                                                               const uint8_t *__restrict__ cnt8, int cnt_ld,
+                                                                               int nblocks, int T, int N, int NE, int K,
+                                                                               float alpha, float w, float *__restrict__ f,
+                                                                               float *__restrict__ P, float *__restrict__ summary)
 {
+    __shared__ f32x4 s_part[kStatsFinalThreads];
+    __shared__ int s_cnt[kMaxExperts];
     __shared__ float s_f[kMaxExperts], s_P[kMaxExperts];
-    const int e = threadIdx.x;
-    if (e < NE) {
-        float ps = 0.f;
-        long long fs = 0;
-        for (int b = 0; b < nblocks; ++b) {
-            ps += p_part[(size_t)b * NE + e];
-            fs += f_part ? f_part[(size_t)b * NE + e] : (int)cnt8[(size_t)e * cnt_ld + b];
+    const int tid = threadIdx.x, quads = (NE + 3) / 4, parts = kStatsFinalThreads / quads, quad = tid % quads, part = tid / quads;
+    for (int e = tid; e < kMaxExperts; e += kStatsFinalThreads) s_cnt[e] = 0;
+    __syncthreads();
+    if (part < parts) {
+        f32x4 ps = {0.f, 0.f, 0.f, 0.f};
+        int fs[4] = {0, 0, 0, 0};
+        const size_t col = (size_t)quad * 4;
+#pragma unroll 8
+        for (int b = part; b < nblocks; b += parts) {
+            ps += *reinterpret_cast<const f32x4 *>(p_part + (size_t)b * ld + col);
+            if (f_part) {
+                const int4 c = *reinterpret_cast<const int4 *>(f_part + (size_t)b * ld + col);
+                fs[0] += c.x; fs[1] += c.y; fs[2] += c.z; fs[3] += c.w;
+            }
         }
-        s_P[e] = ps / (float)T;
-        s_f[e] = (float)((double)fs / (double)T);
-        f[e] = s_f[e];
-        P[e] = s_P[e];
+        s_part[tid] = ps;
+        if (f_part)
+            for (int q = 0; q < 4; ++q)
+                if (quad * 4 + q < NE) atomicAdd(&s_cnt[quad * 4 + q], fs[q]);
+    }
+    if (!f_part) {
+        const int words = cnt_ld / 16;
+        for (int i = tid; i < NE * words; i += kStatsFinalThreads) {
+            const int e = i / words, wi = i - e * words;
+            const uint4 v = *reinterpret_cast<const uint4 *>(cnt8 + (size_t)e * cnt_ld + wi * 16);
+            const unsigned dw[4] = {v.x, v.y, v.z, v.w};
+            int c = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int b0 = wi * 16 + q * 4;
+                unsigned x = dw[q];
+                if (b0 + 4 > nblocks) x = b0 >= nblocks ? 0u : (x & ((1u << (8 * (nblocks - b0))) - 1u));  // bytes past the last block
+                c += (int)__builtin_amdgcn_sad_u8(x, 0u, 0u);
+            }
+            atomicAdd(&s_cnt[e], c);
+        }
     }
     __syncthreads();
-    if (e == 0) {
-        float fE = 0.f, PE = 0.f, fZ = 0.f, PZ = 0.f, dot = 0.f;
-        for (int i = 0; i < NE; ++i) {
-            dot += s_f[i] * s_P[i];
-            if (i < N) { fE += s_f[i]; PE += s_P[i]; } else { fZ += s_f[i]; PZ += s_P[i]; }
+    if (tid < NE) {
+        float ps = 0.f;
+        for (int q = 0; q < parts; ++q) ps += s_part[q * quads + tid / 4][tid % 4];
+        s_P[tid] = ps / (float)T;
+        s_f[tid] = (float)((double)s_cnt[tid] / (double)T);
+        f[tid] = s_f[tid];
+        P[tid] = s_P[tid];
+    }
+    __syncthreads();
+    // the group sums: one wave, lane l the experts l, l + 64, ..., then a fixed butterfly
+    if (tid < 64) {
+        float v[5] = {0.f, 0.f, 0.f, 0.f, 0.f};  // f_E, P_E, f_Z, P_Z, sum of f P
+        for (int i = tid; i < NE; i += 64) {
+            v[4] += s_f[i] * s_P[i];
+            v[i < N ? 0 : 2] += s_f[i];
+            v[i < N ? 1 : 3] += s_P[i];
         }
-        const int Z = NE - N;
-        summary[0] = fE; summary[1] = PE; summary[2] = fZ; summary[3] = PZ;
-        summary[4] = fZ / (float)K;
-        summary[5] = alpha * (float)NE / (float)K * dot;                                   // Eq. 4
-        summary[6] = alpha * ((float)N + (float)Z * w) / (float)K *
-                     (fE * PE / (float)N + (Z > 0 ? fZ * PZ / ((float)Z * w) : 0.f));       // Eq. 5-6
+#pragma unroll
+        for (int q = 0; q < 5; ++q)
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) v[q] += __shfl_xor(v[q], o);
+        if (tid == 0) {
+            const float fE = v[0], PE = v[1], fZ = v[2], PZ = v[3];
+            const int Z = NE - N;
+            summary[0] = fE; summary[1] = PE; summary[2] = fZ; summary[3] = PZ;
+            summary[4] = fZ / (float)K;
+            summary[5] = alpha * (float)NE / (float)K * v[4];                                  // Eq. 4
+            summary[6] = alpha * ((float)N + (float)Z * w) / (float)K *
+                         (fE * PE / (float)N + (Z > 0 ? fZ * PZ / ((float)Z * w) : 0.f));       // Eq. 5-6
+        }
     }
 }
 
 // scratch: the logit tables, then the per-block sums
 static size_t stats_logits_bytes(const zeda_layer_desc *d)
 {
-    const size_t Tpad = (size_t)ceil_div(d->T, kRouteTokens) * kRouteTokens;
-    return align_up((size_t)route_ksplit(d) * Tpad * ceil_div(d->N + d->Z, 32) * 32 * sizeof(float), 256);
+    const size_t Tpad = (size_t)ceil_div(d->T, kRouteF32Tokens) * kRouteF32Tokens;
+    return align_up(Tpad * ceil_div(d->N + d->Z, 32) * 32 * sizeof(float), 256);
 }
 size_t routing_stats_ws_bytes(const zeda_layer_desc *d)
 {
-    const size_t NE = (size_t)(d->N + d->Z);
+    const size_t NE = (size_t)stats_ld(d->N + d->Z);
     if (d->dtype == ZEDA_BF16)  // split-k scratch of the router, per-block counts, per-block probability sums
         return align_up(route_ws_bytes(d), 256) + route_counts_bytes(d) + align_up((size_t)ceil_div(d->T, 16) * NE * 4, 256);
     const size_t nblk = (size_t)ceil_div(d->T, kStatsTokens);
@@ -696,20 +887,20 @@ int launch_routing_stats(const zeda_layer_desc *d, const void *x, const void *wr
         float *partial = route_ws_bytes(d) ? (float *)ws : nullptr;
         uint8_t *cnt8 = (uint8_t *)ws + align_up(route_ws_bytes(d), 256);
         float *p_part = (float *)(cnt8 + route_counts_bytes(d));
-        const RouteExtras ex = {cnt8, route_counts_ld(d), p_part};
+        const RouteExtras ex = {cnt8, route_counts_ld(d), p_part, {}};
         const int rc = launch_route_bf16_any(d, x, wr, bias, nullptr, nullptr, partial, ex, s);
         if (rc != ZEDA_OK) return rc;
-        route_stats_final_kernel<<<1, kRouteThreads, 0, s>>>(p_part, nullptr, cnt8, ex.cnt_ld, ceil_div(d->T, 16), d->T, d->N, NE,
+        route_stats_final_kernel<<<1, kStatsFinalThreads, 0, s>>>(p_part, nullptr, stats_ld(NE), cnt8, ex.cnt_ld, ceil_div(d->T, 16), d->T, d->N, NE,
                                                              d->K, alpha, w, f, P, summary);
         return last_launch_status();
     }
     const int NB = ceil_div(NE, 32), LDg = NB * 32;
-    const int Tpad = ceil_div(d->T, kRouteTokens) * kRouteTokens, nblk = ceil_div(d->T, kStatsTokens);
+    const int Tpad = ceil_div(d->T, kRouteF32Tokens) * kRouteF32Tokens, nblk = ceil_div(d->T, kStatsTokens);
     float *logits = (float *)ws;
     float *p_part = (float *)((char *)ws + stats_logits_bytes(d));
-    int32_t *f_part = (int32_t *)((char *)p_part + align_up((size_t)nblk * NE * 4, 256));
+    int32_t *f_part = (int32_t *)((char *)p_part + align_up((size_t)nblk * stats_ld(NE) * 4, 256));
     if (launch_route_f32(d, x, wr, bias, nullptr, nullptr, logits, LDg, s) != ZEDA_OK) return ZEDA_EHIP;
-#define ZEDA_STATS(NC) route_stats_kernel<NC><<<nblk, kRouteThreads, 0, s>>>(logits, 1, Tpad, LDg, bias, d->T, NE, d->K, p_part, f_part)
+#define ZEDA_STATS(NC) route_stats_kernel<NC><<<nblk, kStatsThreads, 0, s>>>(logits, 1, Tpad, LDg, bias, d->T, NE, d->K, p_part, f_part)
     switch (ceil_div(NE, 16)) {
         case 1: ZEDA_STATS(1); break;   case 2: ZEDA_STATS(2); break;   case 3: ZEDA_STATS(3); break;
         case 4: ZEDA_STATS(4); break;   case 5: ZEDA_STATS(5); break;   case 6: ZEDA_STATS(6); break;
@@ -720,16 +911,16 @@ int launch_routing_stats(const zeda_layer_desc *d, const void *x, const void *wr
     }
 #undef ZEDA_STATS
     if (hipGetLastError() != hipSuccess) return ZEDA_EHIP;
-    route_stats_final_kernel<<<1, kRouteThreads, 0, s>>>(p_part, f_part, nullptr, 0, nblk, d->T, d->N, NE, d->K, alpha, w, f, P,
+    route_stats_final_kernel<<<1, kStatsFinalThreads, 0, s>>>(p_part, f_part, stats_ld(NE), nullptr, 0, nblk, d->T, d->N, NE, d->K, alpha, w, f, P,
                                                          summary);
     return last_launch_status();
 }
 
-int launch_route(const zeda_layer_desc *d, const void *x, const void *wr, const float *bias, int32_t *ids,
-                 float *gates, float *partial, uint8_t *cnt8, hipStream_t s)
+int launch_route(const zeda_layer_desc *d, const void *x, const void *wr, const float *bias, int32_t *ids, float *gates,
+                 float *partial, uint8_t *cnt8, const PlaceOut *place, hipStream_t s)
 {
     if (d->dtype == ZEDA_BF16) {
-        const RouteExtras ex = {cnt8, cnt8 ? route_counts_ld(d) : 0, nullptr};
+        const RouteExtras ex = {cnt8, cnt8 ? route_counts_ld(d) : 0, nullptr, place ? *place : PlaceOut{}};
         return launch_route_bf16_any(d, x, wr, bias, ids, gates, partial, ex, s);
     }
     return launch_route_f32(d, x, wr, bias, ids, gates, nullptr, 0, s);

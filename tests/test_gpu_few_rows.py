@@ -1,0 +1,80 @@
+"""The expert FFN of small batches and small models, and the router's splits, at the sizes where a tile, a slice or a rule
+ends: whole-layer parity with the oracle in both weight layouts, whose results are the same bits."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import harness
+from paper_2605_18643_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+from gpu_util import full_parity  # noqa: E402
+
+CASES = [
+    # one token; a reduction dimension with fewer 64-wide chunks than waves; one expert
+    dict(T=1, H=128, I=64, N=3, Z=1, K=2),
+    dict(T=1, H=2048, I=768, N=128, Z=32, K=8),
+    dict(T=7, H=256, I=192, N=1, Z=0, K=1),
+    # about 16, 17, 32 and 33 rows per expert (token blocks of 16, tiles of 32), several tiles per expert
+    dict(T=64, H=384, I=64, N=4, Z=0, K=1),
+    dict(T=130, H=1152, I=448, N=4, Z=0, K=1),
+    dict(T=200, H=640, I=320, N=8, Z=2, K=2),
+    # both sides of the 40-rows and 170-rows rules (few weight tiles), of 5 rows per expert (many)
+    dict(T=320, H=512, I=256, N=24, Z=0, K=3),
+    dict(T=321, H=512, I=256, N=24, Z=0, K=3),
+    dict(T=2720, H=128, I=64, N=14, Z=2, K=1),
+    dict(T=2721, H=128, I=64, N=14, Z=2, K=1),
+    dict(T=50, H=256, I=512, N=100, Z=60, K=16),
+    dict(T=51, H=256, I=512, N=100, Z=60, K=16),
+    # router: 16 and 17 tokens with a split (one workgroup that also places), widest pool, slots on every expert
+    dict(T=16, H=2048, I=64, N=60, Z=30, K=16),
+    dict(T=17, H=2048, I=64, N=60, Z=30, K=16),
+    dict(T=33, H=1024, I=64, N=200, Z=56, K=4),
+    dict(T=1, H=1024, I=64, N=5, Z=251, K=16),
+]
+
+
+@pytest.mark.parametrize("cfg", CASES, ids=lambda c: "_".join(f"{k}{v}" for k, v in c.items()))
+def test_small_batches_match_the_oracle_in_both_layouts(cfg):
+    # (weights scaled with the widths so that outputs keep the magnitude the absolute bound is meant for: 0.02 at H = 2048)
+    w = synth.Workload("few", dtype="bf16", seed=401, recipe="plain", x_std=1.0, w_std=min(0.05, 0.9 * cfg["H"] ** -0.5), wr_std=0.05, **cfg)
+    print(w, flush=True)
+    L = harness.gapped_layer(w, "cuda")
+    tokens = None if w.T <= 400 else np.arange(0, w.T, 5)
+    plain, _ = full_parity(w, L, tokens=tokens)
+    tiled, _ = full_parity(w, L, tokens=tokens, tiled=True)
+    assert torch.equal(plain["out"].view(torch.int16), tiled["out"].view(torch.int16))
+
+
+@pytest.mark.parametrize("T", [4096, 4097, 8192])
+def test_router_splits_of_long_batches(T):
+    """One workgroup per 16, 32 and 64 tokens: ids, gates, placement and output of sampled tokens."""
+    w = synth.Workload("route_long", T=T, H=256, I=64, N=40, Z=24, K=5, dtype="bf16", seed=402, recipe="zero_bias", x_std=1.0,
+                       w_std=0.05, wr_std=0.08, zero_bias=0.3)
+    print(w, flush=True)
+    full_parity(w, harness.gapped_layer(w, "cuda"), tokens=np.arange(0, T, 37))
+
+
+def test_masked_experts_are_not_selected_twice():
+    """Experts masked with a bias of -inf: the others come first, then masked ones, each once, with weight zero."""
+    from paper_2605_18643_amd import zeda
+
+    for T in (5, 300, 5000):
+        for dtype, H in (("bf16", 256), ("f32", 64)):
+            g = torch.Generator().manual_seed(T)
+            tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+            N, Z, K = 20, 4, 6
+            x, wr = torch.randn(T, H, generator=g).to(tdt).cuda(), (0.1 * torch.randn(N + Z, H, generator=g)).to(tdt).cuda()
+            bias = torch.full((N + Z,), float("-inf"))
+            keep = [3, 8, 17, 22]
+            bias[keep] = 0.0
+            ids = torch.full((T, K), -1, dtype=torch.int32, device="cuda")
+            gates = torch.full((T, K), float("nan"), device="cuda")
+            d = zeda.make_desc(T, H, 64, N, Z, K, dtype)
+            ws = torch.empty(max(16, zeda.route_workspace_bytes(d)), dtype=torch.uint8, device="cuda")
+            zeda.zeda_route(d, x, wr, bias.cuda(), ids, gates, ws=ws)
+            torch.cuda.synchronize()
+            i, gt = ids.cpu().numpy(), gates.cpu().numpy()
+            assert (np.sort(i[:, :4], axis=1) == keep).all() and (i[:, 4:] == [0, 1]).all()
+            assert (gt[:, 4:] == 0).all() and np.allclose(gt.sum(1), 1.0, atol=1e-5)
