@@ -180,8 +180,8 @@ struct TileScan {
     }
 };
 
-// WNT: fetch the weights with the non-temporal hint (see run_tiles).
-template <class C, bool GATEUP, bool TILED, bool WNT = false>
+// WNT: fetch the weights with the non-temporal hint (see run_tiles_auto).
+template <class C, bool GATEUP, bool TILED, bool WNT>
 struct Stream {
     static constexpr int FB = C::FB, WF = C::WF, BT = C::BT, BF = C::BF, NSW = C::NSW, NST = C::NST, NW = C::NW,
                          NWW = C::NWW, NWT = C::NWT, WST = C::WST, TST = C::TST, KC = C::KC, KS = C::KS, ROWB = C::ROWB,
@@ -193,6 +193,7 @@ struct Stream {
     const bf16_t *tok, *w0, *w1;
     bf16_t *out;
     int Kdim, Fdim, nk;
+    bool rotate;  // start an item at a k chunk of its own (see run_tiles_auto)
     // LDS
     unsigned char *wring, *tring, *stg;
     uint32_t wring_a, tring_a;  // LDS addresses of the two rings
@@ -206,8 +207,8 @@ struct Stream {
     // The next chunk this wave fetches is chunk ikc of item iq, into slot islot of its ring.
     bool wrole;
     const bf16_t *src[NLMAX];
-    int nq, iq, ikc, islot, inl;
-    size_t koff;          // ikc chunks into the rows, in elements
+    int nq, iq, ikc, islot, inl, krot;
+    size_t koff;          // where in the rows chunk ikc of the item is, in elements
     int kstep;            // elements from one chunk of this wave's operand to the next
     uint32_t dbase, doff; // LDS address of this wave's first piece in slot 0 of its ring; byte offset of slot islot
     int hist[NH];  // load instructions of this wave in each of the last chunks issued (newest last)
@@ -229,6 +230,9 @@ struct Stream {
         int ln = lane;
         asm volatile("" : "+v"(ln));  // (recomputed per item rather than kept live)
         const int piece = ln % PPR, rsub = ln / PPR;
+        // first chunk of the item (in units of 64 k, the same for both weight layouts); see run_tiles_auto for rotate
+        krot = rotate ? (int)((unsigned)(expert * 5 + ft * 3) % (unsigned)(Kdim / 64)) * (64 / KC) : 0;
+        koff = (size_t)krot * kstep;
         if (wrole) {
             inl = NLW;
 #pragma unroll
@@ -277,7 +281,7 @@ struct Stream {
         tring_a = lds_addr(tring);
         kstep = (TILED && wrole) ? (Fdim / 32) * 1024 : KC;
         dbase = lds_addr(wrole ? wring + wave * 1024 : tring + (wave - NWW) * 1024);
-        iq = 0; ikc = 0; islot = 0; inl = 0; koff = 0; doff = 0;
+        iq = 0; ikc = 0; islot = 0; inl = 0; koff = 0; doff = 0; krot = 0;
 #pragma unroll
         for (int h = 0; h < NH; ++h) hist[h] = 0;
     }
@@ -297,6 +301,7 @@ struct Stream {
     {
         ++ikc;
         koff += kstep;
+        if (ikc + krot == nk) koff = 0;
         const bool wrap = ++islot == (NSW == NST ? NSW : (wrole ? NSW : NST));
         doff = wrap ? 0 : doff + (WST == TST ? WST : (wrole ? WST : TST));
         islot = wrap ? 0 : islot;
@@ -551,7 +556,7 @@ __device__ __forceinline__ void run_tiles(unsigned char *lds, const TileScan<C> 
                                           const bf16_t *__restrict__ w0,
                                           const bf16_t *__restrict__ w1, const int32_t *__restrict__ offsets,
                                           const int32_t *__restrict__ sorted_slot, bf16_t *__restrict__ out, int N, int K,
-                                          int Kdim, int Fdim, int n_ftiles, int T)
+                                          int Kdim, int Fdim, int n_ftiles, int T, bool rotate)
 {
     static_assert(!GATEUP || C::FB % 2 == 0, "gate and up blocks come in pairs");
     int *s_tok = reinterpret_cast<int *>(lds + C::TOK_OFF);
@@ -591,7 +596,7 @@ __device__ __forceinline__ void run_tiles(unsigned char *lds, const TileScan<C> 
 
         Stream<C, GATEUP, TILED, WNT> st;
         st.tok = tok; st.w0 = w0; st.w1 = w1; st.out = out;
-        st.Kdim = Kdim; st.Fdim = Fdim; st.nk = Kdim / C::KC;
+        st.Kdim = Kdim; st.Fdim = Fdim; st.nk = Kdim / C::KC; st.rotate = rotate;
         st.wring = lds; st.tring = lds + C::TRING_OFF; st.stg = lds + C::STG_OFF + wave * 2048; st.s_tok = s_tok; st.s_loc = s_loc;
         st.lane = lane; st.wave = wave; st.wt = wave / C::WF; st.wf = wave % C::WF; st.col = lane & 31; st.half = lane >> 5;
         st.foff_t = (st.wt * 32 + st.col) * C::ROWB + swz<C::KC>(st.col, st.half) * 16;
@@ -618,6 +623,14 @@ __device__ __forceinline__ void run_tiles(unsigned char *lds, const TileScan<C> 
 // results, which this and the next kernels of the layer re-read, out of the caches (whole layer at 127 rows per
 // expert -4 %, at 3 rows -10 %; at 460 rows per expert the hint costs 2 % instead).  Decided once per launch from
 // the expert loads; the cache-policy field of the load is an immediate, so the two cases are two instantiations.
+//
+// Where the weights are what the kernel waits for, an item also starts at a k chunk that depends on its expert and feature
+// tile: row-major rows are often a multiple of 4 KiB apart, so that one chunk of every row sits on a few memory channels,
+// and workgroups that all start at chunk 0 queue there (4096 tokens, N=64, I=1536, row-major: gate/up 199 -> 186 us, down
+// 110 -> 101; tiled, N=128, I=768: gate/up 172 -> 168).  Not with many rows per expert, where the token rows that the
+// feature tiles of an item share would be fetched at different times (460 rows: 393 -> 404 us), nor with so few that the
+// weights' own order decides (31 rows, tiled: 132 -> 135 us).  The rule looks at nothing but the mean load, so that both
+// weight layouts add in the same order.
 template <class C, bool GATEUP, bool TILED>
 __device__ __forceinline__ void run_tiles_auto(unsigned char *lds, const TileScan<C> &scan0, const bf16_t *__restrict__ tok,
                                                const bf16_t *__restrict__ w0, const bf16_t *__restrict__ w1,
@@ -627,10 +640,11 @@ __device__ __forceinline__ void run_tiles_auto(unsigned char *lds, const TileSca
 {
     const int ne = scan0.experts();
     const bool stream_once = scan0.tiles * 16 <= ne * 17 && offsets[N] < 400 * ne;
+    const bool rotate = offsets[N] >= 64 * ne && offsets[N] < 192 * ne;
     if (stream_once)
-        run_tiles<C, GATEUP, TILED, true>(lds, scan0, tok, w0, w1, offsets, sorted_slot, out, N, K, Kdim, Fdim, n_ftiles, T);
+        run_tiles<C, GATEUP, TILED, true>(lds, scan0, tok, w0, w1, offsets, sorted_slot, out, N, K, Kdim, Fdim, n_ftiles, T, rotate);
     else
-        run_tiles<C, GATEUP, TILED, false>(lds, scan0, tok, w0, w1, offsets, sorted_slot, out, N, K, Kdim, Fdim, n_ftiles, T);
+        run_tiles<C, GATEUP, TILED, false>(lds, scan0, tok, w0, w1, offsets, sorted_slot, out, N, K, Kdim, Fdim, n_ftiles, T, rotate);
 }
 
 template <class C, bool GATEUP, bool TILED>
