@@ -18,10 +18,12 @@ typedef TileCfg<4, 2, 4, 2, 2, 64> CfgPrefill;  // 256 tokens x 256 weight rows,
 typedef TileCfg<4, 2, 2, 2, 2, 64> CfgNarrow;   // 256 tokens x 128 weight rows, 4 waves: any H % 128 == 0, I % 64 == 0
 // tiled weights come in 32-wide k blocks: 32-wide chunks, four deep
 typedef TileCfg<4, 2, 4, 4, 4, 32> CfgPrefillT;
+typedef TileCfg<4, 2, 4, 4, 2, 32, 64> CfgPrefillTP;  // the same, token rows 64 k at a time
 typedef TileCfg<4, 2, 2, 4, 4, 32> CfgNarrowT;
 // 320 tokens x 256 weight rows (token ring three deep): an expert with a few rows more than a multiple of 256 gets
-// one token tile less than CfgPrefillT would give it, i.e. one pass less over its weights.  It is the second
-// geometry of the adaptive kernel, which picks one of the two from the expert loads.
+// one token tile less than CfgPrefillTP would give it, i.e. one pass less over its weights.  It is the second
+// geometry of the adaptive kernel, which picks one of the two from the expert loads.  (With the 64-wide token ring, which
+// leaves it half the room to turn results in, it gains 1-2 % at 8192 tokens and loses 1.5 % at 6000.)
 typedef TileCfg<5, 2, 4, 4, 3, 32> CfgPrefillT5;
 
 // Persistent grid: as many workgroups as the device holds at once, rounded down to a multiple of 8 so that
@@ -86,6 +88,17 @@ static bool rows_may_straddle_tile(const zeda_layer_desc *d)
     return false;
 }
 
+// Whether experts have enough rows for the 64-wide token ring, by the slots per expert of the whole pool.  It saves half of
+// the token rows' trips through the vector memory path (T=4096, N=128: gate/up 172 -> 163 us, down 101 -> 98; N=64, I=1536:
+// 286 -> 275 us a layer), but a row is asked for two chunks ahead instead of three, which tells where a chunk is multiplied
+// in no time (31 rows per expert, 50 slots: gate/up 133 -> 144 us, down 72 -> 81; level at 78 rows, 125 slots).
+static bool rows_fill_groups(const zeda_layer_desc *d) { return (int64_t)d->T * d->K >= 110 * ((int64_t)d->N + d->Z); }
+// That ring addresses token rows (of x, of act) with 32-bit byte offsets.
+static bool rows_addressable(const zeda_layer_desc *d)
+{
+    return (uint64_t)d->T * d->H * 2 <= UINT32_MAX && (uint64_t)d->T * d->K * d->I * 2 <= UINT32_MAX;
+}
+
 template <class C, bool GATEUP, bool TILED>
 static int launch_tile_kernel(const zeda_layer_desc *d, const void *tok, const void *w0, const void *w1,
                               const int32_t *offsets, const int32_t *sorted_slot, void *out, hipStream_t s)
@@ -113,8 +126,9 @@ static int launch_bf16(const zeda_layer_desc *d, const void *tok, const void *w0
 {
     if (d->weight_layout == ZEDA_WEIGHTS_TILED) {
         if (cfg_fits<CfgPrefillT>(d)) {
-            if (rows_may_straddle_tile(d))
-                return launch_adaptive_kernel<CfgPrefillT, CfgPrefillT5, GATEUP, true>(d, tok, w0, w1, offsets, sorted_slot, out, s);
+            if (rows_may_straddle_tile(d) && rows_addressable(d))
+                return launch_adaptive_kernel<CfgPrefillTP, CfgPrefillT5, GATEUP, true>(d, tok, w0, w1, offsets, sorted_slot, out, s);
+            if (rows_fill_groups(d) && rows_addressable(d)) return launch_tile_kernel<CfgPrefillTP, GATEUP, true>(d, tok, w0, w1, offsets, sorted_slot, out, s);
             return launch_tile_kernel<CfgPrefillT, GATEUP, true>(d, tok, w0, w1, offsets, sorted_slot, out, s);
         }
         return launch_tile_kernel<CfgNarrowT, GATEUP, true>(d, tok, w0, w1, offsets, sorted_slot, out, s);

@@ -168,6 +168,7 @@ __global__ __launch_bounds__(kFewThreads) void ffn_few_kernel(const bf16_t *__re
 // real loads are only known on the device) and by the tile kernel's gate/up work items, one per 128 columns of I and expert:
 //  - up to 5 rows both stream weights and nothing else; this one has more of them in flight (N=128, I=768, H=2048:
 //    64 tokens 188 -> 177 us, row-major at 32 tokens 191 -> 168; level at 128 tokens, 3 % behind at 192);
+//  - up to 64 tokens it also wins with more rows (N=8, K=2, I=3072: 75 -> 67 us; N=8, K=6, I=1024: 39 -> 38);
 //  - up to 320 items the tile kernel fills little more than one round of 256 CUs or less (N=48, I=768, H=1536: 100 tokens
 //    92 -> 73 us, 300 tokens row-major 138 -> 115; N=24, I=448, H=1152: 301 tokens 45 -> 40).  This kernel reads the token
 //    rows once per 16 columns, so it falls behind once an expert has more rows than a workgroup: at 94 rows 49 -> 75 us;
@@ -176,7 +177,7 @@ __global__ __launch_bounds__(kFewThreads) void ffn_few_kernel(const bf16_t *__re
 bool ffn_few_supported(const zeda_layer_desc *d)
 {
     const int64_t slots = (int64_t)d->T * d->K, experts = d->N + d->Z, items = (int64_t)d->N * ceil_div(d->I, 128);
-    return slots <= 5 * experts || (items <= 320 && slots <= 40 * experts) || (items <= 40 && slots <= 170 * experts);
+    return d->T <= 64 || slots <= 5 * experts || (items <= 320 && slots <= 40 * experts) || (items <= 40 && slots <= 170 * experts);
 }
 
 template <bool GATEUP, bool TILED>

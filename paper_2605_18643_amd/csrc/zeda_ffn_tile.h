@@ -18,7 +18,7 @@
 // the 16 rows a fragment read touches per phase fall on distinct banks; the permutation is applied on the
 // global address (or is already part of the stored layout, for tiled weights).  Half of the waves fetch
 // weight rows only and the other half token rows only, so every wave's vmcnt counts one stream and the two
-// rings may have different depths.  The chunks of all items of a workgroup form ONE sequence: while the
+// rings may have different depths (with the 64-wide token ring all waves fetch both, see chunk_pair).  The chunks of all items of a workgroup form ONE sequence: while the
 // last chunks of an item are multiplied and its result is written, the first chunks of the next item are
 // already in flight, so HBM never sees the pipeline drain between tiles.  Per chunk there is one counted
 // s_waitcnt (this wave's own loads of that chunk) and one s_barrier (everybody's loads have landed, and
@@ -38,24 +38,28 @@
 
 namespace zeda {
 
-template <int G_, int FB_, int WF_, int NSW_, int NST_, int KC_>
+// KC: k chunk of the weight ring; TKC: of the token ring, KC or two of them (see Stream::chunk_pair).
+template <int G_, int FB_, int WF_, int NSW_, int NST_, int KC_, int TKC_ = KC_>
 struct TileCfg {
-    static constexpr int G = G_, FB = FB_, WF = WF_, NSW = NSW_, NST = NST_, KC = KC_;
+    static constexpr int G = G_, FB = FB_, WF = WF_, NSW = NSW_, NST = NST_, KC = KC_, TKC = TKC_;
+    static constexpr bool PAIR = TKC != KC;
+    static constexpr bool ROT = 64 * G_ <= 256;  // may start items at k chunks of their own (wider tiles are for many rows)
     static constexpr int WT = 2;                  // wave rows: wave row wt owns token blocks wt, wt+2, ...
     static constexpr int BT = 64 * G;             // tokens per tile
     static constexpr int BF = 32 * FB * WF;       // weight rows per tile (gate and up rows both count)
     static constexpr int NW = WT * WF;            // waves
-    static constexpr int NWW = NW / 2;            // waves 0..NWW-1 fetch the weight rows, the others the token rows
-    static constexpr int NWT = NW - NWW;
+    static constexpr int NWW = PAIR ? NW : NW / 2;  // waves 0..NWW-1 fetch the weight rows, the others the token rows (PAIR: all both)
+    static constexpr int NWT = PAIR ? NW : NW - NWW;
     static constexpr int THREADS = 64 * NW;
     static constexpr int ROWB = 2 * KC;           // bytes of one row of a chunk
     static constexpr int PPR = ROWB / 16;         // 16-byte pieces per row
     static constexpr int RPI = 64 / PPR;          // rows covered by one wave load instruction
+    static constexpr int TROWB = 2 * TKC, TPPR = TROWB / 16, TRPI = 64 / TPPR;  // the same for the token ring
     static constexpr int KS = KC / 16;            // MFMA k steps per chunk
-    static constexpr int WST = BF * ROWB, TST = BT * ROWB;  // bytes of a weight / token ring slot
+    static constexpr int WST = BF * ROWB, TST = BT * TROWB;  // bytes of a weight / token ring slot
     static constexpr int WRING = NSW * WST, TRING = NST * TST;
     static constexpr int NLW = BF / RPI / NWW;    // load instructions per chunk of a weight wave
-    static constexpr int nlt(int g) { return 64 * g / RPI / NWT; }  // ... of a token wave with g live 64-row groups
+    static constexpr int nlt(int g) { return 64 * g / TRPI / NWT; }  // ... of a token wave with g live 64-row groups
     static constexpr int NLMAX = NLW > nlt(G) ? NLW : nlt(G);
     static constexpr int MAXQ = 8;                // items looked up at a time
     // Token tiles of an expert with m rows.  Tiles hold at most 256 rows unless the wider tile (BT > 256) saves a
@@ -73,8 +77,8 @@ struct TileCfg {
     static constexpr int STG_OFF = LOC_OFF + MAXQ * 16;      // 2 KiB per wave: output transposition
     static constexpr int LDS_BYTES = STG_OFF + NW * 2048;
     static constexpr int WMAX = (NSW - 2) * NLW > (NST - 2) * nlt(G) ? (NSW - 2) * NLW : (NST - 2) * nlt(G);
-    static_assert(KC == 32 || KC == 64, "rows of 64 or 128 bytes");
-    static_assert((BF / RPI) % NWW == 0 && (64 / RPI) % NWT == 0, "loads must divide evenly over the waves of a role");
+    static_assert((KC == 32 || KC == 64) && (TKC == KC || (KC == 32 && TKC == 64 && NST == 2 && NSW == 4)), "rows of 64 or 128 bytes");
+    static_assert((BF / RPI) % NWW == 0 && (64 / TRPI) % NWT == 0, "loads must divide evenly over the waves of a role");
     static_assert(NSW >= 2 && NST >= 2 && (NSW - 1) * NLW <= 63 && (NST - 1) * nlt(G) <= 63, "vmcnt is a 6-bit counter");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS is 160 KiB per CU");
 };
@@ -185,7 +189,8 @@ template <class C, bool GATEUP, bool TILED, bool WNT>
 struct Stream {
     static constexpr int FB = C::FB, WF = C::WF, BT = C::BT, BF = C::BF, NSW = C::NSW, NST = C::NST, NW = C::NW,
                          NWW = C::NWW, NWT = C::NWT, WST = C::WST, TST = C::TST, KC = C::KC, KS = C::KS, ROWB = C::ROWB,
-                         PPR = C::PPR, RPI = C::RPI, NLMAX = C::NLMAX, NLW = C::NLW;
+                         PPR = C::PPR, RPI = C::RPI, NLMAX = C::NLMAX, NLW = C::NLW, TKC = C::TKC, TROWB = C::TROWB,
+                         TPPR = C::TPPR, TRPI = C::TRPI;
     static constexpr int NH = (NSW > NST ? NSW : NST) > 2 ? (NSW > NST ? NSW : NST) - 2 : 1;
     static_assert(!TILED || KC == 32, "tiled weights are stored in 32-wide k blocks");
 
@@ -206,11 +211,19 @@ struct Stream {
     // NSW-1 chunks ahead of the MFMAs, token waves NST-1 (token rows mostly come from L2 and need less lead).
     // The next chunk this wave fetches is chunk ikc of item iq, into slot islot of its ring.
     bool wrole;
-    const bf16_t *src[NLMAX];
+    const bf16_t *src[C::PAIR ? 1 : NLMAX];
     int nq, iq, ikc, islot, inl, krot;
     size_t koff;          // where in the rows chunk ikc of the item is, in elements
     int kstep;            // elements from one chunk of this wave's operand to the next
+    int nki;              // chunks of this wave's operand in an item
     uint32_t dbase, doff; // LDS address of this wave's first piece in slot 0 of its ring; byte offset of slot islot
+    // PAIR: every wave fetches both operands, two pairs of weight chunks and two token chunks ahead.  Addresses are a
+    // wave-uniform pointer and a 32-bit byte offset per lane, which the load instruction adds itself.
+    const bf16_t *wsrc[C::PAIR ? NLW : 1];
+    uint32_t toff[C::PAIR ? C::nlt(C::G) : 1], loff;
+    size_t koff_w;
+    uint32_t wdst, tdst;  // LDS addresses of this wave's first piece in the slots to fill next
+    int nw1, nt1;         // loads per weight chunk and token chunk of the pair after the one being multiplied
     int hist[NH];  // load instructions of this wave in each of the last chunks issued (newest last)
     // compute side: slots of the chunk being multiplied
     int cslot_w, cslot_t;
@@ -222,6 +235,14 @@ struct Stream {
         return make_int4(__builtin_amdgcn_readfirstlane(v[0]), __builtin_amdgcn_readfirstlane(v[1]),
                          __builtin_amdgcn_readfirstlane(v[2]), __builtin_amdgcn_readfirstlane(v[3]));
     }
+    // tiled weights: what lane ln fetches of 16 rows = one half of a stored 32x32 unit, already in LDS order: piece ln
+    __device__ __forceinline__ const bf16_t *weight_src(int jw, int ln, int expert, int ft) const
+    {
+        const int lb = jw >> 1, blk = lb % FB, wfr = lb / FB;
+        const bf16_t *wbase = (GATEUP && (blk & 1)) ? w1 : w0;
+        const int rb = GATEUP ? ft * (BF / 64) + wfr * (FB / 2) + (blk >> 1) : ft * (BF / 32) + lb;
+        return wbase + ((size_t)expert * (Kdim / 32) * (Fdim / 32) + rb) * 1024 + (jw & 1) * 512 + ln * 8;
+    }
     __device__ __forceinline__ void setup_issue_item()
     {
         if (iq >= nq) { inl = 0; return; }
@@ -229,21 +250,36 @@ struct Stream {
         const int expert = loc.x, rows = loc.z, ft = loc.w;
         int ln = lane;
         asm volatile("" : "+v"(ln));  // (recomputed per item rather than kept live)
-        const int piece = ln % PPR, rsub = ln / PPR;
+        if constexpr (C::PAIR) {
+            krot = C::ROT && rotate ? (int)((unsigned)(expert * 5 + ft * 3) % (unsigned)(Kdim / 64)) : 0;
+            koff = (size_t)krot * 64;
+            koff_w = (size_t)krot * 2 * kstep;
+#pragma unroll
+            for (int i = 0; i < NLW; ++i) wsrc[i] = weight_src(wave + NWW * i, 0, expert, ft);
+            const int g = (rows + 63) >> 6;
+            inl = C::nlt(g);
+            uint32_t srow[NLMAX];
+#pragma unroll
+            for (int i = 0; i < C::nlt(C::G); ++i)
+                srow[i] = lds_read_b32(lds_addr(s_tok + iq * BT + min(wave + NWT * i, NWT * inl - 1) * TRPI + ln / TPPR));
+#pragma unroll
+            for (int i = 0; i < C::nlt(C::G); ++i) lds_wait(srow[i]);
+#pragma unroll
+            for (int i = 0; i < C::nlt(C::G); ++i)
+                toff[i] = (srow[i] * (uint32_t)Kdim + swz<TKC>((wave + NWT * i) * TRPI + ln / TPPR, ln % TPPR) * 8) * 2;
+            return;
+        } else {
         // first chunk of the item (in units of 64 k, the same for both weight layouts); see run_tiles_auto for rotate
-        krot = rotate ? (int)((unsigned)(expert * 5 + ft * 3) % (unsigned)(Kdim / 64)) * (64 / KC) : 0;
+        krot = C::ROT && rotate ? (int)((unsigned)(expert * 5 + ft * 3) % (unsigned)(Kdim / 64)) * (C::PAIR && !wrole ? 1 : 64 / KC) : 0;
         koff = (size_t)krot * kstep;
         if (wrole) {
+            const int piece = ln % PPR, rsub = ln / PPR;
             inl = NLW;
 #pragma unroll
             for (int i = 0; i < NLW; ++i) {
                 const int jw = wave + NWW * i;  // covers rows jw*RPI.. of the weight tile
                 if (TILED) {
-                    // 16 rows = one half of a stored 32x32 unit, already in LDS order: lane l copies piece l
-                    const int lb = jw >> 1, blk = lb % FB, wfr = lb / FB;
-                    const bf16_t *wbase = (GATEUP && (blk & 1)) ? w1 : w0;
-                    const int rb = GATEUP ? ft * (BF / 64) + wfr * (FB / 2) + (blk >> 1) : ft * (BF / 32) + lb;
-                    src[i] = wbase + ((size_t)expert * (Kdim / 32) * (Fdim / 32) + rb) * 1024 + (jw & 1) * 512 + ln * 8;
+                    src[i] = weight_src(jw, ln, expert, ft);
                 } else {
                     const int row = jw * RPI + rsub;
                     const bf16_t *wbase;
@@ -260,26 +296,38 @@ struct Stream {
                 }
             }
         } else {
+            const int piece = ln % TPPR, rsub = ln / TPPR;
             const int g = (rows + 63) >> 6;
             inl = C::nlt(g);
             uint32_t srow[NLMAX];
 #pragma unroll
             for (int i = 0; i < C::nlt(C::G); ++i)  // (entries past the live groups are read, and never used)
-                srow[i] = lds_read_b32(lds_addr(s_tok + iq * BT + min(wave - NWW + NWT * i, NWT * inl - 1) * RPI + rsub));
+                srow[i] = lds_read_b32(lds_addr(s_tok + iq * BT + min(wave - NWW + NWT * i, NWT * inl - 1) * TRPI + rsub));
 #pragma unroll
             for (int i = 0; i < C::nlt(C::G); ++i) lds_wait(srow[i]);
 #pragma unroll
             for (int i = 0; i < C::nlt(C::G); ++i) {
-                const int trow = (wave - NWW + NWT * i) * RPI + rsub;
-                src[i] = tok + (size_t)srow[i] * Kdim + swz<KC>(trow, piece) * 8;
+                const int trow = (wave - NWW + NWT * i) * TRPI + rsub;
+                src[i] = tok + (size_t)srow[i] * Kdim + swz<TKC>(trow, piece) * 8;
             }
+        }
         }
     }
     __device__ __forceinline__ void init_issue()
     {
         wring_a = lds_addr(wring);
         tring_a = lds_addr(tring);
-        kstep = (TILED && wrole) ? (Fdim / 32) * 1024 : KC;
+        if constexpr (C::PAIR) {
+            kstep = (Fdim / 32) * 1024;
+            nki = Kdim / TKC;
+            loff = lane * 16;
+            wdst = wring_a + wave * 1024;
+            tdst = tring_a + wave * 1024;
+            iq = 0; ikc = 0; inl = 0; koff = 0; koff_w = 0; krot = 0;
+            return;
+        }
+        kstep = wrole ? (TILED ? (Fdim / 32) * 1024 : KC) : TKC;
+        nki = wrole ? Kdim / KC : Kdim / TKC;
         dbase = lds_addr(wrole ? wring + wave * 1024 : tring + (wave - NWW) * 1024);
         iq = 0; ikc = 0; islot = 0; inl = 0; koff = 0; doff = 0; krot = 0;
 #pragma unroll
@@ -287,6 +335,7 @@ struct Stream {
     }
     __device__ __forceinline__ void load_piece(int i)
     {
+        if constexpr (!C::PAIR) {
         const uint32_t dst = dbase + doff + i * ((NWW == NWT ? NWW : (wrole ? NWW : NWT)) * 1024);
         // (the cache-policy field of the instruction is an immediate, hence two instructions)
         if (WNT && wrole)
@@ -295,13 +344,14 @@ struct Stream {
         else
             __builtin_amdgcn_global_load_lds(ZEDA_GLOBAL_PTR(src[i] + koff),
                                              (__attribute__((address_space(3))) void *)(uintptr_t)dst, 16, 0, 0);
+        }
     }
     // the issue position moves on by one chunk inside the current item
     __device__ __forceinline__ void next_chunk_same_item()
     {
         ++ikc;
         koff += kstep;
-        if (ikc + krot == nk) koff = 0;
+        if (C::ROT && ikc + krot == nki) koff = 0;
         const bool wrap = ++islot == (NSW == NST ? NSW : (wrole ? NSW : NST));
         doff = wrap ? 0 : doff + (WST == TST ? WST : (wrole ? WST : TST));
         islot = wrap ? 0 : islot;
@@ -320,6 +370,48 @@ struct Stream {
         else if (i < NLW) { if (wrole) load_piece(i); }
         else if (i < NT) { if (!wrole) load_piece(i); }
     }
+    // PAIR: load i of weight half h of the pair to fetch next, and token load i of it
+    __device__ __forceinline__ void load_w(int i, int h)
+    {
+        const uint32_t dst = wdst + i * (NWW * 1024) + h * WST;
+        const char *g = reinterpret_cast<const char *>(wsrc[i] + koff_w + h * kstep) + loff;
+        if (WNT)
+            __builtin_amdgcn_global_load_lds(ZEDA_GLOBAL_PTR(g), (__attribute__((address_space(3))) void *)(uintptr_t)dst, 16, 0, 2 /* nt */);
+        else
+            __builtin_amdgcn_global_load_lds(ZEDA_GLOBAL_PTR(g), (__attribute__((address_space(3))) void *)(uintptr_t)dst, 16, 0, 0);
+    }
+    __device__ __forceinline__ void load_t(int i)
+    {
+        __builtin_amdgcn_global_load_lds(ZEDA_GLOBAL_PTR(reinterpret_cast<const char *>(tok + koff) + toff[i]),
+                                         (__attribute__((address_space(3))) void *)(uintptr_t)(tdst + i * (NWT * 1024)), 16, 0, 0);
+    }
+    // PAIR: the position to fetch moves on by one pair (the rings hold two pairs each)
+    __device__ __forceinline__ void next_pair_same_item()
+    {
+        ++ikc;
+        koff += TKC;
+        koff_w += 2 * kstep;
+        if (C::ROT && ikc + krot == nki) { koff = 0; koff_w = 0; }
+        wdst = wdst - wring_a >= 2 * WST ? wdst - 2 * WST : wdst + 2 * WST;
+        tdst = tdst - tring_a >= TST ? tdst - TST : tdst + TST;
+    }
+    __device__ __forceinline__ void fetch_pair_burst()
+    {
+        const int ni = inl;
+        if (ni > 0) {
+#pragma unroll
+            for (int i = 0; i < NLW; ++i) load_w(i, 0);
+#pragma unroll
+            for (int i = 0; i < C::nlt(C::G); ++i)
+                if (i < ni) load_t(i);
+#pragma unroll
+            for (int i = 0; i < NLW; ++i) load_w(i, 1);
+            next_pair_same_item();
+            next_item_if_done();
+        }
+        nw1 = ni > 0 ? NLW : 0;
+        nt1 = ni;
+    }
     // bookkeeping after the instructions of one chunk were issued (ni of them; 0 once the stream has ended)
     __device__ __forceinline__ void issued(int ni)
     {
@@ -334,7 +426,7 @@ struct Stream {
     // past the last chunk of the item: the next chunk to fetch is the first one of the next item
     __device__ __forceinline__ void next_item_if_done()
     {
-        if (ikc == nk) {
+        if (ikc == nki) {
             ikc = 0;
             koff = 0;
             ++iq;
@@ -376,8 +468,8 @@ struct Stream {
     template <int GA>
     __device__ __forceinline__ void load_frags(uint32_t wslot, uint32_t tslot, int s, u32x4 (&fa)[FB], u32x4 (&tb)[GA]) const
     {
-        read_blocks<0, FB, 32 * ROWB>(wslot + (foff_w ^ (s << 5)), fa);
-        read_blocks<0, GA, 64 * ROWB>(tslot + (foff_t ^ (s << 5)), tb);
+        read_blocks<0, FB, 32 * ROWB>(wslot + (foff_w ^ ((s % KS) << 5)), fa);
+        read_blocks<0, GA, 64 * TROWB>(tslot + (foff_t ^ (s << 5)), tb);
     }
     // the fragments in fa, tb have landed when at most `newer` LDS reads issued after them are still in flight
     template <int NEWER, int GA>
@@ -454,6 +546,81 @@ struct Stream {
         cslot_t = nslot_t;
     }
 
+    // Two chunks of 32 k whose token rows share one 64-wide slot.  Rows are gathered from all over x (or act), and a row's
+    // 64 bytes of a 32-wide chunk are half a cache line: the vector memory path takes lines, so half lines arrive at half
+    // the rate (60 against 129 GB/s per CU out of L2) and every line is asked for twice.  So the token ring moves 64 k at a
+    // time in two slots, while the weights, whose tiled units are contiguous, move in four slots of 32 k.
+    // Every wave fetches both operands, in the order first weight half (issued in the pair's second k step, two pairs
+    // ahead), tokens, second weight half (fourth k step), so the loads that may stay in flight are: in the fourth step,
+    // where the next pair's first half and tokens are awaited, the next pair's second half and the first half just
+    // issued; in the second step, where this pair's second half is awaited, all of the next pair.
+    template <int GA, bool MAIN, bool MORE>
+    __device__ __forceinline__ void chunk_pair(f32x16 (&acc)[GA][FB], u32x4 (&fa)[2][FB], u32x4 (&tb)[2][GA])
+    {
+        static_assert(KS == 2 && NSW == 4 && NST == 2, "two pairs");
+        constexpr int NT = C::nlt(GA), NTMAX = C::nlt(C::G), WM = 2 * NLW + NTMAX;
+        const uint32_t cur_w = wring_a + cslot_w * WST, cur_t = tring_a + cslot_t * TST;
+        int ni = 0;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int p = s & 1;
+            if (p == 0) {
+                load_frags<GA>(cur_w + (s >> 1) * WST, cur_t, s + 1, fa[p ^ 1], tb[p ^ 1]);
+                frags_landed<FB + GA, GA>(fa[p], tb[p]);
+            } else {
+                frags_landed<0, GA>(fa[p], tb[p]);
+                if (s == 1) {
+                    if (MAIN) wait_vmcnt<2 * NLW + NT>();
+                    else wait_vmcnt_tree<0, WM>(2 * nw1 + nt1);
+                    ni = inl;
+                } else {
+                    if (MAIN) wait_vmcnt<2 * NLW>();
+                    else wait_vmcnt_tree<0, 2 * NLW>(nw1 + (ni > 0 ? NLW : 0));
+                }
+                __builtin_amdgcn_s_barrier();
+                if (s == 1) load_frags<GA>(cur_w + WST, cur_t, 2, fa[p ^ 1], tb[p ^ 1]);
+                else if (MORE) load_frags<GA>(wring_a + (cslot_w ^ 2) * WST, tring_a + (cslot_t ^ 1) * TST, 0, fa[p ^ 1], tb[p ^ 1]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            constexpr int NM = GA * FB;
+#pragma unroll
+            for (int a = 0; a < GA; ++a)
+#pragma unroll
+                for (int b = 0; b < FB; ++b) {
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[p][b]),
+                                                                        __builtin_bit_cast(bf16x8, tb[p][a]), acc[a][b], 0, 0, 0);
+                    const int m = a * FB + b;
+                    if (s == 1) {
+#pragma unroll
+                        for (int i = 0; i < NLW; ++i)
+                            if (i * NM / NLW == m && (MAIN || ni > 0)) load_w(i, 0);
+                    } else if (s == 3) {
+                        // the tokens over the first MFMAs, the second weight half after them
+                        constexpr int NL = (MAIN ? NT : NTMAX) + NLW;
+#pragma unroll
+                        for (int i = 0; i < NL; ++i)
+                            if (i * NM / NL == m) {
+                                if (i < NL - NLW) { if (MAIN || i < ni) load_t(i); }
+                                else if (MAIN || ni > 0) load_w(i - (NL - NLW), 1);
+                            }
+                    }
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (MAIN) {
+            next_pair_same_item();
+        } else {
+            nw1 = ni > 0 ? NLW : 0;
+            nt1 = ni;
+            if (ni > 0) {
+                next_pair_same_item();
+                next_item_if_done();
+            }
+        }
+        cslot_w ^= 2;
+        cslot_t ^= 1;
+    }
+
     // One item with GA live 64-row groups: its nk chunks, then the epilogue.
     template <int GA>
     __device__ __forceinline__ void tile_body(int expert, int row0, int rows, int ft)
@@ -471,6 +638,19 @@ struct Stream {
         u32x4 fa[2][FB], tb[2][GA];
         load_frags<GA>(wring_a + cslot_w * WST, tring_a + cslot_t * TST, 0, fa[0], tb[0]);
 
+        if constexpr (C::PAIR) {
+            // the main part as below: pair q fetches pair q + 2, still this item's
+            const int np = Kdim / TKC, n_main = np > 2 ? np - 2 : 0;
+            int q = 0;
+            for (; q < n_main; ++q) chunk_pair<GA, true, true>(acc, fa, tb);
+            if (n_main > 0) {
+                nw1 = NLW;
+                nt1 = C::nlt(GA);
+                next_item_if_done();
+            }
+            for (; q + 1 < np; ++q) chunk_pair<GA, false, true>(acc, fa, tb);
+            chunk_pair<GA, false, false>(acc, fa, tb);
+        } else {
         // Main part: the chunks during which every load in flight belongs to this item, so that the number of loads
         // that may stay outstanding at the wait is a constant of the item's shape (an immediate).  The last chunks,
         // during which the first chunks of the next item are fetched, take the counted path.
@@ -485,6 +665,7 @@ struct Stream {
         }
         for (; kc + 1 < nk; ++kc) chunk<GA, false, true>(acc, fa, tb);
         chunk<GA, false, false>(acc, fa, tb);
+        }
 
         // Epilogue.  acc[a][b][v] is feature 8*(v/4) + 4*half + v%4 of weight block b, token `col` of token
         // block 2a + wt.  Each 32x32 result block goes through this wave's LDS buffer (rows of 32 bf16, pieces
@@ -596,20 +777,29 @@ __device__ __forceinline__ void run_tiles(unsigned char *lds, const TileScan<C> 
 
         Stream<C, GATEUP, TILED, WNT> st;
         st.tok = tok; st.w0 = w0; st.w1 = w1; st.out = out;
-        st.Kdim = Kdim; st.Fdim = Fdim; st.nk = Kdim / C::KC; st.rotate = rotate;
+        st.Kdim = Kdim; st.Fdim = Fdim; st.nk = Kdim / C::KC; st.rotate = __builtin_amdgcn_readfirstlane((int)rotate) != 0;
         st.wring = lds; st.tring = lds + C::TRING_OFF; st.stg = lds + C::STG_OFF + wave * 2048; st.s_tok = s_tok; st.s_loc = s_loc;
         st.lane = lane; st.wave = wave; st.wt = wave / C::WF; st.wf = wave % C::WF; st.col = lane & 31; st.half = lane >> 5;
-        st.foff_t = (st.wt * 32 + st.col) * C::ROWB + swz<C::KC>(st.col, st.half) * 16;
+        st.foff_t = (st.wt * 32 + st.col) * C::TROWB + swz<C::TKC>(st.col, st.half) * 16;
         st.foff_w = (st.wf * C::FB * 32 + st.col) * C::ROWB + swz<C::KC>(st.col, st.half) * 16;
         st.wrole = wave < C::NWW;
         st.nq = nq; st.cslot_w = 0; st.cslot_t = 0;
         st.init_issue();
         st.setup_issue_item();
-        for (int c = 0, n = (st.wrole ? C::NSW : C::NST) - 1; c < n; ++c) st.issue_burst();
-        // all slots of this wave's ring but one are in flight: wait for the first chunk, meet, fill the last slot
-        st.wait_oldest();
-        __builtin_amdgcn_s_barrier();
-        st.issue_burst();
+        if constexpr (C::PAIR) {
+            // both pairs of the rings; the first pair's first weight half and tokens are awaited here (its second half and
+            // the other pair, as much of it as there is, may stay in flight)
+            st.fetch_pair_burst();
+            st.fetch_pair_burst();
+            wait_vmcnt_tree<0, 3 * C::NLW + C::nlt(C::G)>(C::NLW + 2 * st.nw1 + st.nt1);
+            __builtin_amdgcn_s_barrier();
+        } else {
+            for (int c = 0, n = (st.wrole ? C::NSW : C::NST) - 1; c < n; ++c) st.issue_burst();
+            // all slots of this wave's ring but one are in flight: wait for the first chunk, meet, fill the last slot
+            st.wait_oldest();
+            __builtin_amdgcn_s_barrier();
+            st.issue_burst();
+        }
 
         for (int q = 0; q < nq; ++q) {
             const int4 loc = st.read_loc(q);
