@@ -193,6 +193,7 @@ struct Stream {
                          TPPR = C::TPPR, TRPI = C::TRPI;
     static constexpr int NH = (NSW > NST ? NSW : NST) > 2 ? (NSW > NST ? NSW : NST) - 2 : 1;
     static_assert(!TILED || KC == 32, "tiled weights are stored in 32-wide k blocks");
+    static constexpr bool SPLIT_GROUP = NW == 8;  // (four waves: the two wave rows are on different SIMDs)
 
     // kernel arguments
     const bf16_t *tok, *w0, *w1;
@@ -464,29 +465,34 @@ struct Stream {
             read_blocks<I + 1, N, STRIDE>(base, out);
         }
     }
-    // wslot, tslot: LDS addresses of the chunk's weight and token slot
-    template <int GA>
-    __device__ __forceinline__ void load_frags(uint32_t wslot, uint32_t tslot, int s, u32x4 (&fa)[FB], u32x4 (&tb)[GA]) const
+    // wslot, tslot: LDS addresses of the chunk's weight and token slot; GM: token blocks this wave multiplies (see
+    // tile_body), GX = max(GM, 1)
+    template <int GM, int GX>
+    __device__ __forceinline__ void load_frags(uint32_t wslot, uint32_t tslot, int s, u32x4 (&fa)[FB], u32x4 (&tb)[GX]) const
     {
-        read_blocks<0, FB, 32 * ROWB>(wslot + (foff_w ^ ((s % KS) << 5)), fa);
-        read_blocks<0, GA, 64 * TROWB>(tslot + (foff_t ^ (s << 5)), tb);
+        if constexpr (GM > 0) {
+            read_blocks<0, FB, 32 * ROWB>(wslot + (foff_w ^ ((s % KS) << 5)), fa);
+            read_blocks<0, GM, 64 * TROWB>(tslot + (foff_t ^ (s << 5)), tb);
+        }
     }
     // the fragments in fa, tb have landed when at most `newer` LDS reads issued after them are still in flight
-    template <int NEWER, int GA>
-    __device__ __forceinline__ void frags_landed(u32x4 (&fa)[FB], u32x4 (&tb)[GA]) const
+    template <int NEWER, int GM, int GX>
+    __device__ __forceinline__ void frags_landed(u32x4 (&fa)[FB], u32x4 (&tb)[GX]) const
     {
-        asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(NEWER) : "memory");
+        if constexpr (GM > 0) {
+            asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(NEWER) : "memory");
 #pragma unroll
-        for (int b = 0; b < FB; ++b) asm volatile("" : "+v"(fa[b]));
+            for (int b = 0; b < FB; ++b) asm volatile("" : "+v"(fa[b]));
 #pragma unroll
-        for (int a = 0; a < GA; ++a) asm volatile("" : "+v"(tb[a]));
+            for (int a = 0; a < GM; ++a) asm volatile("" : "+v"(tb[a]));
+        }
     }
 
     // One chunk of an item with GA live groups: KS k steps; in the last one the next chunk is awaited, everybody
     // meets, and the slot everybody has left is refilled.  MAIN: all loads in flight are this item's (see tile_body).
     // MORE: the item has another chunk after this one (its first fragments are read here, after the meeting).
-    template <int GA, bool MAIN, bool MORE>
-    __device__ __forceinline__ void chunk(f32x16 (&acc)[GA][FB], u32x4 (&fa)[2][FB], u32x4 (&tb)[2][GA])
+    template <int GA, int GM, bool MAIN, bool MORE, int GX>
+    __device__ __forceinline__ void chunk(f32x16 (&acc)[GX][FB], u32x4 (&fa)[2][FB], u32x4 (&tb)[2][GX])
     {
         const uint32_t cur_w = wring_a + cslot_w * WST, cur_t = tring_a + cslot_t * TST;
         const int nslot_w = cslot_w + 1 == NSW ? 0 : cslot_w + 1, nslot_t = cslot_t + 1 == NST ? 0 : cslot_t + 1;
@@ -495,11 +501,11 @@ struct Stream {
             const int p = s & 1;
             int ni = 0;
             if (s < KS - 1) {
-                load_frags<GA>(cur_w, cur_t, s + 1, fa[p ^ 1], tb[p ^ 1]);
-                frags_landed<FB + GA, GA>(fa[p], tb[p]);
+                load_frags<GM>(cur_w, cur_t, s + 1, fa[p ^ 1], tb[p ^ 1]);
+                frags_landed<FB + GM, GM>(fa[p], tb[p]);
             } else {
                 // every fragment of this chunk is in registers: nobody needs its slot any more
-                frags_landed<0, GA>(fa[p], tb[p]);
+                frags_landed<0, GM>(fa[p], tb[p]);
                 // Wait for the next chunk, meet, refill the slot everybody has just left.  After the item's last
                 // chunk the next chunk is the first one of the next item (nothing, at the end of the stream): it is
                 // awaited HERE, before the epilogue, because the epilogue's stores count in vmcnt too - a wait
@@ -513,20 +519,20 @@ struct Stream {
                     wait_oldest();
                 }
                 __builtin_amdgcn_s_barrier();
-                if (MORE) load_frags<GA>(wring_a + nslot_w * WST, tring_a + nslot_t * TST, 0, fa[p ^ 1], tb[p ^ 1]);
+                if (MORE) load_frags<GM>(wring_a + nslot_w * WST, tring_a + nslot_t * TST, 0, fa[p ^ 1], tb[p ^ 1]);
                 ni = inl;
             }
             // keep the reads of the next step ahead of this step's MFMAs
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int a = 0; a < GA; ++a)
+            for (int a = 0; a < GM; ++a)
 #pragma unroll
                 for (int b = 0; b < FB; ++b) {
                     acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[p][b]),
                                                                         __builtin_bit_cast(bf16x8, tb[p][a]), acc[a][b], 0, 0, 0);
                     if (s == KS - 1) {
                         // the refill of the slot freed by the barrier, spread over this step's MFMAs
-                        constexpr int NM = GA * FB;
+                        constexpr int NM = GM * FB;
                         const int m = a * FB + b;
 #pragma unroll
                         for (int i = 0; i < NLMAX; ++i)
@@ -536,6 +542,13 @@ struct Stream {
                             }
                     }
                 }
+            if (GM == 0 && s == KS - 1) {
+#pragma unroll
+                for (int i = 0; i < NLMAX; ++i) {
+                    if (MAIN) issue_one_of<GA>(i);
+                    else issue_one(i, ni);
+                }
+            }
             __builtin_amdgcn_sched_barrier(0);
             if (s == KS - 1) {
                 if (MAIN) next_chunk_same_item();
@@ -554,8 +567,8 @@ struct Stream {
     // ahead), tokens, second weight half (fourth k step), so the loads that may stay in flight are: in the fourth step,
     // where the next pair's first half and tokens are awaited, the next pair's second half and the first half just
     // issued; in the second step, where this pair's second half is awaited, all of the next pair.
-    template <int GA, bool MAIN, bool MORE>
-    __device__ __forceinline__ void chunk_pair(f32x16 (&acc)[GA][FB], u32x4 (&fa)[2][FB], u32x4 (&tb)[2][GA])
+    template <int GA, int GM, bool MAIN, bool MORE, int GX>
+    __device__ __forceinline__ void chunk_pair(f32x16 (&acc)[GX][FB], u32x4 (&fa)[2][FB], u32x4 (&tb)[2][GX])
     {
         static_assert(KS == 2 && NSW == 4 && NST == 2, "two pairs");
         constexpr int NT = C::nlt(GA), NTMAX = C::nlt(C::G), WM = 2 * NLW + NTMAX;
@@ -565,10 +578,10 @@ struct Stream {
         for (int s = 0; s < 4; ++s) {
             const int p = s & 1;
             if (p == 0) {
-                load_frags<GA>(cur_w + (s >> 1) * WST, cur_t, s + 1, fa[p ^ 1], tb[p ^ 1]);
-                frags_landed<FB + GA, GA>(fa[p], tb[p]);
+                load_frags<GM>(cur_w + (s >> 1) * WST, cur_t, s + 1, fa[p ^ 1], tb[p ^ 1]);
+                frags_landed<FB + GM, GM>(fa[p], tb[p]);
             } else {
-                frags_landed<0, GA>(fa[p], tb[p]);
+                frags_landed<0, GM>(fa[p], tb[p]);
                 if (s == 1) {
                     if (MAIN) wait_vmcnt<2 * NLW + NT>();
                     else wait_vmcnt_tree<0, WM>(2 * nw1 + nt1);
@@ -578,13 +591,13 @@ struct Stream {
                     else wait_vmcnt_tree<0, 2 * NLW>(nw1 + (ni > 0 ? NLW : 0));
                 }
                 __builtin_amdgcn_s_barrier();
-                if (s == 1) load_frags<GA>(cur_w + WST, cur_t, 2, fa[p ^ 1], tb[p ^ 1]);
-                else if (MORE) load_frags<GA>(wring_a + (cslot_w ^ 2) * WST, tring_a + (cslot_t ^ 1) * TST, 0, fa[p ^ 1], tb[p ^ 1]);
+                if (s == 1) load_frags<GM>(cur_w + WST, cur_t, 2, fa[p ^ 1], tb[p ^ 1]);
+                else if (MORE) load_frags<GM>(wring_a + (cslot_w ^ 2) * WST, tring_a + (cslot_t ^ 1) * TST, 0, fa[p ^ 1], tb[p ^ 1]);
             }
             __builtin_amdgcn_sched_barrier(0);
-            constexpr int NM = GA * FB;
+            constexpr int NM = GM * FB;
 #pragma unroll
-            for (int a = 0; a < GA; ++a)
+            for (int a = 0; a < GM; ++a)
 #pragma unroll
                 for (int b = 0; b < FB; ++b) {
                     acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[p][b]),
@@ -605,6 +618,16 @@ struct Stream {
                             }
                     }
                 }
+            if (GM == 0 && (s & 1)) {
+                if (s == 3) {
+#pragma unroll
+                    for (int i = 0; i < (MAIN ? NT : NTMAX); ++i)
+                        if (MAIN || i < ni) load_t(i);
+                }
+#pragma unroll
+                for (int i = 0; i < NLW; ++i)
+                    if (MAIN || ni > 0) load_w(i, s >> 1);
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
         if (MAIN) {
@@ -621,13 +644,16 @@ struct Stream {
         cslot_t ^= 1;
     }
 
-    // One item with GA live 64-row groups: its nk chunks, then the epilogue.
-    template <int GA>
+    // One item with GA live 64-row groups: its nk chunks, then the epilogue.  GM: how many 32-row blocks this wave
+    // multiplies, GA, or GA - 1 for the second wave row where the last group holds at most 32 rows.  Every SIMD holds a
+    // wave of each wave row, so the block left out is time the first wave row's wave gets (GM = 0: the wave only fetches).
+    template <int GA, int GM>
     __device__ __forceinline__ void tile_body(int expert, int row0, int rows, int ft)
     {
-        f32x16 acc[GA][FB];
+        constexpr int GX = GM > 0 ? GM : 1;
+        f32x16 acc[GX][FB];
 #pragma unroll
-        for (int a = 0; a < GA; ++a)
+        for (int a = 0; a < GX; ++a)
 #pragma unroll
             for (int b = 0; b < FB; ++b)
 #pragma unroll
@@ -635,21 +661,21 @@ struct Stream {
 
         // On entry the item's first chunk has landed and everybody has met after waiting for it (the item before,
         // or the start of the stream, saw to that).
-        u32x4 fa[2][FB], tb[2][GA];
-        load_frags<GA>(wring_a + cslot_w * WST, tring_a + cslot_t * TST, 0, fa[0], tb[0]);
+        u32x4 fa[2][FB], tb[2][GX];
+        load_frags<GM>(wring_a + cslot_w * WST, tring_a + cslot_t * TST, 0, fa[0], tb[0]);
 
         if constexpr (C::PAIR) {
             // the main part as below: pair q fetches pair q + 2, still this item's
             const int np = Kdim / TKC, n_main = np > 2 ? np - 2 : 0;
             int q = 0;
-            for (; q < n_main; ++q) chunk_pair<GA, true, true>(acc, fa, tb);
+            for (; q < n_main; ++q) chunk_pair<GA, GM, true, true>(acc, fa, tb);
             if (n_main > 0) {
                 nw1 = NLW;
                 nt1 = C::nlt(GA);
                 next_item_if_done();
             }
-            for (; q + 1 < np; ++q) chunk_pair<GA, false, true>(acc, fa, tb);
-            chunk_pair<GA, false, false>(acc, fa, tb);
+            for (; q + 1 < np; ++q) chunk_pair<GA, GM, false, true>(acc, fa, tb);
+            chunk_pair<GA, GM, false, false>(acc, fa, tb);
         } else {
         // Main part: the chunks during which every load in flight belongs to this item, so that the number of loads
         // that may stay outstanding at the wait is a constant of the item's shape (an immediate).  The last chunks,
@@ -657,14 +683,14 @@ struct Stream {
         constexpr int NSMAX = NSW > NST ? NSW : NST;
         const int n_main = nk > NSMAX ? nk - NSMAX : 0;  // chunk kc refills with chunk kc + depth: still this item's
         int kc = 0;
-        for (; kc < n_main; ++kc) chunk<GA, true, true>(acc, fa, tb);
+        for (; kc < n_main; ++kc) chunk<GA, GM, true, true>(acc, fa, tb);
         if (n_main > 0) {
 #pragma unroll
             for (int h = 0; h < NH; ++h) hist[h] = wrole ? NLW : C::nlt(GA);
             next_item_if_done();  // (the deeper ring's last refill there was the item's last chunk)
         }
-        for (; kc + 1 < nk; ++kc) chunk<GA, false, true>(acc, fa, tb);
-        chunk<GA, false, false>(acc, fa, tb);
+        for (; kc + 1 < nk; ++kc) chunk<GA, GM, false, true>(acc, fa, tb);
+        chunk<GA, GM, false, false>(acc, fa, tb);
         }
 
         // Epilogue.  acc[a][b][v] is feature 8*(v/4) + 4*half + v%4 of weight block b, token `col` of token
@@ -679,7 +705,7 @@ struct Stream {
         const uint32_t stg_w = lds_addr(stg) + ecol * 64 + ((ecol >> 2) & 3) * 16 + ehalf * 8;
         const uint32_t stg_r = lds_addr(stg) + (ln >> 2) * 64 + ((ln & 3) ^ ((ln >> 4) & 3)) * 16;
 #pragma unroll
-        for (int a = 0; a < GA; ++a) {
+        for (int a = 0; a < GM; ++a) {
             const int trow0 = (2 * a + wt) * 32;
             if (trow0 < rows) {
 #pragma unroll
@@ -719,8 +745,10 @@ template <class S, int GA>
 struct TileDispatch {
     static __device__ __forceinline__ void run(S &st, int g, int expert, int row0, int rows, int ft)
     {
-        if (g == GA) st.template tile_body<GA>(expert, row0, rows, ft);
-        else TileDispatch<S, GA - 1>::run(st, g, expert, row0, rows, ft);
+        if (g == GA) {
+            if (S::SPLIT_GROUP && st.wt && rows <= 64 * GA - 32) st.template tile_body<GA, GA - 1>(expert, row0, rows, ft);
+            else st.template tile_body<GA, GA>(expert, row0, rows, ft);
+        } else TileDispatch<S, GA - 1>::run(st, g, expert, row0, rows, ft);
     }
 };
 template <class S>
@@ -875,29 +903,6 @@ __global__ __launch_bounds__(CA::THREADS) void ffn_bf16_adaptive_kernel(const bf
         run_tiles_auto<CB, GATEUP, TILED>(lds, sb, tok, w0, w1, offsets, sorted_slot, out, N, K, Kdim, Fdim, n_ftiles, T);
     else
         run_tiles_auto<CA, GATEUP, TILED>(lds, sa, tok, w0, w1, offsets, sorted_slot, out, N, K, Kdim, Fdim, n_ftiles, T);
-}
-
-// Tiled weight layout.  A matrix W[F][Kd] (F, Kd multiples of 32) is stored as (F/32) x (Kd/32) units of 2 KiB,
-// unit (rb, kb) at index kb * (F/32) + rb, so that the row blocks of one k block follow each other: the
-// consecutive row blocks of a feature tile are then one contiguous run of 8-16 KiB per k chunk.  A
-// unit holds rows 32rb..32rb+31, columns 32kb..32kb+31 as 32 rows of 64 bytes, the four 16-byte pieces of
-// row r permuted as in the LDS ring (piece p at position p ^ ((r >> 2) & 3)): it is the LDS image of that
-// block, so the GEMM copies it with contiguous 1 KiB loads - which is what lets HBM stream at full rate
-// (row-major weights are fetched as 64- or 128-byte pieces 2*Kd bytes apart).
-// One thread per 16-byte piece of the output; `mats` matrices of F x Kd follow each other.
-__global__ __launch_bounds__(256) void pack_weights_kernel(const bf16_t *__restrict__ w, bf16_t *__restrict__ out, int F,
-                                                           int Kd, size_t pieces)
-{
-    const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= pieces) return;
-    const int pos = idx & 3, r = (idx >> 2) & 31;
-    const size_t unit = idx >> 7;
-    const int kbs = Kd / 32, units_per_mat = (F / 32) * kbs;
-    const size_t mat = unit / units_per_mat;
-    const int u = (int)(unit - mat * units_per_mat), rbs = F / 32, kb = u / rbs, rb = u - kb * rbs;
-    const int p = pos ^ ((r >> 2) & 3);
-    const bf16x8 v = *reinterpret_cast<const bf16x8 *>(w + (mat * F + rb * 32 + r) * Kd + kb * 32 + p * 8);
-    *reinterpret_cast<bf16x8 *>(out + idx * 8) = v;
 }
 
 }  // namespace zeda
