@@ -11,10 +11,10 @@
 //
 // Precision: the 32 products of a chunk are added as four sums of eight in the matrix unit and a tree over the four; the
 // chunk sums are added up with a compensated sum (the rounding errors of the additions are added up on the side), so the
-// error does not grow with the number of chunks.  Against 64 bits a layer ends 1.5e-7 (H = 256) and 1.7e-7 (H = 1024) off;
-// sums of sixteen per chunk end at 1.8e-7 and 2.0e-7, one running sum per lane over every 64th product at 1.6e-7 and 2.0e-7.
-// The running sum itself is the plain one: where it overflows or meets an infinity, the errors are no numbers and are
-// left out (total()).
+// error does not grow with the number of chunks; the slices' few sums are added in 64 bits and rounded once.  (Sums of
+// sixteen per chunk and a plain sum over the slices end farther from the 64-bit result than the sums over 64 lanes that
+// these kernels replaced.)  The running sum itself is the plain one: where it overflows or meets an infinity, the errors are no numbers and are
+// left out (error()).
 #pragma once
 #include "zeda_internal.h"
 
@@ -87,13 +87,15 @@ struct F32Tile {
         }
         fold(sum[NA - 1][NB - 1], err[NA - 1][NB - 1], c[(NA * NB - 1) & 1]);
     }
-    __device__ __forceinline__ f32x4 total(int a, int b) const
+    // the collected errors of a block's running sums, zero where they are no numbers
+    __device__ __forceinline__ f32x4 error(int a, int b) const
     {
         f32x4 v;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = fabsf(err[a][b][q]) < INFINITY ? sum[a][b][q] + err[a][b][q] : sum[a][b][q];
+        for (int q = 0; q < 4; ++q) v[q] = fabsf(err[a][b][q]) < INFINITY ? err[a][b][q] : 0.f;
         return v;
     }
+    __device__ __forceinline__ f32x4 total(int a, int b) const { return sum[a][b] + error(a, b); }
     // slice `slice` of `slices`: the 32-wide chunks slice, slice + slices, ..., starting at one that depends on rot (rows
     // are often a multiple of 4 KiB apart, which puts a chunk of every row on one L2 channel: workgroups that start at
     // different chunks spread over the channels)

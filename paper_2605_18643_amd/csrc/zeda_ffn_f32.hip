@@ -49,9 +49,9 @@ __device__ __forceinline__ int3 f32_locate(const int32_t *__restrict__ offsets, 
     return make_int3(__shfl(e, src), __shfl(row0, src), __shfl(rows, src));
 }
 
-// this wave's slice of the sums of the first LIVE token blocks, left in part[a * NB + b][lane]
+// this wave's slice of the sums of the first LIVE token blocks, left in part[a * NB + b][lane], their errors in err
 template <int NA, int NB, int LIVE>
-__device__ __forceinline__ void multiply_rows(f32x4 (*part)[64], const float *const (&pa)[NA], const float *const (&pb)[NB], int wave, int Kd)
+__device__ __forceinline__ void multiply_rows(f32x4 (*part)[64], f32x4 (*err)[64], const float *const (&pa)[NA], const float *const (&pb)[NB], int wave, int Kd)
 {
     const int lane = threadIdx.x & 63;
     const float *p[LIVE];
@@ -62,7 +62,10 @@ __device__ __forceinline__ void multiply_rows(f32x4 (*part)[64], const float *co
 #pragma unroll
     for (int a = 0; a < NA; ++a)
 #pragma unroll
-        for (int b = 0; b < LIVE; ++b) part[a * NB + b][lane] = t.total(a, b);
+        for (int b = 0; b < LIVE; ++b) {
+            part[a * NB + b][lane] = t.sum[a][b];
+            err[a * NB + b][lane] = t.error(a, b);
+        }
 }
 
 // GATEUP: tok = x[T,Kd], w0 = W_gate[N,F,Kd], w1 = W_up, out = act[S,F];  else tok = act[S,Kd], w0 = W_down[N,F,Kd],
@@ -75,7 +78,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void ffn_f32_kernel(const float *__
 {
     constexpr int NB = kF32NB;
     constexpr int NO = (GATEUP ? NA / 2 : NA) * NB;  // output blocks
-    __shared__ f32x4 s_part[kF32Waves][NA * NB][64];
+    __shared__ f32x4 s_part[kF32Waves][NA * NB][64], s_err[kF32Waves][NA * NB][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15;
     const int tile = blockIdx.x / n_ft, ft = blockIdx.x - tile * n_ft;
     const int3 loc = f32_locate(offsets, N, tile);
@@ -95,19 +98,24 @@ __global__ __launch_bounds__(kF32Threads, 2) void ffn_f32_kernel(const float *__
         pb[b] = tok + (size_t)(GATEUP ? min(max(sorted_slot[r] / K, 0), T - 1) : r) * Kd;  // a bad index must not fault
     }
     // only the blocks that hold rows are fetched and multiplied
-    if (rows > 16) multiply_rows<NA, NB, NB>(s_part[wave], pa, pb, wave, Kd);
-    else multiply_rows<NA, NB, 1>(s_part[wave], pa, pb, wave, Kd);
+    if (rows > 16) multiply_rows<NA, NB, NB>(s_part[wave], s_err[wave], pa, pb, wave, Kd);
+    else multiply_rows<NA, NB, 1>(s_part[wave], s_err[wave], pa, pb, wave, Kd);
     __syncthreads();
 
     // block (a, b): lane l holds features 4 (l / 16) .. + 3 of token l % 16
     for (int o = wave; o < NO; o += kF32Waves) {
         const int fb = o / NB, b = o - fb * NB, r = 16 * b + l16, f = f0 + 16 * fb + 4 * (lane >> 4);
         if (r >= rows || f >= F) continue;
-        auto total = [&](int blk) {
-            f32x4 v = s_part[0][blk][lane];
+        auto total = [&](int blk) {  // the waves' sums, in wave order, rounded once
+            f32x4 r;
 #pragma unroll
-            for (int w = 1; w < kF32Waves; ++w) v += s_part[w][blk][lane];
-            return v;
+            for (int k = 0; k < 4; ++k) {
+                double v = 0.0;
+#pragma unroll
+                for (int w = 0; w < kF32Waves; ++w) v += (double)s_part[w][blk][lane][k] + (double)s_err[w][blk][lane][k];
+                r[k] = (float)v;
+            }
+            return r;
         };
         f32x4 v;
         if (GATEUP) {

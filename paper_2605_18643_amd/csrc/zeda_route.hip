@@ -537,10 +537,10 @@ __global__ __launch_bounds__(kRouteF32Threads) void route_f32_kernel(const float
     }
     __syncthreads();
     for (int i = tid; i < kRouteF32Tokens * LD; i += kRouteF32Threads) {
-        float v = lg[i];
+        double v = lg[i];  // (rounded once)
 #pragma unroll
-        for (int q = 1; q < SLICES; ++q) v += lg[q * kRouteF32Tokens * LD + i];
-        lg[i] = v;
+        for (int q = 1; q < SLICES; ++q) v += (double)lg[q * kRouteF32Tokens * LD + i];
+        lg[i] = (float)v;
     }
     __syncthreads();
     if (logits_out) {  // statistics run: hand the logits (without the bias) to route_stats_kernel
