@@ -14,6 +14,7 @@ constexpr int kF32Threads = 256;
 constexpr int kF32Waves = kF32Threads / 64;
 constexpr int kF32Rows = 32;  // token rows per workgroup: two blocks of 16
 constexpr int kF32NB = kF32Rows / 16;
+constexpr int kF32GridTiles = 1 << 14;  // token tiles along grid x (at most 512 feature tiles of 256 threads each: 2^31 work items), more along y
 
 // (expert, first row, rows) of token tile `tile`, or rows = 0 past the last one: lane l holds experts 4l..4l+3
 __device__ __forceinline__ int3 f32_locate(const int32_t *__restrict__ offsets, int N, int tile)
@@ -80,7 +81,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void ffn_f32_kernel(const float *__
     constexpr int NO = (GATEUP ? NA / 2 : NA) * NB;  // output blocks
     __shared__ f32x4 s_part[kF32Waves][NA * NB][64], s_err[kF32Waves][NA * NB][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15;
-    const int tile = blockIdx.x / n_ft, ft = blockIdx.x - tile * n_ft;
+    const int tile_x = blockIdx.x / n_ft, ft = blockIdx.x - tile_x * n_ft, tile = blockIdx.y * kF32GridTiles + tile_x;
     const int3 loc = f32_locate(offsets, N, tile);
     const int rows = loc.z;
     if (rows == 0) return;
@@ -136,7 +137,8 @@ static int launch(const zeda_layer_desc *d, const float *tok, const float *w0, c
     const int Kd = GATEUP ? d->H : d->I, F = GATEUP ? d->I : d->H;
     const int n_ft = ceil_div(F, 16 * (GATEUP ? NA / 2 : NA));
     const int S = d->T * d->K, tiles = (S < d->N ? S : d->N) + S / kF32Rows;  // at most this many token tiles
-    ffn_f32_kernel<GATEUP, NA><<<(unsigned)tiles * n_ft, kF32Threads, 0, s>>>(tok, w0, w1, offsets, sorted_slot, out, d->N, d->K, Kd,
+    const dim3 grid((unsigned)(tiles < kF32GridTiles ? tiles : kF32GridTiles) * n_ft, ceil_div(tiles, kF32GridTiles));
+    ffn_f32_kernel<GATEUP, NA><<<grid, kF32Threads, 0, s>>>(tok, w0, w1, offsets, sorted_slot, out, d->N, d->K, Kd,
                                                                               F, n_ft, d->T);
     return last_launch_status();
 }

@@ -59,3 +59,26 @@ def test_f32_infinities_stay_infinite():
     others = torch.ones(w.T, dtype=torch.bool)
     others[row] = False
     assert torch.equal(y.cpu()[others], base["y_slot"][others])
+
+
+def test_f32_more_token_tiles_than_one_grid_row():
+    """More than 16384 tiles of 32 rows: the launch continues along the grid's second dimension.  Expert FFN alone, every
+    row against float64."""
+    N, H, I, T = 2, 4, 4, 540000
+    g = torch.Generator().manual_seed(11)
+    x = torch.randn(T, H, generator=g)
+    wg, wu = torch.randn(N, I, H, generator=g), torch.randn(N, I, H, generator=g)
+    wd = torch.randn(N, H, I, generator=g)
+    n0 = 270001
+    off = torch.tensor([0, n0, T], dtype=torch.int32)
+    slots = torch.arange(T, dtype=torch.int32)
+    d = zeda.make_desc(T, H, I, N, 0, 1, "f32")
+    y = torch.full((T, H), float("nan"), device="cuda")
+    ws = torch.empty(zeda.expert_ffn_workspace_bytes(d), dtype=torch.uint8, device="cuda")
+    zeda.zeda_expert_ffn(d, x.cuda(), wg.cuda(), wu.cuda(), wd.cuda(), off.cuda(), slots.cuda(), off[2:].cuda(), y, ws)
+    torch.cuda.synchronize()
+    for e, (a, b) in enumerate([(0, n0), (n0, T)]):
+        h = x[a:b].double()
+        ref = (torch.nn.functional.silu(h @ wg[e].double().t()) * (h @ wu[e].double().t())) @ wd[e].double().t()
+        got = y[a:b].cpu().double()
+        assert (got - ref).norm() <= 1e-5 * ref.norm() and (got - ref).abs().max() <= 1e-5 * ref.abs().max()
