@@ -265,11 +265,8 @@ __device__ __forceinline__ void select_block(const float *lg, int LD, int pstrid
     }
 }
 
-// floats from one block's row of the statistics tables to the next: rows start at 16 bytes
-__host__ __device__ constexpr int stats_ld(int NE) { return (NE + 3) & ~3; }
-
 // After select_block (and a barrier): what the workgroup's blocks of 16 tokens hand to the expert-sorted placement
-// and to the routing statistics.  cnt8[e][cnt_ld] bytes: slots of every block on expert e; p_part[block][stats_ld(NE)]: the
+// and to the routing statistics.  cnt8[e][cnt_ld] bytes: slots of every block on expert e; p_part[block][NE]: the
 // block's sum of every expert's routing probability, added in token order.
 template <int THREADS>
 __device__ __forceinline__ void publish_blocks(const int *s_cnt, const float *probs, int LDP, int ntok, int t0, int T, int NE,
@@ -284,7 +281,7 @@ __device__ __forceinline__ void publish_blocks(const int *s_cnt, const float *pr
             float ps = 0.f;
             const int nt = min(16, min(ntok, T - t0) - u * 16);
             for (int t = 0; t < nt; ++t) ps += probs[(u * 16 + t) * LDP + e];
-            p_part[(size_t)blk * stats_ld(NE) + e] = ps;
+            p_part[(size_t)blk * NE + e] = ps;
         }
     }
 }
@@ -334,7 +331,7 @@ template <int NB, int TB>
 __global__ __launch_bounds__(kRouteThreads) void route_bf16_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ wr,
                                                                    const float *__restrict__ bias, int T, int H, int N, int NE,
                                                                    int K, int gate_norm, int32_t *__restrict__ ids,
-                                                                   float *__restrict__ gates, float *__restrict__ partial,
+                                                                   float *__restrict__ gates, float *__restrict__ partial, int Tpad,
                                                                    uint8_t *__restrict__ cnt8, int cnt_ld,
                                                                    float *__restrict__ p_part)
 {
@@ -433,11 +430,11 @@ __global__ __launch_bounds__(kRouteThreads) void route_bf16_kernel(const bf16_t 
                 lg[(ks * C::TOK + u * 16 + l16) * C::LD + (grp + C::GROUPS * b) * 16 + 4 * kq + v] = acc[b][u][v];
     }
     if (partial) {
-        // this slice's sums (the tables added in order) go to partial[slice][token][expert]: route_select_kernel adds the
+        // this slice's sums (the tables added in order) go to partial[slice][token][expert], Tpad tokens: route_select_kernel adds the
         // slices in order and selects
         __syncthreads();
-        f32x4 *dst = reinterpret_cast<f32x4 *>(partial + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * (C::TOK * NB * 32));
-        for (int i = tid; i < C::TOK * NB * 8; i += kRouteThreads) {
+        f32x4 *dst = reinterpret_cast<f32x4 *>(partial + ((size_t)blockIdx.y * Tpad + t0) * (NB * 32));
+        for (int i = tid; i < min(C::TOK, Tpad - t0) * NB * 8; i += kRouteThreads) {
             const float *p = lg + (i / (NB * 8)) * C::LD + (i % (NB * 8)) * 4;
             f32x4 v;
 #pragma unroll
@@ -572,40 +569,44 @@ struct RoutePlan {
     int tb, slices;
 };
 
-// One round of workgroups at most (one per CU).  Among those the split for which a CU moves the least: the rows that a
-// projecting workgroup reads, the logits it writes, the slices' logits a selecting workgroup reads; the second kernel
-// counts as 450 KB.  160 experts, H = 2048, split against one kernel: 13 against 16 us for one token, 14.8 against 15.9
-// at 997, 20.4 against 18.4 at 4096 (four slices of 64-token blocks), 25.3 against 22.6 at 6000.)
+// bytes of one token's logits in the scratch
+static size_t route_row_bytes(const zeda_layer_desc *d) { return (size_t)ceil_div(d->N + d->Z, 32) * 32 * sizeof(float); }
+
+// Scratch for the slices' logits: room for eight slices of 32-token blocks, halved until blocks times slices are within 256
+// and the slices are whole 64-wide chunks.  Callers size workspaces once, for their largest batch, so this size is part of
+// the interface: route_plan takes splits that fit into it.
+size_t route_ws_bytes(const zeda_layer_desc *d)
+{
+    if (d->dtype != ZEDA_BF16) return 0;
+    const int blocks = ceil_div(d->T, 32);
+    size_t c = 1;
+    while (c < 8 && blocks * 2 * c <= 256 && d->H / 64 % (2 * c) == 0) c *= 2;
+    return c == 1 ? 0 : c * blocks * 32 * route_row_bytes(d);
+}
+
+// tokens whose logits the scratch holds: whole blocks of the selecting kernel
+static int route_tpad(const zeda_layer_desc *d) { return ceil_div(d->T, kSelectTokens) * kSelectTokens; }
+
+// One round of workgroups at most (one per CU), logits that fit into the scratch.  Among those the split for which a CU
+// moves the least: the rows that a projecting workgroup reads, the logits it writes, the slices' logits a selecting
+// workgroup reads; the second kernel counts as 450 KB.  160 experts, H = 2048, split against one kernel: 13 against 16 us
+// for one token, 14.8 against 15.9 at 997.
 static RoutePlan route_plan(const zeda_layer_desc *d, bool scratch)
 {
     const int64_t NE = d->N + d->Z;
+    const size_t room = scratch ? route_ws_bytes(d) / route_row_bytes(d) : 0;  // tokens times slices
     RoutePlan best = {4, 1};
     int64_t least = INT64_MAX;
     for (int tb = 1; tb <= 4; tb *= 2) {
         const int64_t tok = 16 * tb, blocks = (d->T + tok - 1) / tok, chunks = d->H / (tb == 1 ? 128 : 64);
         for (int c = 1; c <= 16; c *= 2) {
-            if (c > 1 && (!scratch || chunks % c != 0)) break;
+            if (c > 1 && (chunks % c != 0 || (size_t)c * route_tpad(d) > room)) break;
             if (blocks * c > 256 && !(c == 1 && tb == 4)) break;
             const int64_t cost = (NE + tok) * d->H * 2 / c + (c > 1 ? NE * 4 * tok + c * NE * 4 * 16 + 450000 : 0);
             if (cost < least) { least = cost; best = {tb, c}; }
         }
     }
     return best;
-}
-
-// Scratch: the slices' logits.  (Never less than the tables of an earlier split, whose size callers may rely on being
-// asked for: 32-token blocks, up to eight slices while blocks times slices stay within 256.)
-size_t route_ws_bytes(const zeda_layer_desc *d)
-{
-    if (d->dtype != ZEDA_BF16) return 0;
-    const size_t row = (size_t)ceil_div(d->N + d->Z, 32) * 32 * sizeof(float);
-    const int blocks = ceil_div(d->T, 32);
-    size_t c = 1;
-    while (c < 8 && blocks * 2 * c <= 256 && d->H / 64 % (2 * c) == 0) c *= 2;
-    const size_t floor_bytes = c == 1 ? 0 : c * blocks * 32 * row;
-    const RoutePlan p = route_plan(d, true);
-    const size_t need = p.slices == 1 ? 0 : (size_t)p.slices * ceil_div(d->T, 16 * p.tb) * (16 * p.tb) * row;
-    return need > floor_bytes ? need : floor_bytes;
 }
 
 // Optional outputs of a router launch (see publish_blocks, place_list); all NULL / 0 when not wanted.
@@ -630,9 +631,9 @@ static int launch_route_bf16(const zeda_layer_desc *d, const void *x, const void
             return ZEDA_EHIP;
         done[dev] = true;
     }
-    const int blocks = ceil_div(d->T, C::TOK), Tpad = blocks * C::TOK, NE = d->N + d->Z;
+    const int blocks = ceil_div(d->T, C::TOK), Tpad = route_tpad(d), NE = d->N + d->Z;
     route_bf16_kernel<NB, TB><<<dim3(blocks, slices), kRouteThreads, C::LDS_BYTES, s>>>(
-        (const bf16_t *)x, (const bf16_t *)wr, bias, d->T, d->H, d->N, NE, d->K, d->gate_norm, ids, gates, slices > 1 ? partial : nullptr,
+        (const bf16_t *)x, (const bf16_t *)wr, bias, d->T, d->H, d->N, NE, d->K, d->gate_norm, ids, gates, slices > 1 ? partial : nullptr, Tpad,
         ex.cnt8, ex.cnt_ld, ex.p_part);
     const dim3 sgrid(ceil_div(d->T, kSelectTokens));
 #define ZEDA_SELECT(NP) route_select_kernel<NB, NP><<<sgrid, kRouteThreads, 0, s>>>(partial, Tpad, bias, d->T, d->N, NE, d->K, d->gate_norm, ids, gates, ex.cnt8, ex.cnt_ld, ex.p_part, ex.place)
@@ -771,20 +772,20 @@ __global__ __launch_bounds__(kStatsThreads) void route_stats_kernel(const float 
         int fs = 0;
 #pragma unroll
         for (int r = 0; r < 16; ++r) { ps += s_p[r][tid]; fs += s_f[r][tid]; }
-        p_part[(size_t)blockIdx.x * stats_ld(NE) + tid] = ps;
-        f_part[(size_t)blockIdx.x * stats_ld(NE) + tid] = fs;
+        p_part[(size_t)blockIdx.x * NE + tid] = ps;
+        f_part[(size_t)blockIdx.x * NE + tid] = fs;
     }
 }
 
-// Final workgroup: adds the blocks up.  p_part [nblocks][ld] (ld a multiple of 4: a thread takes four experts with one
-// 16-byte load) and either f_part, int32 counts laid out alike, or cnt8[e][cnt_ld], the counts as bytes.  The threads of
+// Final workgroup: adds the blocks up.  p_part [nblocks][NE] and either f_part, int32 counts laid out alike, or
+// cnt8[e][cnt_ld], the counts as bytes.  A thread takes four experts, with one 16-byte load where rows are that aligned.  The threads of
 // an expert quad take every PARTS-th block, eight loads in flight, and their sums are added in a fixed order; the byte
 // counts are added as integers, so their order does not matter.  (One thread per expert walking all blocks spent 142 us
 // of latency on the 512 blocks of 8192 tokens.)
 constexpr int kStatsFinalThreads = 1024;
 
 __global__ __launch_bounds__(kStatsFinalThreads) void route_stats_final_kernel(const float *__restrict__ p_part,
-                                                                               const int32_t *__restrict__ f_part, int ld,
+                                                                               const int32_t *__restrict__ f_part,
                                                                                const uint8_t *__restrict__ cnt8, int cnt_ld,
                                                                                int nblocks, int T, int N, int NE, int K,
                                                                                float alpha, float w, float *__restrict__ f,
@@ -799,14 +800,25 @@ __global__ __launch_bounds__(kStatsFinalThreads) void route_stats_final_kernel(c
     if (part < parts) {
         f32x4 ps = {0.f, 0.f, 0.f, 0.f};
         int fs[4] = {0, 0, 0, 0};
-        const size_t col = (size_t)quad * 4;
+        const int col = quad * 4;
+        if (NE % 4 == 0) {
 #pragma unroll 8
-        for (int b = part; b < nblocks; b += parts) {
-            ps += *reinterpret_cast<const f32x4 *>(p_part + (size_t)b * ld + col);
-            if (f_part) {
-                const int4 c = *reinterpret_cast<const int4 *>(f_part + (size_t)b * ld + col);
-                fs[0] += c.x; fs[1] += c.y; fs[2] += c.z; fs[3] += c.w;
+            for (int b = part; b < nblocks; b += parts) {
+                ps += *reinterpret_cast<const f32x4 *>(p_part + (size_t)b * NE + col);
+                if (f_part) {
+                    const int4 c = *reinterpret_cast<const int4 *>(f_part + (size_t)b * NE + col);
+                    fs[0] += c.x; fs[1] += c.y; fs[2] += c.z; fs[3] += c.w;
+                }
             }
+        } else {
+#pragma unroll 8
+            for (int b = part; b < nblocks; b += parts)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const size_t at = (size_t)b * NE + min(col + q, NE - 1);  // (past NE: not used)
+                    ps[q] += p_part[at];
+                    if (f_part) fs[q] += f_part[at];
+                }
         }
         s_part[tid] = ps;
         if (f_part)
@@ -864,15 +876,15 @@ __global__ __launch_bounds__(kStatsFinalThreads) void route_stats_final_kernel(c
     }
 }
 
-// scratch: the logit tables, then the per-block sums
+// scratch: the logit tables, then the per-block sums (sizes are part of the interface, see route_ws_bytes)
 static size_t stats_logits_bytes(const zeda_layer_desc *d)
 {
-    const size_t Tpad = (size_t)ceil_div(d->T, kRouteF32Tokens) * kRouteF32Tokens;
+    const size_t Tpad = (size_t)ceil_div(d->T, 32) * 32;
     return align_up(Tpad * ceil_div(d->N + d->Z, 32) * 32 * sizeof(float), 256);
 }
 size_t routing_stats_ws_bytes(const zeda_layer_desc *d)
 {
-    const size_t NE = (size_t)stats_ld(d->N + d->Z);
+    const size_t NE = (size_t)(d->N + d->Z);
     if (d->dtype == ZEDA_BF16)  // split-k scratch of the router, per-block counts, per-block probability sums
         return align_up(route_ws_bytes(d), 256) + route_counts_bytes(d) + align_up((size_t)ceil_div(d->T, 16) * NE * 4, 256);
     const size_t nblk = (size_t)ceil_div(d->T, kStatsTokens);
@@ -890,7 +902,7 @@ int launch_routing_stats(const zeda_layer_desc *d, const void *x, const void *wr
         const RouteExtras ex = {cnt8, route_counts_ld(d), p_part, {}};
         const int rc = launch_route_bf16_any(d, x, wr, bias, nullptr, nullptr, partial, ex, s);
         if (rc != ZEDA_OK) return rc;
-        route_stats_final_kernel<<<1, kStatsFinalThreads, 0, s>>>(p_part, nullptr, stats_ld(NE), cnt8, ex.cnt_ld, ceil_div(d->T, 16), d->T, d->N, NE,
+        route_stats_final_kernel<<<1, kStatsFinalThreads, 0, s>>>(p_part, nullptr, cnt8, ex.cnt_ld, ceil_div(d->T, 16), d->T, d->N, NE,
                                                              d->K, alpha, w, f, P, summary);
         return last_launch_status();
     }
@@ -898,7 +910,7 @@ int launch_routing_stats(const zeda_layer_desc *d, const void *x, const void *wr
     const int Tpad = ceil_div(d->T, kRouteF32Tokens) * kRouteF32Tokens, nblk = ceil_div(d->T, kStatsTokens);
     float *logits = (float *)ws;
     float *p_part = (float *)((char *)ws + stats_logits_bytes(d));
-    int32_t *f_part = (int32_t *)((char *)p_part + align_up((size_t)nblk * stats_ld(NE) * 4, 256));
+    int32_t *f_part = (int32_t *)((char *)p_part + align_up((size_t)nblk * NE * 4, 256));
     if (launch_route_f32(d, x, wr, bias, nullptr, nullptr, logits, LDg, s) != ZEDA_OK) return ZEDA_EHIP;
 #define ZEDA_STATS(NC) route_stats_kernel<NC><<<nblk, kStatsThreads, 0, s>>>(logits, 1, Tpad, LDg, bias, d->T, NE, d->K, p_part, f_part)
     switch (ceil_div(NE, 16)) {
@@ -911,7 +923,7 @@ int launch_routing_stats(const zeda_layer_desc *d, const void *x, const void *wr
     }
 #undef ZEDA_STATS
     if (hipGetLastError() != hipSuccess) return ZEDA_EHIP;
-    route_stats_final_kernel<<<1, kStatsFinalThreads, 0, s>>>(p_part, f_part, stats_ld(NE), nullptr, 0, nblk, d->T, d->N, NE, d->K, alpha, w, f, P,
+    route_stats_final_kernel<<<1, kStatsFinalThreads, 0, s>>>(p_part, f_part, nullptr, 0, nblk, d->T, d->N, NE, d->K, alpha, w, f, P,
                                                          summary);
     return last_launch_status();
 }

@@ -184,3 +184,40 @@ def test_binding_raises_with_the_status_name():
     with pytest.raises(zeda.ZedaError) as ei:
         zeda.workspace_layout(d)
     assert ei.value.status == zeda.ZEDA_EINVAL and "ZEDA_EINVAL" in str(ei.value)
+
+
+def _up(v, a=256):
+    return (v + a - 1) // a * a
+
+
+def _route_scratch(T, H, NE):
+    """Room for eight slices of 32-token blocks of logits, halved until blocks times slices are within 256 and the slices
+    are whole 64-wide chunks; nothing where one slice is left."""
+    blocks, c = -(-T // 32), 1
+    while c < 8 and blocks * 2 * c <= 256 and (H // 64) % (2 * c) == 0:
+        c *= 2
+    return 0 if c == 1 else c * blocks * 32 * -(-NE // 32) * 32 * 4
+
+
+@pytest.mark.parametrize("N, Z, K, H, I", [(128, 64, 8, 2048, 768), (128, 32, 8, 2048, 768), (64, 32, 4, 2048, 1536), (200, 56, 4, 4096, 64),
+                                           (29, 4, 3, 1152, 448), (5, 1, 2, 384, 64), (250, 6, 16, 7168, 64)])
+def test_scratch_sizes_are_kept(N, Z, K, H, I):
+    # a program allocates its workspace once, for its largest batch, and keeps the size: what these queries return does not
+    # follow the splits that the kernels choose
+    NE = N + Z
+    for T in [1, 2, 15, 16, 17, 31, 32, 33, 63, 65, 500, 512, 513, 997, 1024, 1025, 1923, 1984, 2048, 2049, 3000, 4095, 4096, 4097, 8192, 8193, 20000]:
+        d = _desc(T=T, H=H, I=I, N=N, Z=Z, K=K)
+        route, blocks = _route_scratch(T, H, NE), -(-T // 16)
+        assert zeda.route_workspace_bytes(d) == route
+        L = zeda.workspace_layout(d)
+        assert L.total - L.route_ws == _up(max(route, 1)) and zeda.workspace_bytes(d) == L.total
+        stats = int(zeda.lib().zeda_routing_stats_workspace_bytes(ctypes.byref(d)))
+        assert stats == _up(route) + _up(NE * _up(blocks, 16)) + _up(blocks * NE * 4)
+        df = _desc(T=T, H=H, I=I, N=N, Z=Z, K=K, dtype="f32")
+        assert zeda.route_workspace_bytes(df) == 0
+        stats = int(zeda.lib().zeda_routing_stats_workspace_bytes(ctypes.byref(df)))
+        assert stats == _up(-(-T // 32) * 32 * -(-NE // 32) * 32 * 4) + 2 * _up(-(-T // 64) * NE * 4)
+    # the buffer of a batch of 2049 tokens serves the batches below it that it served before
+    if (N, Z, H) == (128, 64, 2048):
+        assert all(zeda.workspace_bytes(_desc(T=T, H=H, I=I, N=N, Z=Z, K=K)) <= zeda.workspace_bytes(_desc(T=2049, H=H, I=I, N=N, Z=Z, K=K))
+                   for T in range(1025, 1985))
