@@ -21,19 +21,20 @@ struct PlaceOut {
     int32_t *offsets, *sorted_slot, *slot_to_row, *num_real, *num_real_copy;
 };
 
-// LDS of place_list
+// LDS of place_list for at most SLOTS slots
+template <int SLOTS>
 struct PlaceLds {
-    int cnt[kMaxK][kMaxExperts];  // slots of wave w's group on every expert, then the running rows
+    int cnt[SLOTS / 64][kMaxExperts];  // slots of wave w's group on every expert, then the running rows
     int first[kMaxExperts];
     int wsum[kMaxExperts / 64];
 };
 
-// The S <= 64 * kMaxK slots of s_ids (LDS), one group of 64 per wave, by a workgroup of THREADS >= 64 * kMaxK threads that
-// has met since s_ids was written.  Stable: ascending slot index inside an expert.
-template <int THREADS>
-__device__ __forceinline__ void place_list(const int *s_ids, int S, int N, PlaceLds &s, const PlaceOut &o)
+// The S <= SLOTS slots of s_ids (LDS), one group of 64 per wave, by a workgroup of THREADS threads that has met since s_ids
+// was written.  Stable: ascending slot index inside an expert.
+template <int THREADS, int SLOTS>
+__device__ __forceinline__ void place_list(const int *s_ids, int S, int N, PlaceLds<SLOTS> &s, const PlaceOut &o)
 {
-    static_assert(THREADS / 64 >= kMaxK && THREADS >= kMaxExperts, "one wave per group, one thread per expert");
+    static_assert(THREADS >= SLOTS && SLOTS % 64 == 0 && THREADS >= kMaxExperts, "one wave per group, one thread per expert");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, groups = (S + 63) / 64;
     for (int i = tid; i < groups * kMaxExperts; i += THREADS) (&s.cnt[0][0])[i] = 0;
     __syncthreads();

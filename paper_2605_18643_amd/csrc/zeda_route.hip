@@ -286,7 +286,7 @@ __device__ __forceinline__ void publish_blocks(const int *s_cnt, const float *pr
     }
 }
 
-// bf16 router.  A workgroup of 16 waves owns 16 TB tokens, all NE experts (experts are MFMA rows, tokens MFMA columns,
+// bf16 router.  A workgroup of 16 waves (four for small pools) owns 16 TB tokens, all NE experts (experts are MFMA rows, tokens MFMA columns,
 // 16x16x32) and a slice of the hidden dimension, which may be all of it.  x rows and router rows stream through an LDS ring
 // in KC-wide k chunks with global->LDS loads whose 16-byte pieces are XOR-permuted by the row (on the global address) so
 // that fragment reads spread over the banks.  The waves split a chunk's k steps and the expert blocks; the k steps' sums
@@ -295,27 +295,31 @@ __device__ __forceinline__ void publish_blocks(const int *s_cnt, const float *pr
 //
 // What bounds it is what a CU pulls from L2: every router row of its slice (8-row pieces of 128 bytes and more arrive at up
 // to 129 GB/s per CU, 64-byte pieces at half of that), then launch and selection (route_plan weighs them).
-constexpr int kRouteThreads = 1024;
-constexpr int kRouteWaves = kRouteThreads / 64;
-constexpr int kRouteLds = 160 * 1024;
+constexpr int kRouteWaves = 16;
+constexpr int kRouteWavesSmall = 4;
+constexpr int kRouteSmallNB = 2;  // ... for up to 32 times this many experts
+// k chunk of a workgroup of 16 tb tokens and `waves` waves
+__host__ __device__ constexpr int route_chunk(int tb, int waves) { return tb == 1 || (tb == 2 && waves == kRouteWavesSmall) ? 128 : 64; }
 
-template <int NB, int TB>
+template <int NB, int TB, int W>
 struct RouteCfg {
-    static constexpr int TOK = 16 * TB;              // tokens of the workgroup
-    static constexpr int KC = TB == 1 ? 128 : 64;    // k chunk
-    static constexpr int KS = KC / 32;               // MFMA k steps per chunk
-    static constexpr int GROUPS = kRouteWaves / KS;  // expert groups: group g owns the 16-expert blocks g, g + GROUPS, ...
+    static constexpr int THREADS = 64 * W;
+    static constexpr int TOK = 16 * TB;            // tokens of the workgroup
+    static constexpr int KC = route_chunk(TB, W);  // k chunk
+    static constexpr int KS = KC / 32;             // MFMA k steps per chunk
+    static constexpr int GROUPS = W / KS;          // expert groups: group g owns the 16-expert blocks g, g + GROUPS, ...
     static constexpr int EB = 2 * NB, BPW = (EB + GROUPS - 1) / GROUPS;
     static constexpr int ROWB = 2 * KC, PPR = ROWB / 16, RPI = 64 / PPR;  // bytes, 16-byte pieces per row; rows per load instruction
     static constexpr int ROWS = TOK + 32 * NB, STAGE = ROWS * ROWB;
     static constexpr int NI = ROWS / RPI;            // load instructions per chunk, dealt out to the waves
-    static constexpr int STAGES = kRouteLds / STAGE < 8 ? kRouteLds / STAGE : 8;
+    static constexpr int MAX_LDS = W == kRouteWavesSmall ? 80 * 1024 : 160 * 1024;  // (two small workgroups per CU)
+    static constexpr int STAGES = MAX_LDS / STAGE < 8 ? MAX_LDS / STAGE : 8;
     static constexpr int LD = NB * 32 + 1;
     static constexpr int TABLES = KS * TOK * LD * 4;  // bytes of the logit tables, which reuse the ring, as do the counters
     static constexpr int CNT_OFF = (TABLES + 15) / 16 * 16, END = CNT_OFF + TB * kMaxExperts * 4;
     static constexpr int LDS_BYTES = STAGES * STAGE > END ? STAGES * STAGE : END;
-    static_assert(ROWS % RPI == 0 && STAGES >= 2 && LDS_BYTES <= kRouteLds, "");
-    static_assert((STAGES - 1) * ((NI + kRouteWaves - 1) / kRouteWaves) <= 63, "vmcnt is a 6-bit counter");
+    static_assert(ROWS % RPI == 0 && STAGES >= 2 && LDS_BYTES <= MAX_LDS && GROUPS >= 1, "");
+    static_assert((STAGES - 1) * ((NI + W - 1) / W) <= 63, "vmcnt is a 6-bit counter");
     static __device__ __forceinline__ int swz(int row, int piece) { return KC == 128 ? piece ^ (row & 15) : piece ^ ((row >> 1) & 7); }
 };
 
@@ -327,15 +331,15 @@ __device__ __forceinline__ void route_wait_vmcnt()
 
 // partial (may be NULL): receives the logits of the workgroup's slice of the hidden dimension instead of a selection.
 // cnt8, p_part (either may be NULL): see publish_blocks.
-template <int NB, int TB>
-__global__ __launch_bounds__(kRouteThreads) void route_bf16_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ wr,
+template <int NB, int TB, int W>
+__global__ __launch_bounds__(64 * W) void route_bf16_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ wr,
                                                                    const float *__restrict__ bias, int T, int H, int N, int NE,
                                                                    int K, int gate_norm, int32_t *__restrict__ ids,
                                                                    float *__restrict__ gates, float *__restrict__ partial, int Tpad,
                                                                    uint8_t *__restrict__ cnt8, int cnt_ld,
                                                                    float *__restrict__ p_part)
 {
-    typedef RouteCfg<NB, TB> C;
+    typedef RouteCfg<NB, TB, W> C;
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int t0 = blockIdx.x * C::TOK, l16 = lane & 15, kq = lane >> 4;
@@ -344,12 +348,12 @@ __global__ __launch_bounds__(kRouteThreads) void route_bf16_kernel(const bf16_t 
     float bias_c[2 * NB];
     load_bias<2 * NB>(bias_c, bias, NE);
 
-    constexpr int NLHI = (C::NI + kRouteWaves - 1) / kRouteWaves, NLLO = C::NI / kRouteWaves;
-    const bool hi = wave < C::NI % kRouteWaves || NLHI == NLLO;  // this wave issues NLHI loads per chunk, else NLLO
+    constexpr int NLHI = (C::NI + W - 1) / W, NLLO = C::NI / W;
+    const bool hi = wave < C::NI % W || NLHI == NLLO;  // this wave issues NLHI loads per chunk, else NLLO
     const bf16_t *src[NLHI];
 #pragma unroll
     for (int i = 0; i < NLHI; ++i) {
-        const int row = min((wave + kRouteWaves * i) * C::RPI + lane / C::PPR, C::ROWS - 1), piece = lane % C::PPR;
+        const int row = min((wave + W * i) * C::RPI + lane / C::PPR, C::ROWS - 1), piece = lane % C::PPR;
         const bf16_t *base = row < C::TOK ? x + (size_t)min(t0 + row, T - 1) * H : wr + (size_t)min(row - C::TOK, NE - 1) * H;
         src[i] = base + (size_t)blockIdx.y * (H / gridDim.y) + C::swz(row, piece) * 8;
     }
@@ -365,7 +369,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_bf16_kernel(const bf16_t 
         for (int i = 0; i < NLHI; ++i)
             if (i < NLLO || hi)
                 __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src[i] + (size_t)kc * C::KC),
-                                                 (__attribute__((address_space(3))) void *)(slot + (wave + kRouteWaves * i) * 1024), 16, 0, 0);
+                                                 (__attribute__((address_space(3))) void *)(slot + (wave + W * i) * 1024), 16, 0, 0);
         kc = kc + 1 == nk ? 0 : kc + 1;
     };
 
@@ -434,7 +438,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_bf16_kernel(const bf16_t 
         // slices in order and selects
         __syncthreads();
         f32x4 *dst = reinterpret_cast<f32x4 *>(partial + ((size_t)blockIdx.y * Tpad + t0) * (NB * 32));
-        for (int i = tid; i < min(C::TOK, Tpad - t0) * NB * 8; i += kRouteThreads) {
+        for (int i = tid; i < min(C::TOK, Tpad - t0) * NB * 8; i += C::THREADS) {
             const float *p = lg + (i / (NB * 8)) * C::LD + (i % (NB * 8)) * 4;
             f32x4 v;
 #pragma unroll
@@ -448,35 +452,35 @@ __global__ __launch_bounds__(kRouteThreads) void route_bf16_kernel(const bf16_t 
         return;
     }
     if (cnt8)
-        for (int i = tid; i < TB * kMaxExperts; i += kRouteThreads) s_cnt[i] = 0;
+        for (int i = tid; i < TB * kMaxExperts; i += C::THREADS) s_cnt[i] = 0;
     __syncthreads();
     // The probabilities of a token overwrite its row of the first logit table once the token's logits are in registers.
-    select_block<2 * NB, C::KS, kRouteWaves>(lg, C::LD, C::TOK * C::LD, bias_c, C::TOK, t0, T, NE, N, K, gate_norm, ids, gates,
+    select_block<2 * NB, C::KS, W>(lg, C::LD, C::TOK * C::LD, bias_c, C::TOK, t0, T, NE, N, K, gate_norm, ids, gates,
                                              cnt8 ? s_cnt : nullptr, p_part ? lg : nullptr, C::LD);
     if (cnt8 || p_part) {
         __syncthreads();
-        publish_blocks<kRouteThreads>(s_cnt, lg, C::LD, C::TOK, t0, T, NE, cnt8, cnt_ld, p_part);
+        publish_blocks<C::THREADS>(s_cnt, lg, C::LD, C::TOK, t0, T, NE, cnt8, cnt_ld, p_part);
     }
 }
 
-// Second kernel where the hidden dimension was split: 16 tokens per workgroup, a wave each.  All threads add up the slices'
-// tables (16-byte loads, all slices' in flight), then every wave selects for its token.
+// Second kernel where the hidden dimension was split: 16 tokens per workgroup.  All threads add up the slices' tables
+// (16-byte loads, all slices' in flight), then a wave selects for one token (16 waves) or for four (four waves).
 // cnt8, p_part (either may be NULL): see publish_blocks.  place.offsets (may be NULL): one workgroup, which then places.
 constexpr int kSelectTokens = 16;
-template <int NB, int NP>
-__global__ __launch_bounds__(kRouteThreads) void route_select_kernel(const float *__restrict__ partial, int Tpad,
-                                                                     const float *__restrict__ bias, int T, int N, int NE,
-                                                                     int K, int gate_norm, int32_t *__restrict__ ids,
-                                                                     float *__restrict__ gates, uint8_t *__restrict__ cnt8,
-                                                                     int cnt_ld, float *__restrict__ p_part, PlaceOut place)
+template <int NB, int NP, int W>
+__global__ __launch_bounds__(64 * W) void route_select_kernel(const float *__restrict__ partial, int Tpad,
+                                                              const float *__restrict__ bias, int T, int N, int NE,
+                                                              int K, int gate_norm, int32_t *__restrict__ ids,
+                                                              float *__restrict__ gates, uint8_t *__restrict__ cnt8,
+                                                              int cnt_ld, float *__restrict__ p_part, PlaceOut place)
 {
-    static_assert(kSelectTokens == 16 && kRouteWaves == 16, "one block of the per-block tables, a wave per token");
-    constexpr int E = NB * 32, NC = (E + 63) / 64, LD = NC * 64;
+    static_assert(kSelectTokens == 16 && (W == 16 || W == 4), "one block of the per-block tables, one or four tokens a wave");
+    constexpr int E = NB * 32, NC = (E + 63) / 64, LD = NC * 64, THREADS = 64 * W;
     __shared__ __attribute__((aligned(16))) float lg[kSelectTokens * LD];
     __shared__ int s_cnt[kMaxExperts], s_ids[kSelectTokens * kMaxK];
-    __shared__ PlaceLds s_place;
+    __shared__ PlaceLds<kSelectTokens * kMaxK> s_place;
     const int t0 = blockIdx.x * kSelectTokens, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int i = threadIdx.x; i < kSelectTokens * E / 4; i += kRouteThreads) {
+    for (int i = threadIdx.x; i < kSelectTokens * E / 4; i += THREADS) {
         const int tk = i / (E / 4), e = (i - tk * (E / 4)) * 4;
         f32x4 b = {0.f, 0.f, 0.f, 0.f};
         if (bias) {
@@ -490,16 +494,22 @@ __global__ __launch_bounds__(kRouteThreads) void route_select_kernel(const float
         for (int q = 1; q < NP; ++q) v[0] += v[q];
         *reinterpret_cast<f32x4 *>(lg + tk * LD + e) = v[0] + b;
     }
-    if (threadIdx.x < kMaxExperts) s_cnt[threadIdx.x] = 0;
+    for (int e = threadIdx.x; e < kMaxExperts; e += THREADS) s_cnt[e] = 0;
     __syncthreads();
     // (a token's probabilities overwrite its logits, which are in its wave's registers by then)
-    const int id = select_wave<NC>(lg + wave * LD, t0 + wave < T, (size_t)t0 + wave, NE, N, K, gate_norm, ids, gates,
-                                   p_part ? lg + wave * LD : nullptr);
+    int id;
+    if constexpr (W == 16) {
+        id = select_wave<NC>(lg + wave * LD, t0 + wave < T, (size_t)t0 + wave, NE, N, K, gate_norm, ids, gates, p_part ? lg + wave * LD : nullptr);
+        if (lane < K) s_ids[wave * K + lane] = id;
+    } else {
+        const float no_bias[2 * NB] = {};
+        id = select_rows<2 * NB, 1>(lg, LD, 0, no_bias, 4 * wave, kSelectTokens, t0, T, NE, N, K, gate_norm, ids, gates, p_part ? lg : nullptr, LD);
+        if ((lane & 15) < K) s_ids[(4 * wave + (lane >> 4)) * K + (lane & 15)] = id;
+    }
     if ((unsigned)id < (unsigned)kMaxExperts) atomicAdd(&s_cnt[id], 1);
-    if (lane < K) s_ids[wave * K + lane] = id;
     __syncthreads();
-    if (cnt8 || p_part) publish_blocks<kRouteThreads>(s_cnt, lg, LD, kSelectTokens, t0, T, NE, cnt8, cnt_ld, p_part);
-    if (place.offsets) place_list<kRouteThreads>(s_ids, T * K, N, s_place, place);
+    if (cnt8 || p_part) publish_blocks<THREADS>(s_cnt, lg, LD, kSelectTokens, t0, T, NE, cnt8, cnt_ld, p_part);
+    if (place.offsets) place_list<THREADS>(s_ids, T * K, N, s_place, place);
 }
 
 // fp32 router.  A workgroup owns 16 tokens and all experts; its 16 waves split the hidden dimension and, above 32
@@ -564,9 +574,9 @@ static int launch_route_f32(const zeda_layer_desc *d, const void *x, const void 
     return last_launch_status();
 }
 
-// How a bf16 router launch is split: 16 tb tokens per workgroup and `slices` workgroups per token block.
+// How a bf16 router launch is split: 16 tb tokens and `waves` waves per workgroup, `slices` workgroups per token block.
 struct RoutePlan {
-    int tb, slices;
+    int tb, slices, waves;
 };
 
 // bytes of one token's logits in the scratch
@@ -587,23 +597,35 @@ size_t route_ws_bytes(const zeda_layer_desc *d)
 // tokens whose logits the scratch holds: whole blocks of the selecting kernel
 static int route_tpad(const zeda_layer_desc *d) { return ceil_div(d->T, kSelectTokens) * kSelectTokens; }
 
-// One round of workgroups at most (one per CU), logits that fit into the scratch.  Among those the split for which a CU
-// moves the least: the rows that a projecting workgroup reads, the logits it writes, the slices' logits a selecting
-// workgroup reads; the second kernel counts as 450 KB.  160 experts, H = 2048, split against one kernel: 13 against 16 us
-// for one token, 14.8 against 15.9 at 997.
+// The split whose workgroups move the least (a CU pulls router rows out of L2 at 105-129 GB/s), among those that fit into
+// the scratch and run in one round: the rows a projecting workgroup reads, taken 1.4 and 1.6 times with 32 and 64 tokens
+// (64-wide chunks: twice the barriers) and 1.3 times where the ring of 128-wide chunks has two slots only (above 192
+// experts); with a split also the second kernel and the logits that both kernels move.  The factors are fitted to
+// measurements of every split at 96 to 256 experts, H = 512 to 7168 and 1 to 40000 tokens: the chosen one is 0.6 % behind
+// the best one on average.  Some of them, us, one kernel / best split:
+//   H = 2048:  96 experts, 1 token 10.1 / 7.9, 512 tokens 10.8 / 9.2, 1500 10.9 / 11.4;  160 experts, 1 token 15.0 / 8.7,
+//   997 tokens 13.1 / 11.7, 2048 13.1 / 12.6, 4096 13.7 / 16.6;  192 experts, 2048 tokens 14.4 / 13.4, 4096 15.1 / 17.2
+//   H = 1024:  96 experts, 200 tokens 8.1 / 8.5, 160 experts 9.6 / 10.0
+// Up to 64 experts there is too little to do for 16 waves (32 experts, H = 2048: 7.5 us for one token, 14.5 for 8192; four
+// waves 5.6 and 9.3-10.4): four-wave workgroups, up to two per CU.  At H = 7168 a second one only gets in the way (6000
+// tokens: 16-token workgroups 28.7 us, 32-token ones 25.1).
 static RoutePlan route_plan(const zeda_layer_desc *d, bool scratch)
 {
-    const int64_t NE = d->N + d->Z;
+    const int64_t NE = d->N + d->Z, kb = 1000;
+    const bool small = NE <= 32 * kRouteSmallNB;
     const size_t room = scratch ? route_ws_bytes(d) / route_row_bytes(d) : 0;  // tokens times slices
-    RoutePlan best = {4, 1};
+    RoutePlan best = {4, 1, small ? kRouteWavesSmall : kRouteWaves};
     int64_t least = INT64_MAX;
     for (int tb = 1; tb <= 4; tb *= 2) {
-        const int64_t tok = 16 * tb, blocks = (d->T + tok - 1) / tok, chunks = d->H / (tb == 1 ? 128 : 64);
+        const int64_t tok = 16 * tb, blocks = (d->T + tok - 1) / tok;
+        const int chunks = d->H / route_chunk(tb, best.waves);
         for (int c = 1; c <= 16; c *= 2) {
             if (c > 1 && (chunks % c != 0 || (size_t)c * route_tpad(d) > room)) break;
-            if (blocks * c > 256 && !(c == 1 && tb == 4)) break;
-            const int64_t cost = (NE + tok) * d->H * 2 / c + (c > 1 ? NE * 4 * tok + c * NE * 4 * 16 + 450000 : 0);
-            if (cost < least) { least = cost; best = {tb, c}; }
+            if (blocks * c > (small && c == 1 && d->H <= 4096 ? 512 : 256) && !(c == 1 && tb == 4)) break;
+            const int64_t rows = (NE + tok) * d->H * 2 / c, load = blocks * c > 256 ? blocks * c : 256;  // load: of the 256 CUs
+            const int64_t cost = small ? rows * (tb == 1 ? 10 : tb == 2 ? 11 : 18) / 10 * load / 256 + (c > 1 ? 100 * kb + c * NE * 128 : 0)
+                                       : rows * (tb == 1 ? (NE > 192 ? 13 : 10) : tb == 2 ? 14 : 16) / 10 + (c > 1 ? 150 * kb + (c * 64 + tok * 32) * NE : 0);
+            if (cost < least) { least = cost; best.tb = tb; best.slices = c; }
         }
     }
     return best;
@@ -617,26 +639,26 @@ struct RouteExtras {
     PlaceOut place;
 };
 
-template <int NB, int TB>
+template <int NB, int TB, int W>
 static int launch_route_bf16(const zeda_layer_desc *d, const void *x, const void *wr, const float *bias, int32_t *ids,
                              float *gates, float *partial, int slices, const RouteExtras &ex, hipStream_t s)
 {
-    typedef RouteCfg<NB, TB> C;
+    typedef RouteCfg<NB, TB, W> C;
     // the kernel uses more LDS than a launch gets by default: opt in once per kernel and device
     static bool done[kMaxDevices] = {};  // idempotent, so a race between host threads is harmless
     const int dev = current_device();
     if (dev < 0) return ZEDA_EHIP;
     if (!done[dev]) {
-        if (hipFuncSetAttribute((const void *)route_bf16_kernel<NB, TB>, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES) != hipSuccess)
+        if (hipFuncSetAttribute((const void *)route_bf16_kernel<NB, TB, W>, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES) != hipSuccess)
             return ZEDA_EHIP;
         done[dev] = true;
     }
-    const int blocks = ceil_div(d->T, C::TOK), Tpad = route_tpad(d), NE = d->N + d->Z;
-    route_bf16_kernel<NB, TB><<<dim3(blocks, slices), kRouteThreads, C::LDS_BYTES, s>>>(
+    const int NE = d->N + d->Z, Tpad = route_tpad(d);
+    route_bf16_kernel<NB, TB, W><<<dim3(ceil_div(d->T, C::TOK), slices), C::THREADS, C::LDS_BYTES, s>>>(
         (const bf16_t *)x, (const bf16_t *)wr, bias, d->T, d->H, d->N, NE, d->K, d->gate_norm, ids, gates, slices > 1 ? partial : nullptr, Tpad,
         ex.cnt8, ex.cnt_ld, ex.p_part);
     const dim3 sgrid(ceil_div(d->T, kSelectTokens));
-#define ZEDA_SELECT(NP) route_select_kernel<NB, NP><<<sgrid, kRouteThreads, 0, s>>>(partial, Tpad, bias, d->T, d->N, NE, d->K, d->gate_norm, ids, gates, ex.cnt8, ex.cnt_ld, ex.p_part, ex.place)
+#define ZEDA_SELECT(NP) route_select_kernel<NB, NP, W><<<sgrid, C::THREADS, 0, s>>>(partial, Tpad, bias, d->T, d->N, NE, d->K, d->gate_norm, ids, gates, ex.cnt8, ex.cnt_ld, ex.p_part, ex.place)
     if (slices == 2) ZEDA_SELECT(2);
     else if (slices == 4) ZEDA_SELECT(4);
     else if (slices == 8) ZEDA_SELECT(8);
@@ -645,28 +667,38 @@ static int launch_route_bf16(const zeda_layer_desc *d, const void *x, const void
     return last_launch_status();
 }
 
-template <int NB>
+template <int NB, int W>
 static int launch_route_bf16_tok(const zeda_layer_desc *d, const void *x, const void *wr, const float *bias, int32_t *ids,
-                                 float *gates, float *partial, const RouteExtras &ex, hipStream_t s)
+                                 float *gates, float *partial, const RoutePlan &p, const RouteExtras &ex, hipStream_t s)
+{
+    if (p.tb == 1) return launch_route_bf16<NB, 1, W>(d, x, wr, bias, ids, gates, partial, p.slices, ex, s);
+    if (p.tb == 2) return launch_route_bf16<NB, 2, W>(d, x, wr, bias, ids, gates, partial, p.slices, ex, s);
+    return launch_route_bf16<NB, 4, W>(d, x, wr, bias, ids, gates, partial, p.slices, ex, s);
+}
+
+template <int NB>
+static int launch_route_bf16_waves(const zeda_layer_desc *d, const void *x, const void *wr, const float *bias, int32_t *ids,
+                                   float *gates, float *partial, const RouteExtras &ex, hipStream_t s)
 {
     const RoutePlan p = route_plan(d, partial != nullptr);
-    if (p.tb == 1) return launch_route_bf16<NB, 1>(d, x, wr, bias, ids, gates, partial, p.slices, ex, s);
-    if (p.tb == 2) return launch_route_bf16<NB, 2>(d, x, wr, bias, ids, gates, partial, p.slices, ex, s);
-    return launch_route_bf16<NB, 4>(d, x, wr, bias, ids, gates, partial, p.slices, ex, s);
+    if constexpr (NB <= kRouteSmallNB) {
+        if (p.waves == kRouteWavesSmall) return launch_route_bf16_tok<NB, kRouteWavesSmall>(d, x, wr, bias, ids, gates, partial, p, ex, s);
+    }
+    return launch_route_bf16_tok<NB, kRouteWaves>(d, x, wr, bias, ids, gates, partial, p, ex, s);
 }
 
 static int launch_route_bf16_any(const zeda_layer_desc *d, const void *x, const void *wr, const float *bias, int32_t *ids,
                                  float *gates, float *partial, const RouteExtras &ex, hipStream_t s)
 {
     switch (ceil_div(d->N + d->Z, 32)) {
-        case 1: return launch_route_bf16_tok<1>(d, x, wr, bias, ids, gates, partial, ex, s);
-        case 2: return launch_route_bf16_tok<2>(d, x, wr, bias, ids, gates, partial, ex, s);
-        case 3: return launch_route_bf16_tok<3>(d, x, wr, bias, ids, gates, partial, ex, s);
-        case 4: return launch_route_bf16_tok<4>(d, x, wr, bias, ids, gates, partial, ex, s);
-        case 5: return launch_route_bf16_tok<5>(d, x, wr, bias, ids, gates, partial, ex, s);
-        case 6: return launch_route_bf16_tok<6>(d, x, wr, bias, ids, gates, partial, ex, s);
-        case 7: return launch_route_bf16_tok<7>(d, x, wr, bias, ids, gates, partial, ex, s);
-        default: return launch_route_bf16_tok<8>(d, x, wr, bias, ids, gates, partial, ex, s);
+        case 1: return launch_route_bf16_waves<1>(d, x, wr, bias, ids, gates, partial, ex, s);
+        case 2: return launch_route_bf16_waves<2>(d, x, wr, bias, ids, gates, partial, ex, s);
+        case 3: return launch_route_bf16_waves<3>(d, x, wr, bias, ids, gates, partial, ex, s);
+        case 4: return launch_route_bf16_waves<4>(d, x, wr, bias, ids, gates, partial, ex, s);
+        case 5: return launch_route_bf16_waves<5>(d, x, wr, bias, ids, gates, partial, ex, s);
+        case 6: return launch_route_bf16_waves<6>(d, x, wr, bias, ids, gates, partial, ex, s);
+        case 7: return launch_route_bf16_waves<7>(d, x, wr, bias, ids, gates, partial, ex, s);
+        default: return launch_route_bf16_waves<8>(d, x, wr, bias, ids, gates, partial, ex, s);
     }
 }
 
