@@ -43,7 +43,7 @@ template <int G_, int FB_, int WF_, int NSW_, int NST_, int KC_, int TKC_ = KC_>
 struct TileCfg {
     static constexpr int G = G_, FB = FB_, WF = WF_, NSW = NSW_, NST = NST_, KC = KC_, TKC = TKC_;
     static constexpr bool PAIR = TKC != KC;
-    static constexpr bool ROT = 64 * G_ <= 256;  // may start items at k chunks of their own (wider tiles are for many rows)
+    static constexpr bool ROT = G_ == 4;          // has a variant that starts items at k chunks of their own (see run_tiles_auto)
     static constexpr int WT = 2;                  // wave rows: wave row wt owns token blocks wt, wt+2, ...
     static constexpr int BT = 64 * G;             // tokens per tile
     static constexpr int BF = 32 * FB * WF;       // weight rows per tile (gate and up rows both count)
@@ -184,8 +184,8 @@ struct TileScan {
     }
 };
 
-// WNT: fetch the weights with the non-temporal hint (see run_tiles_auto).
-template <class C, bool GATEUP, bool TILED, bool WNT>
+// WNT: fetch the weights with the non-temporal hint.  ROT: start an item at a k chunk of its own (see run_tiles_auto).
+template <class C, bool GATEUP, bool TILED, bool WNT, bool ROT>
 struct Stream {
     static constexpr int FB = C::FB, WF = C::WF, BT = C::BT, BF = C::BF, NSW = C::NSW, NST = C::NST, NW = C::NW,
                          NWW = C::NWW, NWT = C::NWT, WST = C::WST, TST = C::TST, KC = C::KC, KS = C::KS, ROWB = C::ROWB,
@@ -199,7 +199,6 @@ struct Stream {
     const bf16_t *tok, *w0, *w1;
     bf16_t *out;
     int Kdim, Fdim, nk;
-    bool rotate;  // start an item at a k chunk of its own (see run_tiles_auto)
     // LDS
     unsigned char *wring, *tring, *stg;
     uint32_t wring_a, tring_a;  // LDS addresses of the two rings
@@ -252,7 +251,7 @@ struct Stream {
         int ln = lane;
         asm volatile("" : "+v"(ln));  // (recomputed per item rather than kept live)
         if constexpr (C::PAIR) {
-            krot = C::ROT && rotate ? (int)((unsigned)(expert * 5 + ft * 3) % (unsigned)(Kdim / 64)) : 0;
+            krot = ROT ? (int)((unsigned)(expert * 5 + ft * 3) % (unsigned)(Kdim / 64)) : 0;
             koff = (size_t)krot * 64;
             koff_w = (size_t)krot * 2 * kstep;
 #pragma unroll
@@ -270,8 +269,8 @@ struct Stream {
                 toff[i] = (srow[i] * (uint32_t)Kdim + swz<TKC>((wave + NWT * i) * TRPI + ln / TPPR, ln % TPPR) * 8) * 2;
             return;
         } else {
-        // first chunk of the item (in units of 64 k, the same for both weight layouts); see run_tiles_auto for rotate
-        krot = C::ROT && rotate ? (int)((unsigned)(expert * 5 + ft * 3) % (unsigned)(Kdim / 64)) * (C::PAIR && !wrole ? 1 : 64 / KC) : 0;
+        // first chunk of the item (in units of 64 k, the same for both weight layouts)
+        krot = ROT ? (int)((unsigned)(expert * 5 + ft * 3) % (unsigned)(Kdim / 64)) * (64 / KC) : 0;
         koff = (size_t)krot * kstep;
         if (wrole) {
             const int piece = ln % PPR, rsub = ln / PPR;
@@ -352,7 +351,7 @@ struct Stream {
     {
         ++ikc;
         koff += kstep;
-        if (C::ROT && ikc + krot == nki) koff = 0;
+        if (ROT && ikc + krot == nki) koff = 0;
         const bool wrap = ++islot == (NSW == NST ? NSW : (wrole ? NSW : NST));
         doff = wrap ? 0 : doff + (WST == TST ? WST : (wrole ? WST : TST));
         islot = wrap ? 0 : islot;
@@ -392,7 +391,7 @@ struct Stream {
         ++ikc;
         koff += TKC;
         koff_w += 2 * kstep;
-        if (C::ROT && ikc + krot == nki) { koff = 0; koff_w = 0; }
+        if (ROT && ikc + krot == nki) { koff = 0; koff_w = 0; }
         wdst = wdst - wring_a >= 2 * WST ? wdst - 2 * WST : wdst + 2 * WST;
         tdst = tdst - tring_a >= TST ? tdst - TST : tdst + TST;
     }
@@ -760,12 +759,12 @@ struct TileDispatch<S, 0> {
 // DOWN:   tok = act[S,Kdim], w0 = W_down[N,Fdim,Kdim], out = y_slot[S,Fdim]        (Fdim = H, Kdim = I).
 // Kdim is a multiple of KC; Fdim a multiple of the feature tile (BF/2 for GATEUP, BF for DOWN).
 // TILED: the weights are in the layout pack_weights_kernel writes.  The grid is a multiple of 8 workgroups.
-template <class C, bool GATEUP, bool TILED, bool WNT>
+template <class C, bool GATEUP, bool TILED, bool WNT, bool ROT>
 __device__ __forceinline__ void run_tiles(unsigned char *lds, const TileScan<C> &scan0, const bf16_t *__restrict__ tok,
                                           const bf16_t *__restrict__ w0,
                                           const bf16_t *__restrict__ w1, const int32_t *__restrict__ offsets,
                                           const int32_t *__restrict__ sorted_slot, bf16_t *__restrict__ out, int N, int K,
-                                          int Kdim, int Fdim, int n_ftiles, int T, bool rotate)
+                                          int Kdim, int Fdim, int n_ftiles, int T)
 {
     static_assert(!GATEUP || C::FB % 2 == 0, "gate and up blocks come in pairs");
     int *s_tok = reinterpret_cast<int *>(lds + C::TOK_OFF);
@@ -803,9 +802,9 @@ __device__ __forceinline__ void run_tiles(unsigned char *lds, const TileScan<C> 
         }
         __syncthreads();
 
-        Stream<C, GATEUP, TILED, WNT> st;
+        Stream<C, GATEUP, TILED, WNT, ROT> st;
         st.tok = tok; st.w0 = w0; st.w1 = w1; st.out = out;
-        st.Kdim = Kdim; st.Fdim = Fdim; st.nk = Kdim / C::KC; st.rotate = __builtin_amdgcn_readfirstlane((int)rotate) != 0;
+        st.Kdim = Kdim; st.Fdim = Fdim; st.nk = Kdim / C::KC;
         st.wring = lds; st.tring = lds + C::TRING_OFF; st.stg = lds + C::STG_OFF + wave * 2048; st.s_tok = s_tok; st.s_loc = s_loc;
         st.lane = lane; st.wave = wave; st.wt = wave / C::WF; st.wf = wave % C::WF; st.col = lane & 31; st.half = lane >> 5;
         st.foff_t = (st.wt * 32 + st.col) * C::TROWB + swz<C::TKC>(st.col, st.half) * 16;
@@ -831,7 +830,7 @@ __device__ __forceinline__ void run_tiles(unsigned char *lds, const TileScan<C> 
 
         for (int q = 0; q < nq; ++q) {
             const int4 loc = st.read_loc(q);
-            TileDispatch<Stream<C, GATEUP, TILED, WNT>, C::G>::run(st, (loc.z + 63) >> 6, loc.x, loc.y, loc.z, loc.w);
+            TileDispatch<Stream<C, GATEUP, TILED, WNT, ROT>, C::G>::run(st, (loc.z + 63) >> 6, loc.x, loc.y, loc.z, loc.w);
         }
     }
 }
@@ -842,13 +841,14 @@ __device__ __forceinline__ void run_tiles(unsigned char *lds, const TileScan<C> 
 // expert -4 %, at 3 rows -10 %; at 460 rows per expert the hint costs 2 % instead).  Decided once per launch from
 // the expert loads; the cache-policy field of the load is an immediate, so the two cases are two instantiations.
 //
-// Where the weights are what the kernel waits for, an item also starts at a k chunk that depends on its expert and feature
-// tile: row-major rows are often a multiple of 4 KiB apart, so that one chunk of every row sits on a few memory channels,
-// and workgroups that all start at chunk 0 queue there (4096 tokens, N=64, I=1536, row-major: gate/up 199 -> 186 us, down
-// 110 -> 101; tiled, N=128, I=768: gate/up 172 -> 168).  Not with many rows per expert, where the token rows that the
-// feature tiles of an item share would be fetched at different times (460 rows: 393 -> 404 us), nor with so few that the
-// weights' own order decides (31 rows, tiled: 132 -> 135 us).  The rule looks at nothing but the mean load, so that both
-// weight layouts add in the same order.
+// There, from 64 to 191 rows per expert, an item also starts at a k chunk that depends on its expert and feature tile:
+// row-major rows are often a multiple of 4 KiB apart, so that one chunk of every row sits on a few memory channels, and
+// workgroups that all start at chunk 0 queue there (expert FFN, row-major, even loads: N=64, I=1408, 140 rows 301 -> 274 us,
+// N=64, I=1536, 125 rows 305 -> 285; tiled +-1 %).  Loads of several tiles per expert gain nothing from it (Zipf loads,
+// N=64, I=1536, row-major: 0 to +3 %), and the code for it costs kernels that do not use it 3-5 % (N=16, I=256, H=512, 500
+// rows: 31 -> 32.5 us; 2-5 % of the large prefills), so it is an instantiation of its own.  The rule looks at the 256-row
+// tiles and the mean load only, both the same for both weight layouts, and experts of one tile each leave nothing to the
+// 320-row geometry: both layouts add in the same order.
 template <class C, bool GATEUP, bool TILED>
 __device__ __forceinline__ void run_tiles_auto(unsigned char *lds, const TileScan<C> &scan0, const bf16_t *__restrict__ tok,
                                                const bf16_t *__restrict__ w0, const bf16_t *__restrict__ w1,
@@ -858,11 +858,15 @@ __device__ __forceinline__ void run_tiles_auto(unsigned char *lds, const TileSca
 {
     const int ne = scan0.experts();
     const bool stream_once = scan0.tiles * 16 <= ne * 17 && offsets[N] < 400 * ne;
-    const bool rotate = offsets[N] >= 64 * ne && offsets[N] < 192 * ne;
-    if (stream_once)
-        run_tiles<C, GATEUP, TILED, true>(lds, scan0, tok, w0, w1, offsets, sorted_slot, out, N, K, Kdim, Fdim, n_ftiles, T, rotate);
-    else
-        run_tiles<C, GATEUP, TILED, false>(lds, scan0, tok, w0, w1, offsets, sorted_slot, out, N, K, Kdim, Fdim, n_ftiles, T, rotate);
+    if (stream_once) {
+        if constexpr (C::ROT) {
+            if (offsets[N] >= 64 * ne && offsets[N] < 192 * ne)
+                return run_tiles<C, GATEUP, TILED, true, true>(lds, scan0, tok, w0, w1, offsets, sorted_slot, out, N, K, Kdim, Fdim, n_ftiles, T);
+        }
+        run_tiles<C, GATEUP, TILED, true, false>(lds, scan0, tok, w0, w1, offsets, sorted_slot, out, N, K, Kdim, Fdim, n_ftiles, T);
+    } else {
+        run_tiles<C, GATEUP, TILED, false, false>(lds, scan0, tok, w0, w1, offsets, sorted_slot, out, N, K, Kdim, Fdim, n_ftiles, T);
+    }
 }
 
 template <class C, bool GATEUP, bool TILED>
