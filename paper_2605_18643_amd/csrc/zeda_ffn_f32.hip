@@ -7,6 +7,7 @@
 // and 41 us for down, a third of the HBM rate: fp32 products (20 us of matrix time), the sums' bookkeeping and the 64-byte
 // row pieces share the rest.  One workgroup per row, which re-read an expert's weights for every row, took 658 and 627 us.
 #include "zeda_f32_tile.h"
+#include "zeda_place.h"
 
 namespace zeda {
 
@@ -15,40 +16,6 @@ constexpr int kF32Waves = kF32Threads / 64;
 constexpr int kF32Rows = 32;  // token rows per workgroup: two blocks of 16
 constexpr int kF32NB = kF32Rows / 16;
 constexpr int kF32GridTiles = 1 << 14;  // token tiles along grid x (at most 512 feature tiles of 256 threads each: 2^31 work items), more along y
-
-// (expert, first row, rows) of token tile `tile`, or rows = 0 past the last one: lane l holds experts 4l..4l+3
-__device__ __forceinline__ int3 f32_locate(const int32_t *__restrict__ offsets, int N, int tile)
-{
-    const int lane = threadIdx.x & 63;
-    int off[5], nt[4], local = 0;
-#pragma unroll
-    for (int q = 0; q < 5; ++q) off[q] = offsets[min(4 * lane + q, N)];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        nt[q] = (off[q + 1] - off[q] + kF32Rows - 1) / kF32Rows;
-        local += nt[q];
-    }
-    int incl = local;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int v = __shfl_up(incl, o);
-        if (lane >= o) incl += v;
-    }
-    int excl = incl - local, e = 0, row0 = 0, rows = 0;
-    const unsigned long long mine = __ballot(tile >= excl && tile < incl);
-    if (mine == 0) return make_int3(0, 0, 0);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        if (tile >= excl && tile < excl + nt[q]) {
-            e = 4 * lane + q;
-            row0 = off[q] + (tile - excl) * kF32Rows;
-            rows = min(kF32Rows, off[q + 1] - row0);
-        }
-        excl += nt[q];
-    }
-    const int src = __ffsll((long long)mine) - 1;
-    return make_int3(__shfl(e, src), __shfl(row0, src), __shfl(rows, src));
-}
 
 // this wave's slice of the sums of the first LIVE token blocks, left in part[a * NB + b][lane], their errors in err
 template <int NA, int NB, int LIVE>
@@ -82,7 +49,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void ffn_f32_kernel(const float *__
     __shared__ f32x4 s_part[kF32Waves][NA * NB][64], s_err[kF32Waves][NA * NB][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15;
     const int tile_x = blockIdx.x / n_ft, ft = blockIdx.x - tile_x * n_ft, tile = blockIdx.y * kF32GridTiles + tile_x;
-    const int3 loc = f32_locate(offsets, N, tile);
+    const int4 loc = locate_rows<kF32Rows>(offsets, N, tile);
     const int rows = loc.z;
     if (rows == 0) return;
     const int f0 = ft * 16 * (GATEUP ? NA / 2 : NA);

@@ -9,50 +9,16 @@
 // one row, a tiled 32x32 unit is two such fragments of one contiguous KiB each.  No LDS and no barrier until the waves' sums
 // meet; a wave keeps DEPTH chunks of 64 k in flight.  Bound by HBM: 64 tokens, 106 experts hit, 667 MB of gate/up weights
 // in 107 us = 6.2 TB/s; one token, gate/up and down 23 + 13 -> 11 + 8 us (launch included).
-#include "zeda_internal.h"
+#include "zeda_place.h"
 
 namespace zeda {
 
 constexpr int kFewThreads = 256;
 constexpr int kFewWaves = kFewThreads / 64;
 
-// (expert, first row, rows) of token tile `tile`, or rows = 0 past the last one: lane l holds experts 4l..4l+3
-template <int ROWS>
-__device__ __forceinline__ int3 few_locate(const int32_t *__restrict__ offsets, int N, int tile)
-{
-    const int lane = threadIdx.x & 63;
-    int off[5], nt[4], local = 0;
-#pragma unroll
-    for (int q = 0; q < 5; ++q) off[q] = offsets[min(4 * lane + q, N)];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        nt[q] = (off[q + 1] - off[q] + ROWS - 1) / ROWS;
-        local += nt[q];
-    }
-    int incl = local;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int v = __shfl_up(incl, o);
-        if (lane >= o) incl += v;
-    }
-    int excl = incl - local, e = 0, row0 = 0, rows = 0;
-    const unsigned long long mine = __ballot(tile >= excl && tile < incl);
-    if (mine == 0) return make_int3(0, 0, 0);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        if (tile >= excl && tile < excl + nt[q]) {
-            e = 4 * lane + q;
-            row0 = off[q] + (tile - excl) * ROWS;
-            rows = min(ROWS, off[q + 1] - row0);
-        }
-        excl += nt[q];
-    }
-    const int src = __ffsll((long long)mine) - 1;
-    return make_int3(__builtin_amdgcn_readlane(e, src), __builtin_amdgcn_readlane(row0, src), __builtin_amdgcn_readlane(rows, src));
-}
-
-// this wave's share of the reduction for the first LIVE token blocks: part[a * NB + b][lane] of part
-template <bool TILED, int NA, int NB, int LIVE, int DEPTH>
+// this wave's share of the reduction for the first LIVE token blocks: part[a * NB + b][lane] of part.  NT: fetch the weights
+// with the non-temporal hint
+template <bool TILED, int NA, int NB, int LIVE, int DEPTH, bool NT>
 __device__ __forceinline__ void few_multiply(f32x4 (*part)[64], const bf16_t *const (&pa)[NA], const bf16_t *const (&pt)[NB], size_t wstep,
                                              int wave, int start, int Kd)
 {
@@ -72,7 +38,10 @@ __device__ __forceinline__ void few_multiply(f32x4 (*part)[64], const bf16_t *co
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
 #pragma unroll
-            for (int a = 0; a < NA; ++a) fa[d][s][a] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8 *>(pa[a] + (kb + s) * wstep));
+            for (int a = 0; a < NA; ++a) {
+                const bf16x8 *p = reinterpret_cast<const bf16x8 *>(pa[a] + (kb + s) * wstep);
+                fa[d][s][a] = NT ? __builtin_nontemporal_load(p) : *p;
+            }
 #pragma unroll
             for (int b = 0; b < LIVE; ++b) fb[d][s][b] = *reinterpret_cast<const bf16x8 *>(pt[b] + (kb + s) * 32);
         }
@@ -101,9 +70,22 @@ __device__ __forceinline__ void few_multiply(f32x4 (*part)[64], const bf16_t *co
         for (int b = 0; b < LIVE; ++b) part[a * NB + b][lane] = acc[a][b];
 }
 
+// few_multiply of as many token blocks as hold rows.  Three and four blocks keep two chunks in flight: registers.
+template <bool TILED, int NA, int NB, int DEPTH, bool NT>
+__device__ __forceinline__ void few_multiply_rows(int rows, f32x4 (*part)[64], const bf16_t *const (&pa)[NA], const bf16_t *const (&pt)[NB],
+                                                  size_t wstep, int wave, int start, int Kd)
+{
+    if constexpr (NB == 4) {
+        if (rows > 48) return few_multiply<TILED, NA, NB, 4, 2, NT>(part, pa, pt, wstep, wave, start, Kd);
+        if (rows > 32) return few_multiply<TILED, NA, NB, 3, 2, NT>(part, pa, pt, wstep, wave, start, Kd);
+    }
+    if (rows > 16) few_multiply<TILED, NA, NB, 2, DEPTH, NT>(part, pa, pt, wstep, wave, start, Kd);
+    else few_multiply<TILED, NA, NB, 1, DEPTH, NT>(part, pa, pt, wstep, wave, start, Kd);
+}
+
 // GATEUP: tok = x[T,Kd], w0 = W_gate[N,F,Kd], w1 = W_up, out = act[S,F];  else tok = act[S,Kd], w0 = W_down[N,F,Kd],
-// out = y_slot[S,F].  Kd a multiple of 64, F of 16 NF.  Up to 16 NB token rows.  Blocks past the last token tile return
-// at once.
+// out = y_slot[S,F].  Kd a multiple of 64, F of 16 NF.  Up to 16 NB token rows (NB 2 or 4).  Blocks past the last token
+// tile return at once.
 template <bool GATEUP, bool TILED, int NF, int NB, int DEPTH>
 __global__ __launch_bounds__(kFewThreads) void ffn_few_kernel(const bf16_t *__restrict__ tok, const bf16_t *__restrict__ w0,
                                                               const bf16_t *__restrict__ w1, const int32_t *__restrict__ offsets,
@@ -114,7 +96,7 @@ __global__ __launch_bounds__(kFewThreads) void ffn_few_kernel(const bf16_t *__re
     __shared__ f32x4 s_part[kFewWaves][NA * NB][64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, kq = lane >> 4;
     const int tile = blockIdx.x / n_ft, ft = blockIdx.x - tile * n_ft;
-    const int3 loc = few_locate<16 * NB>(offsets, N, tile);
+    const int4 loc = locate_rows<16 * NB>(offsets, N, tile);
     if (loc.z == 0) return;
     const bf16_t *pt[NB];
 #pragma unroll
@@ -135,9 +117,10 @@ __global__ __launch_bounds__(kFewThreads) void ffn_few_kernel(const bf16_t *__re
     // the same chunk of row-major rows, often a multiple of 4 KiB apart, sits on a few memory channels.  All feature tiles
     // of an expert start alike: neighbours then read neighbouring units of tiled weights at the same time.
     const int start = loc.x * 5;
-    static_assert(NB == 2, "one or two live blocks");
-    if (loc.z > 16) few_multiply<TILED, NA, NB, NB, DEPTH>(s_part[wave], pa, pt, wstep, wave, start, Kd);
-    else few_multiply<TILED, NA, NB, 1, DEPTH>(s_part[wave], pa, pt, wstep, wave, start, Kd);
+    // An expert of several token tiles has its weights fetched by each of them: they are meant to stay in the caches then.
+    // (N=16, I=2048, K=1, 64 tokens, loads with one hot expert of 39 rows: 0.88 -> 0.83 of the tile kernel's time)
+    if (loc.w <= 16 * NB) few_multiply_rows<TILED, NA, NB, DEPTH, true>(loc.z, s_part[wave], pa, pt, wstep, wave, start, Kd);
+    else few_multiply_rows<TILED, NA, NB, DEPTH, false>(loc.z, s_part[wave], pa, pt, wstep, wave, start, Kd);
     __syncthreads();
 
     // a block's lane l holds features 4 (l / 16) .. + 3 of token l % 16
@@ -164,34 +147,68 @@ __global__ __launch_bounds__(kFewThreads) void ffn_few_kernel(const bf16_t *__re
     }
 }
 
-// Where this kernel beats the tile kernel, by the rows an expert gets if the slots fall evenly on all N + Z experts (the
-// real loads are only known on the device) and by the tile kernel's gate/up work items, one per 128 columns of I and expert:
-//  - up to 5 rows both stream weights and nothing else; this one has more of them in flight (N=128, I=768, H=2048:
-//    64 tokens 188 -> 177 us, row-major at 32 tokens 191 -> 168; level at 128 tokens, 3 % behind at 192);
-//  - up to 64 tokens it also wins with more rows (N=8, K=2, I=3072: 75 -> 67 us; N=8, K=6, I=1024: 39 -> 38);
-//  - up to 320 items the tile kernel fills little more than one round of 256 CUs or less (N=48, I=768, H=1536: 100 tokens
-//    92 -> 73 us, 300 tokens row-major 138 -> 115; N=24, I=448, H=1152: 301 tokens 45 -> 40).  This kernel reads the token
-//    rows once per 16 columns, so it falls behind once an expert has more rows than a workgroup: at 94 rows 49 -> 75 us;
-//  - up to 40 items there is next to nothing to fill the chip with (N=16, I=256, H=512: 500 tokens 38 -> 23 us, 2000 tokens,
-//    167 rows, 39 -> 30; level at 250 rows with N=32, I=128).
-bool ffn_few_supported(const zeda_layer_desc *d)
+// Where this kernel beats the tile kernels, and with how many 16-row token blocks a workgroup (0: not).  The real loads are
+// only known on the device; what is known here is the slots per expert if they fell evenly on all N + Z experts, and the
+// tile kernel's gate/up work items, one per 128 columns of I and expert.  Fitted to 37 layer shapes with 1 to 1000 tokens
+// under even, Zipf and one-hot-expert loads, and with half of the slots on zero experts.  Below: this kernel's time over the
+// better tile kernel's, row-major / tiled, even loads where nothing else is said.
+//  - up to 40 items there is next to nothing to fill the chip with (N=16, I=256, H=512: 1000 tokens 0.60 / 0.66, 2000
+//    tokens, 167 rows, 0.89 / 0.84);
+//  - decode batches: up to 64 items the tile kernel fills a quarter of the chip (N=8, K=6, I=1024: 48 rows 0.83 / 0.83 with
+//    four token blocks, 1.06 / 1.00 with two); more of them, and the rows count: N=8, I=3072, 192 items: 16 rows 0.82 /
+//    0.87; N=16, I=2304, K=16, 288 items: 16 rows 0.87 / 0.94, 32 rows 1.06 / 1.15; a filled chip, N=8, I=14336: 8 rows 1.01 /
+//    1.02, 12 rows 1.05 / 1.05, but N=128, I=768: 2 rows 0.9 / 0.98, N=64, I=2048, 6 rows 0.96 / 0.97;
+//  - short reductions leave the four waves a chunk or two each: N=64, I=512, H=512: 4 rows 1.00 / 0.95, 8 rows 1.07 / 1.01;
+//    N=256, I=256, H=1024: half a slot per expert 0.97 / 1.0, one 1.04 / 1.01 and 1.09 / 1.17 with Zipf loads;
+//  - longer batches on a chip that the tile kernel fills: N=128, Z=32, I=768, 5 slots per expert: 0.95 / 1.01 with half of the
+//    slots on zero experts (Zipf loads 0.90 / 0.94), 1.09 / 1.04 with a fifth of them; without zero experts and from H = 4096
+//    on the row-major loads fall behind (N=192, I=2048, H=4096, 3 rows 1.09-1.17 / 0.96-1.01).  N=128, I=384, 384 items: 5 slots
+//    0.85 / 0.99, 10 slots 0.90 / 1.05;
+//  - between one and two rounds of 256 CUs the tile kernel idles: N=48, I=768, 288 items: 18 rows 0.80 / 0.88, 25 rows 0.87 /
+//    0.94, 30 rows 0.82 / 0.93 with four blocks, 1.02 / 1.11 with two; N=24, I=448, 96 items: 30 rows 0.98 / 1.07 (20 of them
+//    real: 0.91 / 0.97) with four, 1.17 with two; N=12, I=704, 72 items: 40 rows 0.90 / 0.98.  With one full round it does not:
+//    N=60, I=512, 240 items: 12 rows 0.97 / 0.99, 16 rows 1.02 / 1.06, 19 rows 1.04 / 1.11.
+int ffn_few_blocks(const zeda_layer_desc *d)
 {
-    const int64_t slots = (int64_t)d->T * d->K, experts = d->N + d->Z, items = (int64_t)d->N * ceil_div(d->I, 128);
-    return d->T <= 64 || slots <= 5 * experts || (items <= 320 && slots <= 40 * experts) || (items <= 40 && slots <= 170 * experts);
+    const int64_t slots = (int64_t)d->T * d->K, experts = d->N + d->Z, cols = ceil_div(d->I, 128), items = d->N * cols;
+    const int64_t hit = slots < d->N ? slots : d->N, hit_items = hit * cols;
+    const bool wide = d->H >= 768 && d->I >= 384;
+    // one dimension of workgroups: 2^32 work items, i.e. 2^24 workgroups (the tile kernels' grids do not grow with the layer)
+    if ((hit + slots / 32) * (d->I / 16 > d->H / 32 ? d->I / 16 : d->H / 32) >= 1 << 24) return 0;
+    if (items <= 40) return d->T <= 64 || slots <= 170 * experts ? 2 : 0;
+    if (d->T <= 64) {
+        if (hit_items <= 64) return slots <= 25 * experts ? 2 : 4;
+        if (wide) return slots <= (hit_items <= 320 ? 16 : 8) * experts ? 2 : 0;
+        if (d->I >= 384) return slots <= 4 * experts ? 2 : 0;
+        return (hit_items <= 128 ? 2 * slots <= 3 * d->N : slots < d->N) ? 2 : 0;
+    }
+    if (items > 512) return d->Z > 0 && d->H < 4096 && wide && slots <= 5 * experts ? 2 : 0;
+    if (items > 320) return slots <= (wide ? 5 : 2) * experts ? 2 : 0;
+    if ((items > 192 && items <= 256) || (items > 64 && !wide)) return slots <= 13 * experts ? 2 : 0;
+    if (slots <= 25 * experts) return 2;
+    return slots <= (items <= 80 ? 40 : d->Z > 0 ? 32 : 25) * experts ? 4 : 0;
+}
+
+template <bool GATEUP, bool TILED, int NB>
+static int launch_blocks(const zeda_layer_desc *d, const void *tok, const void *w0, const void *w1, const int32_t *offsets,
+                         const int32_t *sorted_slot, void *out, hipStream_t s)
+{
+    // 16 gate and 16 up rows, or 32 rows of W_down (16 make twice the workgroups and token reads: 58 -> 61 us at 64 tokens);
+    // three chunks of 64 k in flight (four leave fewer waves per SIMD: 177.5 -> 176.5 us)
+    constexpr int NF = GATEUP ? 1 : 2, DEPTH = 3;
+    const int Kd = GATEUP ? d->H : d->I, F = GATEUP ? d->I : d->H, n_ft = F / (16 * NF);
+    const int S = d->T * d->K, tiles = (S < d->N ? S : d->N) + S / (16 * NB);  // at most this many token tiles
+    ffn_few_kernel<GATEUP, TILED, NF, NB, DEPTH><<<(unsigned)tiles * n_ft, kFewThreads, 0, s>>>(
+        (const bf16_t *)tok, (const bf16_t *)w0, (const bf16_t *)w1, offsets, sorted_slot, (bf16_t *)out, d->N, d->K, Kd, F, n_ft, d->T);
+    return last_launch_status();
 }
 
 template <bool GATEUP, bool TILED>
 static int launch(const zeda_layer_desc *d, const void *tok, const void *w0, const void *w1, const int32_t *offsets,
                   const int32_t *sorted_slot, void *out, hipStream_t s)
 {
-    // 16 gate and 16 up rows, or 32 rows of W_down (16 make twice the workgroups and token reads: 58 -> 61 us at 64 tokens);
-    // two token blocks; three chunks of 64 k in flight (four leave fewer waves per SIMD: 177.5 -> 176.5 us)
-    constexpr int NF = GATEUP ? 1 : 2, NB = 2, DEPTH = 3;
-    const int Kd = GATEUP ? d->H : d->I, F = GATEUP ? d->I : d->H, n_ft = F / (16 * NF);
-    const int S = d->T * d->K, tiles = (S < d->N ? S : d->N) + S / (16 * NB);  // at most this many token tiles
-    ffn_few_kernel<GATEUP, TILED, NF, NB, DEPTH><<<(unsigned)tiles * n_ft, kFewThreads, 0, s>>>(
-        (const bf16_t *)tok, (const bf16_t *)w0, (const bf16_t *)w1, offsets, sorted_slot, (bf16_t *)out, d->N, d->K, Kd, F, n_ft, d->T);
-    return last_launch_status();
+    return ffn_few_blocks(d) == 2 ? launch_blocks<GATEUP, TILED, 2>(d, tok, w0, w1, offsets, sorted_slot, out, s)
+                                  : launch_blocks<GATEUP, TILED, 4>(d, tok, w0, w1, offsets, sorted_slot, out, s);
 }
 
 int launch_gateup_few(const zeda_layer_desc *d, const void *x, const void *wg, const void *wu, const int32_t *offsets,

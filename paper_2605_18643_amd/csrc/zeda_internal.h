@@ -73,7 +73,7 @@ int launch_gateup_f32(const zeda_layer_desc *d, const void *x, const void *wg, c
 int launch_down_f32(const zeda_layer_desc *d, const void *act, const void *wd, const int32_t *offsets, void *y_slot,
                     hipStream_t s);
 // the same for bf16 layers whose experts have a handful of rows each (launch_gateup and launch_down call them)
-bool ffn_few_supported(const zeda_layer_desc *d);
+int ffn_few_blocks(const zeda_layer_desc *d);  // token blocks of a workgroup, 0 where the tile kernels are the better ones
 int launch_gateup_few(const zeda_layer_desc *d, const void *x, const void *wg, const void *wu, const int32_t *offsets,
                       const int32_t *sorted_slot, void *act, hipStream_t s);
 int launch_down_few(const zeda_layer_desc *d, const void *act, const void *wd, const int32_t *offsets, void *y_slot,

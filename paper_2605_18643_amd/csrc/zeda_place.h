@@ -1,4 +1,5 @@
-// Expert-sorted placement of a short slot list by one workgroup (Section 2.1: slots on zero experts are dropped).
+// Expert-sorted placement of a short slot list by one workgroup (Section 2.1: slots on zero experts are dropped), and the
+// way back from a tile of the sorted rows to its expert.
 #pragma once
 #include "zeda_internal.h"
 
@@ -82,6 +83,44 @@ __device__ __forceinline__ void place_list(const int *s_ids, int S, int N, Place
     } else if (in) {
         o.slot_to_row[slot] = -1;
     }
+}
+
+// Token tile `tile` of the expert-sorted rows, ROWS rows to a tile: {expert, first row, rows, rows of the expert}, rows = 0
+// past the last tile.  By a whole wave (lane l holds experts 4l..4l+3); the same for all lanes.
+template <int ROWS>
+__device__ __forceinline__ int4 locate_rows(const int32_t *__restrict__ offsets, int N, int tile)
+{
+    const int lane = threadIdx.x & 63;
+    int off[5], nt[4], local = 0;
+#pragma unroll
+    for (int q = 0; q < 5; ++q) off[q] = offsets[min(4 * lane + q, N)];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        nt[q] = (off[q + 1] - off[q] + ROWS - 1) / ROWS;
+        local += nt[q];
+    }
+    int incl = local;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(incl, o);
+        if (lane >= o) incl += v;
+    }
+    int excl = incl - local, e = 0, row0 = 0, rows = 0, all = 0;
+    const unsigned long long mine = __ballot(tile >= excl && tile < incl);
+    if (mine == 0) return make_int4(0, 0, 0, 0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if (tile >= excl && tile < excl + nt[q]) {
+            e = 4 * lane + q;
+            row0 = off[q] + (tile - excl) * ROWS;
+            all = off[q + 1] - off[q];
+            rows = min(ROWS, off[q + 1] - row0);
+        }
+        excl += nt[q];
+    }
+    const int src = __ffsll((long long)mine) - 1;
+    return make_int4(__builtin_amdgcn_readlane(e, src), __builtin_amdgcn_readlane(row0, src), __builtin_amdgcn_readlane(rows, src),
+                     __builtin_amdgcn_readlane(all, src));
 }
 
 }  // namespace zeda

@@ -20,14 +20,28 @@ CASES = [
     dict(T=64, H=384, I=64, N=4, Z=0, K=1),
     dict(T=130, H=1152, I=448, N=4, Z=0, K=1),
     dict(T=200, H=640, I=320, N=8, Z=2, K=2),
-    # both sides of the 40-rows and 170-rows rules (few weight tiles), of 5 rows per expert (many)
-    dict(T=320, H=512, I=256, N=24, Z=0, K=3),
-    dict(T=321, H=512, I=256, N=24, Z=0, K=3),
+    # both sides of the rules, in slots per expert of the pool: 170 (next to no weight tiles), 40 and 30 (four token blocks a
+    # workgroup, few weight tiles), 25 to 26 (two blocks to four), 13 (one full round of the chip), 5 (more than that)
     dict(T=2720, H=128, I=64, N=14, Z=2, K=1),
     dict(T=2721, H=128, I=64, N=14, Z=2, K=1),
-    dict(T=50, H=256, I=512, N=100, Z=60, K=16),
-    dict(T=51, H=256, I=512, N=100, Z=60, K=16),
-    # router: 16 and 17 tokens with a split (one workgroup that also places), widest pool, slots on every expert
+    dict(T=320, H=1280, I=704, N=12, Z=4, K=2),
+    dict(T=321, H=1280, I=704, N=12, Z=4, K=2),
+    dict(T=341, H=1152, I=448, N=24, Z=8, K=3),
+    dict(T=342, H=1152, I=448, N=24, Z=8, K=3),
+    dict(T=200, H=1152, I=448, N=24, Z=0, K=3),
+    dict(T=201, H=1152, I=448, N=24, Z=0, K=3),
+    dict(T=208, H=768, I=512, N=60, Z=4, K=4),
+    dict(T=209, H=768, I=512, N=60, Z=4, K=4),
+    dict(T=100, H=768, I=1024, N=100, Z=60, K=8),
+    dict(T=101, H=768, I=1024, N=100, Z=60, K=8),
+    # decode batches: three and four live token blocks; both sides of the rule beyond which the 64-row tile takes over; a
+    # reduction too short for the waves
+    dict(T=50, H=1024, I=1024, N=8, Z=0, K=6),
+    dict(T=64, H=512, I=512, N=16, Z=0, K=16),
+    dict(T=50, H=768, I=1024, N=50, Z=0, K=8),
+    dict(T=51, H=768, I=1024, N=50, Z=0, K=8),
+    dict(T=64, H=512, I=256, N=200, Z=20, K=8),
+    # both sides of the 16 tokens that the router may place itself, widest pool, slots on every expert
     dict(T=16, H=2048, I=64, N=60, Z=30, K=16),
     dict(T=17, H=2048, I=64, N=60, Z=30, K=16),
     dict(T=33, H=1024, I=64, N=200, Z=56, K=4),
@@ -47,13 +61,15 @@ def test_small_batches_match_the_oracle_in_both_layouts(cfg):
     assert torch.equal(plain["out"].view(torch.int16), tiled["out"].view(torch.int16))
 
 
-@pytest.mark.parametrize("T", [4096, 4097, 8192])
+@pytest.mark.parametrize("T", [4096, 4097, 8192, 8193, 8250, 16390])
 def test_router_splits_of_long_batches(T):
-    """One workgroup per 16, 32 and 64 tokens: ids, gates, placement and output of sampled tokens."""
-    w = synth.Workload("route_long", T=T, H=256, I=64, N=40, Z=24, K=5, dtype="bf16", seed=402, recipe="zero_bias", x_std=1.0,
-                       w_std=0.05, wr_std=0.08, zero_bias=0.3)
-    print(w, flush=True)
-    full_parity(w, harness.gapped_layer(w, "cuda"), tokens=np.arange(0, T, 37))
+    """One workgroup per 16, 32 and 64 tokens, the last one partly filled, through the per-block counts that the placement
+    starts from: ids, gates, placement and output of sampled tokens.  160 experts: 16 waves; 64: four."""
+    for N, Z in ((128, 32), (40, 24)):
+        w = synth.Workload("route_long", T=T, H=256, I=64, N=N, Z=Z, K=5, dtype="bf16", seed=402, recipe="zero_bias", x_std=1.0,
+                           w_std=0.05, wr_std=0.08, zero_bias=0.3)
+        print(w, flush=True)
+        full_parity(w, harness.gapped_layer(w, "cuda"), tokens=np.arange(0, T, 37))
 
 
 def test_masked_experts_are_not_selected_twice():

@@ -47,7 +47,8 @@ def test_route_alone(dtype, gate_norm):
 @pytest.mark.parametrize("T,H", [(203, 1024), (64, 2048), (5, 512), (1000, 384)])
 def test_route_with_scratch_splits_the_hidden_dimension(T, H):
     # few token blocks: with scratch several workgroups share a block (each a slice of H) and a second kernel
-    # selects; the result must be the oracle's either way
+    # selects, where that pays (of these sizes the second; test_gpu_router_splits.py counts slices at more); the result
+    # must be the oracle's either way
     w = synth.Workload("route_ws", T=T, H=H, I=64, N=70, Z=27, K=6, dtype="bf16", seed=52, recipe="zero_bias",
                        wr_std=0.05, zero_bias=0.35)
     print(w, flush=True)
@@ -69,8 +70,8 @@ def test_route_with_scratch_splits_the_hidden_dimension(T, H):
 @pytest.mark.parametrize("T, N, Z", [(8192, 128, 32), (8193, 128, 32), (9001, 70, 26), (12288, 128, 32), (12301, 30, 10),
                                      (13000, 150, 42), (12500, 200, 56)])
 def test_route_of_many_tokens(T, N, Z):
-    # above 8192 tokens the bf16 router gives a workgroup 64 tokens instead of 32 (routers of up to 192
-    # experts; wider ones keep the 32-token blocks): exact ids and gates against the oracle, ragged last block
+    # above 8192 tokens the bf16 router gives a workgroup 64 tokens (32 up to 64 experts, from 16385 tokens on 64 there too),
+    # 32 below: exact ids and gates against the oracle, ragged last block
     w = synth.Workload("route_wide", T=T, H=256, I=64, N=N, Z=Z, K=6, dtype="bf16", seed=53, recipe="zero_bias",
                        wr_std=0.08, zero_bias=0.3)
     print(w, flush=True)
