@@ -774,21 +774,25 @@ __global__ __launch_bounds__(kStatsThreads) void route_stats_kernel(const float 
             for (int c = 0; c < NC; ++c) psum[c] += ex[c] / all;
         }
         // the top-K set, as in select_rows: K rounds of (row maximum, lowest index among equals)
-        for (int j = 0; j < K; ++j) {
-            float mm = cand[0];
+        int key[NC];
 #pragma unroll
-            for (int c = 1; c < NC; ++c) mm = fmaxf(mm, cand[c]);
+        for (int c = 0; c < NC; ++c) key[c] = ok && l16 + 16 * c < NE ? logit_key(cand[c]) : kNoKey;
+        for (int j = 0; j < K; ++j) {
+            int mm = key[0];
+#pragma unroll
+            for (int c = 1; c < NC; ++c) mm = max(mm, key[c]);
             mm = row_max(mm);
             int mine = INT_MAX;
 #pragma unroll
             for (int c = NC - 1; c >= 0; --c)
-                if (cand[c] == mm) mine = l16 + 16 * c;
-            const int win = row_min(mine);
+                if (key[c] == mm) mine = l16 + 16 * c;
+            int win = row_min(mine);
+            if (mm == kNoKey) win = INT_MAX;  // nothing but no-numbers left: no expert
 #pragma unroll
             for (int c = 0; c < NC; ++c)
                 if (win == l16 + 16 * c) {
-                    cand[c] = -INFINITY;
-                    if (ok) ++fcnt[c];
+                    key[c] = kNoKey;
+                    ++fcnt[c];
                 }
         }
     }

@@ -94,3 +94,27 @@ def test_masked_experts_are_not_selected_twice():
             i, gt = ids.cpu().numpy(), gates.cpu().numpy()
             assert (np.sort(i[:, :4], axis=1) == keep).all() and (i[:, 4:] == [0, 1]).all()
             assert (gt[:, 4:] == 0).all() and np.allclose(gt.sum(1), 1.0, atol=1e-5)
+
+
+@pytest.mark.parametrize("dtype,H", [("bf16", 256), ("bf16", 1024), ("f32", 64)])
+@pytest.mark.parametrize("N,Z", [(20, 4), (70, 27)])
+def test_statistics_count_masked_experts_once(dtype, H, N, Z):
+    """f_i (Eq. 4) of experts masked with a bias of -inf: the selected slots of the router itself."""
+    from paper_2605_18643_amd import zeda
+
+    for T in (5, 300):
+        g = torch.Generator().manual_seed(T)
+        tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+        K, NE = 6, N + Z
+        x, wr = torch.randn(T, H, generator=g).to(tdt).cuda(), (0.1 * torch.randn(NE, H, generator=g)).to(tdt).cuda()
+        bias = torch.full((NE,), float("-inf"))
+        bias[[3, 8, 17, 22]] = 0.0
+        d = zeda.make_desc(T, H, 64, N, Z, K, dtype)
+        f, P, _ = zeda.zeda_routing_stats(d, x, wr, bias.cuda())
+        ids = torch.full((T, K), -1, dtype=torch.int32, device="cuda")
+        zeda.zeda_route(d, x, wr, bias.cuda(), ids, torch.empty((T, K), device="cuda"))
+        torch.cuda.synchronize()
+        counts = np.bincount(ids.cpu().numpy().ravel(), minlength=NE)
+        assert np.array_equal(f.cpu().numpy(), (counts / T).astype(np.float32))
+        assert f.max() <= 1 and np.allclose(f.cpu().numpy()[[0, 1]], 1.0)
+        np.testing.assert_allclose(P.cpu().numpy().sum(), 1.0, rtol=1e-5)
