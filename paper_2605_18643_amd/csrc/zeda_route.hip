@@ -147,8 +147,8 @@ __device__ __forceinline__ int select_rows(const float *lg, int LD, int pstride,
 #pragma unroll
         for (int c = 0; c < NC; ++c)
             if (win == l16 + 16 * c) cand[c] = kNoKey;
-        if (m == kNoKey) win = INT_MAX;  // nothing but no-numbers left: no expert
-        if (l16 == j) { my_id = win; my_logit = key_logit(m); }
+        if (m == kNoKey) win = INT_MAX;  // nothing but no-numbers left: no expert, gate 0
+        if (l16 == j) { my_id = win; my_logit = m == kNoKey ? -INFINITY : key_logit(m); }
     }
     const bool slot = l16 < K;
     const float ex = slot ? expf(my_logit - all_max) : 0.f;
@@ -218,8 +218,8 @@ __device__ __forceinline__ int select_wave(const float *lg, bool ok, size_t t, i
 #pragma unroll
         for (int c = 0; c < NC; ++c)
             if (win == lane + 64 * c) cand[c] = kNoKey;
-        if (m == kNoKey) win = INT_MAX;  // nothing but no-numbers left: no expert
-        if (lane == j) { my_id = win; my_logit = key_logit(m); }
+        if (m == kNoKey) win = INT_MAX;  // nothing but no-numbers left: no expert, gate 0
+        if (lane == j) { my_id = win; my_logit = m == kNoKey ? -INFINITY : key_logit(m); }
     }
     const bool slot = lane < K;
     const float ex = slot ? expf(my_logit - all_max) : 0.f;

@@ -118,3 +118,33 @@ def test_statistics_count_masked_experts_once(dtype, H, N, Z):
         assert np.array_equal(f.cpu().numpy(), (counts / T).astype(np.float32))
         assert f.max() <= 1 and np.allclose(f.cpu().numpy()[[0, 1]], 1.0)
         np.testing.assert_allclose(P.cpu().numpy().sum(), 1.0, rtol=1e-5)
+
+
+@pytest.mark.parametrize("dtype,H,N", [("bf16", 2048, 90), ("bf16", 256, 90), ("bf16", 256, 20), ("f32", 64, 20)])
+def test_experts_without_a_logit_leave_the_other_gates_alone(dtype, H, N):
+    """Fewer than K experts have a logit that is a number: those come first, with the gates that they have among
+    themselves, and the remaining slots weigh nothing."""
+    from paper_2605_18643_amd import zeda
+
+    for T in (5, 300):
+        g = torch.Generator().manual_seed(T)
+        tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+        K, Z = 6, 4
+        x, wr = torch.randn(T, H, generator=g).to(tdt).cuda(), (0.02 * torch.randn(N + Z, H, generator=g)).to(tdt).cuda()
+        bias = torch.full((N + Z,), float("nan"))
+        keep = [3, 8, 17, N + 2]
+        bias[keep] = 0.0
+        for norm in (zeda.GATE_TOPK_NORM, zeda.GATE_REAL_RENORM):
+            d = zeda.make_desc(T, H, 64, N, Z, K, dtype, gate_norm=norm)
+            ids = torch.full((T, K), -1, dtype=torch.int32, device="cuda")
+            gates = torch.full((T, K), float("nan"), device="cuda")
+            ws = torch.empty(max(16, zeda.route_workspace_bytes(d)), dtype=torch.uint8, device="cuda")
+            zeda.zeda_route(d, x, wr, bias.cuda(), ids, gates, ws=ws)
+            torch.cuda.synchronize()
+            i, gt = ids.cpu().numpy(), gates.cpu().numpy()
+            assert (np.sort(i[:, :4], axis=1) == keep).all() and (gt[:, 4:] == 0).all()
+            logit = np.take_along_axis((x.double() @ wr.double().T).cpu().numpy(), i[:, :4], 1)
+            ex = np.exp(logit - logit.max(1, keepdims=True))
+            real = np.ones_like(ex) if norm == zeda.GATE_TOPK_NORM else i[:, :4] < N
+            # (fp32 logits of up to H = 2048 products of |x w| of about 0.016: within 1e-4)
+            np.testing.assert_allclose(gt[:, :4], ex / (ex * real).sum(1, keepdims=True), rtol=5e-4)
