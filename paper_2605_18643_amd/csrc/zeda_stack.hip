@@ -83,12 +83,15 @@ __global__ __launch_bounds__(kStackThreads) void rmsnorm_vec_kernel(const T *__r
     }
 }
 
-// The vector form where the rows allow it; it reads a row whole before it writes it, so out may be x, as before.
+// The vector form where the rows allow it and are more than half a wave of vectors long: of shorter rows the other form
+// reads an element or less per thread and its second pass is as cheap (8192 rows, vector / element form: 64 bf16 7.1 / 5.4
+// us, 256 7.4 / 7.7 and up to 1000 rows 4 % behind, 264 7.7 / 8.7; fp32: 128 7.0 / 6.4, 192 7.7 / 8.1).  Either reads a
+// row whole, or an element in the same thread, before it writes it, so out may be x.
 template <typename T>
 static void launch_rmsnorm(int T_, int H, const void *x, const void *gamma, float eps, void *out, hipStream_t s)
 {
     constexpr int VN = 16 / sizeof(T);
-    if (H % VN == 0 && H / VN <= kNormVecs * kStackThreads && aligned16(x) && aligned16(gamma) && aligned16(out))
+    if (H % VN == 0 && H > 32 * VN && H / VN <= kNormVecs * kStackThreads && aligned16(x) && aligned16(gamma) && aligned16(out))
         rmsnorm_vec_kernel<T, VN><<<T_, kStackThreads, 0, s>>>((const T *)x, (const T *)gamma, eps, (T *)out, H);
     else
         rmsnorm_kernel<T><<<T_, kStackThreads, 0, s>>>((const T *)x, (const T *)gamma, eps, (T *)out, H);

@@ -36,6 +36,23 @@ def test_rmsnorm_and_residual_kernels():
         assert torch.equal(x, want)
 
 
+@pytest.mark.parametrize("H", [1, 64, 128, 132, 256, 264, 1000, 4096, 4100, 8192, 8200])
+def test_rmsnorm_of_short_long_and_unaligned_rows(H):
+    """Both sides of the lengths between which rows go by whole vectors; in place; rows that start off 16 bytes."""
+    # (one rounding to the type, and fp32 sums of up to 33 terms a thread and 256 threads)
+    for dt, tol in ((torch.bfloat16, 2 ** -8 + 1e-5), (torch.float32, 1e-5)):
+        buf = (torch.randn(35 * H + 1) * 1.7).to(dt).cuda()
+        g = (torch.rand(H) + 0.5).to(dt).cuda()
+        for x in (buf[:35 * H].view(35, H), buf[1:].view(35, H)):
+            ref = orc.rmsnorm(x.double().cpu().numpy(), g.double().cpu().numpy(), EPS)
+            out = torch.empty_like(x)
+            zeda.zeda_rmsnorm(x, g, EPS, out)
+            np.testing.assert_allclose(out.double().cpu().numpy(), ref, rtol=tol, atol=1e-30)
+            same = x.clone() if x.data_ptr() % 16 == 0 else torch.cat([buf[:1], x.flatten()])[1:].view(35, H)
+            zeda.zeda_rmsnorm(same, g, EPS, same)
+            assert torch.equal(same, out)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("copy_expert", [False, True])
 def test_block_forward_against_the_oracle(dtype, copy_expert):
