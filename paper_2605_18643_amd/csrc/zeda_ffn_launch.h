@@ -87,7 +87,7 @@ static bool rows_may_straddle_tile(const zeda_layer_desc *d)
 // 286 -> 275 us a layer), but a row is asked for two chunks ahead instead of three, which tells where a chunk is multiplied
 // in no time (31 rows per expert, 50 slots: gate/up 133 -> 144 us, down 72 -> 81; level at 78 rows, 125 slots).
 static bool rows_fill_groups(const zeda_layer_desc *d) { return (int64_t)d->T * d->K >= 110 * ((int64_t)d->N + d->Z); }
-// That ring addresses token rows (of x, of act) with 32-bit byte offsets.
+// That ring addresses token rows (of x, of act) with 32-bit byte offsets; above 4 GiB of them the 32-wide one is taken.
 static bool rows_addressable(const zeda_layer_desc *d)
 {
     return (uint64_t)d->T * d->H * 2 <= UINT32_MAX && (uint64_t)d->T * d->K * d->I * 2 <= UINT32_MAX;
@@ -126,8 +126,9 @@ static int launch_bf16(const zeda_layer_desc *d, const void *tok, const void *w0
     }
     if (d->weight_layout == ZEDA_WEIGHTS_TILED) {
         if (cfg_fits<CfgPrefillT>(d)) {
-            if (rows_may_straddle_tile(d) && rows_addressable(d))
-                return launch_adaptive_kernel<CfgPrefillTP, CfgPrefillT5, GATEUP, true>(d, tok, w0, w1, offsets, sorted_slot, out, s);
+            if (rows_may_straddle_tile(d))
+                return rows_addressable(d) ? launch_adaptive_kernel<CfgPrefillTP, CfgPrefillT5, GATEUP, true>(d, tok, w0, w1, offsets, sorted_slot, out, s)
+                                           : launch_adaptive_kernel<CfgPrefillT, CfgPrefillT5, GATEUP, true>(d, tok, w0, w1, offsets, sorted_slot, out, s);
             if (rows_fill_groups(d) && rows_addressable(d)) return launch_tile_kernel<CfgPrefillTP, GATEUP, true>(d, tok, w0, w1, offsets, sorted_slot, out, s);
             return launch_tile_kernel<CfgPrefillT, GATEUP, true>(d, tok, w0, w1, offsets, sorted_slot, out, s);
         }
