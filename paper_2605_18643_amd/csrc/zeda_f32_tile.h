@@ -9,20 +9,21 @@
 // loads in flight and the number of waves, not the matrix units: the hidden dimension of one output tile is split over the
 // waves of a workgroup, each keeps the loads of the next 32 k in flight, and nothing goes through LDS but the waves' sums.
 //
-// Precision: the 32 products of a chunk are added as four sums of eight in the matrix unit and a tree over the four; the
-// chunk sums are added up with a compensated sum (the rounding errors of the additions are added up on the side), so the
-// error does not grow with the number of chunks; the slices' few sums are added in 64 bits and rounded once.  (Sums of
-// sixteen per chunk and a plain sum over the slices end farther from the 64-bit result than the sums over 64 lanes that
-// these kernels replaced.)  The running sum itself is the plain one: where it overflows or meets an infinity, the errors are no numbers and are
-// left out (error()).
+// Precision: the 32 products of a chunk are added as four sums of eight in the matrix unit and a tree over the four; chunk
+// sums and the FFN's slices are added in 64 bits and rounded once, so that the error is the chunks' own, however many there
+// are.  (Sums of sixteen per chunk and a plain sum over the slices end farther from the 64-bit result than the sums over 64
+// lanes that these kernels replaced.  A compensated fp32 sum that is exact whichever summand
+// is the larger one takes six additions where this takes a conversion and an addition: 6 % more of the FFN, 2 % of the router.)
 #pragma once
 #include "zeda_internal.h"
 
 namespace zeda {
 
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+
 template <int NA, int NB>
 struct F32Tile {
-    f32x4 sum[NA][NB], err[NA][NB];
+    f64x2 acc[NA][NB][2];
 
     struct Frags {
         f32x4 a[2][NA], b[2][NB];
@@ -33,10 +34,7 @@ struct F32Tile {
 #pragma unroll
         for (int a = 0; a < NA; ++a)
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                sum[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-                err[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-            }
+            for (int b = 0; b < NB; ++b) acc[a][b][0] = acc[a][b][1] = f64x2{0., 0.};
     }
     // pa, pb: this lane's rows (at k = 0); the 32 k from k0 on; past Kd (a multiple of 4) both operands are zero
     __device__ __forceinline__ static void load(Frags &f, const float *const (&pa)[NA], const float *const (&pb)[NB], int k0, int Kd)
@@ -60,11 +58,11 @@ struct F32Tile {
             }
         }
     }
-    __device__ __forceinline__ void fold(f32x4 &sm, f32x4 &er, const f32x4 (&c)[4])
+    __device__ __forceinline__ static void fold(f64x2 (&sm)[2], const f32x4 (&c)[4])
     {
-        const f32x4 v = (c[0] + c[1]) + (c[2] + c[3]), t = sm + v;
-        er += v - (t - sm);
-        sm = t;
+        const f32x4 v = (c[0] + c[1]) + (c[2] + c[3]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sm[q >> 1][q & 1] += (double)v[q];
     }
     // (the scheduling barriers keep the compiler from starting all blocks at once, which costs more registers than there
     // are; a block's sums are folded while the next block's products run)
@@ -82,20 +80,19 @@ struct F32Tile {
                 for (int h = 0; h < 4; ++h)
                     c[i & 1][h] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.a[h >> 1][a][2 * (h & 1) + q], f.b[h >> 1][b][2 * (h & 1) + q],
                                                                        c[i & 1][h], 0, 0, 0);
-            if (i > 0) fold(sum[(i - 1) / NB][(i - 1) % NB], err[(i - 1) / NB][(i - 1) % NB], c[(i & 1) ^ 1]);
+            if (i > 0) fold(acc[(i - 1) / NB][(i - 1) % NB], c[(i & 1) ^ 1]);
             __builtin_amdgcn_sched_barrier(0);
         }
-        fold(sum[NA - 1][NB - 1], err[NA - 1][NB - 1], c[(NA * NB - 1) & 1]);
+        fold(acc[NA - 1][NB - 1], c[(NA * NB - 1) & 1]);
     }
-    // the collected errors of a block's running sums, zero where they are no numbers
-    __device__ __forceinline__ f32x4 error(int a, int b) const
+    // a block's sums, rounded
+    __device__ __forceinline__ f32x4 total(int a, int b) const
     {
         f32x4 v;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = fabsf(err[a][b][q]) < INFINITY ? err[a][b][q] : 0.f;
+        for (int q = 0; q < 4; ++q) v[q] = (float)acc[a][b][q >> 1][q & 1];
         return v;
     }
-    __device__ __forceinline__ f32x4 total(int a, int b) const { return sum[a][b] + error(a, b); }
     // slice `slice` of `slices`: the 32-wide chunks slice, slice + slices, ..., starting at one that depends on rot (rows
     // are often a multiple of 4 KiB apart, which puts a chunk of every row on one L2 channel: workgroups that start at
     // different chunks spread over the channels)

@@ -17,9 +17,9 @@ constexpr int kF32Rows = 32;  // token rows per workgroup: two blocks of 16
 constexpr int kF32NB = kF32Rows / 16;
 constexpr int kF32GridTiles = 1 << 14;  // token tiles along grid x (at most 512 feature tiles of 256 threads each: 2^31 work items), more along y
 
-// this wave's slice of the sums of the first LIVE token blocks, left in part[a * NB + b][lane], their errors in err
+// this wave's slice of the sums of the first LIVE token blocks, left in part[2 (a * NB + b)][lane] and the row after it
 template <int NA, int NB, int LIVE>
-__device__ __forceinline__ void multiply_rows(f32x4 (*part)[64], f32x4 (*err)[64], const float *const (&pa)[NA], const float *const (&pb)[NB], int wave, int Kd)
+__device__ __forceinline__ void multiply_rows(f64x2 (*part)[64], const float *const (&pa)[NA], const float *const (&pb)[NB], int wave, int Kd)
 {
     const int lane = threadIdx.x & 63;
     const float *p[LIVE];
@@ -31,8 +31,8 @@ __device__ __forceinline__ void multiply_rows(f32x4 (*part)[64], f32x4 (*err)[64
     for (int a = 0; a < NA; ++a)
 #pragma unroll
         for (int b = 0; b < LIVE; ++b) {
-            part[a * NB + b][lane] = t.sum[a][b];
-            err[a * NB + b][lane] = t.error(a, b);
+            part[2 * (a * NB + b)][lane] = t.acc[a][b][0];
+            part[2 * (a * NB + b) + 1][lane] = t.acc[a][b][1];
         }
 }
 
@@ -46,7 +46,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void ffn_f32_kernel(const float *__
 {
     constexpr int NB = kF32NB;
     constexpr int NO = (GATEUP ? NA / 2 : NA) * NB;  // output blocks
-    __shared__ f32x4 s_part[kF32Waves][NA * NB][64], s_err[kF32Waves][NA * NB][64];
+    __shared__ f64x2 s_part[kF32Waves][NA * NB * 2][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15;
     const int tile_x = blockIdx.x / n_ft, ft = blockIdx.x - tile_x * n_ft, tile = blockIdx.y * kF32GridTiles + tile_x;
     const int4 loc = locate_rows<kF32Rows>(offsets, N, tile);
@@ -66,8 +66,8 @@ __global__ __launch_bounds__(kF32Threads, 2) void ffn_f32_kernel(const float *__
         pb[b] = tok + (size_t)(GATEUP ? min(max(sorted_slot[r] / K, 0), T - 1) : r) * Kd;  // a bad index must not fault
     }
     // only the blocks that hold rows are fetched and multiplied
-    if (rows > 16) multiply_rows<NA, NB, NB>(s_part[wave], s_err[wave], pa, pb, wave, Kd);
-    else multiply_rows<NA, NB, 1>(s_part[wave], s_err[wave], pa, pb, wave, Kd);
+    if (rows > 16) multiply_rows<NA, NB, NB>(s_part[wave], pa, pb, wave, Kd);
+    else multiply_rows<NA, NB, 1>(s_part[wave], pa, pb, wave, Kd);
     __syncthreads();
 
     // block (a, b): lane l holds features 4 (l / 16) .. + 3 of token l % 16
@@ -80,7 +80,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void ffn_f32_kernel(const float *__
             for (int k = 0; k < 4; ++k) {
                 double v = 0.0;
 #pragma unroll
-                for (int w = 0; w < kF32Waves; ++w) v += (double)s_part[w][blk][lane][k] + (double)s_err[w][blk][lane][k];
+                for (int w = 0; w < kF32Waves; ++w) v += s_part[w][2 * blk + (k >> 1)][lane][k & 1];
                 r[k] = (float)v;
             }
             return r;

@@ -82,3 +82,26 @@ def test_f32_more_token_tiles_than_one_grid_row():
         ref = (torch.nn.functional.silu(h @ wg[e].double().t()) * (h @ wu[e].double().t())) @ wd[e].double().t()
         got = y[a:b].cpu().double()
         assert (got - ref).norm() <= 1e-5 * ref.norm() and (got - ref).abs().max() <= 1e-5 * ref.abs().max()
+
+
+def test_chunk_sums_that_cancel():
+    """The running sums keep what an addition rounds off, also where the summand is the larger one: 2^28 comes and goes
+    between summands below one, which survive to fp32 accuracy.  (One product per 32-wide chunk, so that the sums within a
+    chunk are exact; whatever chunk a slice of 16 starts with, a small sum meets 2^28 in it.)"""
+    H, slices, per = 4096, 16, 8
+    g = torch.Generator().manual_seed(9)
+    big = 2.0 ** 28
+    pattern = torch.tensor([0.0, big, -big, 0.0, big, -big, 0.0, 0.0])
+    small = torch.rand(per, slices, generator=g) * (pattern == 0)[:, None] / slices
+    wr = torch.zeros(2, H)
+    wr[0, ::32] = (pattern[:, None] + small).flatten()  # chunk i * slices + s is the i-th of slice s
+    x = torch.ones(3, H)
+    d = zeda.make_desc(3, H, 64, 2, 0, 2, "f32")
+    ids = torch.full((3, 2), -1, dtype=torch.int32, device="cuda")
+    gates = torch.empty((3, 2), device="cuda")
+    zeda.zeda_route(d, x.cuda(), wr.cuda(), None, ids, gates)
+    torch.cuda.synchronize()
+    logit = small.double().sum()
+    assert logit > 1 and (ids.cpu() == torch.tensor([0, 1], dtype=torch.int32)).all()
+    # (16 slices of four errors, added in fp32: within 1e-6)
+    np.testing.assert_allclose(gates.cpu().double().numpy()[:, 0], float(1 / (1 + torch.exp(-logit))), rtol=2e-6)
