@@ -36,26 +36,33 @@ struct F32Tile {
 #pragma unroll
             for (int b = 0; b < NB; ++b) acc[a][b][0] = acc[a][b][1] = f64x2{0., 0.};
     }
-    // pa, pb: this lane's rows (at k = 0); the 32 k from k0 on; past Kd (a multiple of 4) both operands are zero
+    // pa, pb: this lane's rows (at k = 0); the 32 k from k0 on.  Past Kd (a multiple of 4) the rows' first values stand in
+    // until mask() clears them: a select here would wait for the loads where they are issued
     __device__ __forceinline__ static void load(Frags &f, const float *const (&pa)[NA], const float *const (&pb)[NB], int k0, int Kd)
     {
         const int kl = k0 + 4 * ((threadIdx.x & 63) >> 4);
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            const int k = kl + 16 * s;
-            const bool in = k < Kd;
-            const int kc = in ? k : 0;
-            const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+            const int k = kl + 16 * s, kc = k < Kd ? k : 0;
 #pragma unroll
-            for (int a = 0; a < NA; ++a) {
-                const f32x4 v = *reinterpret_cast<const f32x4 *>(pa[a] + kc);
-                f.a[s][a] = in ? v : zero;
-            }
+            for (int a = 0; a < NA; ++a) f.a[s][a] = *reinterpret_cast<const f32x4 *>(pa[a] + kc);
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const f32x4 v = *reinterpret_cast<const f32x4 *>(pb[b] + kc);
-                f.b[s][b] = in ? v : zero;
-            }
+            for (int b = 0; b < NB; ++b) f.b[s][b] = *reinterpret_cast<const f32x4 *>(pb[b] + kc);
+        }
+    }
+    // zero both operands past Kd in the chunk at k0
+    __device__ __forceinline__ static void mask(Frags &f, int k0, int Kd)
+    {
+        if (k0 + 32 <= Kd) return;
+        const int kl = k0 + 4 * ((threadIdx.x & 63) >> 4);
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const bool in = kl + 16 * s < Kd;
+#pragma unroll
+            for (int a = 0; a < NA; ++a) f.a[s][a] = in ? f.a[s][a] : zero;
+#pragma unroll
+            for (int b = 0; b < NB; ++b) f.b[s][b] = in ? f.b[s][b] : zero;
         }
     }
     __device__ __forceinline__ static void fold(f64x2 (&sm)[2], const f32x4 (&c)[4])
@@ -106,12 +113,14 @@ struct F32Tile {
         Frags cur, nxt;
         load(cur, pa, pb, k0, Kd);
         for (int i = 1; i < n; ++i) {
-            k0 += step;
-            if (k0 >= end) k0 = 32 * slice;
-            load(nxt, pa, pb, k0, Kd);
+            const int k1 = k0 + step < end ? k0 + step : 32 * slice;
+            load(nxt, pa, pb, k1, Kd);
+            mask(cur, k0, Kd);
             multiply(cur);
             cur = nxt;
+            k0 = k1;
         }
+        mask(cur, k0, Kd);
         multiply(cur);
     }
 };
