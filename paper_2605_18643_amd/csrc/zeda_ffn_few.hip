@@ -86,7 +86,8 @@ __device__ __forceinline__ void few_multiply_rows(int rows, f32x4 (*part)[64], c
 // GATEUP: tok = x[T,Kd], w0 = W_gate[N,F,Kd], w1 = W_up, out = act[S,F];  else tok = act[S,Kd], w0 = W_down[N,F,Kd],
 // out = y_slot[S,F].  Kd a multiple of 64, F of 16 NF.  Up to 16 NB token rows (NB 2 or 4).  Blocks past the last token
 // tile return at once.
-template <bool GATEUP, bool TILED, int NF, int NB, int DEPTH>
+// MULTI: an expert may have more rows than a workgroup takes.
+template <bool GATEUP, bool TILED, int NF, int NB, int DEPTH, bool MULTI>
 __global__ __launch_bounds__(kFewThreads) void ffn_few_kernel(const bf16_t *__restrict__ tok, const bf16_t *__restrict__ w0,
                                                               const bf16_t *__restrict__ w1, const int32_t *__restrict__ offsets,
                                                               const int32_t *__restrict__ sorted_slot, bf16_t *__restrict__ out,
@@ -119,7 +120,7 @@ __global__ __launch_bounds__(kFewThreads) void ffn_few_kernel(const bf16_t *__re
     const int start = loc.x * 5;
     // An expert of several token tiles has its weights fetched by each of them: they are meant to stay in the caches then.
     // (N=16, I=2048, K=1, 64 tokens, loads with one hot expert of 39 rows: 0.88 -> 0.83 of the tile kernel's time)
-    if (loc.w <= 16 * NB) few_multiply_rows<TILED, NA, NB, DEPTH, true>(loc.z, s_part[wave], pa, pt, wstep, wave, start, Kd);
+    if (!MULTI || loc.w <= 16 * NB) few_multiply_rows<TILED, NA, NB, DEPTH, true>(loc.z, s_part[wave], pa, pt, wstep, wave, start, Kd);
     else few_multiply_rows<TILED, NA, NB, DEPTH, false>(loc.z, s_part[wave], pa, pt, wstep, wave, start, Kd);
     __syncthreads();
 
@@ -189,7 +190,7 @@ int ffn_few_blocks(const zeda_layer_desc *d)
     return slots <= (items <= 80 ? 40 : d->Z > 0 ? 32 : 25) * experts ? 4 : 0;
 }
 
-template <bool GATEUP, bool TILED, int NB>
+template <bool GATEUP, bool TILED, int NB, bool MULTI>
 static int launch_blocks(const zeda_layer_desc *d, const void *tok, const void *w0, const void *w1, const int32_t *offsets,
                          const int32_t *sorted_slot, void *out, hipStream_t s)
 {
@@ -198,17 +199,21 @@ static int launch_blocks(const zeda_layer_desc *d, const void *tok, const void *
     constexpr int NF = GATEUP ? 1 : 2, DEPTH = 3;
     const int Kd = GATEUP ? d->H : d->I, F = GATEUP ? d->I : d->H, n_ft = F / (16 * NF);
     const int S = d->T * d->K, tiles = (S < d->N ? S : d->N) + S / (16 * NB);  // at most this many token tiles
-    ffn_few_kernel<GATEUP, TILED, NF, NB, DEPTH><<<(unsigned)tiles * n_ft, kFewThreads, 0, s>>>(
+    ffn_few_kernel<GATEUP, TILED, NF, NB, DEPTH, MULTI><<<(unsigned)tiles * n_ft, kFewThreads, 0, s>>>(
         (const bf16_t *)tok, (const bf16_t *)w0, (const bf16_t *)w1, offsets, sorted_slot, (bf16_t *)out, d->N, d->K, Kd, F, n_ft, d->T);
     return last_launch_status();
 }
 
+// With a few slots per expert, an expert of several token tiles is one of many whose weights are fetched, and the second copy of
+// the multiplication costs all workgroups 0.7 % (N=128, I=768, H=2048, 64 tokens row-major: 230.2 -> 233.5 us).
 template <bool GATEUP, bool TILED>
 static int launch(const zeda_layer_desc *d, const void *tok, const void *w0, const void *w1, const int32_t *offsets,
                   const int32_t *sorted_slot, void *out, hipStream_t s)
 {
-    return ffn_few_blocks(d) == 2 ? launch_blocks<GATEUP, TILED, 2>(d, tok, w0, w1, offsets, sorted_slot, out, s)
-                                  : launch_blocks<GATEUP, TILED, 4>(d, tok, w0, w1, offsets, sorted_slot, out, s);
+    if (ffn_few_blocks(d) == 4) return launch_blocks<GATEUP, TILED, 4, true>(d, tok, w0, w1, offsets, sorted_slot, out, s);
+    const bool multi = d->T > 32 && (int64_t)d->T * d->K > 8 * ((int64_t)d->N + d->Z);
+    return multi ? launch_blocks<GATEUP, TILED, 2, true>(d, tok, w0, w1, offsets, sorted_slot, out, s)
+                 : launch_blocks<GATEUP, TILED, 2, false>(d, tok, w0, w1, offsets, sorted_slot, out, s);
 }
 
 int launch_gateup_few(const zeda_layer_desc *d, const void *x, const void *wg, const void *wu, const int32_t *offsets,

@@ -34,6 +34,9 @@ CASES = [
     dict(T=209, H=768, I=512, N=60, Z=4, K=4),
     dict(T=100, H=768, I=1024, N=100, Z=60, K=8),
     dict(T=101, H=768, I=1024, N=100, Z=60, K=8),
+    # both sides of 8 slots per expert (weights of experts with several token tiles kept in the caches or not)
+    dict(T=128, H=768, I=512, N=30, Z=2, K=2),
+    dict(T=129, H=768, I=512, N=30, Z=2, K=2),
     # decode batches: three and four live token blocks; both sides of the rule beyond which the 64-row tile takes over; a
     # reduction too short for the waves
     dict(T=50, H=1024, I=1024, N=8, Z=0, K=6),
