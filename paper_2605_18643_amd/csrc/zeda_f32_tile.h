@@ -12,8 +12,8 @@
 // Precision: the 32 products of a chunk are added as four sums of eight in the matrix unit and a tree over the four; chunk
 // sums and the FFN's slices are added in 64 bits and rounded once, so that the error is the chunks' own, however many there
 // are.  (Sums of sixteen per chunk and a plain sum over the slices end farther from the 64-bit result than the sums over 64
-// lanes that these kernels replaced.  A compensated fp32 sum that is exact whichever summand
-// is the larger one takes six additions where this takes a conversion and an addition: 6 % more of the FFN, 2 % of the router.)
+// lanes that these kernels replaced.  A compensated fp32 sum that is exact whichever summand is the larger one takes six
+// additions where this takes a conversion and an addition: 6 % more of the FFN, 2 % of the router.)
 #pragma once
 #include "zeda_internal.h"
 

@@ -3,9 +3,9 @@
 //   down:     y_slot[r,h] = <act[r], W_down[e][h]>
 // A workgroup owns up to 32 rows of one expert and NA blocks of 16 weight rows (gate and up blocks alternate); its four waves
 // split the reduction dimension, and their sums meet in LDS in wave order.  Any H and I that are multiples of 4.
-// Bound by memory on paper (513 tokens, H=1024, I=512, 32 experts: 134 MB of gate/up weights); measured 70 us for gate/up
-// and 41 us for down, a third of the HBM rate: fp32 products (20 us of matrix time), the sums' bookkeeping and the 64-byte
-// row pieces share the rest.  One workgroup per row, which re-read an expert's weights for every row, took 658 and 627 us.
+// Bound by memory on paper (513 tokens, H=1024, I=512, 32 experts: 134 MB of gate/up weights); measured 60 us for gate/up and
+// 34 us for down, 40 % of the HBM rate: fp32 products (20 us of matrix time), 64-byte row pieces and two waves per SIMD share
+// the rest.  One workgroup per row, which re-read an expert's weights for every row, took 658 and 627 us.
 #include "zeda_f32_tile.h"
 #include "zeda_place.h"
 
