@@ -162,8 +162,10 @@ __global__ __launch_bounds__(kFewThreads) void ffn_few_kernel(const bf16_t *__re
 //  - short reductions leave the four waves a chunk or two each: N=64, I=512, H=512: 4 rows 1.00 / 0.95, 8 rows 1.07 / 1.01;
 //    N=256, I=256, H=1024: half a slot per expert 0.97 / 1.0, one 1.04 / 1.01 and 1.09 / 1.17 with Zipf loads;
 //  - longer batches on a chip that the tile kernel fills: N=128, Z=32, I=768, 5 slots per expert: 0.95 / 1.01 with half of the
-//    slots on zero experts (Zipf loads 0.90 / 0.94), 1.09 / 1.04 with a fifth of them; without zero experts and from H = 4096
-//    on the row-major loads fall behind (N=192, I=2048, H=4096, 3 rows 1.09-1.17 / 0.96-1.01).  N=128, I=384, 384 items: 5 slots
+//    slots on zero experts (Zipf loads 0.90 / 0.94), 1.09 / 1.04 with a fifth of them.  Without zero experts: I >= 1024 0.86-1.02
+//    / 0.88-1.03 (N=100, H=1536), N=128, I=768 0.95 / 0.99 at H = 1024 but 1.03 / 1.03 at H = 2048, N=200, I=512 0.92-1.08 / 0.90-1.00
+//    from machine to machine; from H = 4096 on the row-major loads fall behind (N=192, I=2048, H=4096, 3 rows 1.09-1.17 / 0.96-1.01).
+//    N=128, I=384, 384 items: 5 slots
 //    0.85 / 0.99, 10 slots 0.90 / 1.05;
 //  - between one and two rounds of 256 CUs the tile kernel idles: N=48, I=768, 288 items: 18 rows 0.80 / 0.88, 25 rows 0.87 /
 //    0.94, 30 rows 0.82 / 0.93 with four blocks, 1.02 / 1.11 with two; N=24, I=448, 96 items: 30 rows 0.98 / 1.07 (20 of them
@@ -183,7 +185,7 @@ int ffn_few_blocks(const zeda_layer_desc *d)
         if (d->I >= 384) return slots <= 4 * experts ? 2 : 0;
         return (hit_items <= 128 ? 2 * slots <= 3 * d->N : slots < d->N) ? 2 : 0;
     }
-    if (items > 512) return d->Z > 0 && d->H < 4096 && wide && slots <= 5 * experts ? 2 : 0;
+    if (items > 512) return (d->Z > 0 || d->I >= 1024 || d->H <= 1024) && d->H < 4096 && wide && slots <= 5 * experts ? 2 : 0;
     if (items > 320) return slots <= (wide ? 5 : 2) * experts ? 2 : 0;
     if ((items > 192 && items <= 256) || (items > 64 && !wide)) return slots <= 13 * experts ? 2 : 0;
     if (slots <= 25 * experts) return 2;

@@ -34,6 +34,8 @@ CASES = [
     dict(T=209, H=768, I=512, N=60, Z=4, K=4),
     dict(T=100, H=768, I=1024, N=100, Z=60, K=8),
     dict(T=101, H=768, I=1024, N=100, Z=60, K=8),
+    dict(T=80, H=768, I=1088, N=64, Z=0, K=4),
+    dict(T=81, H=768, I=1088, N=64, Z=0, K=4),
     # both sides of 8 slots per expert (weights of experts with several token tiles kept in the caches or not)
     dict(T=128, H=768, I=512, N=30, Z=2, K=2),
     dict(T=129, H=768, I=512, N=30, Z=2, K=2),
