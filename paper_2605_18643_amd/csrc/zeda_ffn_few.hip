@@ -165,8 +165,7 @@ __global__ __launch_bounds__(kFewThreads) void ffn_few_kernel(const bf16_t *__re
 //    slots on zero experts (Zipf loads 0.90 / 0.94), 1.09 / 1.04 with a fifth of them.  Without zero experts: I >= 1024 0.86-1.02
 //    / 0.88-1.03 (N=100, H=1536), N=128, I=768 0.95 / 0.99 at H = 1024 but 1.03 / 1.03 at H = 2048, N=200, I=512 0.92-1.08 / 0.90-1.00
 //    from machine to machine; from H = 4096 on the row-major loads fall behind (N=192, I=2048, H=4096, 3 rows 1.09-1.17 / 0.96-1.01).
-//    N=128, I=384, 384 items: 5 slots
-//    0.85 / 0.99, 10 slots 0.90 / 1.05;
+//    N=128, I=384, 384 items: 5 slots 0.85 / 0.99, 10 slots 0.90 / 1.05;
 //  - between one and two rounds of 256 CUs the tile kernel idles: N=48, I=768, 288 items: 18 rows 0.80 / 0.88, 25 rows 0.87 /
 //    0.94, 30 rows 0.82 / 0.93 with four blocks, 1.02 / 1.11 with two; N=24, I=448, 96 items: 30 rows 0.98 / 1.07 (20 of them
 //    real: 0.91 / 0.97) with four, 1.17 with two; N=12, I=704, 72 items: 40 rows 0.90 / 0.98.  With one full round it does not:
