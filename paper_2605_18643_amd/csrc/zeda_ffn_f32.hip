@@ -3,9 +3,11 @@
 //   down:     y_slot[r,h] = <act[r], W_down[e][h]>
 // A workgroup owns up to 32 rows of one expert and NA blocks of 16 weight rows (gate and up blocks alternate); its four waves
 // split the reduction dimension, and their sums meet in LDS in wave order.  Any H and I that are multiples of 4.
-// Bound by memory on paper (513 tokens, H=1024, I=512, 32 experts: 134 MB of gate/up weights); measured 60 us for gate/up and
-// 34 us for down, 40 % of the HBM rate: fp32 products (20 us of matrix time), 64-byte row pieces and two waves per SIMD share
-// the rest.  One workgroup per row, which re-read an expert's weights for every row, took 658 and 627 us.
+// What bounds it: splitting the operands and adding up the chunks on the vector unit, then the weights (513 tokens, H=1024,
+// I=512, 32 experts: 134 MB of gate/up weights).  There gate/up takes 48 us and down 27; with the fp32 matrix instruction and
+// operands loaded straight into its registers 60 and 35.  Three workgroups per CU: with 48 and 64 rows a workgroup (two per CU) the
+// last round is nearly empty or registers spill (53 + 31 and 41 + 26 us).
+#include "zeda_f32_split.h"
 #include "zeda_f32_tile.h"
 #include "zeda_place.h"
 
@@ -97,7 +99,134 @@ __global__ __launch_bounds__(kF32Threads, 2) void ffn_f32_kernel(const float *__
     }
 }
 
-template <bool GATEUP, int NA>
+constexpr int kF32Slots = 6;            // ring blocks a wave keeps in flight
+
+// GATEUP: tok = x[T,Kd], w0 = W_gate[N,F,Kd], w1 = W_up, out = act[S,F];  else tok = act[S,Kd], w0 = W_down[N,F,Kd],
+// out = y_slot[S,F].  n_ft feature tiles per token tile of up to 16 NB rows; blocks past the last token tile return at once.
+template <bool GATEUP, int NA, int NB>
+struct F32Ffn {
+    static constexpr int NF = GATEUP ? NA / 2 : NA;  // feature blocks: gate and up blocks alternate
+    static constexpr int RING = WaveRing<kF32Slots>::BYTES;
+    static constexpr int PART = NA * 2 * 64 * (int)sizeof(f64x2);  // a wave's sums of one token block
+    static constexpr int HUGE_OFF = kF32Waves * (RING > PART ? RING : PART);  // the rings, then the waves' sums; then a byte per row:
+    static constexpr int HUGE_W = 16 * NB, HUGE = HUGE_W + 16 * NA;           // does it hold an element past kSplitMax (token rows first)
+    static constexpr int LDS_BYTES = HUGE_OFF + HUGE;
+    typedef f64x2 (*Part)[NA * 2][64];
+
+    // the tile's rows are out's rows first .. first + rows - 1, in LIVE blocks of 16; features f0 ..; tok_row(r): row r's token values
+    template <int LIVE, typename TokRow>
+    __device__ __forceinline__ static void run(unsigned char *lds, const float *w0, const float *w1, const uint32_t (&wo)[NA][2],
+                                               const float *const (&pb)[NB][2], int Kd, float *__restrict__ out, int first, int rows, int f0, int F,
+                                               const TokRow &tok_row)
+    {
+        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15;
+        const float *p[LIVE][2];
+#pragma unroll
+        for (int b = 0; b < LIVE; ++b) { p[b][0] = pb[b][0]; p[b][1] = pb[b][1]; }
+        const uint8_t *huge = lds + HUGE_OFF;
+        F32Split<NA, LIVE, kF32Slots> t;
+        t.run(lds_addr(lds) + wave * RING, w0, w1, wo, p, lds_addr(huge), lds_addr(huge + HUGE_W), wave, kF32Waves, (int)blockIdx.x * 3, Kd);
+        Part part = reinterpret_cast<Part>(lds);
+#pragma unroll
+        for (int b = 0; b < LIVE; ++b) {
+            __syncthreads();  // everyone is done with the rings, and with the sums of the block before
+#pragma unroll
+            for (int a = 0; a < NA; ++a) {
+                part[wave][2 * a][lane] = t.acc[a][b][0];
+                part[wave][2 * a + 1][lane] = t.acc[a][b][1];
+            }
+            __syncthreads();
+            // block (a, b): lane l holds features 4 (l / 16) .. + 3 of token l % 16
+            const int r = 16 * b + l16;
+            for (int fb = wave; fb < NF; fb += kF32Waves) {
+                const int f = f0 + 16 * fb + 4 * (lane >> 4);
+                if (r >= rows || f >= F) continue;
+                auto total = [&](int a) {  // the waves' sums, in wave order, rounded once
+                    f32x4 v;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        double sum = 0.0;
+#pragma unroll
+                        for (int w = 0; w < kF32Waves; ++w) sum += part[w][2 * a + (k >> 1)][lane][k & 1];
+                        v[k] = (float)sum;
+                    }
+                    return v;
+                };
+                f32x4 v;
+                if (GATEUP) {
+                    const f32x4 g = total(2 * fb), u = total(2 * fb + 1);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) v[k] = swiglu(g[k], u[k]);
+                } else {
+                    v = total(fb);
+                }
+                *reinterpret_cast<f32x4 *>(out + (size_t)(first + r) * F + f) = v;
+            }
+        }
+        // What depends on a row with an element past kSplitMax came out as no number: a thread adds its products up in 64 bits
+        // (a value at a time: this is for infinities, not for speed).
+        const int tid = threadIdx.x;
+        if (!__syncthreads_or(tid < HUGE ? huge[tid] : 0)) return;  // (the stores above have been waited for)
+        for (int i = tid; i < rows * 16 * NF; i += kF32Threads) {
+            const int r = i / (16 * NF), c = i - r * (16 * NF), fb = c / 16, f = f0 + c;
+            if (f >= F) continue;
+            const uint8_t *hw = huge + HUGE_W + 16 * (GATEUP ? 2 * fb : fb) + c % 16;
+            if (!(huge[r] | hw[0] | (GATEUP ? hw[16] : 0))) continue;
+            const float *x = tok_row(r), *a = w0 + (size_t)f * Kd, *u = w1 + (size_t)f * Kd;
+            double s0 = 0.0, s1 = 0.0;
+            for (int k = 0; k < Kd; ++k) {
+                s0 += (double)x[k] * a[k];
+                if (GATEUP) s1 += (double)x[k] * u[k];
+            }
+            out[(size_t)(first + r) * F + f] = GATEUP ? swiglu((float)s0, (float)s1) : (float)s0;
+        }
+    }
+    __device__ __forceinline__ static float swiglu(float g, float u) { return g / (1.f + expf(-g)) * u; }
+};
+
+template <bool GATEUP, int NA, int NB>
+__global__ __launch_bounds__(kF32Threads, 3) void ffn_f32_split_kernel(const float *__restrict__ tok, const float *__restrict__ w0,
+                                                              const float *__restrict__ w1, const int32_t *__restrict__ offsets,
+                                                              const int32_t *__restrict__ sorted_slot, float *__restrict__ out,
+                                                              int N, int K, int Kd, int F, int n_ft, int T)
+{
+    typedef F32Ffn<GATEUP, NA, NB> C;
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[C::LDS_BYTES];
+    const int lane = threadIdx.x & 63, r8 = lane >> 3;
+    const int tile_x = blockIdx.x / n_ft, ft = blockIdx.x - tile_x * n_ft, tile = blockIdx.y * kF32GridTiles + tile_x;
+    const int4 loc = locate_rows<16 * NB>(offsets, N, tile);
+    const int rows = loc.z;
+    if (rows == 0) return;
+    static_assert(C::HUGE <= kF32Threads, "a thread per row");
+    if (threadIdx.x < C::HUGE) lds[C::HUGE_OFF + threadIdx.x] = 0;
+    __syncthreads();
+    const int f0 = ft * 16 * C::NF;
+
+    auto tok_row = [&](int row) {
+        const int r = loc.y + row;
+        return tok + (size_t)(GATEUP ? min(max(sorted_slot[r] / K, 0), T - 1) : r) * Kd;  // a bad index must not fault
+    };
+    const float *pb[NB][2];
+    uint32_t wo[NA][2];  // (an expert's matrix has 604 MB at most)
+    w0 += (size_t)loc.x * F * Kd;
+    w1 = GATEUP ? w1 + (size_t)loc.x * F * Kd : w0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int a = 0; a < NA; ++a) {
+            const int f = min(f0 + 16 * (GATEUP ? a / 2 : a) + 8 * h + r8, F - 1);  // rows past F repeat the last one (never stored)
+            wo[a][h] = (uint32_t)f * Kd * 4;
+        }
+#pragma unroll
+        for (int b = 0; b < NB; ++b) pb[b][h] = tok_row(min(16 * b + 8 * h + r8, rows - 1));
+    }
+    // only the blocks that hold rows are fetched and multiplied
+    if (rows > 16) C::template run<2>(lds, w0, w1, wo, pb, Kd, out, loc.y, rows, f0, F, tok_row);
+    else C::template run<1>(lds, w0, w1, wo, pb, Kd, out, loc.y, rows, f0, F, tok_row);
+}
+
+// SPLIT: the kernel for many rows per expert
+template <bool GATEUP, int NA, bool SPLIT>
 static int launch(const zeda_layer_desc *d, const float *tok, const float *w0, const float *w1, const int32_t *offsets,
                   const int32_t *sorted_slot, float *out, hipStream_t s)
 {
@@ -105,10 +234,19 @@ static int launch(const zeda_layer_desc *d, const float *tok, const float *w0, c
     const int n_ft = ceil_div(F, 16 * (GATEUP ? NA / 2 : NA));
     const int S = d->T * d->K, tiles = (S < d->N ? S : d->N) + S / kF32Rows;  // at most this many token tiles
     const dim3 grid((unsigned)(tiles < kF32GridTiles ? tiles : kF32GridTiles) * n_ft, ceil_div(tiles, kF32GridTiles));
-    ffn_f32_kernel<GATEUP, NA><<<grid, kF32Threads, 0, s>>>(tok, w0, w1, offsets, sorted_slot, out, d->N, d->K, Kd,
-                                                                              F, n_ft, d->T);
+    if constexpr (SPLIT)
+        ffn_f32_split_kernel<GATEUP, NA, kF32NB><<<grid, kF32Threads, 0, s>>>(tok, w0, w1, offsets, sorted_slot, out, d->N, d->K, Kd, F, n_ft, d->T);
+    else
+        ffn_f32_kernel<GATEUP, NA><<<grid, kF32Threads, 0, s>>>(tok, w0, w1, offsets, sorted_slot, out, d->N, d->K, Kd, F, n_ft, d->T);
     return last_launch_status();
 }
+
+// Where the split kernel is the faster one, by the slots per expert of the whole pool (whole layer, its time over the other's):
+// H=1024, I=512, N=32, K=4: 4 slots 1.01, 8 0.98, 16 0.91, 32 0.76, 128 0.75; with Z=8: 6.4 1.01, 12.8 0.95, 51 0.86; H=2048, I=1024,
+// N=16: 6.4 0.96, 19 0.88, 102 0.74; H=768, N=48: 9 0.96, 27 0.82; H=512, I=512, N=16: 8 0.99, 24 0.93, 128 0.88.  With a row or two per
+// expert it is 3 us slower (one more turn through LDS before the first product; H=820, I=360, one token: 30 -> 35 us), as it is
+// throughout for layers that are not wide.
+static bool f32_many_rows(const zeda_layer_desc *d) { return (int64_t)d->T * d->K >= 8 * ((int64_t)d->N + d->Z); }
 
 // Four weight blocks per workgroup halve the token reads per weight byte; two make twice the workgroups, for layers whose
 // experts are too few and too narrow to fill the device otherwise.
@@ -118,8 +256,9 @@ static int launch_any(const zeda_layer_desc *d, const void *tok, const void *w0,
 {
     const int F = GATEUP ? 2 * d->I : d->H;
     const bool wide = (int64_t)d->N * F >= 256 * 64;
-    return wide ? launch<GATEUP, 4>(d, (const float *)tok, (const float *)w0, (const float *)w1, offsets, sorted_slot, (float *)out, s)
-                : launch<GATEUP, 2>(d, (const float *)tok, (const float *)w0, (const float *)w1, offsets, sorted_slot, (float *)out, s);
+    if (wide && f32_many_rows(d)) return launch<GATEUP, 4, true>(d, (const float *)tok, (const float *)w0, (const float *)w1, offsets, sorted_slot, (float *)out, s);
+    return wide ? launch<GATEUP, 4, false>(d, (const float *)tok, (const float *)w0, (const float *)w1, offsets, sorted_slot, (float *)out, s)
+                : launch<GATEUP, 2, false>(d, (const float *)tok, (const float *)w0, (const float *)w1, offsets, sorted_slot, (float *)out, s);
 }
 
 int launch_gateup_f32(const zeda_layer_desc *d, const void *x, const void *wg, const void *wu, const int32_t *offsets,
