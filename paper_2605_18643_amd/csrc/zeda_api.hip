@@ -109,22 +109,28 @@ static int forward_impl(const zeda_layer_desc *desc, const void *x, const void *
         for (int i = 1; i <= ZEDA_NUM_STAGES; ++i) mark(i);
         return rc;
     }
-    if (route_places(desc)) {
-        const PlaceOut place = {offsets, sorted_slot, slot_to_row, num_real, num_real_out};
-        if ((rc = launch_route(desc, x, w_router, router_bias, ids, gates, route_ws, nullptr, &place, s)) != ZEDA_OK) return rc;
+    const PlaceOut place = {offsets, sorted_slot, slot_to_row, num_real, num_real_out};
+    // Few slots: the gate/up kernel places them, and selects for a handful of tokens (the tables it leaves are the same).
+    TilePlace tp = {ids, place, gates, nullptr, router_bias, 0, 0, 0, desc->N + desc->Z, desc->gate_norm};
+    const bool places = gateup_places(desc);
+    if (places) {
+        if ((rc = launch_route(desc, x, w_router, router_bias, ids, gates, route_ws, nullptr, nullptr, gateup_selects(desc) ? &tp : nullptr, s)) != ZEDA_OK) return rc;
+        mark(1 + ZEDA_STAGE_ROUTE);
+    } else if (route_places(desc)) {
+        if ((rc = launch_route(desc, x, w_router, router_bias, ids, gates, route_ws, nullptr, &place, nullptr, s)) != ZEDA_OK) return rc;
         mark(1 + ZEDA_STAGE_ROUTE);
     } else if (fused_counts(desc)) {
         uint8_t *cnt8 = (uint8_t *)(w + L.dispatch_ws);
-        if ((rc = launch_route(desc, x, w_router, router_bias, ids, gates, route_ws, cnt8, nullptr, s)) != ZEDA_OK) return rc;
+        if ((rc = launch_route(desc, x, w_router, router_bias, ids, gates, route_ws, cnt8, nullptr, nullptr, s)) != ZEDA_OK) return rc;
         mark(1 + ZEDA_STAGE_ROUTE);
         if ((rc = launch_dispatch_counts(desc, ids, cnt8, offsets, sorted_slot, slot_to_row, num_real, num_real_out, s)) != ZEDA_OK) return rc;
     } else {
-        if ((rc = launch_route(desc, x, w_router, router_bias, ids, gates, route_ws, nullptr, nullptr, s)) != ZEDA_OK) return rc;
+        if ((rc = launch_route(desc, x, w_router, router_bias, ids, gates, route_ws, nullptr, nullptr, nullptr, s)) != ZEDA_OK) return rc;
         mark(1 + ZEDA_STAGE_ROUTE);
         if ((rc = launch_dispatch(desc, ids, offsets, sorted_slot, slot_to_row, num_real, num_real_out, w + L.dispatch_ws, s)) != ZEDA_OK) return rc;
     }
     mark(1 + ZEDA_STAGE_DISPATCH);
-    if ((rc = launch_gateup(desc, x, w_gate, w_up, offsets, sorted_slot, act, s)) != ZEDA_OK) return rc;
+    if ((rc = launch_gateup(desc, x, w_gate, w_up, offsets, sorted_slot, act, places ? &tp : nullptr, s)) != ZEDA_OK) return rc;
     mark(1 + ZEDA_STAGE_GATEUP);
     if ((rc = launch_down(desc, act, w_down, offsets, y_slot, s)) != ZEDA_OK) return rc;
     mark(1 + ZEDA_STAGE_DOWN);
@@ -356,7 +362,7 @@ int zeda_route(const zeda_layer_desc *desc, const void *x, const void *w_router,
     if (ws && ws_bytes < route_ws_bytes(desc)) return ZEDA_EWORKSPACE;
     if (desc->T == 0) return ZEDA_OK;
     float *partial = (ws && route_ws_bytes(desc)) ? (float *)ws : nullptr;
-    return launch_route(desc, x, w_router, router_bias, topk_ids, topk_gates, partial, nullptr, nullptr, (hipStream_t)stream);
+    return launch_route(desc, x, w_router, router_bias, topk_ids, topk_gates, partial, nullptr, nullptr, nullptr, (hipStream_t)stream);
 }
 
 int zeda_dispatch(const zeda_layer_desc *desc, const int32_t *topk_ids, int32_t *expert_offsets, int32_t *sorted_slot,
@@ -408,7 +414,7 @@ int zeda_expert_ffn(const zeda_layer_desc *desc, const void *x, const void *w_ga
     if (desc->T == 0) return ZEDA_OK;
     // num_real equals expert_offsets[N]; the kernels read the offsets, so R never crosses to the host.
     hipStream_t s = (hipStream_t)stream;
-    if ((rc = launch_gateup(desc, x, w_gate, w_up, expert_offsets, sorted_slot, ws, s)) != ZEDA_OK) return rc;
+    if ((rc = launch_gateup(desc, x, w_gate, w_up, expert_offsets, sorted_slot, ws, nullptr, s)) != ZEDA_OK) return rc;
     return launch_down(desc, ws, w_down, expert_offsets, y_slot, s);
 }
 

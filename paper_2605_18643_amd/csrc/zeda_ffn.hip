@@ -42,11 +42,11 @@ int launch_pack_weights(const zeda_layer_desc *d, const void *w, void *out, bool
 }
 
 int launch_gateup(const zeda_layer_desc *d, const void *x, const void *wg, const void *wu, const int32_t *offsets,
-                  const int32_t *sorted_slot, void *act, hipStream_t s)
+                  const int32_t *sorted_slot, void *act, const TilePlace *tp, hipStream_t s)
 {
-    if (d->dtype == ZEDA_BF16 && ffn_few_blocks(d)) return launch_gateup_few(d, x, wg, wu, offsets, sorted_slot, act, s);
+    if (d->dtype == ZEDA_BF16 && ffn_few_blocks(d)) return launch_gateup_few(d, x, wg, wu, offsets, sorted_slot, act, tp, s);
     if (d->dtype == ZEDA_BF16) return launch_bf16<true>(d, x, wg, wu, offsets, sorted_slot, act, s);
-    return launch_gateup_f32(d, x, wg, wu, offsets, sorted_slot, act, s);
+    return launch_gateup_f32(d, x, wg, wu, offsets, sorted_slot, act, tp, s);
 }
 
 }  // namespace zeda

@@ -19,6 +19,15 @@ constexpr int kF32Rows = 32;  // token rows per workgroup: two blocks of 16
 constexpr int kF32NB = kF32Rows / 16;
 constexpr int kF32GridTiles = 1 << 14;  // token tiles along grid x (at most 512 feature tiles of 256 threads each: 2^31 work items), more along y
 
+// where token tile `tile` is; PLACE: found from the ids of all slots, whose tables the first feature tiles write
+template <bool PLACE>
+__device__ __forceinline__ int4 locate_f32(const int32_t *offsets, int N, int K, int T, int tile, int ft, TilePlaceLds<PLACE ? kF32Rows : 1> &s, const TilePlace &tp)
+{
+    static_assert(kF32Threads == kTileThreads, "");
+    if constexpr (PLACE) return place_tile<kF32Rows>([&](int slot) { return tp.ids[slot]; }, T * K, N, tile, ft == 0, tile == 0 && ft == 0, s, tp.out);
+    else return locate_rows<kF32Rows>(offsets, N, tile);
+}
+
 // this wave's slice of the sums of the first LIVE token blocks, left in part[2 (a * NB + b)][lane] and the row after it
 template <int NA, int NB, int LIVE>
 __device__ __forceinline__ void multiply_rows(f64x2 (*part)[64], const float *const (&pa)[NA], const float *const (&pb)[NB], int wave, int Kd)
@@ -40,18 +49,20 @@ __device__ __forceinline__ void multiply_rows(f64x2 (*part)[64], const float *co
 
 // GATEUP: tok = x[T,Kd], w0 = W_gate[N,F,Kd], w1 = W_up, out = act[S,F];  else tok = act[S,Kd], w0 = W_down[N,F,Kd],
 // out = y_slot[S,F].  n_ft feature tiles per token tile; blocks past the last token tile return at once.
-template <bool GATEUP, int NA>
+// PLACE: the workgroup places the slots itself, from their ids (tp).
+template <bool GATEUP, int NA, bool PLACE>
 __global__ __launch_bounds__(kF32Threads, 2) void ffn_f32_kernel(const float *__restrict__ tok, const float *__restrict__ w0,
                                                               const float *__restrict__ w1, const int32_t *__restrict__ offsets,
                                                               const int32_t *__restrict__ sorted_slot, float *__restrict__ out,
-                                                              int N, int K, int Kd, int F, int n_ft, int T)
+                                                              int N, int K, int Kd, int F, int n_ft, int T, TilePlace tp)
 {
     constexpr int NB = kF32NB;
     constexpr int NO = (GATEUP ? NA / 2 : NA) * NB;  // output blocks
     __shared__ f64x2 s_part[kF32Waves][NA * NB * 2][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15;
     const int tile_x = blockIdx.x / n_ft, ft = blockIdx.x - tile_x * n_ft, tile = blockIdx.y * kF32GridTiles + tile_x;
-    const int4 loc = locate_rows<kF32Rows>(offsets, N, tile);
+    __shared__ TilePlaceLds<PLACE ? kF32Rows : 1> s_place;
+    const int4 loc = locate_f32<PLACE>(offsets, N, K, T, tile, ft, s_place, tp);
     const int rows = loc.z;
     if (rows == 0) return;
     const int f0 = ft * 16 * (GATEUP ? NA / 2 : NA);
@@ -64,8 +75,8 @@ __global__ __launch_bounds__(kF32Threads, 2) void ffn_f32_kernel(const float *__
     }
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-        const int r = loc.y + min(16 * b + l16, rows - 1);
-        pb[b] = tok + (size_t)(GATEUP ? min(max(sorted_slot[r] / K, 0), T - 1) : r) * Kd;  // a bad index must not fault
+        const int row = min(16 * b + l16, rows - 1), slot = PLACE ? s_place.list[row] : GATEUP ? sorted_slot[loc.y + row] : 0;
+        pb[b] = tok + (size_t)(GATEUP ? min(max(slot / K, 0), T - 1) : loc.y + row) * Kd;  // a bad index must not fault
     }
     // only the blocks that hold rows are fetched and multiplied
     if (rows > 16) multiply_rows<NA, NB, NB>(s_part[wave], pa, pb, wave, Kd);
@@ -184,17 +195,19 @@ struct F32Ffn {
     __device__ __forceinline__ static float swiglu(float g, float u) { return g / (1.f + expf(-g)) * u; }
 };
 
-template <bool GATEUP, int NA, int NB>
+template <bool GATEUP, int NA, int NB, bool PLACE>
 __global__ __launch_bounds__(kF32Threads, 3) void ffn_f32_split_kernel(const float *__restrict__ tok, const float *__restrict__ w0,
                                                               const float *__restrict__ w1, const int32_t *__restrict__ offsets,
                                                               const int32_t *__restrict__ sorted_slot, float *__restrict__ out,
-                                                              int N, int K, int Kd, int F, int n_ft, int T)
+                                                              int N, int K, int Kd, int F, int n_ft, int T, TilePlace tp)
 {
     typedef F32Ffn<GATEUP, NA, NB> C;
     __shared__ __attribute__((aligned(1024))) unsigned char lds[C::LDS_BYTES];
     const int lane = threadIdx.x & 63, r8 = lane >> 3;
     const int tile_x = blockIdx.x / n_ft, ft = blockIdx.x - tile_x * n_ft, tile = blockIdx.y * kF32GridTiles + tile_x;
-    const int4 loc = locate_rows<16 * NB>(offsets, N, tile);
+    static_assert(16 * NB == kF32Rows, "");
+    __shared__ TilePlaceLds<PLACE ? kF32Rows : 1> s_place;
+    const int4 loc = locate_f32<PLACE>(offsets, N, K, T, tile, ft, s_place, tp);
     const int rows = loc.z;
     if (rows == 0) return;
     static_assert(C::HUGE <= kF32Threads, "a thread per row");
@@ -203,8 +216,8 @@ __global__ __launch_bounds__(kF32Threads, 3) void ffn_f32_split_kernel(const flo
     const int f0 = ft * 16 * C::NF;
 
     auto tok_row = [&](int row) {
-        const int r = loc.y + row;
-        return tok + (size_t)(GATEUP ? min(max(sorted_slot[r] / K, 0), T - 1) : r) * Kd;  // a bad index must not fault
+        const int slot = PLACE ? s_place.list[row] : GATEUP ? sorted_slot[loc.y + row] : 0;
+        return tok + (size_t)(GATEUP ? min(max(slot / K, 0), T - 1) : loc.y + row) * Kd;  // a bad index must not fault
     };
     const float *pb[NB][2];
     uint32_t wo[NA][2];  // (an expert's matrix has 604 MB at most)
@@ -228,16 +241,22 @@ __global__ __launch_bounds__(kF32Threads, 3) void ffn_f32_split_kernel(const flo
 // SPLIT: the kernel for many rows per expert
 template <bool GATEUP, int NA, bool SPLIT>
 static int launch(const zeda_layer_desc *d, const float *tok, const float *w0, const float *w1, const int32_t *offsets,
-                  const int32_t *sorted_slot, float *out, hipStream_t s)
+                  const int32_t *sorted_slot, float *out, const TilePlace *tp, hipStream_t s)
 {
     const int Kd = GATEUP ? d->H : d->I, F = GATEUP ? d->I : d->H;
     const int n_ft = ceil_div(F, 16 * (GATEUP ? NA / 2 : NA));
     const int S = d->T * d->K, tiles = (S < d->N ? S : d->N) + S / kF32Rows;  // at most this many token tiles
     const dim3 grid((unsigned)(tiles < kF32GridTiles ? tiles : kF32GridTiles) * n_ft, ceil_div(tiles, kF32GridTiles));
-    if constexpr (SPLIT)
-        ffn_f32_split_kernel<GATEUP, NA, kF32NB><<<grid, kF32Threads, 0, s>>>(tok, w0, w1, offsets, sorted_slot, out, d->N, d->K, Kd, F, n_ft, d->T);
-    else
-        ffn_f32_kernel<GATEUP, NA><<<grid, kF32Threads, 0, s>>>(tok, w0, w1, offsets, sorted_slot, out, d->N, d->K, Kd, F, n_ft, d->T);
+    auto go = [&](auto *kernel) { kernel<<<grid, kF32Threads, 0, s>>>(tok, w0, w1, offsets, sorted_slot, out, d->N, d->K, Kd, F, n_ft, d->T, tp ? *tp : TilePlace{}); };
+    if constexpr (GATEUP) {
+        if (tp) {
+            if constexpr (SPLIT) go(ffn_f32_split_kernel<GATEUP, NA, kF32NB, true>);
+            else go(ffn_f32_kernel<GATEUP, NA, true>);
+            return last_launch_status();
+        }
+    }
+    if constexpr (SPLIT) go(ffn_f32_split_kernel<GATEUP, NA, kF32NB, false>);
+    else go(ffn_f32_kernel<GATEUP, NA, false>);
     return last_launch_status();
 }
 
@@ -252,24 +271,25 @@ static bool f32_many_rows(const zeda_layer_desc *d) { return (int64_t)d->T * d->
 // experts are too few and too narrow to fill the device otherwise.
 template <bool GATEUP>
 static int launch_any(const zeda_layer_desc *d, const void *tok, const void *w0, const void *w1, const int32_t *offsets,
-                      const int32_t *sorted_slot, void *out, hipStream_t s)
+                      const int32_t *sorted_slot, void *out, const TilePlace *tp, hipStream_t s)
 {
     const int F = GATEUP ? 2 * d->I : d->H;
     const bool wide = (int64_t)d->N * F >= 256 * 64;
-    if (wide && f32_many_rows(d)) return launch<GATEUP, 4, true>(d, (const float *)tok, (const float *)w0, (const float *)w1, offsets, sorted_slot, (float *)out, s);
-    return wide ? launch<GATEUP, 4, false>(d, (const float *)tok, (const float *)w0, (const float *)w1, offsets, sorted_slot, (float *)out, s)
-                : launch<GATEUP, 2, false>(d, (const float *)tok, (const float *)w0, (const float *)w1, offsets, sorted_slot, (float *)out, s);
+    const float *t = (const float *)tok, *a = (const float *)w0, *b = (const float *)w1;
+    if (wide && f32_many_rows(d)) return launch<GATEUP, 4, true>(d, t, a, b, offsets, sorted_slot, (float *)out, tp, s);
+    return wide ? launch<GATEUP, 4, false>(d, t, a, b, offsets, sorted_slot, (float *)out, tp, s)
+                : launch<GATEUP, 2, false>(d, t, a, b, offsets, sorted_slot, (float *)out, tp, s);
 }
 
 int launch_gateup_f32(const zeda_layer_desc *d, const void *x, const void *wg, const void *wu, const int32_t *offsets,
-                      const int32_t *sorted_slot, void *act, hipStream_t s)
+                      const int32_t *sorted_slot, void *act, const TilePlace *tp, hipStream_t s)
 {
-    return launch_any<true>(d, x, wg, wu, offsets, sorted_slot, act, s);
+    return launch_any<true>(d, x, wg, wu, offsets, sorted_slot, act, tp, s);
 }
 
 int launch_down_f32(const zeda_layer_desc *d, const void *act, const void *wd, const int32_t *offsets, void *y_slot, hipStream_t s)
 {
-    return launch_any<false>(d, act, wd, nullptr, offsets, nullptr, y_slot, s);
+    return launch_any<false>(d, act, wd, nullptr, offsets, nullptr, y_slot, nullptr, s);
 }
 
 }  // namespace zeda

@@ -10,6 +10,7 @@
 // meet; a wave keeps DEPTH chunks of 64 k in flight.  Bound by HBM: 64 tokens, 106 experts hit, 667 MB of gate/up weights
 // in 107 us = 6.2 TB/s; one token, gate/up and down 23 + 13 -> 11 + 8 us (launch included).
 #include "zeda_place.h"
+#include "zeda_select.h"
 
 namespace zeda {
 
@@ -87,23 +88,73 @@ __device__ __forceinline__ void few_multiply_rows(int rows, f32x4 (*part)[64], c
 // out = y_slot[S,F].  Kd a multiple of 64, F of 16 NF.  Up to 16 NB token rows (NB 2 or 4).  Blocks past the last token
 // tile return at once.
 // MULTI: an expert may have more rows than a workgroup takes.
-template <bool GATEUP, bool TILED, int NF, int NB, int DEPTH, bool MULTI>
+// FROM: where the tile's rows come from: the tables of a placement, the ids of all slots, or the logits of all tokens (tp).
+enum FewFrom { kFromTables, kFromIds, kFromLogits };
+
+// select_tokens: the routing of up to kTileSelTokens tokens from their partial logits, a token per wave; s_ids receives the ids.
+// The same additions and the same selection as in the router's second kernel.
+__device__ __forceinline__ void select_tokens(const TilePlace &tp, int T, int N, int K, bool lead, float (*lg)[kMaxExperts], int *s_ids)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (wave < T) {
+        // (all loads in flight together: each is a trip to another XCD's results)
+        constexpr int NC = kMaxExperts / 64, MAXQ = 16;
+        float v[MAXQ][NC], bias[NC] = {};
+#pragma unroll
+        for (int q = 0; q < MAXQ; ++q)
+            if (q < tp.slices) {
+#pragma unroll
+                for (int c = 0; c < NC; ++c) v[q][c] = tp.partial[((size_t)q * tp.Tpad + wave) * tp.E + min(lane + 64 * c, tp.E - 1)];
+            }
+        if (tp.bias) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c) bias[c] = tp.bias[min(lane + 64 * c, tp.NE - 1)];
+        }
+#pragma unroll
+        for (int q = 1; q < MAXQ; ++q)
+            if (q < tp.slices) {
+#pragma unroll
+                for (int c = 0; c < NC; ++c) v[0][c] += v[q][c];
+            }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) lg[wave][lane + 64 * c] = v[0][c] + bias[c];
+        // (a wave reads what it wrote; experts past NE are left out)
+        const int id = select_wave<kMaxExperts / 64>(lg[wave], true, wave, tp.NE, N, K, tp.gate_norm, lead ? tp.ids : nullptr, tp.gates);
+        if (lane < K) s_ids[wave * K + lane] = id;
+    }
+    __syncthreads();
+}
+
+template <bool GATEUP, bool TILED, int NF, int NB, int DEPTH, bool MULTI, int FROM>
 __global__ __launch_bounds__(kFewThreads) void ffn_few_kernel(const bf16_t *__restrict__ tok, const bf16_t *__restrict__ w0,
                                                               const bf16_t *__restrict__ w1, const int32_t *__restrict__ offsets,
                                                               const int32_t *__restrict__ sorted_slot, bf16_t *__restrict__ out,
-                                                              int N, int K, int Kd, int F, int n_ft, int T)
+                                                              int N, int K, int Kd, int F, int n_ft, int T, TilePlace tp)
 {
+    static_assert(kFewThreads == kTileThreads && (GATEUP || FROM == kFromTables) && kTileSelTokens <= kFewWaves, "");
     constexpr int NA = GATEUP ? 2 * NF : NF;  // weight blocks: gate and up blocks alternate
     __shared__ f32x4 s_part[kFewWaves][NA * NB][64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, kq = lane >> 4;
     const int tile = blockIdx.x / n_ft, ft = blockIdx.x - tile * n_ft;
-    const int4 loc = locate_rows<16 * NB>(offsets, N, tile);
+    int4 loc;
+    __shared__ TilePlaceLds<16 * NB> s_place;
+    if constexpr (FROM == kFromTables) {
+        loc = locate_rows<16 * NB>(offsets, N, tile);
+    } else if constexpr (FROM == kFromIds) {
+        loc = place_tile<16 * NB>([&](int slot) { return tp.ids[slot]; }, T * K, N, tile, ft == 0, blockIdx.x == 0, s_place, tp.out);
+    } else {
+        __shared__ float s_lg[kTileSelTokens][kMaxExperts];
+        __shared__ int s_ids[kTileSelTokens * kMaxK];
+        select_tokens(tp, T, N, K, blockIdx.x == 0, s_lg, s_ids);
+        loc = place_tile<16 * NB>([&](int slot) { return s_ids[slot]; }, T * K, N, tile, ft == 0, blockIdx.x == 0, s_place, tp.out);
+    }
     if (loc.z == 0) return;
     const bf16_t *pt[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-        const int r = loc.y + min(16 * b + l16, loc.z - 1);  // columns past the tile repeat its last row (never stored)
-        pt[b] = tok + (size_t)(GATEUP ? min(max(sorted_slot[r] / K, 0), T - 1) : r) * Kd + kq * 8;  // a bad index must not fault
+        const int row = min(16 * b + l16, loc.z - 1);  // columns past the tile repeat its last row (never stored)
+        const int slot = FROM != kFromTables ? s_place.list[row] : GATEUP ? sorted_slot[loc.y + row] : 0;
+        pt[b] = tok + (size_t)(GATEUP ? min(max(slot / K, 0), T - 1) : loc.y + row) * Kd + kq * 8;  // a bad index must not fault
     }
     const bf16_t *pa[NA];
 #pragma unroll
@@ -193,41 +244,69 @@ int ffn_few_blocks(const zeda_layer_desc *d)
 
 template <bool GATEUP, bool TILED, int NB, bool MULTI>
 static int launch_blocks(const zeda_layer_desc *d, const void *tok, const void *w0, const void *w1, const int32_t *offsets,
-                         const int32_t *sorted_slot, void *out, hipStream_t s)
+                         const int32_t *sorted_slot, void *out, const TilePlace *tp, hipStream_t s)
 {
     // 16 gate and 16 up rows, or 32 rows of W_down (16 make twice the workgroups and token reads: 58 -> 61 us at 64 tokens);
     // three chunks of 64 k in flight (four leave fewer waves per SIMD: 177.5 -> 176.5 us)
     constexpr int NF = GATEUP ? 1 : 2, DEPTH = 3;
     const int Kd = GATEUP ? d->H : d->I, F = GATEUP ? d->I : d->H, n_ft = F / (16 * NF);
     const int S = d->T * d->K, tiles = (S < d->N ? S : d->N) + S / (16 * NB);  // at most this many token tiles
-    ffn_few_kernel<GATEUP, TILED, NF, NB, DEPTH, MULTI><<<(unsigned)tiles * n_ft, kFewThreads, 0, s>>>(
-        (const bf16_t *)tok, (const bf16_t *)w0, (const bf16_t *)w1, offsets, sorted_slot, (bf16_t *)out, d->N, d->K, Kd, F, n_ft, d->T);
+#define ZEDA_FEW(FROM) ffn_few_kernel<GATEUP, TILED, NF, NB, DEPTH, MULTI, FROM><<<(unsigned)tiles * n_ft, kFewThreads, 0, s>>>( \
+        (const bf16_t *)tok, (const bf16_t *)w0, (const bf16_t *)w1, offsets, sorted_slot, (bf16_t *)out, d->N, d->K, Kd, F, n_ft, d->T, tp ? *tp : TilePlace{})
+    if constexpr (GATEUP) {
+        if constexpr (NB == 2 && !MULTI) {
+            if (tp && tp->partial) {
+                ZEDA_FEW(kFromLogits);
+                return last_launch_status();
+            }
+        }
+        if (tp) ZEDA_FEW(kFromIds);
+        else ZEDA_FEW(kFromTables);
+    } else {
+        ZEDA_FEW(kFromTables);
+    }
+#undef ZEDA_FEW
     return last_launch_status();
 }
 
 // With a few slots per expert, an expert of several token tiles is one of many whose weights are fetched, and the second copy of
 // the multiplication costs all workgroups 0.7 % (N=128, I=768, H=2048, 64 tokens row-major: 230.2 -> 233.5 us).
+static bool few_multi(const zeda_layer_desc *d) { return d->T > 32 && (int64_t)d->T * d->K > 8 * ((int64_t)d->N + d->Z); }
+
 template <bool GATEUP, bool TILED>
 static int launch(const zeda_layer_desc *d, const void *tok, const void *w0, const void *w1, const int32_t *offsets,
-                  const int32_t *sorted_slot, void *out, hipStream_t s)
+                  const int32_t *sorted_slot, void *out, const TilePlace *tp, hipStream_t s)
 {
-    if (ffn_few_blocks(d) == 4) return launch_blocks<GATEUP, TILED, 4, true>(d, tok, w0, w1, offsets, sorted_slot, out, s);
-    const bool multi = d->T > 32 && (int64_t)d->T * d->K > 8 * ((int64_t)d->N + d->Z);
-    return multi ? launch_blocks<GATEUP, TILED, 2, true>(d, tok, w0, w1, offsets, sorted_slot, out, s)
-                 : launch_blocks<GATEUP, TILED, 2, false>(d, tok, w0, w1, offsets, sorted_slot, out, s);
+    if (ffn_few_blocks(d) == 4) return launch_blocks<GATEUP, TILED, 4, true>(d, tok, w0, w1, offsets, sorted_slot, out, tp, s);
+    return few_multi(d) ? launch_blocks<GATEUP, TILED, 2, true>(d, tok, w0, w1, offsets, sorted_slot, out, tp, s)
+                        : launch_blocks<GATEUP, TILED, 2, false>(d, tok, w0, w1, offsets, sorted_slot, out, tp, s);
+}
+
+// Up to 1024 slots (four a thread) the kernels with a workgroup per 16 or 32 columns place the slots themselves.
+bool gateup_places(const zeda_layer_desc *d)
+{
+    if ((int64_t)d->T * d->K > kTileMaxSlots) return false;
+    return d->dtype == ZEDA_F32 || ffn_few_blocks(d) > 0;
+}
+
+// A wave per token, so up to four tokens are selected there too: 4 us in front of a workgroup's weights, for a kernel of 6.6 (N=128,
+// Z=32, I=768, whole layer: one token 27.4 -> 23.3 us, two 33.0 -> 29.4, four, 700 workgroups with rows, 48.3 -> 47.2).
+bool gateup_selects(const zeda_layer_desc *d)
+{
+    return gateup_places(d) && d->dtype == ZEDA_BF16 && d->T <= kTileSelTokens && ffn_few_blocks(d) == 2 && !few_multi(d) && route_splits(d);
 }
 
 int launch_gateup_few(const zeda_layer_desc *d, const void *x, const void *wg, const void *wu, const int32_t *offsets,
-                      const int32_t *sorted_slot, void *act, hipStream_t s)
+                      const int32_t *sorted_slot, void *act, const TilePlace *tp, hipStream_t s)
 {
-    return d->weight_layout == ZEDA_WEIGHTS_TILED ? launch<true, true>(d, x, wg, wu, offsets, sorted_slot, act, s)
-                                                  : launch<true, false>(d, x, wg, wu, offsets, sorted_slot, act, s);
+    return d->weight_layout == ZEDA_WEIGHTS_TILED ? launch<true, true>(d, x, wg, wu, offsets, sorted_slot, act, tp, s)
+                                                  : launch<true, false>(d, x, wg, wu, offsets, sorted_slot, act, tp, s);
 }
 
 int launch_down_few(const zeda_layer_desc *d, const void *act, const void *wd, const int32_t *offsets, void *y_slot, hipStream_t s)
 {
-    return d->weight_layout == ZEDA_WEIGHTS_TILED ? launch<false, true>(d, act, wd, nullptr, offsets, nullptr, y_slot, s)
-                                                  : launch<false, false>(d, act, wd, nullptr, offsets, nullptr, y_slot, s);
+    return d->weight_layout == ZEDA_WEIGHTS_TILED ? launch<false, true>(d, act, wd, nullptr, offsets, nullptr, y_slot, nullptr, s)
+                                                  : launch<false, false>(d, act, wd, nullptr, offsets, nullptr, y_slot, nullptr, s);
 }
 
 }  // namespace zeda

@@ -36,9 +36,12 @@ inline size_t elt_size(const zeda_layer_desc *d) { return d->dtype == ZEDA_BF16 
 // partial: scratch of route_ws_bytes(d) for a split of the hidden dimension, or NULL (one kernel, no scratch)
 // cnt8: route_counts_bytes(d) of scratch that receives the per-block expert counts, or NULL (bf16 only)
 // place: where the expert-sorted placement goes (only where route_places(d)), or NULL
+// tp (may be NULL): receives where the partial logits are, and no selection is launched (only where gateup_selects(d))
 struct PlaceOut;
+struct TilePlace;
 int launch_route(const zeda_layer_desc *d, const void *x, const void *wr, const float *bias, int32_t *ids, float *gates,
-                 float *partial, uint8_t *cnt8, const PlaceOut *place, hipStream_t s);
+                 float *partial, uint8_t *cnt8, const PlaceOut *place, TilePlace *tp, hipStream_t s);
+bool route_splits(const zeda_layer_desc *d);  // given scratch, the router is two kernels
 bool route_places(const zeda_layer_desc *d);  // given scratch, the router can place the whole batch itself
 size_t route_ws_bytes(const zeda_layer_desc *d);
 // Per-block expert counts of the bf16 router: cnt8 [N+Z][route_counts_ld(d)] bytes receive, per block of 16 tokens,
@@ -63,19 +66,22 @@ size_t dispatch_ws_bytes(const zeda_layer_desc *d);
 void *dispatch_static_scratch();          // its address on the current device, NULL if the lookup fails
 size_t dispatch_static_scratch_bytes();
 int dispatch_static_max_slots();          // slot lists up to this length are accepted by that entry point
+// tp (may be NULL): the kernel places the slots itself (only where gateup_places(d)); offsets and sorted_slot are then outputs
+bool gateup_places(const zeda_layer_desc *d);
+bool gateup_selects(const zeda_layer_desc *d);  // ... and selects, from the partial logits of the router's first kernel
 int launch_gateup(const zeda_layer_desc *d, const void *x, const void *wg, const void *wu, const int32_t *offsets,
-                  const int32_t *sorted_slot, void *act, hipStream_t s);
+                  const int32_t *sorted_slot, void *act, const TilePlace *tp, hipStream_t s);
 int launch_down(const zeda_layer_desc *d, const void *act, const void *wd, const int32_t *offsets, void *y_slot,
                 hipStream_t s);
 // the same for fp32 layers (launch_gateup and launch_down call them)
 int launch_gateup_f32(const zeda_layer_desc *d, const void *x, const void *wg, const void *wu, const int32_t *offsets,
-                      const int32_t *sorted_slot, void *act, hipStream_t s);
+                      const int32_t *sorted_slot, void *act, const TilePlace *tp, hipStream_t s);
 int launch_down_f32(const zeda_layer_desc *d, const void *act, const void *wd, const int32_t *offsets, void *y_slot,
                     hipStream_t s);
 // the same for bf16 layers whose experts have a handful of rows each (launch_gateup and launch_down call them)
 int ffn_few_blocks(const zeda_layer_desc *d);  // token blocks of a workgroup, 0 where the tile kernels are the better ones
 int launch_gateup_few(const zeda_layer_desc *d, const void *x, const void *wg, const void *wu, const int32_t *offsets,
-                      const int32_t *sorted_slot, void *act, hipStream_t s);
+                      const int32_t *sorted_slot, void *act, const TilePlace *tp, hipStream_t s);
 int launch_down_few(const zeda_layer_desc *d, const void *act, const void *wd, const int32_t *offsets, void *y_slot,
                     hipStream_t s);
 // row-major -> tiled copy of one expert weight tensor (down: [N,H,I], else [N,I,H])

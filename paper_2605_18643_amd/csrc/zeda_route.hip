@@ -1,238 +1,12 @@
 // Router of the augmented expert pool (Section 2.1): logits over N normal + Z zero experts, the
 // top-K set with a deterministic lower-index tie-break, and the routing weights (Section 4.3.4 for
 // the normalisation choices).  One fused kernel: projection -> LDS -> wave-level selection.
-#include <limits.h>
-
 #include "zeda_f32_tile.h"
 #include "zeda_lds.h"
 #include "zeda_place.h"
+#include "zeda_select.h"
 
 namespace zeda {
-
-
-// Selection runs four tokens per wave, one per row of 16 lanes (the unit of the VALU's data-parallel-primitive
-// cross-lane path), so all reductions stay inside a row and need no LDS traffic and no scalar round trips.
-// row_ror rotates a value inside its row; max/min folded over rotations by 8, 4, 2, 1 leave every lane of the
-// row with the row's result, and since max and min do not depend on the order all lanes agree exactly.
-template <int N>
-__device__ __forceinline__ int dpp_row_ror(int v)
-{
-    return __builtin_amdgcn_mov_dpp(v, 0x120 + N, 0xf, 0xf, true);
-}
-__device__ __forceinline__ int row_max(int v)
-{
-    v = max(v, dpp_row_ror<8>(v));
-    v = max(v, dpp_row_ror<4>(v));
-    v = max(v, dpp_row_ror<2>(v));
-    v = max(v, dpp_row_ror<1>(v));
-    return v;
-}
-__device__ __forceinline__ float row_max(float v)
-{
-    v = fmaxf(v, __int_as_float(dpp_row_ror<8>(__float_as_int(v))));
-    v = fmaxf(v, __int_as_float(dpp_row_ror<4>(__float_as_int(v))));
-    v = fmaxf(v, __int_as_float(dpp_row_ror<2>(__float_as_int(v))));
-    v = fmaxf(v, __int_as_float(dpp_row_ror<1>(__float_as_int(v))));
-    return v;
-}
-__device__ __forceinline__ int row_min(int v)
-{
-    v = min(v, dpp_row_ror<8>(v));
-    v = min(v, dpp_row_ror<4>(v));
-    v = min(v, dpp_row_ror<2>(v));
-    v = min(v, dpp_row_ror<1>(v));
-    return v;
-}
-// Integers in the order of the floats (both zeros alike; no-numbers come last, as kNoKey): one max instruction takes the
-// lane permutation along, where a float max first quiets its operands.
-constexpr int kNoKey = INT_MIN;
-__device__ __forceinline__ int logit_key(float v)
-{
-    const int b = __float_as_int(v + 0.0f);  // -0 -> +0
-    return v == v ? b ^ ((b >> 31) & 0x7fffffff) : kNoKey;
-}
-__device__ __forceinline__ float key_logit(int k) { return __int_as_float(k ^ ((k >> 31) & 0x7fffffff)); }
-// Sum over the row in one fixed order (an inclusive scan with row_shr 1, 2, 4, 8 leaves the total in the row's
-// last lane), handed to every lane of the row, so that all lanes divide by the same number.
-__device__ __forceinline__ float row_sum(float v)
-{
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x111, 0xf, 0xf, false));  // lanes without a source add zero
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x112, 0xf, 0xf, false));
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x114, 0xf, 0xf, false));
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x118, 0xf, 0xf, false));
-    const float r0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 15));
-    const float r1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 31));
-    const float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 47));
-    const float r3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
-    const int r = (threadIdx.x & 63) >> 4;
-    return r == 0 ? r0 : r == 1 ? r1 : r == 2 ? r2 : r3;
-}
-
-// Sum over all 64 lanes in a fixed order, returned to every lane.
-__device__ __forceinline__ float wave_sum(float v)
-{
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x111, 0xf, 0xf, false));
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x112, 0xf, 0xf, false));
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x114, 0xf, 0xf, false));
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x118, 0xf, 0xf, false));
-    const float r0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 15));
-    const float r1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 31));
-    const float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 47));
-    const float r3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
-    return (r0 + r1) + (r2 + r3);
-}
-
-// Selection and gates for the four tokens tk0..tk0+3 of the workgroup's block (whose fp32 logits are rows of
-// lg in LDS), executed by one wave: token tk0 + r belongs to lane row r, and lane l of the row holds the
-// candidates l, l + 16, ... (NC of them).  One round: the row maximum, then the lowest expert index among the
-// candidates equal to it (ties go to the lower index), which its owner then removes.  Lane j of the row keeps
-// slot j, so lanes 0..K-1 end up with the slots in descending-logit order (K <= 16).
-// Returns the expert of the slot this lane keeps (lane j < K of a row: slot j of the row's token), or -1.
-// bias: this lane's candidates' biases.
-// probs (may be NULL): an LDS table [token][LDP] that receives, for every token of the wave, the routing
-// probability of every expert (softmax over all NE logits).
-template <int NC, int NP>
-__device__ __forceinline__ int select_rows(const float *lg, int LD, int pstride, const float (&bias)[NC], int tk0,
-                                           int ntok, int t0, int T, int NE, int N, int K, int gate_norm,
-                                           int32_t *__restrict__ ids, float *__restrict__ gates, float *probs = nullptr,
-                                           int LDP = 0)
-{
-    const int lane = threadIdx.x & 63, l16 = lane & 15, tk = tk0 + (lane >> 4);
-    const bool ok = tk < ntok && t0 + tk < T;
-    int cand[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        const int e = l16 + 16 * c;
-        // the NP partial sums over slices of the hidden dimension, added in a fixed order, then the bias (columns past
-        // NE of the tables are readable and left out)
-        float v = lg[tk * LD + e];
-#pragma unroll
-        for (int q = 1; q < NP; ++q) v += lg[q * pstride + tk * LD + e];
-        int key = logit_key(v + bias[c]);
-        asm volatile("" : "+v"(key));  // (no branch around every candidate)
-        cand[c] = ok && e < NE ? key : kNoKey;
-    }
-    auto local_max = [&]() {
-        int m = cand[0];
-#pragma unroll
-        for (int c = 1; c < NC; ++c) m = max(m, cand[c]);
-        return m;
-    };
-    int m = row_max(local_max());
-    const float all_max = key_logit(m);
-    float all_sum = 0.f;
-    if (gate_norm == ZEDA_GATE_SOFTMAX || probs) {
-        float ex[NC], sacc = 0.f;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            ex[c] = (ok && l16 + 16 * c < NE) ? expf(key_logit(cand[c]) - all_max) : 0.f;
-            sacc += ex[c];
-        }
-        all_sum = row_sum(sacc);
-        if (probs && ok) {
-#pragma unroll
-            for (int c = 0; c < NC; ++c)
-                if (l16 + 16 * c < NE) probs[tk * LDP + l16 + 16 * c] = ex[c] / all_sum;
-        }
-    }
-    int my_id = 0;
-    float my_logit = -INFINITY;
-    for (int j = 0; j < K; ++j) {
-        if (j > 0) m = row_max(local_max());
-        int mine = INT_MAX;
-#pragma unroll
-        for (int c = NC - 1; c >= 0; --c)
-            if (cand[c] == m) mine = l16 + 16 * c;  // descending c: the lowest index survives
-        int win = row_min(mine);
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-            if (win == l16 + 16 * c) cand[c] = kNoKey;
-        if (m == kNoKey) win = INT_MAX;  // nothing but no-numbers left: no expert, gate 0
-        if (l16 == j) { my_id = win; my_logit = m == kNoKey ? -INFINITY : key_logit(m); }
-    }
-    const bool slot = l16 < K;
-    const float ex = slot ? expf(my_logit - all_max) : 0.f;
-    float dn;
-    if (gate_norm == ZEDA_GATE_SOFTMAX) dn = all_sum;
-    else if (gate_norm == ZEDA_GATE_TOPK_NORM) dn = row_sum(ex);
-    else dn = row_sum((slot && my_id < N) ? ex : 0.f);
-    if (slot && ok && ids) {
-        const size_t o = (size_t)(t0 + tk) * K + l16;
-        ids[o] = my_id;
-        gates[o] = dn > 0.f ? ex / dn : 0.f;
-    }
-    return (slot && ok) ? my_id : -1;
-}
-
-// The same for one token by a whole wave: lane l holds the candidates l, l + 64, ...; a round's winner is found from
-// ballots, lowest candidate group and lane first, i.e. the lowest index.  Shorter rounds than the above (few
-// candidates per lane): for workgroups with a wave for every token.  lg: the token's logits, biases included.
-template <int NC>
-__device__ __forceinline__ int select_wave(const float *lg, bool ok, size_t t, int NE, int N, int K, int gate_norm,
-                                           int32_t *__restrict__ ids, float *__restrict__ gates, float *probs = nullptr)
-{
-    const int lane = threadIdx.x & 63;
-    int cand[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        const int e = lane + 64 * c;
-        int key = logit_key(lg[e]);
-        asm volatile("" : "+v"(key));
-        cand[c] = ok && e < NE ? key : kNoKey;
-    }
-    auto wave_max = [&]() {
-        int m = cand[0];
-#pragma unroll
-        for (int c = 1; c < NC; ++c) m = max(m, cand[c]);
-        m = row_max(m);
-        return max(max(__builtin_amdgcn_readlane(m, 0), __builtin_amdgcn_readlane(m, 16)),
-                   max(__builtin_amdgcn_readlane(m, 32), __builtin_amdgcn_readlane(m, 48)));
-    };
-    int m = wave_max();
-    const float all_max = key_logit(m);
-    float all_sum = 0.f;
-    if (gate_norm == ZEDA_GATE_SOFTMAX || probs) {
-        float ex[NC], sacc = 0.f;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            ex[c] = (ok && lane + 64 * c < NE) ? expf(key_logit(cand[c]) - all_max) : 0.f;
-            sacc += ex[c];
-        }
-        all_sum = wave_sum(sacc);
-        if (probs && ok) {
-#pragma unroll
-            for (int c = 0; c < NC; ++c)
-                if (lane + 64 * c < NE) probs[lane + 64 * c] = ex[c] / all_sum;
-        }
-    }
-    int my_id = 0;
-    float my_logit = -INFINITY;
-    for (int j = 0; j < K; ++j) {
-        if (j > 0) m = wave_max();
-        int win = INT_MAX;
-#pragma unroll
-        for (int c = NC - 1; c >= 0; --c) {
-            const unsigned long long eq = __ballot(cand[c] == m);
-            if (eq) win = 64 * c + __ffsll((long long)eq) - 1;
-        }
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-            if (win == lane + 64 * c) cand[c] = kNoKey;
-        if (m == kNoKey) win = INT_MAX;  // nothing but no-numbers left: no expert, gate 0
-        if (lane == j) { my_id = win; my_logit = m == kNoKey ? -INFINITY : key_logit(m); }
-    }
-    const bool slot = lane < K;
-    const float ex = slot ? expf(my_logit - all_max) : 0.f;
-    float dn;
-    if (gate_norm == ZEDA_GATE_SOFTMAX) dn = all_sum;
-    else if (gate_norm == ZEDA_GATE_TOPK_NORM) dn = row_sum(ex);
-    else dn = row_sum((slot && my_id < N) ? ex : 0.f);
-    if (slot && ok && ids) {
-        ids[t * K + lane] = my_id;
-        gates[t * K + lane] = dn > 0.f ? ex / dn : 0.f;
-    }
-    return (slot && ok) ? my_id : -1;
-}
 
 // this lane's NC candidates' router biases (past NE: any)
 template <int NC>
@@ -637,6 +411,7 @@ struct RouteExtras {
     int cnt_ld;
     float *p_part;
     PlaceOut place;
+    TilePlace *tp;  // given: the gate/up kernel selects
 };
 
 template <int NB, int TB, int W>
@@ -657,6 +432,13 @@ static int launch_route_bf16(const zeda_layer_desc *d, const void *x, const void
     route_bf16_kernel<NB, TB, W><<<dim3(ceil_div(d->T, C::TOK), slices), C::THREADS, C::LDS_BYTES, s>>>(
         (const bf16_t *)x, (const bf16_t *)wr, bias, d->T, d->H, d->N, NE, d->K, d->gate_norm, ids, gates, slices > 1 ? partial : nullptr, Tpad,
         ex.cnt8, ex.cnt_ld, ex.p_part);
+    if (ex.tp && slices > 1) {
+        ex.tp->partial = partial;
+        ex.tp->slices = slices;
+        ex.tp->Tpad = Tpad;
+        ex.tp->E = NB * 32;
+        return last_launch_status();
+    }
     const dim3 sgrid(ceil_div(d->T, kSelectTokens));
 #define ZEDA_SELECT(NP) route_select_kernel<NB, NP, W><<<sgrid, C::THREADS, 0, s>>>(partial, Tpad, bias, d->T, d->N, NE, d->K, d->gate_norm, ids, gates, ex.cnt8, ex.cnt_ld, ex.p_part, ex.place)
     if (slices == 2) ZEDA_SELECT(2);
@@ -702,10 +484,8 @@ static int launch_route_bf16_any(const zeda_layer_desc *d, const void *x, const 
     }
 }
 
-bool route_places(const zeda_layer_desc *d)
-{
-    return d->dtype == ZEDA_BF16 && d->T <= kSelectTokens && route_plan(d, true).slices > 1;
-}
+bool route_splits(const zeda_layer_desc *d) { return d->dtype == ZEDA_BF16 && route_plan(d, true).slices > 1; }
+bool route_places(const zeda_layer_desc *d) { return d->T <= kSelectTokens && route_splits(d); }
 
 int route_counts_ld(const zeda_layer_desc *d) { return (int)align_up((size_t)ceil_div(d->T, 16), 16); }
 size_t route_counts_bytes(const zeda_layer_desc *d) { return align_up((size_t)(d->N + d->Z) * route_counts_ld(d), 256); }
@@ -936,7 +716,7 @@ int launch_routing_stats(const zeda_layer_desc *d, const void *x, const void *wr
         float *partial = route_ws_bytes(d) ? (float *)ws : nullptr;
         uint8_t *cnt8 = (uint8_t *)ws + align_up(route_ws_bytes(d), 256);
         float *p_part = (float *)(cnt8 + route_counts_bytes(d));
-        const RouteExtras ex = {cnt8, route_counts_ld(d), p_part, {}};
+        const RouteExtras ex = {cnt8, route_counts_ld(d), p_part, {}, nullptr};
         const int rc = launch_route_bf16_any(d, x, wr, bias, nullptr, nullptr, partial, ex, s);
         if (rc != ZEDA_OK) return rc;
         route_stats_final_kernel<<<1, kStatsFinalThreads, 0, s>>>(p_part, nullptr, cnt8, ex.cnt_ld, ceil_div(d->T, 16), d->T, d->N, NE,
@@ -966,10 +746,10 @@ int launch_routing_stats(const zeda_layer_desc *d, const void *x, const void *wr
 }
 
 int launch_route(const zeda_layer_desc *d, const void *x, const void *wr, const float *bias, int32_t *ids, float *gates,
-                 float *partial, uint8_t *cnt8, const PlaceOut *place, hipStream_t s)
+                 float *partial, uint8_t *cnt8, const PlaceOut *place, TilePlace *tp, hipStream_t s)
 {
     if (d->dtype == ZEDA_BF16) {
-        const RouteExtras ex = {cnt8, cnt8 ? route_counts_ld(d) : 0, nullptr, place ? *place : PlaceOut{}};
+        const RouteExtras ex = {cnt8, cnt8 ? route_counts_ld(d) : 0, nullptr, place ? *place : PlaceOut{}, tp};
         return launch_route_bf16_any(d, x, wr, bias, ids, gates, partial, ex, s);
     }
     return launch_route_f32(d, x, wr, bias, ids, gates, nullptr, 0, s);
