@@ -40,22 +40,26 @@ __device__ __forceinline__ void select_block(const float *lg, int LD, int pstrid
 }
 
 // After select_block (and a barrier): what the workgroup's blocks of 16 tokens hand to the expert-sorted placement
-// and to the routing statistics.  cnt8[e][cnt_ld] bytes: slots of every block on expert e; p_part[block][NE]: the
-// block's sum of every expert's routing probability, added in token order.
+// and what it hands to the routing statistics.  cnt8[e][cnt_ld] bytes: slots of every block on expert e;
+// p_part[workgroup][NE]: the sum of every expert's routing probability over the workgroup's tokens, added in token order.
 template <int THREADS>
 __device__ __forceinline__ void publish_blocks(const int *s_cnt, const float *probs, int LDP, int ntok, int t0, int T, int NE,
                                                uint8_t *__restrict__ cnt8, int cnt_ld, float *__restrict__ p_part)
 {
     const int nblk = (ntok + 15) >> 4;
-    for (int i = threadIdx.x; i < nblk * NE; i += THREADS) {
-        const int u = i / NE, e = i - u * NE, blk = (t0 >> 4) + u;
-        if (t0 + u * 16 >= T) continue;
-        if (cnt8) cnt8[(size_t)e * cnt_ld + blk] = (uint8_t)s_cnt[u * kMaxExperts + e];
-        if (p_part) {
+    if (cnt8) {
+        for (int i = threadIdx.x; i < nblk * NE; i += THREADS) {
+            const int u = i / NE, e = i - u * NE, blk = (t0 >> 4) + u;
+            if (t0 + u * 16 < T) cnt8[(size_t)e * cnt_ld + blk] = (uint8_t)s_cnt[u * kMaxExperts + e];
+        }
+    }
+    if (p_part) {
+        const int nt = min(ntok, T - t0);
+        for (int e = threadIdx.x; e < NE; e += THREADS) {
             float ps = 0.f;
-            const int nt = min(16, min(ntok, T - t0) - u * 16);
-            for (int t = 0; t < nt; ++t) ps += probs[(u * 16 + t) * LDP + e];
-            p_part[(size_t)blk * NE + e] = ps;
+#pragma unroll 16
+            for (int t = 0; t < nt; ++t) ps += probs[t * LDP + e];
+            p_part[(size_t)blockIdx.x * NE + e] = ps;
         }
     }
 }
@@ -593,16 +597,17 @@ __global__ __launch_bounds__(kStatsThreads) void route_stats_kernel(const float 
     }
 }
 
-// Final workgroup: adds the blocks up.  p_part [nblocks][NE] and either f_part, int32 counts laid out alike, or
-// cnt8[e][cnt_ld], the counts as bytes.  A thread takes four experts, with one 16-byte load where rows are that aligned.  The threads of
-// an expert quad, kStatsParts at most, take every parts-th block, eight loads in flight, and their sums are added in a fixed
-// order (16 experts, 16 tokens: 256 threads a quad cost 3 us, 32 cost 0.3); the byte
-// counts are added as integers, so their order does not matter.  (One thread per expert walking all blocks spent 142 us
-// of latency on the 512 blocks of 8192 tokens.)
+// Final workgroup: adds everything up.  p_part [rows][NE], a row per workgroup of the kernel before, and either f_part, int32
+// counts laid out alike, or cnt8[e][cnt_ld], the counts of nblocks blocks of 16 tokens as bytes.  A thread takes four experts of
+// p_part, with one 16-byte load where rows are that aligned.  The threads of an expert quad, kStatsParts at most, take every
+// parts-th row, twelve loads in flight, and their sums are added in a fixed order (16 experts, 16 tokens: 256 threads a quad cost
+// 3 us, 32 cost 0.3); a wave takes an expert's byte counts, eight experts in flight, and adds them as integers, so their order
+// does not matter.  What it waits for is one CU's share of memory: 8192 tokens, 160 experts 10.1 us with a row of p_part per 16
+// tokens and an LDS addition per 16 counts, 7.8 now.  (One thread per expert walking all rows: 142 us.)
 constexpr int kStatsFinalThreads = 1024;
 constexpr int kStatsParts = 32;
 
-__global__ __launch_bounds__(kStatsFinalThreads) void route_stats_final_kernel(const float *__restrict__ p_part,
+__global__ __launch_bounds__(kStatsFinalThreads) void route_stats_final_kernel(const float *__restrict__ p_part, int prows,
                                                                                const int32_t *__restrict__ f_part,
                                                                                const uint8_t *__restrict__ cnt8, int cnt_ld,
                                                                                int nblocks, int T, int N, int NE, int K,
@@ -612,58 +617,71 @@ __global__ __launch_bounds__(kStatsFinalThreads) void route_stats_final_kernel(c
     __shared__ f32x4 s_part[kStatsFinalThreads];
     __shared__ int s_cnt[kMaxExperts];
     __shared__ float s_f[kMaxExperts], s_P[kMaxExperts];
-    const int tid = threadIdx.x, quads = (NE + 3) / 4, parts = min(min(kStatsFinalThreads / quads, kStatsParts), nblocks);
+    const int tid = threadIdx.x, quads = (NE + 3) / 4, parts = min(min(kStatsFinalThreads / quads, kStatsParts), prows);
     const int quad = tid % quads, part = tid / quads;
     for (int e = tid; e < kMaxExperts; e += kStatsFinalThreads) s_cnt[e] = 0;
     __syncthreads();
+    if (!f_part) {
+        constexpr int WAVES = kStatsFinalThreads / 64, U = 8;
+        const int words = cnt_ld / 16, lane = tid & 63;
+        for (int e0 = tid >> 6; e0 < NE; e0 += WAVES * U) {
+            int c[U] = {};
+            for (int wi = lane; wi < words; wi += 64) {
+                uint4 v[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const uint4 *>(cnt8 + (size_t)min(e0 + WAVES * u, NE - 1) * cnt_ld + wi * 16);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const unsigned dw[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int b0 = wi * 16 + q * 4;
+                        unsigned x = dw[q];
+                        if (b0 + 4 > nblocks) x = b0 >= nblocks ? 0u : (x & ((1u << (8 * (nblocks - b0))) - 1u));  // bytes past the last block
+                        c[u] = (int)__builtin_amdgcn_sad_u8(x, 0u, (unsigned)c[u]);
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int all = __builtin_amdgcn_readlane(wave_scan(c[u]), 63);
+                if (lane == 0 && e0 + WAVES * u < NE) s_cnt[e0 + WAVES * u] = all;
+            }
+        }
+    }
     if (part < parts) {
         f32x4 ps = {0.f, 0.f, 0.f, 0.f};
         int fs[4] = {0, 0, 0, 0};
         const int col = quad * 4;
-        if (NE % 4 == 0) {
-#pragma unroll 8
-            for (int b = part; b < nblocks; b += parts) {
-                ps += *reinterpret_cast<const f32x4 *>(p_part + (size_t)b * NE + col);
-                if (f_part) {
-                    const int4 c = *reinterpret_cast<const int4 *>(f_part + (size_t)b * NE + col);
-                    fs[0] += c.x; fs[1] += c.y; fs[2] += c.z; fs[3] += c.w;
-                }
-            }
-        } else {
-#pragma unroll 8
-            for (int b = part; b < nblocks; b += parts)
+        constexpr int U = 12;  // (a loop unrolled by the compiler would take what is left over one load after the other)
+        for (int b0 = part; b0 < prows; b0 += parts * U) {
+            f32x4 v[U];
+            if (NE % 4 == 0) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const size_t at = (size_t)b * NE + min(col + q, NE - 1);  // (past NE: not used)
-                    ps[q] += p_part[at];
-                    if (f_part) fs[q] += f_part[at];
-                }
+                for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const f32x4 *>(p_part + (size_t)min(b0 + u * parts, prows - 1) * NE + col);
+            } else {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) v[u][q] = p_part[(size_t)min(b0 + u * parts, prows - 1) * NE + min(col + q, NE - 1)];  // (past NE: not used)
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) ps += b0 + u * parts < prows ? v[u] : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        if (f_part) {
+            for (int b = part; b < prows; b += parts)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) fs[q] += f_part[(size_t)b * NE + min(col + q, NE - 1)];
         }
         s_part[tid] = ps;
         if (f_part)
             for (int q = 0; q < 4; ++q)
                 if (quad * 4 + q < NE) atomicAdd(&s_cnt[quad * 4 + q], fs[q]);
     }
-    if (!f_part) {
-        const int words = cnt_ld / 16;
-        for (int i = tid; i < NE * words; i += kStatsFinalThreads) {
-            const int e = i / words, wi = i - e * words;
-            const uint4 v = *reinterpret_cast<const uint4 *>(cnt8 + (size_t)e * cnt_ld + wi * 16);
-            const unsigned dw[4] = {v.x, v.y, v.z, v.w};
-            int c = 0;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int b0 = wi * 16 + q * 4;
-                unsigned x = dw[q];
-                if (b0 + 4 > nblocks) x = b0 >= nblocks ? 0u : (x & ((1u << (8 * (nblocks - b0))) - 1u));  // bytes past the last block
-                c += (int)__builtin_amdgcn_sad_u8(x, 0u, 0u);
-            }
-            atomicAdd(&s_cnt[e], c);
-        }
-    }
     __syncthreads();
     if (tid < NE) {
         float ps = 0.f;
+#pragma unroll 8
         for (int q = 0; q < parts; ++q) ps += s_part[q * quads + tid / 4][tid % 4];
         s_P[tid] = ps / (float)T;
         s_f[tid] = (float)((double)s_cnt[tid] / (double)T);
@@ -717,9 +735,11 @@ int launch_routing_stats(const zeda_layer_desc *d, const void *x, const void *wr
         uint8_t *cnt8 = (uint8_t *)ws + align_up(route_ws_bytes(d), 256);
         float *p_part = (float *)(cnt8 + route_counts_bytes(d));
         const RouteExtras ex = {cnt8, route_counts_ld(d), p_part, {}, nullptr};
+        const RoutePlan plan = route_plan(d, partial != nullptr);
+        const int prows = ceil_div(d->T, plan.slices > 1 ? kSelectTokens : 16 * plan.tb);  // workgroups that select
         const int rc = launch_route_bf16_any(d, x, wr, bias, nullptr, nullptr, partial, ex, s);
         if (rc != ZEDA_OK) return rc;
-        route_stats_final_kernel<<<1, kStatsFinalThreads, 0, s>>>(p_part, nullptr, cnt8, ex.cnt_ld, ceil_div(d->T, 16), d->T, d->N, NE,
+        route_stats_final_kernel<<<1, kStatsFinalThreads, 0, s>>>(p_part, prows, nullptr, cnt8, ex.cnt_ld, ceil_div(d->T, 16), d->T, d->N, NE,
                                                              d->K, alpha, w, f, P, summary);
         return last_launch_status();
     }
@@ -740,7 +760,7 @@ int launch_routing_stats(const zeda_layer_desc *d, const void *x, const void *wr
     }
 #undef ZEDA_STATS
     if (hipGetLastError() != hipSuccess) return ZEDA_EHIP;
-    route_stats_final_kernel<<<1, kStatsFinalThreads, 0, s>>>(p_part, f_part, nullptr, 0, nblk, d->T, d->N, NE, d->K, alpha, w, f, P,
+    route_stats_final_kernel<<<1, kStatsFinalThreads, 0, s>>>(p_part, nblk, f_part, nullptr, 0, nblk, d->T, d->N, NE, d->K, alpha, w, f, P,
                                                          summary);
     return last_launch_status();
 }
