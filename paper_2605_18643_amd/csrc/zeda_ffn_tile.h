@@ -194,6 +194,13 @@ struct Stream {
     static constexpr int NH = (NSW > NST ? NSW : NST) > 2 ? (NSW > NST ? NSW : NST) - 2 : 1;
     static_assert(!TILED || KC == 32, "tiled weights are stored in 32-wide k blocks");
     static constexpr bool SPLIT_GROUP = NW == 8;  // (four waves: the two wave rows are on different SIMDs)
+    // Wave priorities.  Every SIMD holds a wave of each wave row, and with equal priorities the two go through a chunk side by
+    // side: both wait, then both want the matrix unit.  ROW_PRIO lets the second wave row, which also fetches the tokens, go
+    // first throughout, so that one wave's reads and waits lie under the other's products (whole layer: row-major N=64, I=1536, 4096
+    // tokens 308 -> 297 us, N=128, I=768, 2048 tokens 303 -> 288; 320-row tiles, 8192 tokens 416 -> 408; 256-row tiled ones +0.7 % at
+    // 2048 tokens, four waves +1.4 %: not there).  With the 64-wide token ring, where both rows fetch both operands, a wave that
+    // multiplies goes before one that does not (4096 tokens 274 -> 272 us, N=64, I=1536 258 -> 256; from 460 rows per expert on level).
+    static constexpr bool ROW_PRIO = SPLIT_GROUP && (!TILED || C::G == 5), MUL_PRIO = C::PAIR;
 
     // kernel arguments
     const bf16_t *tok, *w0, *w1;
@@ -595,6 +602,7 @@ struct Stream {
             }
             __builtin_amdgcn_sched_barrier(0);
             constexpr int NM = GM * FB;
+            if (MUL_PRIO) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
             for (int a = 0; a < GM; ++a)
 #pragma unroll
@@ -617,6 +625,7 @@ struct Stream {
                             }
                     }
                 }
+            if (MUL_PRIO) __builtin_amdgcn_s_setprio(0);
             if (GM == 0 && (s & 1)) {
                 if (s == 3) {
 #pragma unroll
@@ -650,6 +659,7 @@ struct Stream {
     __device__ __forceinline__ void tile_body(int expert, int row0, int rows, int ft)
     {
         constexpr int GX = GM > 0 ? GM : 1;
+        if (ROW_PRIO && wt) __builtin_amdgcn_s_setprio(1);
         f32x16 acc[GX][FB];
 #pragma unroll
         for (int a = 0; a < GX; ++a)
