@@ -9,8 +9,11 @@
 // one row, a tiled 32x32 unit is two such fragments of one contiguous KiB each.  No LDS and no barrier until the waves' sums
 // meet; a wave keeps DEPTH chunks of 64 k in flight.  Bound by HBM: 64 tokens, 106 experts hit, 667 MB of gate/up weights
 // in 107 us = 6.2 TB/s; one token, gate/up and down 23 + 13 -> 11 + 8 us (launch included).
+// Row-major weights take a turn through LDS instead (few_multiply_ring): loaded in fragment order, neighbouring lanes touch
+// different rows, and such loads arrive at 37 GB/s per CU, half of what the row-major weights and the token rows of a call need.
 #include "zeda_place.h"
 #include "zeda_select.h"
+#include "zeda_wave_ring.h"
 
 namespace zeda {
 
@@ -84,6 +87,85 @@ __device__ __forceinline__ void few_multiply_rows(int rows, f32x4 (*part)[64], c
     else few_multiply<TILED, NA, NB, 1, DEPTH, NT>(part, pa, pt, wstep, wave, start, Kd);
 }
 
+// The same from row-major weights through a ring of the wave's own in LDS (zeda_wave_ring.h): the same products in the same order.
+// pa, pt: this lane's pieces of rows lane / 8 and 8 + lane / 8 of every block.  lds: the rings, whose memory holds part afterwards.
+constexpr int kFewSlots = 8;
+template <int NA, int NB, int LIVE, bool NT>
+__device__ __forceinline__ void few_multiply_ring(uint32_t lds, f32x4 (*part)[64], const char *const (&pa)[NA][2], const char *const (&pt)[NB][2],
+                                                  int wave, int start, int Kd)
+{
+    constexpr int SEQ = LIVE + NA, D = kFewSlots;  // blocks of a chunk of 64 k: token rows first
+    const int lane = threadIdx.x & 63;
+    f32x4 acc[NA][LIVE];
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int b = 0; b < LIVE; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int n = (Kd / 64 - wave + kFewWaves - 1) / kFewWaves, first = n > 0 ? (int)((unsigned)start % (unsigned)n) : 0, total = n * SEQ;
+    WaveRing<D> ring;
+    ring.init(lds + wave * WaveRing<D>::BYTES);
+    auto col = [&](int c) { const int q = c + first; return (uint32_t)(wave + kFewWaves * (q >= n ? q - n : q)) * 128u; };
+    auto fetch = [&](int j, uint32_t at) {
+        if (j < LIVE) ring.fetch(pt[j < LIVE ? j : 0][0] + at, pt[j < LIVE ? j : 0][1] + at);
+        else ring.template fetch<NT ? 2 : 0>(pa[j < LIVE ? 0 : j - LIVE][0] + at, pa[j < LIVE ? 0 : j - LIVE][1] + at);
+    };
+#pragma unroll
+    for (int i = 0; i < D; ++i)
+        if (i < total) fetch(i % SEQ, col(i / SEQ));
+    for (int k = 0; k < n; ++k) {
+        const int i0 = k * SEQ;
+        uint32_t at[D / SEQ + 2];
+#pragma unroll
+        for (int u = 0; u < D / SEQ + 2; ++u) at[u] = col(min(k + u, n - 1));
+        // A block's fragments are read while the block before is multiplied.  (No branch lies between a read and its wait: the
+        // compiler could copy the registers there, before the data is in them.)
+        u32x4 cur[2], tb[LIVE][2];
+        auto read = [&](int i) {
+            if (i + D <= total) ring_wait_loads<2 * (D - 1)>();
+            else ring_wait_loads<0>();
+            ring.read(cur);
+        };
+        read(i0);
+#pragma unroll
+        for (int j = 0; j < SEQ; ++j) {
+            lds_wait(cur[0], cur[1]);
+            if (i0 + j + D < total) fetch((j + D) % SEQ, at[(j + D) / SEQ]);
+            const u32x4 f[2] = {cur[0], cur[1]};
+            if (j + 1 < SEQ) read(i0 + j + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            if (j < LIVE) {
+                tb[j < LIVE ? j : 0][0] = f[0];
+                tb[j < LIVE ? j : 0][1] = f[1];
+            } else {
+                const int a = j < LIVE ? 0 : j - LIVE;
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+#pragma unroll
+                    for (int b = 0; b < LIVE; ++b)
+                        acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f[s]), __builtin_bit_cast(bf16x8, tb[b][s]), acc[a][b], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    __syncthreads();  // everyone is done with the rings
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int b = 0; b < LIVE; ++b) part[a * NB + b][lane] = acc[a][b];
+}
+
+template <int NA, int NB, bool NT>
+__device__ __forceinline__ void few_multiply_ring_rows(int rows, uint32_t lds, f32x4 (*part)[64], const char *const (&pa)[NA][2],
+                                                       const char *const (&pt)[NB][2], int wave, int start, int Kd)
+{
+    if constexpr (NB == 4) {
+        if (rows > 48) return few_multiply_ring<NA, NB, 4, NT>(lds, part, pa, pt, wave, start, Kd);
+        if (rows > 32) return few_multiply_ring<NA, NB, 3, NT>(lds, part, pa, pt, wave, start, Kd);
+    }
+    if (rows > 16) few_multiply_ring<NA, NB, 2, NT>(lds, part, pa, pt, wave, start, Kd);
+    else few_multiply_ring<NA, NB, 1, NT>(lds, part, pa, pt, wave, start, Kd);
+}
+
 // GATEUP: tok = x[T,Kd], w0 = W_gate[N,F,Kd], w1 = W_up, out = act[S,F];  else tok = act[S,Kd], w0 = W_down[N,F,Kd],
 // out = y_slot[S,F].  Kd a multiple of 64, F of 16 NF.  Up to 16 NB token rows (NB 2 or 4).  Blocks past the last token
 // tile return at once.
@@ -125,7 +207,7 @@ __device__ __forceinline__ void select_tokens(const TilePlace &tp, int T, int N,
     __syncthreads();
 }
 
-template <bool GATEUP, bool TILED, int NF, int NB, int DEPTH, bool MULTI, int FROM>
+template <bool GATEUP, bool TILED, bool RING, int NF, int NB, int DEPTH, bool MULTI, int FROM>
 __global__ __launch_bounds__(kFewThreads) void ffn_few_kernel(const bf16_t *__restrict__ tok, const bf16_t *__restrict__ w0,
                                                               const bf16_t *__restrict__ w1, const int32_t *__restrict__ offsets,
                                                               const int32_t *__restrict__ sorted_slot, bf16_t *__restrict__ out,
@@ -133,7 +215,9 @@ __global__ __launch_bounds__(kFewThreads) void ffn_few_kernel(const bf16_t *__re
 {
     static_assert(kFewThreads == kTileThreads && (GATEUP || FROM == kFromTables) && kTileSelTokens <= kFewWaves, "");
     constexpr int NA = GATEUP ? 2 * NF : NF;  // weight blocks: gate and up blocks alternate
-    __shared__ f32x4 s_part[kFewWaves][NA * NB][64];
+    constexpr int PART = kFewWaves * NA * NB * 64 * 16, RINGS = RING ? kFewWaves * WaveRing<kFewSlots>::BYTES : 0;
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[PART > RINGS ? PART : RINGS];
+    auto s_part = reinterpret_cast<f32x4(*)[NA * NB][64]>(lds);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, kq = lane >> 4;
     const int tile = blockIdx.x / n_ft, ft = blockIdx.x - tile * n_ft;
     int4 loc;
@@ -149,30 +233,50 @@ __global__ __launch_bounds__(kFewThreads) void ffn_few_kernel(const bf16_t *__re
         loc = place_tile<16 * NB>([&](int slot) { return s_ids[slot]; }, T * K, N, tile, ft == 0, blockIdx.x == 0, s_place, tp.out);
     }
     if (loc.z == 0) return;
-    const bf16_t *pt[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const int row = min(16 * b + l16, loc.z - 1);  // columns past the tile repeat its last row (never stored)
+    // (columns past the tile repeat its last row and are never stored; a bad index must not fault)
+    auto tok_row = [&](int row) {
+        row = min(row, loc.z - 1);
         const int slot = FROM != kFromTables ? s_place.list[row] : GATEUP ? sorted_slot[loc.y + row] : 0;
-        pt[b] = tok + (size_t)(GATEUP ? min(max(slot / K, 0), T - 1) : loc.y + row) * Kd + kq * 8;  // a bad index must not fault
-    }
-    const bf16_t *pa[NA];
-#pragma unroll
-    for (int a = 0; a < NA; ++a) {
-        const int f = (ft * NF + (GATEUP ? a / 2 : a)) * 16;
-        const bf16_t *w = ((GATEUP && (a & 1)) ? w1 : w0) + (size_t)loc.x * F * Kd;
-        const int row = (f & 31) + l16;  // of the stored unit
-        pa[a] = TILED ? w + (size_t)(f >> 5) * 1024 + row * 32 + (kq ^ ((row >> 2) & 3)) * 8 : w + (size_t)(f + l16) * Kd + kq * 8;
-    }
-    const size_t wstep = TILED ? (size_t)F * 32 : 32;  // elements from one 32-wide k block to the next
+        return tok + (size_t)(GATEUP ? min(max(slot / K, 0), T - 1) : loc.y + row) * Kd;
+    };
     // An expert starts at a chunk of its own, so that not all workgroups stream the same columns: with few rows per expert
     // the same chunk of row-major rows, often a multiple of 4 KiB apart, sits on a few memory channels.  All feature tiles
     // of an expert start alike: neighbours then read neighbouring units of tiled weights at the same time.
     const int start = loc.x * 5;
-    // An expert of several token tiles has its weights fetched by each of them: they are meant to stay in the caches then.
-    // (N=16, I=2048, K=1, 64 tokens, loads with one hot expert of 39 rows: 0.88 -> 0.83 of the tile kernel's time)
-    if (!MULTI || loc.w <= 16 * NB) few_multiply_rows<TILED, NA, NB, DEPTH, true>(loc.z, s_part[wave], pa, pt, wstep, wave, start, Kd);
-    else few_multiply_rows<TILED, NA, NB, DEPTH, false>(loc.z, s_part[wave], pa, pt, wstep, wave, start, Kd);
+    if constexpr (RING) {
+        const int r8 = lane >> 3;
+        const uint32_t piece[2] = {WaveRing<kFewSlots>::piece0(), WaveRing<kFewSlots>::piece1()};
+        const char *pt[NB][2], *pa[NA][2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) pt[b][h] = reinterpret_cast<const char *>(tok_row(16 * b + 8 * h + r8)) + piece[h];
+#pragma unroll
+            for (int a = 0; a < NA; ++a) {
+                const size_t f = (size_t)(ft * NF + (GATEUP ? a / 2 : a)) * 16 + 8 * h + r8;
+                pa[a][h] = reinterpret_cast<const char *>(((GATEUP && (a & 1)) ? w1 : w0) + ((size_t)loc.x * F + f) * Kd) + piece[h];
+            }
+        }
+        if (!MULTI || loc.w <= 16 * NB) few_multiply_ring_rows<NA, NB, true>(loc.z, lds_addr(lds), s_part[wave], pa, pt, wave, start, Kd);
+        else few_multiply_ring_rows<NA, NB, false>(loc.z, lds_addr(lds), s_part[wave], pa, pt, wave, start, Kd);
+    } else {
+        const bf16_t *pt[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) pt[b] = tok_row(16 * b + l16) + kq * 8;
+        const bf16_t *pa[NA];
+#pragma unroll
+        for (int a = 0; a < NA; ++a) {
+            const int f = (ft * NF + (GATEUP ? a / 2 : a)) * 16;
+            const bf16_t *w = ((GATEUP && (a & 1)) ? w1 : w0) + (size_t)loc.x * F * Kd;
+            const int row = (f & 31) + l16;  // of the stored unit
+            pa[a] = TILED ? w + (size_t)(f >> 5) * 1024 + row * 32 + (kq ^ ((row >> 2) & 3)) * 8 : w + (size_t)(f + l16) * Kd + kq * 8;
+        }
+        const size_t wstep = TILED ? (size_t)F * 32 : 32;  // elements from one 32-wide k block to the next
+        // An expert of several token tiles has its weights fetched by each of them: they are meant to stay in the caches then.
+        // (N=16, I=2048, K=1, 64 tokens, loads with one hot expert of 39 rows: 0.88 -> 0.83 of the tile kernel's time)
+        if (!MULTI || loc.w <= 16 * NB) few_multiply_rows<TILED, NA, NB, DEPTH, true>(loc.z, s_part[wave], pa, pt, wstep, wave, start, Kd);
+        else few_multiply_rows<TILED, NA, NB, DEPTH, false>(loc.z, s_part[wave], pa, pt, wstep, wave, start, Kd);
+    }
     __syncthreads();
 
     // a block's lane l holds features 4 (l / 16) .. + 3 of token l % 16
@@ -242,7 +346,7 @@ int ffn_few_blocks(const zeda_layer_desc *d)
     return slots <= (items <= 80 ? 40 : d->Z > 0 ? 32 : 25) * experts ? 4 : 0;
 }
 
-template <bool GATEUP, bool TILED, int NB, bool MULTI>
+template <bool GATEUP, bool TILED, bool RING, int NB, bool MULTI>
 static int launch_blocks(const zeda_layer_desc *d, const void *tok, const void *w0, const void *w1, const int32_t *offsets,
                          const int32_t *sorted_slot, void *out, const TilePlace *tp, hipStream_t s)
 {
@@ -251,7 +355,7 @@ static int launch_blocks(const zeda_layer_desc *d, const void *tok, const void *
     constexpr int NF = GATEUP ? 1 : 2, DEPTH = 3;
     const int Kd = GATEUP ? d->H : d->I, F = GATEUP ? d->I : d->H, n_ft = F / (16 * NF);
     const int S = d->T * d->K, tiles = (S < d->N ? S : d->N) + S / (16 * NB);  // at most this many token tiles
-#define ZEDA_FEW(FROM) ffn_few_kernel<GATEUP, TILED, NF, NB, DEPTH, MULTI, FROM><<<(unsigned)tiles * n_ft, kFewThreads, 0, s>>>( \
+#define ZEDA_FEW(FROM) ffn_few_kernel<GATEUP, TILED, RING, NF, NB, DEPTH, MULTI, FROM><<<(unsigned)tiles * n_ft, kFewThreads, 0, s>>>( \
         (const bf16_t *)tok, (const bf16_t *)w0, (const bf16_t *)w1, offsets, sorted_slot, (bf16_t *)out, d->N, d->K, Kd, F, n_ft, d->T, tp ? *tp : TilePlace{})
     if constexpr (GATEUP) {
         if constexpr (NB == 2 && !MULTI) {
@@ -273,13 +377,28 @@ static int launch_blocks(const zeda_layer_desc *d, const void *tok, const void *
 // the multiplication costs all workgroups 0.7 % (N=128, I=768, H=2048, 64 tokens row-major: 230.2 -> 233.5 us).
 static bool few_multi(const zeda_layer_desc *d) { return d->T > 32 && (int64_t)d->T * d->K > 8 * ((int64_t)d->N + d->Z); }
 
-template <bool GATEUP, bool TILED>
+// Row-major weights go through the rings where a wave has a chunk to itself (N=32, I=128, H=768, whose down projection has not: 64
+// tokens 17.4 -> 18.3 us with them).  Whole layer, without / with: N=128, I=768, H=2048 one token 26.2 / 22.8 us, 32 tokens 161 / 147, 64
+// tokens 214 / 191; N=64, I=1536, 64 tokens 214 / 178; N=48, I=768, 301 tokens 112 / 89; N=24, I=448, 301 tokens 36.6 / 35.4.
+template <bool GATEUP>
+static bool few_ring(const zeda_layer_desc *d) { return (GATEUP ? d->H : d->I) >= 64 * kFewWaves; }
+
+template <bool GATEUP, bool TILED, bool RING>
 static int launch(const zeda_layer_desc *d, const void *tok, const void *w0, const void *w1, const int32_t *offsets,
                   const int32_t *sorted_slot, void *out, const TilePlace *tp, hipStream_t s)
 {
-    if (ffn_few_blocks(d) == 4) return launch_blocks<GATEUP, TILED, 4, true>(d, tok, w0, w1, offsets, sorted_slot, out, tp, s);
-    return few_multi(d) ? launch_blocks<GATEUP, TILED, 2, true>(d, tok, w0, w1, offsets, sorted_slot, out, tp, s)
-                        : launch_blocks<GATEUP, TILED, 2, false>(d, tok, w0, w1, offsets, sorted_slot, out, tp, s);
+    if (ffn_few_blocks(d) == 4) return launch_blocks<GATEUP, TILED, RING, 4, true>(d, tok, w0, w1, offsets, sorted_slot, out, tp, s);
+    return few_multi(d) ? launch_blocks<GATEUP, TILED, RING, 2, true>(d, tok, w0, w1, offsets, sorted_slot, out, tp, s)
+                        : launch_blocks<GATEUP, TILED, RING, 2, false>(d, tok, w0, w1, offsets, sorted_slot, out, tp, s);
+}
+
+template <bool GATEUP>
+static int launch_layout(const zeda_layer_desc *d, const void *tok, const void *w0, const void *w1, const int32_t *offsets,
+                         const int32_t *sorted_slot, void *out, const TilePlace *tp, hipStream_t s)
+{
+    if (d->weight_layout == ZEDA_WEIGHTS_TILED) return launch<GATEUP, true, false>(d, tok, w0, w1, offsets, sorted_slot, out, tp, s);
+    return few_ring<GATEUP>(d) ? launch<GATEUP, false, true>(d, tok, w0, w1, offsets, sorted_slot, out, tp, s)
+                       : launch<GATEUP, false, false>(d, tok, w0, w1, offsets, sorted_slot, out, tp, s);
 }
 
 // Up to 1024 slots (four a thread) the kernels with a workgroup per 16 or 32 columns place the slots themselves.
@@ -299,14 +418,12 @@ bool gateup_selects(const zeda_layer_desc *d)
 int launch_gateup_few(const zeda_layer_desc *d, const void *x, const void *wg, const void *wu, const int32_t *offsets,
                       const int32_t *sorted_slot, void *act, const TilePlace *tp, hipStream_t s)
 {
-    return d->weight_layout == ZEDA_WEIGHTS_TILED ? launch<true, true>(d, x, wg, wu, offsets, sorted_slot, act, tp, s)
-                                                  : launch<true, false>(d, x, wg, wu, offsets, sorted_slot, act, tp, s);
+    return launch_layout<true>(d, x, wg, wu, offsets, sorted_slot, act, tp, s);
 }
 
 int launch_down_few(const zeda_layer_desc *d, const void *act, const void *wd, const int32_t *offsets, void *y_slot, hipStream_t s)
 {
-    return d->weight_layout == ZEDA_WEIGHTS_TILED ? launch<false, true>(d, act, wd, nullptr, offsets, nullptr, y_slot, nullptr, s)
-                                                  : launch<false, false>(d, act, wd, nullptr, offsets, nullptr, y_slot, nullptr, s);
+    return launch_layout<false>(d, act, wd, nullptr, offsets, nullptr, y_slot, nullptr, s);
 }
 
 }  // namespace zeda

@@ -41,14 +41,15 @@ struct WaveRing {
     // byte of a row's 128 that this lane fetches, in the first and in the second half of a block
     __device__ __forceinline__ static uint32_t piece0() { return (uint32_t)ring_swz((threadIdx.x & 63) >> 3, threadIdx.x & 7) * 16; }
     __device__ __forceinline__ static uint32_t piece1() { return piece0() ^ 64; }
-    // lo, hi: where this lane's pieces of rows 0..7 and 8..15 are
+    // lo, hi: where this lane's pieces of rows 0..7 and 8..15 are.  CPOL: cache policy bits of the loads (2: non-temporal)
+    template <int CPOL = 0>
     __device__ __forceinline__ void fetch(const void *lo, const void *hi)
     {
         typedef const __attribute__((address_space(1))) void *global_ptr;
         typedef __attribute__((address_space(3))) void *lds_ptr;
         const uint32_t at = base + fill;
-        __builtin_amdgcn_global_load_lds((global_ptr)lo, (lds_ptr)(uintptr_t)at, 16, 0, 0);
-        __builtin_amdgcn_global_load_lds((global_ptr)hi, (lds_ptr)(uintptr_t)(at + 1024), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((global_ptr)lo, (lds_ptr)(uintptr_t)at, 16, 0, CPOL);
+        __builtin_amdgcn_global_load_lds((global_ptr)hi, (lds_ptr)(uintptr_t)(at + 1024), 16, 0, CPOL);
         fill = fill == (D - 1) * kRingBlock ? 0 : fill + kRingBlock;
     }
     // start reading the two fragments of the next block.  (Not to be left in flight across a branch or around a loop: the compiler
