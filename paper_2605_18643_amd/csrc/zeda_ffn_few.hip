@@ -89,7 +89,9 @@ __device__ __forceinline__ void few_multiply_rows(int rows, f32x4 (*part)[64], c
 
 // The same from row-major weights through a ring of the wave's own in LDS (zeda_wave_ring.h): the same products in the same order.
 // pa, pt: this lane's pieces of rows lane / 8 and 8 + lane / 8 of every block.  lds: the rings, whose memory holds part afterwards.
-constexpr int kFewSlots = 8;
+// Four blocks in flight per wave, 32 KiB of LDS a workgroup: with eight, two workgroups fit on a CU and too little is in flight between
+// one's end and the next one's start (N=128, I=768, 64 tokens 191 us, four 173, three 174, two 175).
+constexpr int kFewSlots = 4;
 template <int NA, int NB, int LIVE, bool NT>
 __device__ __forceinline__ void few_multiply_ring(uint32_t lds, f32x4 (*part)[64], const char *const (&pa)[NA][2], const char *const (&pt)[NB][2],
                                                   int wave, int start, int Kd)
@@ -378,8 +380,9 @@ static int launch_blocks(const zeda_layer_desc *d, const void *tok, const void *
 static bool few_multi(const zeda_layer_desc *d) { return d->T > 32 && (int64_t)d->T * d->K > 8 * ((int64_t)d->N + d->Z); }
 
 // Row-major weights go through the rings where a wave has a chunk to itself (N=32, I=128, H=768, whose down projection has not: 64
-// tokens 17.4 -> 18.3 us with them).  Whole layer, without / with: N=128, I=768, H=2048 one token 26.2 / 22.8 us, 32 tokens 161 / 147, 64
-// tokens 214 / 191; N=64, I=1536, 64 tokens 214 / 178; N=48, I=768, 301 tokens 112 / 89; N=24, I=448, 301 tokens 36.6 / 35.4.
+// tokens 17.4 -> 18.3 us with them).  Whole layer, without / with: N=128, I=768, H=2048 one token 26.2 / 23.0 us, 32 tokens 161 / 132, 64
+// tokens 214 / 173; N=64, I=1536, 64 tokens 214 / 177; N=48, I=768, 301 tokens 112 / 82; N=24, I=448, 301 tokens 36.6 / 28.9.  Tiled
+// weights, whose fragments are contiguous KiB already, lose by it (N=128, I=768, 64 tokens 174 -> 189 us with eight blocks in flight).
 template <bool GATEUP>
 static bool few_ring(const zeda_layer_desc *d) { return (GATEUP ? d->H : d->I) >= 64 * kFewWaves; }
 
