@@ -14,8 +14,12 @@
 // waves are added in 64 bits and rounded once.  Error against 64 bits, 2-norm, whole layer: T=513, H=1024, I=512 1.46e-7 (four sums of
 // eight products on the fp32 instruction and a tree over them: 1.60e-7).
 //
-// Magnitudes that round to a bf16 infinity have no such sum: rows with one are reported, and the caller computes what depends
-// on them in another way.
+// The window: nonzero magnitudes from 2^-110 to 2^60.  Inside it the parts are bf16 numbers, subnormal ones among them, which
+// the matrix unit takes and gives as the fp32 instruction does (probed: products, accumulators and results down to 2^-149); and
+// neither a product nor a chunk's sum of 32 can overflow (2^125).  Below it low parts fall off the end of bf16; above it an
+// overflowing product is infinity minus infinity in its parts, or infinite where both factors' hi rounded up.  Rows with an
+// element outside are reported, and the caller multiplies them on the fp32 instruction (zeda_f32_tile.h).  No-numbers pass: they
+// come out as such either way.
 #pragma once
 #include "zeda_wave_ring.h"
 
@@ -25,13 +29,16 @@ typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
-constexpr float kSplitMax = 3.38e38f;  // (the largest bf16 is 3.3895e38)
+constexpr float kSplitMin = 0x1p-110f, kSplitMax = 0x1p60f;
 
 // D: blocks that the wave keeps in flight
 template <int NA, int NB, int D>
 struct F32Split {
     static constexpr int SEQ = NB + NA;  // blocks of a chunk of 32 k: token rows first
+    static_assert(16 * NB <= 32 && 16 * NA <= 64, "a bit per row");
     f64x2 acc[NA][NB][2];
+    uint32_t odd_tok;  // bit 16 b + r: row r of token block b has an element outside the window, its sums are not to be used
+    uint64_t odd_w;    // the same of the weight blocks
 
     struct Parts {
         bf16x8 hi, mid, lo;
@@ -58,15 +65,29 @@ struct F32Split {
         for (int q = 0; q < 4; ++q) sm[q >> 1][q & 1] += (double)v[q];
         asm volatile("" : "+v"(sm[0]), "+v"(sm[1]));  // (here, not for all blocks at the chunk's end: registers)
     }
-    // eight elements a lane.  huge: whether one of them is past kSplitMax
-    __device__ __forceinline__ static Parts split(const u32x4 (&f)[2], bool &huge)
+    // eight elements a lane.  odd: receives a bit for each of the block's 16 rows, is there an element outside the window
+    __device__ __forceinline__ static Parts split(const u32x4 (&f)[2], uint32_t &odd)
     {
+        float largest = 0.f, least = kSplitMin;
+#pragma unroll
+        for (int i = 0; i < 8; i += 2) {
+            const float v0 = __uint_as_float(f[i >> 2][i & 3]), v1 = __uint_as_float(f[i >> 2][(i & 3) + 1]);
+            largest = fmaxf(fmaxf(fabsf(v0), fabsf(v1)), largest);
+            least = fminf(fminf(fabsf(v0), fabsf(v1)), least);
+        }
+        odd = 0;
+        if (__any(largest > kSplitMax || least < kSplitMin)) {  // (zeros come here too)
+            uint32_t low = ~0u;  // smallest 2 |element| - 1 in bits, which zeros leave alone
+#pragma unroll
+            for (int i = 0; i < 8; ++i) low = min(low, 2 * f[i >> 2][i & 3] - 1);
+            const unsigned long long m = __ballot(largest > kSplitMax || low < 2 * __float_as_uint(kSplitMin) - 1);
+            const uint32_t h = (uint32_t)(m | (m >> 32));
+            odd = (h | (h >> 16)) & 0xffffu;
+        }
         u32x4 part[3];
-        float largest = 0.f;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             float v0 = __uint_as_float(f[i >> 1][2 * (i & 1)]), v1 = __uint_as_float(f[i >> 1][2 * (i & 1) + 1]);
-            largest = fmaxf(fmaxf(fabsf(v0), fabsf(v1)), largest);
 #pragma unroll
             for (int p = 0; p < 3; ++p) {
                 const uint32_t two = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){v0, v1}, bf16x2));
@@ -75,24 +96,23 @@ struct F32Split {
                 v1 -= __uint_as_float(two & 0xffff0000u);
             }
         }
-        huge = largest > kSplitMax;
         return {__builtin_bit_cast(bf16x8, part[0]), __builtin_bit_cast(bf16x8, part[1]), __builtin_bit_cast(bf16x8, part[2])};
     }
 
     // lds: this wave's ring.  The rows of weight block a start at base[a % 2] + wo[a][.] bytes, those of token block b at pb[b][.]
-    // ([0]: row lane / 8 of the block, [1]: row 8 + lane / 8).  Kd: a multiple of 4.  huge_tok, huge_w: LDS addresses of 16 NB and 16 NA
-    // bytes, zeroed by the caller, that receive ones for rows with an element past kSplitMax.
+    // ([0]: row lane / 8 of the block, [1]: row 8 + lane / 8).  Kd: a multiple of 4.
     // Slice `slice` of `slices`: the 32-wide chunks slice, slice + slices, ..., starting at one that depends on rot (rows
     // are often a multiple of 4 KiB apart, which puts a chunk of every row on one L2 channel: workgroups that start at
     // different chunks spread over the channels)
     __device__ __forceinline__ void run(uint32_t lds, const float *base0, const float *base1, const uint32_t (&wo)[NA][2],
-                                        const float *const (&pb)[NB][2], uint32_t huge_tok, uint32_t huge_w, int slice, int slices, int rot,
-                                        int Kd)
+                                        const float *const (&pb)[NB][2], int slice, int slices, int rot, int Kd)
     {
         clear();
+        odd_tok = 0;
+        odd_w = 0;
         const int n = ((Kd + 31) / 32 - slice + slices - 1) / slices;
         if (n <= 0) return;
-        const int first = (int)((unsigned)rot % (unsigned)n), total = n * SEQ, l16 = threadIdx.x & 15;
+        const int first = (int)((unsigned)rot % (unsigned)n), total = n * SEQ;
         const uint32_t rowb = (uint32_t)Kd * 4;
         WaveRing<D> ring;
         ring.init(lds);
@@ -113,7 +133,9 @@ struct F32Split {
         for (int i = 0; i < D; ++i)
             if (i < total) fetch(i % SEQ, col(i / SEQ));
         Parts tb[NB];
-        for (int k = 0; k < n; ++k) {
+        constexpr uint32_t ALL_TOK = ~0u >> (32 - 16 * NB);
+        constexpr uint64_t ALL_W = ~0ull >> (64 - 16 * NA);
+        for (int k = 0; k < n; k = odd_tok == ALL_TOK || odd_w == ALL_W ? n : k + 1) {  // (then nothing of this will be used)
             const int i0 = k * SEQ;
             uint32_t at[D / SEQ + 2];
 #pragma unroll
@@ -133,9 +155,10 @@ struct F32Split {
                 if (i0 + j + D < total) fetch((j + D) % SEQ, at[(j + D) / SEQ]);
                 mask(cur, rowb - at[0]);
                 const int a = j < NB ? 0 : j - NB, t = j < NB ? j : 0;
-                bool huge;
-                const Parts w = split(cur, huge);
-                if (__any(huge) && huge) lds_write_b8((j < NB ? huge_tok + 16 * t : huge_w + 16 * a) + l16, 1);
+                uint32_t odd;
+                const Parts w = split(cur, odd);
+                if (j < NB) odd_tok |= odd << (16 * t);
+                else odd_w |= (uint64_t)odd << (16 * a);
                 if (j + 1 < SEQ) read(i0 + j + 1);
                 __builtin_amdgcn_sched_barrier(0);
                 if (j < NB) {
@@ -161,6 +184,7 @@ struct F32Split {
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
+        ring_wait_loads<0>();
     }
 };
 

@@ -119,9 +119,7 @@ struct F32Ffn {
     static constexpr int NF = GATEUP ? NA / 2 : NA;  // feature blocks: gate and up blocks alternate
     static constexpr int RING = WaveRing<kF32Slots>::BYTES;
     static constexpr int PART = NA * 2 * 64 * (int)sizeof(f64x2);  // a wave's sums of one token block
-    static constexpr int HUGE_OFF = kF32Waves * (RING > PART ? RING : PART);  // the rings, then the waves' sums; then a byte per row:
-    static constexpr int HUGE_W = 16 * NB, HUGE = HUGE_W + 16 * NA;           // does it hold an element past kSplitMax (token rows first)
-    static constexpr int LDS_BYTES = HUGE_OFF + HUGE;
+    static constexpr int LDS_BYTES = kF32Waves * (RING > PART ? RING : PART);  // the rings, then the waves' sums
     typedef f64x2 (*Part)[NA * 2][64];
 
     // the tile's rows are out's rows first .. first + rows - 1, in LIVE blocks of 16; features f0 ..; tok_row(r): row r's token values
@@ -134,9 +132,8 @@ struct F32Ffn {
         const float *p[LIVE][2];
 #pragma unroll
         for (int b = 0; b < LIVE; ++b) { p[b][0] = pb[b][0]; p[b][1] = pb[b][1]; }
-        const uint8_t *huge = lds + HUGE_OFF;
         F32Split<NA, LIVE, kF32Slots> t;
-        t.run(lds_addr(lds) + wave * RING, w0, w1, wo, p, lds_addr(huge), lds_addr(huge + HUGE_W), wave, kF32Waves, (int)blockIdx.x * 3, Kd);
+        t.run(lds_addr(lds) + wave * RING, w0, w1, wo, p, wave, kF32Waves, (int)blockIdx.x * 3, Kd);
         Part part = reinterpret_cast<Part>(lds);
 #pragma unroll
         for (int b = 0; b < LIVE; ++b) {
@@ -146,6 +143,8 @@ struct F32Ffn {
                 part[wave][2 * a][lane] = t.acc[a][b][0];
                 part[wave][2 * a + 1][lane] = t.acc[a][b][1];
             }
+            const uint32_t odd_tok = (t.odd_tok >> (16 * b)) & 0xffffu;
+            if (odd_tok || t.odd_w) multiply_odd(part[wave], odd_tok, t.odd_w, w0, w1, tok_row(min(16 * b + l16, rows - 1)), f0, F, wave, Kd);
             __syncthreads();
             // block (a, b): lane l holds features 4 (l / 16) .. + 3 of token l % 16
             const int r = 16 * b + l16;
@@ -174,22 +173,33 @@ struct F32Ffn {
                 *reinterpret_cast<f32x4 *>(out + (size_t)(first + r) * F + f) = v;
             }
         }
-        // What depends on a row with an element past kSplitMax came out as no number: a thread adds its products up in 64 bits
-        // (a value at a time: this is for infinities, not for speed).
-        const int tid = threadIdx.x;
-        if (!__syncthreads_or(tid < HUGE ? huge[tid] : 0)) return;  // (the stores above have been waited for)
-        for (int i = tid; i < rows * 16 * NF; i += kF32Threads) {
-            const int r = i / (16 * NF), c = i - r * (16 * NF), fb = c / 16, f = f0 + c;
-            if (f >= F) continue;
-            const uint8_t *hw = huge + HUGE_W + 16 * (GATEUP ? 2 * fb : fb) + c % 16;
-            if (!(huge[r] | hw[0] | (GATEUP ? hw[16] : 0))) continue;
-            const float *x = tok_row(r), *a = w0 + (size_t)f * Kd, *u = w1 + (size_t)f * Kd;
-            double s0 = 0.0, s1 = 0.0;
-            for (int k = 0; k < Kd; ++k) {
-                s0 += (double)x[k] * a[k];
-                if (GATEUP) s1 += (double)x[k] * u[k];
+    }
+    // What rows outside the split's window contribute to one token block (row l % 16 of it: tok), in this wave's slice of the
+    // reduction: their sums on the fp32 instruction take the place of the split's.  Ordinary pairs of rows keep theirs, so a
+    // token's result does not depend on its neighbours.
+    __device__ __forceinline__ static void multiply_odd(f64x2 (*part)[64], uint32_t odd_tok, uint64_t odd_w, const float *w0, const float *w1,
+                                                        const float *tok, int f0, int F, int wave, int Kd)
+    {
+        const int lane = threadIdx.x & 63, l16 = lane & 15;
+        static_assert(NA % 2 == 0, "two weight blocks at a time");
+#pragma unroll 1
+        for (int a0 = 0; a0 < NA; a0 += 2) {
+            const uint32_t ow = (uint32_t)(odd_w >> (16 * a0));
+            if (!(odd_tok | ow)) continue;
+            const float *pa[2], *pb[1] = {tok};
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int f = min(f0 + 16 * (GATEUP ? a0 / 2 : a0 + i) + l16, F - 1);
+                pa[i] = (GATEUP && i ? w1 : w0) + (size_t)f * Kd;
             }
-            out[(size_t)(first + r) * F + f] = GATEUP ? swiglu((float)s0, (float)s1) : (float)s0;
+            F32Tile<2, 1> t;
+            t.run(pa, pb, wave, kF32Waves, (int)blockIdx.x * 3, Kd);
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (((odd_tok >> l16) | (ow >> (16 * i + 4 * (lane >> 4) + k))) & 1)
+                        part[2 * (a0 + i) + (k >> 1)][lane][k & 1] = t.acc[i][0][k >> 1][k & 1];
         }
     }
     __device__ __forceinline__ static float swiglu(float g, float u) { return g / (1.f + expf(-g)) * u; }
@@ -210,9 +220,6 @@ __global__ __launch_bounds__(kF32Threads, 3) void ffn_f32_split_kernel(const flo
     const int4 loc = locate_f32<PLACE>(offsets, N, K, T, tile, ft, s_place, tp);
     const int rows = loc.z;
     if (rows == 0) return;
-    static_assert(C::HUGE <= kF32Threads, "a thread per row");
-    if (threadIdx.x < C::HUGE) lds[C::HUGE_OFF + threadIdx.x] = 0;
-    __syncthreads();
     const int f0 = ft * 16 * C::NF;
 
     auto tok_row = [&](int row) {

@@ -34,10 +34,6 @@ __device__ __forceinline__ void lds_write_b64(uint32_t a, u32x2 v)
 {
     asm volatile("ds_write_b64 %0, %1" ::"v"(a), "v"(v) : "memory");
 }
-__device__ __forceinline__ void lds_write_b8(uint32_t a, uint32_t v)
-{
-    asm volatile("ds_write_b8 %0, %1" ::"v"(a), "v"(v) : "memory");
-}
 // results of the reads above may be used after this
 __device__ __forceinline__ void lds_wait() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 __device__ __forceinline__ void lds_wait(uint32_t &a) { asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a)::"memory"); }
