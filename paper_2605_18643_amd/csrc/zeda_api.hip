@@ -111,7 +111,7 @@ static int forward_impl(const zeda_layer_desc *desc, const void *x, const void *
     }
     const PlaceOut place = {offsets, sorted_slot, slot_to_row, num_real, num_real_out};
     // Few slots: the gate/up kernel places them, and selects for a handful of tokens (the tables it leaves are the same).
-    TilePlace tp = {ids, place, gates, nullptr, router_bias, 0, 0, 0, desc->N + desc->Z, desc->gate_norm};
+    TilePlace tp = {ids, place, gates, nullptr, router_bias, 0, 0, 0, desc->N + desc->Z, desc->gate_norm, false};
     const bool places = gateup_places(desc);
     if (places) {
         if ((rc = launch_route(desc, x, w_router, router_bias, ids, gates, route_ws, nullptr, nullptr, gateup_selects(desc) ? &tp : nullptr, s)) != ZEDA_OK) return rc;

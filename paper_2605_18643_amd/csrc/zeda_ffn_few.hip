@@ -203,7 +203,7 @@ __device__ __forceinline__ void select_tokens(const TilePlace &tp, int T, int N,
 #pragma unroll
         for (int c = 0; c < NC; ++c) lg[wave][lane + 64 * c] = v[0][c] + bias[c];
         // (a wave reads what it wrote; experts past NE are left out)
-        const int id = select_wave<kMaxExperts / 64>(lg[wave], true, wave, tp.NE, N, K, tp.gate_norm, lead ? tp.ids : nullptr, tp.gates);
+        const int id = select_wave<kMaxExperts / 64>(lg[wave], true, wave, tp.NE, N, K, tp.gate_norm, lead ? tp.ids : nullptr, tp.gates, nullptr, tp.by_rows);
         if (lane < K) s_ids[wave * K + lane] = id;
     }
     __syncthreads();

@@ -139,7 +139,7 @@ constexpr int kTileThreads = 256;
 constexpr int kTileMaxSlots = 4 * kTileThreads;
 
 // What such a kernel starts from and writes: the ids of all slots, or the logits of up to kTileSelTokens tokens, left by the router's
-// first kernel in `slices` tables [Tpad][E], from which it selects.
+// first kernel in `slices` tables [Tpad][E], from which it selects (by_rows: the router's second kernel would do so with four waves).
 constexpr int kTileSelTokens = 4;
 struct TilePlace {
     int32_t *ids;
@@ -147,6 +147,7 @@ struct TilePlace {
     float *gates;
     const float *partial, *bias;
     int slices, Tpad, E, NE, gate_norm;
+    bool by_rows;
 };
 
 template <int ROWS>

@@ -75,7 +75,7 @@ __device__ __forceinline__ void publish_blocks(const int *s_cnt, const float *pr
 // to 129 GB/s per CU, 64-byte pieces at half of that), then launch and selection (route_plan weighs them).
 constexpr int kRouteWaves = 16;
 constexpr int kRouteWavesSmall = 4;
-constexpr int kRouteSmallNB = 2;  // ... for up to 32 times this many experts
+constexpr int kRouteSmallNB = 2;  // ... for up to 32 times this many experts (select_wave's by_rows: a candidate a lane)
 // k chunk of a workgroup of 16 tb tokens and `waves` waves
 __host__ __device__ constexpr int route_chunk(int tb, int waves) { return tb == 1 || (tb == 2 && waves == kRouteWavesSmall) ? 128 : 64; }
 
@@ -441,6 +441,7 @@ static int launch_route_bf16(const zeda_layer_desc *d, const void *x, const void
         ex.tp->slices = slices;
         ex.tp->Tpad = Tpad;
         ex.tp->E = NB * 32;
+        ex.tp->by_rows = W == kRouteWavesSmall;
         return last_launch_status();
     }
     const dim3 sgrid(ceil_div(d->T, kSelectTokens));

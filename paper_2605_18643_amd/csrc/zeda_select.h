@@ -164,9 +164,11 @@ __device__ __forceinline__ int select_rows(const float *lg, int LD, int pstride,
 // The same for one token by a whole wave: lane l holds the candidates l, l + 64, ...; a round's winner is found from
 // ballots, lowest candidate group and lane first, i.e. the lowest index.  Shorter rounds than the above (few
 // candidates per lane): for workgroups with a wave for every token.  lg: the token's logits, biases included.
+// by_rows (NE <= 64): the softmax denominator is added in the order of select_rows; everything else does not depend on an order.
 template <int NC>
 __device__ __forceinline__ int select_wave(const float *lg, bool ok, size_t t, int NE, int N, int K, int gate_norm,
-                                           int32_t *__restrict__ ids, float *__restrict__ gates, float *probs = nullptr)
+                                           int32_t *__restrict__ ids, float *__restrict__ gates, float *probs = nullptr,
+                                           bool by_rows = false)
 {
     const int lane = threadIdx.x & 63;
     int cand[NC];
@@ -195,7 +197,14 @@ __device__ __forceinline__ int select_wave(const float *lg, bool ok, size_t t, i
             ex[c] = (ok && lane + 64 * c < NE) ? expf(key_logit(cand[c]) - all_max) : 0.f;
             sacc += ex[c];
         }
-        all_sum = wave_sum(sacc);
+        if (by_rows) {
+            sacc = 0.f;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) sacc += __shfl(ex[0], (lane & 15) + 16 * c);
+            all_sum = row_sum(sacc);
+        } else {
+            all_sum = wave_sum(sacc);
+        }
         if (probs && ok) {
 #pragma unroll
             for (int c = 0; c < NC; ++c)
