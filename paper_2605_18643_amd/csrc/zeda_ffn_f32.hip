@@ -245,14 +245,20 @@ __global__ __launch_bounds__(kF32Threads, 3) void ffn_f32_split_kernel(const flo
     else C::template run<1>(lds, w0, w1, wo, pb, Kd, out, loc.y, rows, f0, F, tok_row);
 }
 
+// at most this many token tiles
+static int f32_tiles(const zeda_layer_desc *d)
+{
+    const int S = d->T * d->K;
+    return (S < d->N ? S : d->N) + S / kF32Rows;
+}
+
 // SPLIT: the kernel for many rows per expert
 template <bool GATEUP, int NA, bool SPLIT>
 static int launch(const zeda_layer_desc *d, const float *tok, const float *w0, const float *w1, const int32_t *offsets,
                   const int32_t *sorted_slot, float *out, const TilePlace *tp, hipStream_t s)
 {
     const int Kd = GATEUP ? d->H : d->I, F = GATEUP ? d->I : d->H;
-    const int n_ft = ceil_div(F, 16 * (GATEUP ? NA / 2 : NA));
-    const int S = d->T * d->K, tiles = (S < d->N ? S : d->N) + S / kF32Rows;  // at most this many token tiles
+    const int n_ft = ceil_div(F, 16 * (GATEUP ? NA / 2 : NA)), tiles = f32_tiles(d);
     const dim3 grid((unsigned)(tiles < kF32GridTiles ? tiles : kF32GridTiles) * n_ft, ceil_div(tiles, kF32GridTiles));
     auto go = [&](auto *kernel) { kernel<<<grid, kF32Threads, 0, s>>>(tok, w0, w1, offsets, sorted_slot, out, d->N, d->K, Kd, F, n_ft, d->T, tp ? *tp : TilePlace{}); };
     if constexpr (GATEUP) {
@@ -276,12 +282,18 @@ static bool f32_many_rows(const zeda_layer_desc *d) { return (int64_t)d->T * d->
 
 // Four weight blocks per workgroup halve the token reads per weight byte; two make twice the workgroups, for layers whose
 // experts are too few and too narrow to fill the device otherwise.
+static bool f32_wide(const zeda_layer_desc *d, int rows) { return (int64_t)d->N * rows >= 256 * 64; }  // rows: of an expert's weights
+
+int64_t gateup_f32_workgroups(const zeda_layer_desc *d)
+{
+    return (int64_t)f32_tiles(d) * ceil_div(d->I, f32_wide(d, 2 * d->I) ? 32 : 16);
+}
+
 template <bool GATEUP>
 static int launch_any(const zeda_layer_desc *d, const void *tok, const void *w0, const void *w1, const int32_t *offsets,
                       const int32_t *sorted_slot, void *out, const TilePlace *tp, hipStream_t s)
 {
-    const int F = GATEUP ? 2 * d->I : d->H;
-    const bool wide = (int64_t)d->N * F >= 256 * 64;
+    const bool wide = f32_wide(d, GATEUP ? 2 * d->I : d->H);
     const float *t = (const float *)tok, *a = (const float *)w0, *b = (const float *)w1;
     if (wide && f32_many_rows(d)) return launch<GATEUP, 4, true>(d, t, a, b, offsets, sorted_slot, (float *)out, tp, s);
     return wide ? launch<GATEUP, 4, false>(d, t, a, b, offsets, sorted_slot, (float *)out, tp, s)

@@ -348,6 +348,13 @@ int ffn_few_blocks(const zeda_layer_desc *d)
     return slots <= (items <= 80 ? 40 : d->Z > 0 ? 32 : 25) * experts ? 4 : 0;
 }
 
+// at most this many token tiles of 16 nb rows
+static int64_t few_tiles(const zeda_layer_desc *d, int nb)
+{
+    const int64_t slots = (int64_t)d->T * d->K;
+    return (slots < d->N ? slots : d->N) + slots / (16 * nb);
+}
+
 template <bool GATEUP, bool TILED, bool RING, int NB, bool MULTI>
 static int launch_blocks(const zeda_layer_desc *d, const void *tok, const void *w0, const void *w1, const int32_t *offsets,
                          const int32_t *sorted_slot, void *out, const TilePlace *tp, hipStream_t s)
@@ -356,8 +363,8 @@ static int launch_blocks(const zeda_layer_desc *d, const void *tok, const void *
     // three chunks of 64 k in flight (four leave fewer waves per SIMD: 177.5 -> 176.5 us)
     constexpr int NF = GATEUP ? 1 : 2, DEPTH = 3;
     const int Kd = GATEUP ? d->H : d->I, F = GATEUP ? d->I : d->H, n_ft = F / (16 * NF);
-    const int S = d->T * d->K, tiles = (S < d->N ? S : d->N) + S / (16 * NB);  // at most this many token tiles
-#define ZEDA_FEW(FROM) ffn_few_kernel<GATEUP, TILED, RING, NF, NB, DEPTH, MULTI, FROM><<<(unsigned)tiles * n_ft, kFewThreads, 0, s>>>( \
+    const unsigned grid = (unsigned)few_tiles(d, NB) * n_ft;
+#define ZEDA_FEW(FROM) ffn_few_kernel<GATEUP, TILED, RING, NF, NB, DEPTH, MULTI, FROM><<<grid, kFewThreads, 0, s>>>( \
         (const bf16_t *)tok, (const bf16_t *)w0, (const bf16_t *)w1, offsets, sorted_slot, (bf16_t *)out, d->N, d->K, Kd, F, n_ft, d->T, tp ? *tp : TilePlace{})
     if constexpr (GATEUP) {
         if constexpr (NB == 2 && !MULTI) {
@@ -404,18 +411,29 @@ static int launch_layout(const zeda_layer_desc *d, const void *tok, const void *
                        : launch<GATEUP, false, false>(d, tok, w0, w1, offsets, sorted_slot, out, tp, s);
 }
 
-// Up to 1024 slots (four a thread) the kernels with a workgroup per 16 or 32 columns place the slots themselves.
+// Up to 1024 slots (four a thread) the kernels with a workgroup per 16 or 32 columns place the slots themselves, unless there are
+// so many workgroups that placing in each of them costs more than the launch it saves.  How much of it disappears under the loads
+// of the CU's other workgroups depends on how long these are, i.e. on H.  Whole layer, us, with a launch / without:
+//   bf16, H=2048: 12700 workgroups 264 / 257, 13800 367.7 / 365.5, 15400 383 / 386;  H=1024: 6300 73.8 / 73.1, 7700 118.1 / 123.5, 8700
+//   137.7 / 142.7, 15400 212 / 225;  H=512: 6300 46.3 / 45.9, 8700 73.4 / 74.9;  H=4096: 29700 1082 / 1077
+//   fp32, 640 workgroups 28.4 / 24.6 and 59.9 / 55.6;  H=256: 3300 82.5 / 80.6, 3800 100.3 / 103.0, 8700 199 / 209;  H=1024: 3300 238.3 / 236.8,
+//   3800 286.6 / 291.2, 8700 584 / 596;  H=512: 18400 586 / 669;  H=2048: 5100 682 / 674, 8700 1132 / 1122
 bool gateup_places(const zeda_layer_desc *d)
 {
     if ((int64_t)d->T * d->K > kTileMaxSlots) return false;
-    return d->dtype == ZEDA_F32 || ffn_few_blocks(d) > 0;
+    if (d->dtype == ZEDA_F32) return gateup_f32_workgroups(d) <= (d->H < 2048 ? 3500 : 9 * (int64_t)d->H / 2);
+    const int nb = ffn_few_blocks(d);
+    return nb > 0 && few_tiles(d, nb) * (d->I / 16) <= 7 * (int64_t)(d->H > 1024 ? d->H : 1024);
 }
 
-// A wave per token, so up to four tokens are selected there too: 4 us in front of a workgroup's weights, for a kernel of 6.6 (N=128,
-// Z=32, I=768, whole layer: one token 27.4 -> 23.3 us, two 33.0 -> 29.4, four, 700 workgroups with rows, 48.3 -> 47.2).
+// A wave per token, so up to four tokens are selected there too, for a kernel of 6.6 us: 4 us in front of every workgroup's weights,
+// which pays with up to four workgroups a CU.  Whole layer, us, with the kernel / without: H=2048, 384 workgroups 26.6 / 24.4, 768 32.1 /
+// 30.6, 1536 49.0 / 50.6, 3200 81.9 / 89.1, 12700 266 / 328;  H=1024, 384 22.5 / 20.5, 768 28.2 / 26.3, 1536 36.4 / 38.2, 12700 158 / 219;
+// H=4096, 768 64.4 / 60.7, 1584 89.1 / 90.5.
 bool gateup_selects(const zeda_layer_desc *d)
 {
-    return gateup_places(d) && d->dtype == ZEDA_BF16 && d->T <= kTileSelTokens && ffn_few_blocks(d) == 2 && !few_multi(d) && route_splits(d);
+    return d->dtype == ZEDA_BF16 && d->T <= kTileSelTokens && gateup_places(d) && ffn_few_blocks(d) == 2 && few_tiles(d, 2) * (d->I / 16) <= 1024 &&
+           route_splits(d);
 }
 
 int launch_gateup_few(const zeda_layer_desc *d, const void *x, const void *wg, const void *wu, const int32_t *offsets,

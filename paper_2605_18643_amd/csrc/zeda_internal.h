@@ -68,6 +68,7 @@ size_t dispatch_static_scratch_bytes();
 int dispatch_static_max_slots();          // slot lists up to this length are accepted by that entry point
 // tp (may be NULL): the kernel places the slots itself (only where gateup_places(d)); offsets and sorted_slot are then outputs
 bool gateup_places(const zeda_layer_desc *d);
+int64_t gateup_f32_workgroups(const zeda_layer_desc *d);
 bool gateup_selects(const zeda_layer_desc *d);  // ... and selects, from the partial logits of the router's first kernel
 int launch_gateup(const zeda_layer_desc *d, const void *x, const void *wg, const void *wu, const int32_t *offsets,
                   const int32_t *sorted_slot, void *act, const TilePlace *tp, hipStream_t s);

@@ -132,9 +132,9 @@ __device__ __forceinline__ int4 locate_rows(const int32_t *__restrict__ offsets,
 
 // Short slot lists are placed by the gate/up kernels themselves: every workgroup counts the experts' slots, finds the expert of
 // its token tile and collects the tile's slots; what the later kernels read is written by the workgroups of the first feature
-// tile.  Instead of a launch of 4 to 5 us that is half a microsecond of a workgroup that starts at once, and 5 us in all where 27
-// workgroups follow each other on a CU.  Whole layer, with the launch / without: T=64, H=256, I=128, N=8, K=2, fp32 22.9 / 18.3 us;
-// N=24, I=448, 300 tokens (900 slots) 39.7 / 36.6; N=128, I=768, 64 tokens (512 slots, 6900 workgroups) 175.3 / 173.8.
+// tile.  Instead of a launch of 4 to 5 us that is half a microsecond or more of every workgroup (gateup_places: for how many it
+// pays).  Whole layer, with the launch / without: T=64, H=256, I=128, N=8, K=2, fp32 22.9 / 18.3 us; N=24, I=448, 300 tokens
+// (900 slots) 39.7 / 36.6; N=128, I=768, 64 tokens (512 slots, 6900 workgroups) 175.3 / 173.8.
 constexpr int kTileThreads = 256;
 constexpr int kTileMaxSlots = 4 * kTileThreads;
 
