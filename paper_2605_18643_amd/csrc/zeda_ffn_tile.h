@@ -196,11 +196,16 @@ struct Stream {
     static constexpr bool SPLIT_GROUP = NW == 8;  // (four waves: the two wave rows are on different SIMDs)
     // Wave priorities.  Every SIMD holds a wave of each wave row, and with equal priorities the two go through a chunk side by
     // side: both wait, then both want the matrix unit.  ROW_PRIO lets the second wave row, which also fetches the tokens, go
-    // first throughout, so that one wave's reads and waits lie under the other's products (whole layer: row-major N=64, I=1536, 4096
-    // tokens 308 -> 297 us, N=128, I=768, 2048 tokens 303 -> 288; 320-row tiles, 8192 tokens 416 -> 408; 256-row tiled ones +0.7 % at
-    // 2048 tokens, four waves +1.4 %: not there).  With the 64-wide token ring, where both rows fetch both operands, a wave that
-    // multiplies goes before one that does not (4096 tokens 274 -> 272 us, N=64, I=1536 258 -> 256; from 460 rows per expert on level).
-    static constexpr bool ROW_PRIO = SPLIT_GROUP && (!TILED || C::G == 5), MUL_PRIO = C::PAIR;
+    // first throughout, so that one wave's reads and waits lie under the other's products (whole layer, row-major: N=64, I=1536, 4096
+    // tokens 313.2 -> 297.9 us, N=128, I=768, 2048 tokens 333.5 -> 321.8, 8192 tokens 470 -> 467, Z=0 784 -> 783; 256-row tiled tiles +0.7 %
+    // at 2048 tokens, four waves +1.4 %: not there).  In the 320-row tiles (LOAD_PRIO) it is right while the weights are what a tile
+    // waits for, and wrong where the matrix unit is busy without it.  N=128, I=768, rows per expert, without -> with: 195 341.3 ->
+    // 342.6, 227 395.6 -> 387.5, 256 (Z=0) 406.9 -> 400.8, 277 514 -> 537, 294 (Z=0) 500 -> 517, 512 (Z=0) 783 -> 804, 625 (Z=0) 966 -> 992; N=64, I=1536: 251 398.8
+    // -> 394.4, 281 494 -> 516; skewed loads of several tiles an expert, mean 225 462.9 -> 468.7, 203 470.1 -> 477.2.
+    // With the 64-wide token ring, where both rows fetch both operands, a wave that multiplies goes before one that does not (MUL_PRIO;
+    // 4096 tokens 273.7 -> 272.7 us, 5120 tokens 301.8 -> 300.9, from 200 rows per expert on level).
+    static constexpr bool ROW_PRIO = SPLIT_GROUP && !TILED, LOAD_PRIO = SPLIT_GROUP && TILED && C::G == 5, MUL_PRIO = C::PAIR;
+    bool row_first;  // LOAD_PRIO: the second wave row goes first (run_tiles_auto)
 
     // kernel arguments
     const bf16_t *tok, *w0, *w1;
@@ -659,7 +664,7 @@ struct Stream {
     __device__ __forceinline__ void tile_body(int expert, int row0, int rows, int ft)
     {
         constexpr int GX = GM > 0 ? GM : 1;
-        if (ROW_PRIO && wt) __builtin_amdgcn_s_setprio(1);
+        if ((ROW_PRIO || (LOAD_PRIO && row_first)) && wt) __builtin_amdgcn_s_setprio(1);
         f32x16 acc[GX][FB];
 #pragma unroll
         for (int a = 0; a < GX; ++a)
@@ -774,7 +779,7 @@ __device__ __forceinline__ void run_tiles(unsigned char *lds, const TileScan<C> 
                                           const bf16_t *__restrict__ w0,
                                           const bf16_t *__restrict__ w1, const int32_t *__restrict__ offsets,
                                           const int32_t *__restrict__ sorted_slot, bf16_t *__restrict__ out, int N, int K,
-                                          int Kdim, int Fdim, int n_ftiles, int T)
+                                          int Kdim, int Fdim, int n_ftiles, int T, bool row_first)
 {
     static_assert(!GATEUP || C::FB % 2 == 0, "gate and up blocks come in pairs");
     int *s_tok = reinterpret_cast<int *>(lds + C::TOK_OFF);
@@ -819,7 +824,7 @@ __device__ __forceinline__ void run_tiles(unsigned char *lds, const TileScan<C> 
         st.lane = lane; st.wave = wave; st.wt = wave / C::WF; st.wf = wave % C::WF; st.col = lane & 31; st.half = lane >> 5;
         st.foff_t = (st.wt * 32 + st.col) * C::TROWB + swz<C::TKC>(st.col, st.half) * 16;
         st.foff_w = (st.wf * C::FB * 32 + st.col) * C::ROWB + swz<C::KC>(st.col, st.half) * 16;
-        st.wrole = wave < C::NWW;
+        st.wrole = wave < C::NWW; st.row_first = row_first;
         st.nq = nq; st.cslot_w = 0; st.cslot_t = 0;
         st.init_issue();
         st.setup_issue_item();
@@ -851,6 +856,8 @@ __device__ __forceinline__ void run_tiles(unsigned char *lds, const TileScan<C> 
 // expert -4 %, at 3 rows -10 %; at 460 rows per expert the hint costs 2 % instead).  Decided once per launch from
 // the expert loads; the cache-policy field of the load is an immediate, so the two cases are two instantiations.
 //
+// The 320-row tiles of experts with one tile each and up to 264 rows on average put their second wave row first (see Stream).
+//
 // There, from 64 to 191 rows per expert, an item also starts at a k chunk that depends on its expert and feature tile:
 // row-major rows are often a multiple of 4 KiB apart, so that one chunk of every row sits on a few memory channels, and
 // workgroups that all start at chunk 0 queue there (expert FFN, row-major, even loads: N=64, I=1408, 140 rows 301 -> 274 us,
@@ -867,15 +874,16 @@ __device__ __forceinline__ void run_tiles_auto(unsigned char *lds, const TileSca
                                                int T)
 {
     const int ne = scan0.experts();
-    const bool stream_once = scan0.tiles * 16 <= ne * 17 && offsets[N] < 400 * ne;
+    const bool one_tile = scan0.tiles * 16 <= ne * 17, stream_once = one_tile && offsets[N] < 400 * ne;
+    const bool row_first = __builtin_amdgcn_readfirstlane(one_tile && offsets[N] <= 264 * ne);
     if (stream_once) {
         if constexpr (C::ROT) {
             if (offsets[N] >= 64 * ne && offsets[N] < 192 * ne)
-                return run_tiles<C, GATEUP, TILED, true, true>(lds, scan0, tok, w0, w1, offsets, sorted_slot, out, N, K, Kdim, Fdim, n_ftiles, T);
+                return run_tiles<C, GATEUP, TILED, true, true>(lds, scan0, tok, w0, w1, offsets, sorted_slot, out, N, K, Kdim, Fdim, n_ftiles, T, row_first);
         }
-        run_tiles<C, GATEUP, TILED, true, false>(lds, scan0, tok, w0, w1, offsets, sorted_slot, out, N, K, Kdim, Fdim, n_ftiles, T);
+        run_tiles<C, GATEUP, TILED, true, false>(lds, scan0, tok, w0, w1, offsets, sorted_slot, out, N, K, Kdim, Fdim, n_ftiles, T, row_first);
     } else {
-        run_tiles<C, GATEUP, TILED, false, false>(lds, scan0, tok, w0, w1, offsets, sorted_slot, out, N, K, Kdim, Fdim, n_ftiles, T);
+        run_tiles<C, GATEUP, TILED, false, false>(lds, scan0, tok, w0, w1, offsets, sorted_slot, out, N, K, Kdim, Fdim, n_ftiles, T, row_first);
     }
 }
 
