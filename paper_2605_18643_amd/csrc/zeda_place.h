@@ -152,7 +152,7 @@ struct TilePlace {
 
 template <int ROWS>
 struct TilePlaceLds {
-    int hist[kMaxExperts];              // slots on every expert
+    alignas(16) int hist[kMaxExperts];  // slots on every expert (read four at a time)
     int cnt[kTileMaxSlots / 64];        // slots of every 64-slot group on the tile's expert
     int list[ROWS];                     // the tile's slots, ascending
 };
@@ -163,6 +163,7 @@ template <int ROWS, typename IdOf>
 __device__ __forceinline__ int4 place_tile(const IdOf &id_of, int S, int N, int tile, bool first, bool lead, TilePlaceLds<ROWS> &s, const PlaceOut &o)
 {
     static_assert(kTileThreads == kMaxExperts, "one thread per expert");
+    static_assert(alignof(TilePlaceLds<ROWS>) == alignof(int4), "hist is read in 16-byte pieces");
     constexpr int G = kTileMaxSlots / kTileThreads, W = kTileThreads / 64;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int id[G];
