@@ -120,13 +120,17 @@ def make_desc(T, H, I, N, Z, K, dtype, gate_norm=GATE_TOPK_NORM, weight_layout=0
 
 
 # Arguments go to ctypes as plain integers (the functions' argtypes say what they are), and the current stream is asked for
-# by its handle: ten c_void_p objects and a Stream object a call were 4 us of a small layer's 18 us on the host.
+# by its handle, where this torch has the (private) function for it: ten c_void_p objects and a Stream object a call were 4 us
+# of a small layer's 18 us on the host.
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
 def _stream(stream) -> int:
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) if stream is None else stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return torch.cuda.current_stream().cuda_stream if raw is None else raw(torch.cuda.current_device())
 
 
 def _check(rc: int, where: str) -> None:
