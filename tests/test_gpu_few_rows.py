@@ -46,7 +46,7 @@ CASES = [
     dict(T=50, H=768, I=1024, N=50, Z=0, K=8),
     dict(T=51, H=768, I=1024, N=50, Z=0, K=8),
     dict(T=64, H=512, I=256, N=200, Z=20, K=8),
-    # both sides of the 16 tokens that the router may place itself, widest pool, slots on every expert
+    # both sides of the 16 tokens of the router's selecting workgroups, widest pool, slots on every expert
     dict(T=16, H=2048, I=64, N=60, Z=30, K=16),
     dict(T=17, H=2048, I=64, N=60, Z=30, K=16),
     dict(T=33, H=1024, I=64, N=200, Z=56, K=4),

@@ -1,6 +1,7 @@
-"""The bf16 router where the hidden dimension is split over workgroups and a second kernel selects (and, up to 16 tokens,
-places), and where it is not, for both workgroup sizes: ids, gates, placement and statistics against the oracle.  How many
-slices ran is read off the scratch, so that a case cannot stop reaching the kernels it is here for."""
+"""The bf16 router where the hidden dimension is split over workgroups and a second kernel selects, and where it is not, for both
+workgroup sizes: ids, gates, placement and statistics against the oracle.  How many slices ran is read off the scratch, so
+that a case cannot stop reaching the kernels it is here for.  (zeda_route and the statistics run the second kernel; whole-layer
+calls of few slots place, and up to four tokens select, in the gate/up kernel.  Its own placement: test_gpu_place_list.)"""
 import ctypes
 
 import numpy as np
@@ -35,7 +36,7 @@ def _slices(d, ws, nbytes):
 
 # (T, H, N, Z, K, slices)
 CASES = [
-    # 16 waves: eight slices; 64, 128 and 256 slots in the placing workgroup; both sides of its 16 tokens; sixteen slices
+    # 16 waves: eight slices; both sides of the 16 tokens of a selecting workgroup; sixteen slices
     (1, 2048, 128, 32, 8, 8),
     (9, 2048, 128, 32, 8, 8),
     (16, 2048, 128, 32, 16, 8),
@@ -53,7 +54,7 @@ CASES = [
     (2500, 512, 128, 32, 8, 0),
     (5000, 256, 128, 32, 8, 0),
     (16500, 128, 70, 26, 3, 0),
-    # four waves: splits, placement of 256 slots, one kernel with 16, 32 and 64 tokens a workgroup
+    # four waves: splits, a full and a ragged selecting workgroup, one kernel with 16, 32 and 64 tokens a workgroup
     (1, 2048, 24, 8, 2, 8),
     (16, 2048, 20, 12, 16, 8),
     (17, 2048, 40, 24, 4, 8),

@@ -15,11 +15,13 @@ GATES = [zeda.GATE_SOFTMAX, zeda.GATE_TOPK_NORM, zeda.GATE_REAL_RENORM]
 
 
 # H: such that the router is split over the hidden dimension (eight or sixteen slices).  I = 2688: 1008 workgroups, 2752: 1032
+SHAPES = [(1, 24, 8, 2, 2048, 64), (2, 5, 2, 3, 4096, 64), (4, 40, 24, 6, 2048, 64), (3, 33, 20, 4, 4096, 64), (4, 20, 12, 16, 2048, 64),
+          (5, 40, 24, 6, 2048, 64), (1, 60, 5, 4, 2048, 64), (4, 128, 32, 8, 2048, 64), (3, 200, 56, 8, 4096, 64), (1, 40, 24, 6, 2048, 2688),
+          (1, 40, 24, 6, 2048, 2752), (1, 128, 32, 6, 2048, 2752)]
+
+
 @pytest.mark.parametrize("gate", GATES)
-@pytest.mark.parametrize("shape", [(1, 24, 8, 2, 2048, 64), (2, 5, 2, 3, 2048, 64), (4, 40, 24, 6, 2048, 64), (3, 33, 20, 4, 4096, 64),
-                                   (4, 20, 12, 16, 2048, 64), (5, 40, 24, 6, 2048, 64), (1, 60, 5, 4, 2048, 64), (4, 128, 32, 8, 2048, 64),
-                                   (3, 200, 56, 8, 4096, 64), (1, 40, 24, 6, 2048, 2688), (1, 40, 24, 6, 2048, 2752), (1, 128, 32, 6, 2048, 2752)],
-                         ids=lambda s: "T%d_N%d_Z%d_K%d_H%d_I%d" % s)
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "T%d_N%d_Z%d_K%d_H%d_I%d" % s)
 def test_layer_and_router_select_alike(shape, gate):
     T, N, Z, K, H, I = shape
     w = synth.Workload("select_bits", T=T, H=H, I=I, N=N, Z=Z, K=K, dtype="bf16", seed=811, recipe="zero_bias", x_std=1.0, w_std=0.02,

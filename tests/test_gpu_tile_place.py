@@ -81,7 +81,10 @@ def test_tokens_without_an_expert(dtype, T):
 
 
 # the number of workgroups from which on the slots get a launch of their own: 6960 and 7424 (bound 7168), 3456 and 3600 (bound 3500)
-@pytest.mark.parametrize("dtype,H,I,N", [("bf16", 256, 960, 100), ("bf16", 256, 1024, 100), ("f32", 64, 768, 128), ("f32", 64, 800, 128)])
+BOUND_CASES = [("bf16", 256, 960, 100), ("bf16", 256, 1024, 100), ("f32", 64, 768, 128), ("f32", 64, 800, 128)]
+
+
+@pytest.mark.parametrize("dtype,H,I,N", BOUND_CASES)
 def test_tables_on_both_sides_of_the_workgroup_bound(dtype, H, I, N):
     w = synth.Workload("tile_place", T=64, H=H, I=I, N=N, Z=30, K=8, dtype=dtype, seed=702, recipe="zero_bias", x_std=1.0, w_std=0.02, wr_std=0.05,
                        zero_bias=0.1)
