@@ -166,7 +166,10 @@ int zeda_moe_forward(const zeda_layer_desc *desc, const void *x, const void *w_r
 
 /* Same as zeda_moe_forward, and records caller-created hipEvent_t handles around the kernels:
  * events[0] before the first kernel, events[i] after stage i in the order of zeda_stage
- * (ZEDA_NUM_STAGES + 1 events; host array of handles).  For profiling only. */
+ * (ZEDA_NUM_STAGES + 1 events; host array of handles).  For profiling only.
+ * A stage without a launch of its own takes no time between its events: up to 1024 slots the gate/up kernels of fp32 layers and
+ * of few rows per expert do the dispatch, and for up to four tokens the selection of the routing too (ZEDA_STAGE_GATEUP then holds
+ * it, ZEDA_STAGE_ROUTE the logits); in most other calls of up to 16 tokens the router does the dispatch. */
 enum {
     ZEDA_STAGE_ROUTE = 0,
     ZEDA_STAGE_DISPATCH = 1,

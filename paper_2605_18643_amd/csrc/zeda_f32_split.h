@@ -3,16 +3,19 @@
 //
 // Why not the fp32 instruction: it runs at the rate of the vector unit and keeps vector instructions out while it does (16x16x4
 // in a register-only loop, two waves per SIMD: 32 cycles each, 59 with the 20 vector instructions between every eight that add
-// the sums up).  x = hi + mid + lo is exact with each part rounded to nearest; of the nine products of parts six matter, the
-// other three are below 2^-26 of the product.  Six 16x16x32 take 96 cycles of the matrix unit where eight 16x16x4 take 256, and
-// the vector unit is free for the splitting (44 instructions per 16 x 32 block of an operand).
+// the sums up).  x = hi + mid + lo is exact inside the window below, with each part rounded to nearest; of the nine products of parts
+// six are formed, the other three are below 2^-26 of the product (Henry, Tang, Heinecke, "Leveraging the bfloat16 Artificial
+// Intelligence Datatype For Higher-Precision Computations", ARITH 2019).  Six 16x16x32 take 96 cycles of the matrix unit where
+// eight 16x16x4 take 256, and the vector unit is free for the splitting (44 instructions per 16 x 32 block of an operand, and 8 for
+// the window: 513 tokens, H=1024, I=512 94.3 -> 96.4 us a layer).
 //
 // A lane's fragments are two pieces of four consecutive k of one row: lane l holds row l % 16, pieces l / 16 and 4 + l / 16 of
 // the 32 k; both operands are permuted alike, so the sum runs over all of them.
 //
-// Precision: the products of a chunk of 32 k are added in the matrix unit, smallest parts first; chunk sums and the slices of the
-// waves are added in 64 bits and rounded once.  Error against 64 bits, 2-norm, whole layer: T=513, H=1024, I=512 1.46e-7 (four sums of
-// eight products on the fp32 instruction and a tree over them: 1.60e-7).
+// Precision: a chunk's 6 x 32 products of parts are added in one fp32 accumulator of the matrix unit, smallest parts first, where the
+// fp32 instruction adds eight whole products; chunk sums and the slices of the waves are added in 64 bits and rounded once.  Error
+// against 64 bits, 2-norm, whole layer: T=513, H=1024, I=512 1.46e-7 (four sums of eight products on the fp32 instruction and a tree
+// over them: 1.60e-7).
 //
 // The window: nonzero magnitudes from 2^-110 to 2^60.  Inside it the parts are bf16 numbers, subnormal ones among them, which
 // the matrix unit takes and gives as the fp32 instruction does (probed: products, accumulators and results down to 2^-149); and

@@ -168,15 +168,8 @@ __device__ __forceinline__ void few_multiply_ring_rows(int rows, uint32_t lds, f
     else few_multiply_ring<NA, NB, 1, NT>(lds, part, pa, pt, wave, start, Kd);
 }
 
-// GATEUP: tok = x[T,Kd], w0 = W_gate[N,F,Kd], w1 = W_up, out = act[S,F];  else tok = act[S,Kd], w0 = W_down[N,F,Kd],
-// out = y_slot[S,F].  Kd a multiple of 64, F of 16 NF.  Up to 16 NB token rows (NB 2 or 4).  Blocks past the last token
-// tile return at once.
-// MULTI: an expert may have more rows than a workgroup takes.
-// FROM: where the tile's rows come from: the tables of a placement, the ids of all slots, or the logits of all tokens (tp).
-enum FewFrom { kFromTables, kFromIds, kFromLogits };
-
-// select_tokens: the routing of up to kTileSelTokens tokens from their partial logits, a token per wave; s_ids receives the ids.
-// The same additions and the same selection as in the router's second kernel.
+// The routing of up to kTileSelTokens tokens from their partial logits, a token per wave; s_ids receives the ids.  The same
+// additions and the same selection as in the router's second kernel, of four waves or of sixteen (tp.by_rows).
 __device__ __forceinline__ void select_tokens(const TilePlace &tp, int T, int N, int K, bool lead, float (*lg)[kMaxExperts], int *s_ids)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -209,6 +202,14 @@ __device__ __forceinline__ void select_tokens(const TilePlace &tp, int T, int N,
     __syncthreads();
 }
 
+// Where a tile's rows come from: the tables of a placement, the ids of all slots, or the logits of all tokens (tp).
+enum FewFrom { kFromTables, kFromIds, kFromLogits };
+
+// GATEUP: tok = x[T,Kd], w0 = W_gate[N,F,Kd], w1 = W_up, out = act[S,F];  else tok = act[S,Kd], w0 = W_down[N,F,Kd],
+// out = y_slot[S,F].  Kd a multiple of 64, F of 16 NF.  Up to 16 NB token rows (NB 2 or 4).  Blocks past the last token
+// tile return at once.
+// RING: weights and tokens go through LDS (row-major weights).
+// MULTI: an expert may have more rows than a workgroup takes.
 template <bool GATEUP, bool TILED, bool RING, int NF, int NB, int DEPTH, bool MULTI, int FROM>
 __global__ __launch_bounds__(kFewThreads) void ffn_few_kernel(const bf16_t *__restrict__ tok, const bf16_t *__restrict__ w0,
                                                               const bf16_t *__restrict__ w1, const int32_t *__restrict__ offsets,
@@ -308,25 +309,27 @@ __global__ __launch_bounds__(kFewThreads) void ffn_few_kernel(const bf16_t *__re
 // Where this kernel beats the tile kernels, and with how many 16-row token blocks a workgroup (0: not).  The real loads are
 // only known on the device; what is known here is the slots per expert if they fell evenly on all N + Z experts, and the
 // tile kernel's gate/up work items, one per 128 columns of I and expert.  Fitted to 37 layer shapes with 1 to 1000 tokens
-// under even, Zipf and one-hot-expert loads, and with half of the slots on zero experts.  Below: this kernel's time over the
-// better tile kernel's, row-major / tiled, even loads where nothing else is said.
-//  - up to 40 items there is next to nothing to fill the chip with (N=16, I=256, H=512: 1000 tokens 0.60 / 0.66, 2000
-//    tokens, 167 rows, 0.89 / 0.84);
-//  - decode batches: up to 64 items the tile kernel fills a quarter of the chip (N=8, K=6, I=1024: 48 rows 0.83 / 0.83 with
-//    four token blocks, 1.06 / 1.00 with two); more of them, and the rows count: N=8, I=3072, 192 items: 16 rows 0.82 /
-//    0.87; N=16, I=2304, K=16, 288 items: 16 rows 0.87 / 0.94, 32 rows 1.06 / 1.15; a filled chip, N=8, I=14336: 8 rows 1.01 /
-//    1.02, 12 rows 1.05 / 1.05, but N=128, I=768: 2 rows 0.9 / 0.98, N=64, I=2048, 6 rows 0.96 / 0.97;
-//  - short reductions leave the four waves a chunk or two each: N=64, I=512, H=512: 4 rows 1.00 / 0.95, 8 rows 1.07 / 1.01;
-//    N=256, I=256, H=1024: half a slot per expert 0.97 / 1.0, one 1.04 / 1.01 and 1.09 / 1.17 with Zipf loads;
-//  - longer batches on a chip that the tile kernel fills: N=128, Z=32, I=768, 5 slots per expert: 0.95 / 1.01 with half of the
-//    slots on zero experts (Zipf loads 0.90 / 0.94), 1.09 / 1.04 with a fifth of them.  Without zero experts: I >= 1024 0.86-1.02
-//    / 0.88-1.03 (N=100, H=1536), N=128, I=768 0.95 / 0.99 at H = 1024 but 1.03 / 1.03 at H = 2048, N=200, I=512 0.92-1.08 / 0.90-1.00
-//    from machine to machine; from H = 4096 on the row-major loads fall behind (N=192, I=2048, H=4096, 3 rows 1.09-1.17 / 0.96-1.01).
-//    N=128, I=384, 384 items: 5 slots 0.85 / 0.99, 10 slots 0.90 / 1.05;
-//  - between one and two rounds of 256 CUs the tile kernel idles: N=48, I=768, 288 items: 18 rows 0.80 / 0.88, 25 rows 0.87 /
-//    0.94, 30 rows 0.82 / 0.93 with four blocks, 1.02 / 1.11 with two; N=24, I=448, 96 items: 30 rows 0.98 / 1.07 (20 of them
-//    real: 0.91 / 0.97) with four, 1.17 with two; N=12, I=704, 72 items: 40 rows 0.90 / 0.98.  With one full round it does not:
-//    N=60, I=512, 240 items: 12 rows 0.97 / 0.99, 16 rows 1.02 / 1.06, 19 rows 1.04 / 1.11.
+// under even, Zipf and one-hot-expert loads, and with half of the slots on zero experts.  One rule for both layouts, so that both
+// add in the same order; where they differ the tiled one decides: row-major weights, which the rings fetch by whole cache lines,
+// would gain from this kernel almost everywhere (last item).  Below: the expert FFN's time here over the better tile kernel's,
+// row-major / tiled, even loads, weights from HBM, H = 2048 where nothing else is said.
+//  - up to 40 items there is next to nothing to fill the chip with (N=16, I=256, H=512: 83 rows 0.50 / 0.65, 166 rows 0.62 / 0.85);
+//  - decode batches: up to 64 items the tile kernel fills a quarter of the chip (N=8, K=6, I=1024: 48 rows 0.61 / 0.92 with
+//    four token blocks, 0.72 / 1.24 with two); more of them, and the rows count: N=8, I=3072, 192 items: 16 rows 0.60 / 0.83;
+//    N=16, I=2304, K=16, 288 items: 16 rows 0.68 / 0.91, 32 rows 0.73 / 1.10; a filled chip, N=8, I=14336: 8 rows 0.69 / 0.88, 12 rows
+//    0.70 / 0.90, at H = 4096 0.73 / 1.04 and 0.77 / 1.04; N=128, I=768: 2 rows 0.75 / 1.00, N=64, I=2048, 6 rows 0.75 / 0.98;
+//  - short reductions leave the four waves a chunk or two each: N=64, I=512, H=512: 4 rows 0.77 / 0.91, 8 rows 0.78 / 0.94;
+//    N=256, I=256, H=1024: half a slot per expert 0.84 / 1.03, one 0.73 / 1.03 (tiled, Zipf loads: 1.17);
+//  - longer batches on a chip that the tile kernel fills: N=128, Z=32, I=768, 5 slots per expert: 0.82 / 1.01 with half of the
+//    slots on zero experts (Zipf loads, tiled: 0.94), 0.82 / 1.02 with a fifth of them.  Without zero experts: N=100, I=1024, H=1536
+//    0.64 / 0.91, N=128, I=768 0.74 / 0.98 at H = 1024 but 0.82 / 1.02 at H = 2048, N=200, I=512 0.76 / 0.93 (tiled 0.90-1.00 from machine to
+//    machine); from H = 4096 on tiled weights are level (N=192, I=2048, 5 rows 0.97 / 0.99; N=96, I=1536 0.83 / 0.99).
+//    N=128, I=384, 384 items: 5 slots 0.74 / 0.96, 10 slots 0.73 / 1.01;
+//  - between one and two rounds of 256 CUs the tile kernel idles: N=48, I=768, 288 items: 18 rows 0.59 / 0.89, 25 rows 0.63 / 0.98, 30
+//    rows 0.66 / 1.05; N=24, I=448, H=1152, 96 items: 30 rows 0.71 / 0.97 (20 of them real: 0.67 / 0.92) with four blocks; N=12,
+//    I=704, 72 items: 40 rows 0.62 / 0.93 with four, 0.70 / 1.09 with two.  With one full round it does not: N=60, I=512, 240 items:
+//    12 rows 0.69 / 1.05, 16 rows 0.70 / 1.09, 19 rows 0.72 / 1.14;
+//  - beyond the rule: N=128, Z=32, I=768: 6 rows 0.83 / 1.04, 12 rows 0.85 / 1.11, 31 rows 1.00 / 1.33; N=64, I=1536: 12 rows 0.83 / 1.07.
 int ffn_few_blocks(const zeda_layer_desc *d)
 {
     const int64_t slots = (int64_t)d->T * d->K, experts = d->N + d->Z, cols = ceil_div(d->I, 128), items = d->N * cols;
@@ -383,7 +386,8 @@ static int launch_blocks(const zeda_layer_desc *d, const void *tok, const void *
 }
 
 // With a few slots per expert, an expert of several token tiles is one of many whose weights are fetched, and the second copy of
-// the multiplication costs all workgroups 0.7 % (N=128, I=768, H=2048, 64 tokens row-major: 230.2 -> 233.5 us).
+// the multiplication costs all workgroups up to half a percent (N=128, I=768, H=2048, 64 tokens, expert FFN: row-major 177.5 -> 178.0
+// us, tiled 184.4 -> 185.2).
 static bool few_multi(const zeda_layer_desc *d) { return d->T > 32 && (int64_t)d->T * d->K > 8 * ((int64_t)d->N + d->Z); }
 
 // Row-major weights go through the rings where a wave has a chunk to itself (N=32, I=128, H=768, whose down projection has not: 64

@@ -203,7 +203,7 @@ struct Stream {
     // 342.6, 227 395.6 -> 387.5, 256 (Z=0) 406.9 -> 400.8, 277 514 -> 537, 294 (Z=0) 500 -> 517, 512 (Z=0) 783 -> 804, 625 (Z=0) 966 -> 992; N=64, I=1536: 251 398.8
     // -> 394.4, 281 494 -> 516; skewed loads of several tiles an expert, mean 225 462.9 -> 468.7, 203 470.1 -> 477.2.
     // With the 64-wide token ring, where both rows fetch both operands, a wave that multiplies goes before one that does not (MUL_PRIO;
-    // 4096 tokens 273.7 -> 272.7 us, 5120 tokens 301.8 -> 300.9, from 200 rows per expert on level).
+    // 4096 tokens 282.7 -> 281.4 us, twice, runs of one side 0.3 us apart; from 200 rows per expert on level).
     static constexpr bool ROW_PRIO = SPLIT_GROUP && !TILED, LOAD_PRIO = SPLIT_GROUP && TILED && C::G == 5, MUL_PRIO = C::PAIR;
     bool row_first;  // LOAD_PRIO: the second wave row goes first (run_tiles_auto)
 
