@@ -41,7 +41,8 @@ __device__ __forceinline__ void select_block(const float *lg, int LD, int pstrid
 
 // After select_block (and a barrier): what the workgroup's blocks of 16 tokens hand to the expert-sorted placement
 // and what it hands to the routing statistics.  cnt8[e][cnt_ld] bytes: slots of every block on expert e;
-// p_part[workgroup][NE]: the sum of every expert's routing probability over the workgroup's tokens, added in token order.
+// p_part[workgroup][NE]: the sum of every expert's routing probability over the workgroup's tokens, added in token order (up to 64;
+// 16 by 16 is no nearer to 64 bits beyond what draws differ by: 8.4e-8 and 8.6e-8, 8192 to 16384 tokens).
 template <int THREADS>
 __device__ __forceinline__ void publish_blocks(const int *s_cnt, const float *probs, int LDP, int ntok, int t0, int T, int NE,
                                                uint8_t *__restrict__ cnt8, int cnt_ld, float *__restrict__ p_part)
@@ -601,13 +602,20 @@ __global__ __launch_bounds__(kStatsThreads) void route_stats_kernel(const float 
 // Final workgroup: adds everything up.  p_part [rows][NE], a row per workgroup of the kernel before, and either f_part, int32
 // counts laid out alike, or cnt8[e][cnt_ld], the counts of nblocks blocks of 16 tokens as bytes.  A thread takes four experts of
 // p_part, with one 16-byte load where rows are that aligned.  The threads of an expert quad, kStatsParts at most, take every
-// parts-th row, twelve loads in flight, and their sums are added in a fixed order (16 experts, 16 tokens: 256 threads a quad cost
-// 3 us, 32 cost 0.3); a wave takes an expert's byte counts, eight experts in flight, and adds them as integers, so their order
-// does not matter.  What it waits for is one CU's share of memory: 8192 tokens, 160 experts 10.1 us with a row of p_part per 16
-// tokens and an LDS addition per 16 counts, 7.8 now.  (One thread per expert walking all rows: 142 us.)
+// parts-th row, and their sums are added in a fixed order (16 experts, 16 tokens: 256 threads a quad cost 3 us, 32 cost 0.3); counts
+// are added as integers, so their order does not matter.  (One thread per expert walking all rows: 142 us at 8192 tokens.)
+// What it waits for is one CU's share of memory, and in short calls its own instructions, which nobody has fetched before it.  LONG
+// (stats_long): twelve loads of p_part a thread in flight, and a wave for an expert's counts, eight experts in flight; else short
+// loops, and a word of counts a thread.
 constexpr int kStatsFinalThreads = 1024;
 constexpr int kStatsParts = 32;
 
+// Short loops / LONG, us, H = 2048: 160 experts, 16 tokens 2.7 / 8.1, 1500 4.6 / 8.5, 6000 7.2 / 9.2, 8192 9.1 / 7.6, 10000 9.7 / 8.1, 16384
+// 13.7 / 7.9;  96 experts, 1500 tokens 3.9 / 5.4, 5000 5.1 / 5.6, 8192 6.3 / 4.9;  32, 8192 tokens 4.3 / 4.4, 16384 5.2 / 4.8;  256, 6000
+// tokens 8.1 / 9.2, 8192 11.6 / 8.6;  250, whose rows have no 16-byte pieces, 8192 tokens 19.6 / 24.8, 16384 25.1 / 24.8.
+static bool stats_long(int cnt_ld, int NE) { return cnt_ld >= 32 * 16 && NE % 4 == 0; }
+
+template <bool LONG>
 __global__ __launch_bounds__(kStatsFinalThreads) void route_stats_final_kernel(const float *__restrict__ p_part, int prows,
                                                                                const int32_t *__restrict__ f_part,
                                                                                const uint8_t *__restrict__ cnt8, int cnt_ld,
@@ -622,26 +630,36 @@ __global__ __launch_bounds__(kStatsFinalThreads) void route_stats_final_kernel(c
     const int quad = tid % quads, part = tid / quads;
     for (int e = tid; e < kMaxExperts; e += kStatsFinalThreads) s_cnt[e] = 0;
     __syncthreads();
-    if (!f_part) {
+    // of a word of counts (blocks 16 wi .. + 15): what is there
+    auto clip = [&](uint4 &v, int wi) {
+        auto mask = [&](int q) {
+            const int left = nblocks - (wi * 16 + q * 4);
+            return left >= 4 ? ~0u : left <= 0 ? 0u : (1u << (8 * left)) - 1u;
+        };
+        v.x &= mask(0); v.y &= mask(1); v.z &= mask(2); v.w &= mask(3);
+    };
+    auto add_word = [](const uint4 &v, int c) {
+        c = (int)__builtin_amdgcn_sad_u8(v.x, 0u, (unsigned)c);
+        c = (int)__builtin_amdgcn_sad_u8(v.y, 0u, (unsigned)c);
+        c = (int)__builtin_amdgcn_sad_u8(v.z, 0u, (unsigned)c);
+        return (int)__builtin_amdgcn_sad_u8(v.w, 0u, (unsigned)c);
+    };
+    const int words = cnt_ld / 16;
+    if constexpr (LONG) {
         constexpr int WAVES = kStatsFinalThreads / 64, U = 8;
-        const int words = cnt_ld / 16, lane = tid & 63;
+        const int lane = tid & 63;
         for (int e0 = tid >> 6; e0 < NE; e0 += WAVES * U) {
             int c[U] = {};
             for (int wi = lane; wi < words; wi += 64) {
                 uint4 v[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const uint4 *>(cnt8 + (size_t)min(e0 + WAVES * u, NE - 1) * cnt_ld + wi * 16);
+                if (wi * 16 + 16 > nblocks) {
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const unsigned dw[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int b0 = wi * 16 + q * 4;
-                        unsigned x = dw[q];
-                        if (b0 + 4 > nblocks) x = b0 >= nblocks ? 0u : (x & ((1u << (8 * (nblocks - b0))) - 1u));  // bytes past the last block
-                        c[u] = (int)__builtin_amdgcn_sad_u8(x, 0u, (unsigned)c[u]);
-                    }
+                    for (int u = 0; u < U; ++u) clip(v[u], wi);
                 }
+#pragma unroll
+                for (int u = 0; u < U; ++u) c[u] = add_word(v[u], c[u]);
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -654,35 +672,51 @@ __global__ __launch_bounds__(kStatsFinalThreads) void route_stats_final_kernel(c
         f32x4 ps = {0.f, 0.f, 0.f, 0.f};
         int fs[4] = {0, 0, 0, 0};
         const int col = quad * 4;
-        constexpr int U = 12;  // (a loop unrolled by the compiler would take what is left over one load after the other)
-        for (int b0 = part; b0 < prows; b0 += parts * U) {
-            f32x4 v[U];
-            if (NE % 4 == 0) {
+        if constexpr (LONG) {
+            constexpr int U = 12;  // (a loop unrolled by the compiler would take what is left over one load after the other)
+            for (int b0 = part; b0 < prows; b0 += parts * U) {
+                f32x4 v[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const f32x4 *>(p_part + (size_t)min(b0 + u * parts, prows - 1) * NE + col);
-            } else {
 #pragma unroll
-                for (int u = 0; u < U; ++u)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) v[u][q] = p_part[(size_t)min(b0 + u * parts, prows - 1) * NE + min(col + q, NE - 1)];  // (past NE: not used)
+                for (int u = 0; u < U; ++u) ps += b0 + u * parts < prows ? v[u] : f32x4{0.f, 0.f, 0.f, 0.f};
             }
-#pragma unroll
-            for (int u = 0; u < U; ++u) ps += b0 + u * parts < prows ? v[u] : f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-        if (f_part) {
+        } else if (NE % 4 == 0) {
+#pragma unroll 8
+            for (int b = part; b < prows; b += parts) {
+                ps += *reinterpret_cast<const f32x4 *>(p_part + (size_t)b * NE + col);
+                if (f_part) {
+                    const int4 c = *reinterpret_cast<const int4 *>(f_part + (size_t)b * NE + col);
+                    fs[0] += c.x; fs[1] += c.y; fs[2] += c.z; fs[3] += c.w;
+                }
+            }
+        } else {
+#pragma unroll 8
             for (int b = part; b < prows; b += parts)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) fs[q] += f_part[(size_t)b * NE + min(col + q, NE - 1)];
+                for (int q = 0; q < 4; ++q) {
+                    const size_t at = (size_t)b * NE + min(col + q, NE - 1);  // (past NE: not used)
+                    ps[q] += p_part[at];
+                    if (f_part) fs[q] += f_part[at];
+                }
         }
         s_part[tid] = ps;
-        if (f_part)
+        if (!LONG && f_part)
             for (int q = 0; q < 4; ++q)
                 if (quad * 4 + q < NE) atomicAdd(&s_cnt[quad * 4 + q], fs[q]);
+    }
+    if (!LONG && !f_part) {
+        for (int i = tid; i < NE * words; i += kStatsFinalThreads) {
+            const int e = i / words, wi = i - e * words;
+            uint4 v = *reinterpret_cast<const uint4 *>(cnt8 + (size_t)e * cnt_ld + wi * 16);
+            clip(v, wi);
+            atomicAdd(&s_cnt[e], add_word(v, 0));
+        }
     }
     __syncthreads();
     if (tid < NE) {
         float ps = 0.f;
-#pragma unroll 8
+#pragma unroll LONG ? 8 : 4
         for (int q = 0; q < parts; ++q) ps += s_part[q * quads + tid / 4][tid % 4];
         s_P[tid] = ps / (float)T;
         s_f[tid] = (float)((double)s_cnt[tid] / (double)T);
@@ -740,8 +774,8 @@ int launch_routing_stats(const zeda_layer_desc *d, const void *x, const void *wr
         const int prows = ceil_div(d->T, plan.slices > 1 ? kSelectTokens : 16 * plan.tb);  // workgroups that select
         const int rc = launch_route_bf16_any(d, x, wr, bias, nullptr, nullptr, partial, ex, s);
         if (rc != ZEDA_OK) return rc;
-        route_stats_final_kernel<<<1, kStatsFinalThreads, 0, s>>>(p_part, prows, nullptr, cnt8, ex.cnt_ld, ceil_div(d->T, 16), d->T, d->N, NE,
-                                                             d->K, alpha, w, f, P, summary);
+        const auto kernel = stats_long(ex.cnt_ld, NE) ? route_stats_final_kernel<true> : route_stats_final_kernel<false>;
+        kernel<<<1, kStatsFinalThreads, 0, s>>>(p_part, prows, nullptr, cnt8, ex.cnt_ld, ceil_div(d->T, 16), d->T, d->N, NE, d->K, alpha, w, f, P, summary);
         return last_launch_status();
     }
     const int NB = ceil_div(NE, 32), LDg = NB * 32;
@@ -761,7 +795,7 @@ int launch_routing_stats(const zeda_layer_desc *d, const void *x, const void *wr
     }
 #undef ZEDA_STATS
     if (hipGetLastError() != hipSuccess) return ZEDA_EHIP;
-    route_stats_final_kernel<<<1, kStatsFinalThreads, 0, s>>>(p_part, nblk, f_part, nullptr, 0, nblk, d->T, d->N, NE, d->K, alpha, w, f, P,
+    route_stats_final_kernel<false><<<1, kStatsFinalThreads, 0, s>>>(p_part, nblk, f_part, nullptr, 0, nblk, d->T, d->N, NE, d->K, alpha, w, f, P,
                                                          summary);
     return last_launch_status();
 }
