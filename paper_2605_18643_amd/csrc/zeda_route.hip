@@ -48,6 +48,18 @@ __device__ __forceinline__ void publish_blocks(const int *s_cnt, const float *pr
                                                uint8_t *__restrict__ cnt8, int cnt_ld, float *__restrict__ p_part)
 {
     const int nblk = (ntok + 15) >> 4;
+    if (nblk == 1) {  // (one short loop: the two below cost 0.4 us of 16, statistics of 160 experts, 4096 tokens)
+        const int nt = min(ntok, T - t0);
+        for (int e = threadIdx.x; e < NE && nt > 0; e += THREADS) {
+            if (cnt8) cnt8[(size_t)e * cnt_ld + (t0 >> 4)] = (uint8_t)s_cnt[e];
+            if (p_part) {
+                float ps = 0.f;
+                for (int t = 0; t < nt; ++t) ps += probs[t * LDP + e];
+                p_part[(size_t)blockIdx.x * NE + e] = ps;
+            }
+        }
+        return;
+    }
     if (cnt8) {
         for (int i = threadIdx.x; i < nblk * NE; i += THREADS) {
             const int u = i / NE, e = i - u * NE, blk = (t0 >> 4) + u;
